@@ -11,7 +11,7 @@
 // Softmax runs in fp32 in the log2 domain with a running maximum; masked keys (padding of the list,
 // slots beyond len) get a -inf bias and zeroed K/V rows.
 //
-// fp32 path (small reference-precision case): one thread per query, K/V tiles broadcast from LDS.
+// fp32: attention_f32.hip.
 #include "common.hpp"
 
 namespace fastar {
@@ -272,101 +272,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
         lse[(size_t)h * n_q + q_idx] = l_tot > 0.0f ? (m_run + __log2f(l_tot)) * LN2 : -INFINITY;
 }
 
-// ---- fp32 reference-precision path ----------------------------------------------------------------------
-constexpr int TKF = 32;  // keys per LDS sub-tile of the fp32 path
-
-template <int D>
-__global__ __launch_bounds__(128) void attn_f32_kernel(const float *__restrict__ Q, const float *__restrict__ K,
-                                                       const float *__restrict__ V, const int32_t *__restrict__ cnt,
-                                                       const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
-                                                       const int32_t *__restrict__ nsel, int n_q, int C, int BQ, int BK,
-                                                       int n_sel, int n_qb, float scale_log2, float *__restrict__ O,
-                                                       float *__restrict__ lse) {
-    __shared__ __attribute__((aligned(16))) float Ks[TKF * D];
-    __shared__ __attribute__((aligned(16))) float Vs[TKF * D];
-    __shared__ float bias[TKF];
-    const int b = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-    const int L = min(len[h], C);
-    const int n_listed = min(nsel[(size_t)h * n_qb + b], n_sel);
-    const int32_t *sel_row = sel + ((size_t)h * n_qb + b) * n_sel;
-    const int qi = b * BQ + tid;
-    const bool active = tid < BQ && qi < n_q;
-    float q[D], o[D];
-    {
-        const float *qrow = Q + ((size_t)h * n_q + (active ? qi : 0)) * D;
-#pragma unroll
-        for (int t = 0; t < D; ++t) {
-            q[t] = qrow[t];
-            o[t] = 0.0f;
-        }
-    }
-    float m_run = -INFINITY, l_run = 0.0f;
-    for (int e = 0; e < n_listed; ++e) {
-        const int kb = sel_row[e];
-        if (kb < 0) continue;  // uniform over the workgroup
-        const int kend = min((kb + 1) * BK, L);
-        for (int k0 = kb * BK; k0 < kend; k0 += TKF) {
-            const int nk = min(TKF, kend - k0);
-            __syncthreads();
-            for (int x = tid; x < nk * (D / 4); x += blockDim.x) {
-                const int row = x / (D / 4), c4 = x % (D / 4);
-                *(f32x4 *)(Ks + row * D + 4 * c4) = *(const f32x4 *)(K + ((size_t)h * C + k0 + row) * D + 4 * c4);
-                *(f32x4 *)(Vs + row * D + 4 * c4) = *(const f32x4 *)(V + ((size_t)h * C + k0 + row) * D + 4 * c4);
-            }
-            if (tid < nk) bias[tid] = cnt ? log2f((float)cnt[(size_t)h * C + k0 + tid]) : 0.0f;
-            __syncthreads();
-            float s[TKF];
-            float mx = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < TKF; ++j) {
-                float acc = -INFINITY;
-                if (j < nk) {
-                    acc = 0.0f;
-#pragma unroll
-                    for (int t = 0; t < D; t += 4) {
-                        const f32x4 kv = *(const f32x4 *)(Ks + j * D + t);
-                        acc = fmaf(q[t], kv[0], acc);
-                        acc = fmaf(q[t + 1], kv[1], acc);
-                        acc = fmaf(q[t + 2], kv[2], acc);
-                        acc = fmaf(q[t + 3], kv[3], acc);
-                    }
-                    acc = fmaf(acc, scale_log2, bias[j]);
-                }
-                s[j] = acc;
-                mx = fmaxf(mx, acc);
-            }
-            const float m_new = fmaxf(m_run, mx);  // nk >= 1, so m_new is finite
-            const float alpha = exp2f(m_run - m_new);
-            l_run *= alpha;
-#pragma unroll
-            for (int t = 0; t < D; ++t) o[t] *= alpha;
-#pragma unroll
-            for (int j = 0; j < TKF; ++j) {
-                if (j < nk) {
-                    const float p = exp2f(s[j] - m_new);
-                    l_run += p;
-#pragma unroll
-                    for (int t = 0; t < D; t += 4) {
-                        const f32x4 vv = *(const f32x4 *)(Vs + j * D + t);
-                        o[t] = fmaf(p, vv[0], o[t]);
-                        o[t + 1] = fmaf(p, vv[1], o[t + 1]);
-                        o[t + 2] = fmaf(p, vv[2], o[t + 2]);
-                        o[t + 3] = fmaf(p, vv[3], o[t + 3]);
-                    }
-                }
-            }
-            m_run = m_new;
-        }
-    }
-    if (active) {
-        const float inv = l_run > 0.0f ? 1.0f / l_run : 0.0f;
-        float *orow = O + ((size_t)h * n_q + qi) * D;
-#pragma unroll
-        for (int t = 0; t < D; ++t) orow[t] = o[t] * inv;
-        if (lse) lse[(size_t)h * n_q + qi] = l_run > 0.0f ? (m_run + log2f(l_run)) * LN2 : -INFINITY;
-    }
-}
-
+int launch_attn_f32(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len, int H, int C,
+                    int d, const int32_t *sel, const int32_t *nsel, int BQ, int BK, int n_sel, float scale_log2, void *O,
+                    float *lse, hipStream_t s);
 int launch_attn_bf16_d128(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len,
                           int H, int C, const int32_t *sel, const int32_t *nsel, int BQ, int bk_shift, int n_sel,
                           float scale_log2, void *O, float *lse, hipStream_t s);
@@ -454,15 +362,7 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
 #undef FASTAR_ATTN
     } else {
         if (BQ > 128 || BK > 64) return FASTAR_ERR_UNSUPPORTED;
-        const dim3 grid(n_qb, H);
-        if (d == 128)
-            hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(128), 0, s, (const float *)Q, (const float *)K,
-                               (const float *)V, cnt, len, sel, nsel, n_q, C, BQ, BK, n_sel, n_qb, scale_log2,
-                               (float *)O, lse);
-        else
-            hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(128), 0, s, (const float *)Q, (const float *)K,
-                               (const float *)V, cnt, len, sel, nsel, n_q, C, BQ, BK, n_sel, n_qb, scale_log2,
-                               (float *)O, lse);
+        return launch_attn_f32(Q, n_q, K, V, cnt, len, H, C, d, sel, nsel, BQ, BK, n_sel, scale_log2, O, lse, s);
     }
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;

@@ -381,6 +381,9 @@ def check_attention(Q, K, V, cnt, length, sel, nsel, BQ, BK, scale, dtype):
 @pytest.mark.parametrize("dtype,H,n_q,C,d,BQ,BK,n_sel,lens,use_cnt", [
     ("fp32", 2, 256, 1280, 64, 128, 64, 6, [1280, 546], True),       # cfg1-shaped
     ("fp32", 1, 100, 300, 128, 64, 16, 9, [291], False),
+    ("fp32", 3, 400, 700, 128, 128, 64, 5, [700, 0, 333], True),      # fp32: groups of 16 queries, four wavefronts each
+    ("fp32", 7, 330, 500, 64, 100, 48, 3, [500] * 6 + [47], True),    # query blocks that 16 does not divide, key blocks of 48
+    ("fp32", 9, 401, 400, 128, 128, 1, 37, [400] * 9, False),         # token-granular lists, no multiplicities
     ("bf16", 3, 700, 64 * 50, 128, 128, 64, 12, [3200, 2011, 0], True),   # ragged query tail, ragged / empty caches
     ("bf16", 2, 300, 2048, 128, 128, 1, 64, [2048, 1500], False),    # token-granular gather (cross-attention)
     ("bf16", 2, 260, 1024, 64, 64, 64, 5, [1024, 1000], True),       # d = 64, BQ = 64
