@@ -280,7 +280,7 @@ int launch_attn_bf16_d128(const void *Q, int n_q, const void *K, const void *V, 
                           float scale_log2, void *O, float *lse, hipStream_t s);
 int launch_attn_bf16_d128_pp(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt,
                              const int32_t *len, int H, int C, const int32_t *sel, const int32_t *nsel, int bk_shift,
-                             int n_sel, float scale_log2, void *O, float *lse, hipStream_t s);
+                             int n_sel, float scale_log2, void *O, float *lse, int n_parts, void *ws, hipStream_t s);
 
 size_t attn_sk_ws_bytes();
 int launch_attn_bf16_d128_sk(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len,
@@ -353,8 +353,18 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
         if (ws && d == 128 && BQ == 128 && full_per > 0)
             return launch_attn_bf16_d128_sk(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, ws,
                                             full_per, s);
+        // At most one query block per compute unit: both groups of the two-block kernel on one block (156 blocks of 48 tiles
+        // 85 -> 51 us, one-block workgroups take 67), with a workspace several workgroups per block where that pays
+        // (8 blocks of 96 tiles 161 -> 21 us).  Very short lists stay with the one-block kernel (3 tiles: 8.5 us against 9.5,
+        // 6 tiles 12.2 against 12.1), also beyond 256 blocks (444 blocks of 64 single keys 9.9 us against 11.2).
+        if (d == 128 && BQ == 128 && n_items <= 256 && n_tiles > 5)
+            return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse,
+                                            ws ? attn_parts(n_items, n_tiles, 2, 1.65f, 0.0f) : 1, ws, s);
+        if (d == 128 && BQ == 128 && n_items <= 512 && n_tiles <= 5 && (n_items <= 256 || n_tiles <= 2))
+            return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
         if (d == 128 && BQ == 128 && (n_items <= 512 || n_items % 512 == 0 || n_items % 512 >= 256))
-            return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, s);
+            return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, 0,
+                                            nullptr, s);
         if (d == 128)  // tuned path: direct-to-LDS tiles, LDS transpose loads
             return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
         if (BQ == 128) FASTAR_ATTN(64, 4);

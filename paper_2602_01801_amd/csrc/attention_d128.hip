@@ -137,7 +137,7 @@ static_assert(PART_O_FLOATS == ATTN_PART_O_FLOATS && PART_FLOATS == ATTN_PART_FL
 
 // One query block (h, b) over the tiles [t_begin, t_end) of its selection list (t_end may lie beyond the list: it is
 // clipped).  part == nullptr: the block's output rows and lse are written.  Otherwise the fragment's unnormalised
-// result goes to `part`: O^T accumulators as they sit in registers ([wave][db][v][lane] floats), then the reference
+// result goes to `part`: O^T accumulators as they sit in registers ([wave][db][v / 4][lane] of four floats), then the reference
 // maxima and the row sums ([wave][lane] each), for attn_combine_kernel.  All NW * 64 threads of a workgroup.
 template <int NW>
 __device__ __forceinline__ void attend_item(
@@ -375,7 +375,10 @@ __device__ __forceinline__ void attend_item(
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[((wave * (D / 32) + db) * 16 + v) * 64 + lane] = o_acc[db][v];
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 w = {o_acc[db][4 * q4], o_acc[db][4 * q4 + 1], o_acc[db][4 * q4 + 2], o_acc[db][4 * q4 + 3]};
+                ((f32x4 *)part)[((wave * (D / 32) + db) * 4 + q4) * 64 + lane] = w;
+            }
         part[NW * PART_O_FLOATS + wave * 64 + lane] = m_ref;
         part[NW * PART_O_FLOATS + NW * 64 + wave * 64 + lane] = l_tot;
         __syncthreads();   // the tile stages and row tables are free for the next block
@@ -506,21 +509,22 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
     float l_tot = 0.0f;
     constexpr int FB = 4;   // fragments whose rows are loaded together
     for (int f0 = 0; f0 < n_frag; f0 += FB) {
-        float mf[FB], lf[FB], of[FB][16];
+        float mf[FB], lf[FB];
+        f32x4 of[FB][4];
 #pragma unroll
         for (int u = 0; u < FB; ++u) {
             const float *p = frag(min(f0 + u, n_frag - 1));
             mf[u] = p[4 * PART_O_FLOATS + wave * 64 + lane];
             lf[u] = p[4 * PART_O_FLOATS + 4 * 64 + wave * 64 + lane];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) of[u][v] = p[((wave * (D / 32) + db) * 16 + v) * 64 + lane];
+            for (int q4 = 0; q4 < 4; ++q4) of[u][q4] = ((const f32x4 *)p)[((wave * (D / 32) + db) * 4 + q4) * 64 + lane];
         }
 #pragma unroll
         for (int u = 0; u < FB; ++u) {
             const float w = (f0 + u >= n_frag || mf[u] == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f((mf[u] - m_all) * scale_log2);
             l_tot += w * lf[u];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) o[v] += w * of[u][v];
+            for (int v = 0; v < 16; ++v) o[v] += w * of[u][v / 4][v % 4];
         }
     }
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
@@ -547,6 +551,76 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float *__restri
         lse[(size_t)h * n_q + q_idx] = l_tot > 0.0f ? (m_all * scale_log2 + lse_offset + __log2f(l_tot)) * LN2 : -INFINITY;
 }
 
+
+// The n_parts fragments of a query block (attn_bf16_d128_pp_kernel, SPLIT; attn_fp8_d128_parts_kernel), put together: workgroup (item, db) of this
+// launch for the 32 coordinates db of d.  Same wavefront / lane layout as the fragments, eight fragments' rows in flight.
+__global__ __launch_bounds__(256) void attn_combine_parts_kernel(const float *__restrict__ frag, int n_parts, int n_q, int n_qb,
+                                                                 float scale_log2, float lse_offset,
+                                                                 unsigned short *__restrict__ O, float *__restrict__ lse) {
+    constexpr int FB = 8, OS = 32 + 8;   // OS: bf16 elements per staged row (this quarter of d, padded)
+    __shared__ __attribute__((aligned(16))) unsigned short stage[4 * 32 * OS];
+    const int item = blockIdx.x, db = blockIdx.y;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int col = lane & 31, g = lane >> 5;
+    const int h = item / n_qb, b = item % n_qb;
+    const float *base = frag + (size_t)item * n_parts * ATTN_PART_FLOATS;
+    float m_all = -INFINITY, l_tot = 0.0f, o[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+    for (int f0 = 0; f0 < n_parts; f0 += FB) {
+        float mf[FB], lf[FB];
+        f32x4 of[FB][4];
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+            if (f0 + u < n_parts) {   // uniform
+                const float *p = base + (size_t)(f0 + u) * ATTN_PART_FLOATS;
+                mf[u] = p[4 * ATTN_PART_O_FLOATS + wave * 64 + lane];
+                lf[u] = p[4 * ATTN_PART_O_FLOATS + (4 + wave) * 64 + lane];
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) of[u][q4] = ((const f32x4 *)p)[((wave * (D / 32) + db) * 4 + q4) * 64 + lane];
+            }
+        }
+        float m_new = m_all;
+#pragma unroll
+        for (int u = 0; u < FB; ++u)
+            if (f0 + u < n_parts) m_new = fmaxf(m_new, mf[u]);
+        const float keep = m_all == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_all - m_new) * scale_log2);
+        m_all = m_new;
+        l_tot *= keep;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] *= keep;
+#pragma unroll
+        for (int u = 0; u < FB; ++u)
+            if (f0 + u < n_parts) {
+                const float w = mf[u] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mf[u] - m_all) * scale_log2);
+                l_tot += w * lf[u];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[v] += w * of[u][v / 4][v % 4];
+            }
+    }
+    const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+    unsigned short *Os = stage + (size_t)wave * 32 * OS;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+        bf16x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[4 * q4 + e] * inv);
+        *(bf16x4 *)(Os + col * OS + 8 * q4 + 4 * g) = w;
+    }
+    __syncthreads();
+    const int rr = lane >> 2, cc = lane & 3;
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int r = it * 16 + rr;
+        const int qi = b * 128 + wave * 32 + r;
+        if (qi < n_q) *(u32x4 *)(O + ((size_t)h * n_q + qi) * D + 32 * db + cc * 8) = *(const u32x4 *)(Os + r * OS + cc * 8);
+    }
+    const int q_idx = b * 128 + wave * 32 + col;
+    if (db == 0 && lse && g == 0 && q_idx < n_q)
+        lse[(size_t)h * n_q + q_idx] = l_tot > 0.0f ? (m_all * scale_log2 + lse_offset + __log2f(l_tot)) * LN2 : -INFINITY;
+}
+
 }  // namespace d128
 
 // The combination launch for any kernel that leaves fragments in the layout above (the bf16 and the 8-bit one).
@@ -555,6 +629,15 @@ int launch_attn_combine(const void *ws, int n_q, int n_qb, TailMap tm, int NT, f
     using namespace d128;
     hipLaunchKernelGGL(attn_combine_kernel, dim3(SK_WORKGROUPS, D / 32), dim3(256), 4 * 32 * (32 + 8) * 2, s, (const float *)ws,
                        SK_WORKGROUPS, n_q, n_qb, tm, NT, scale_log2, lse_offset, (unsigned short *)O, lse);
+    if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;
+    return FASTAR_OK;
+}
+
+int launch_attn_combine_parts(const void *ws, int n_parts, int n_q, int n_qb, int H, float scale_log2, float lse_offset, void *O,
+                              float *lse, hipStream_t s) {
+    using namespace d128;
+    hipLaunchKernelGGL(attn_combine_parts_kernel, dim3(n_qb * H, D / 32), dim3(256), 0, s, (const float *)ws, n_parts, n_q, n_qb,
+                       scale_log2, lse_offset, (unsigned short *)O, lse);
     if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;
     return FASTAR_OK;
 }

@@ -138,12 +138,16 @@ __device__ __forceinline__ void wg_barrier() {
 // requested there, instead of at the head of the vector phase.  That shortens the vector phase (the longer one), but the
 // compiler's wait for the multiplicities then also waits for the tile loads the vector phase in between has issued:
 // good while those come from L2 / the memory-side cache, bad once the cache outgrows them.
-template <int NWG, bool CONTIG, bool BIAS_X>
+// SPLIT: both groups take the SAME query block, each its half of the tiles, and put their halves together through LDS at
+// the end; with n_parts > 1 a block is first cut into n_parts runs of tiles, a workgroup each, which leave fragments in
+// `frag` for attn_combine_parts_kernel.  For launches whose query blocks would leave compute units idle: 156 blocks of 48
+// tiles take 85 us as 78 pairs, 67 us as 156 one-block workgroups and 51 us as 156 split workgroups.
+template <int NWG, bool CONTIG, bool BIAS_X, bool SPLIT>
 __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
     const unsigned short *__restrict__ Q, const unsigned short *__restrict__ K, const unsigned short *__restrict__ V,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int bk_shift, int n_sel, int n_qb, int H, float scale_log2,
-    float inv_scale_log2, unsigned short *__restrict__ O, float *__restrict__ lse) {
+    float inv_scale_log2, unsigned short *__restrict__ O, float *__restrict__ lse, int n_parts, float *__restrict__ frag) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int GT = NWG * 64;            // threads per group
     constexpr int IPW = (TK / 4) / NWG;     // 1-KiB direct-load instructions per wavefront and tensor
@@ -154,15 +158,15 @@ __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
     const int gtid = tid - grp * GT;
     const int col = lane & 31, g = lane >> 5;
 
-    // workgroup -> pair of consecutive (head, query block) items; XCD-contiguous ranges of pairs
+    // workgroup -> pair of consecutive (head, query block) items (SPLIT: part of an item); XCD-contiguous ranges of them
     const int total = n_qb * H;
-    const int pairs = (total + 1) / 2;
-    int pair;
+    const int units = SPLIT ? total * n_parts : (total + 1) / 2;
+    int unit;
     {
         const int wg = blockIdx.x;
-        const int per = (pairs + 7) / 8;
-        pair = (wg & 7) * per + (wg >> 3);
-        if (pair >= pairs) return;
+        const int per = (units + 7) / 8;
+        unit = (wg & 7) * per + (wg >> 3);
+        if (unit >= units) return;
     }
     auto tiles_of = [&](int item) -> int {   // uniform
         if (item >= total) return 0;
@@ -171,9 +175,21 @@ __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
         const int nl = Lh > 0 ? min(nsel[(size_t)hh * n_qb + bb], n_sel) : 0;
         return ((nl << bk_shift) + TK - 1) / TK;
     };
-    const int nt0 = tiles_of(2 * pair), nt1 = tiles_of(2 * pair + 1);
-    const int item = min(2 * pair + grp, total - 1);
-    const bool valid = 2 * pair + grp < total;
+    int nt0, nt1, item, toff = 0;   // tiles of the two groups; this group's item and the first tile of its run
+    bool valid = true;
+    if constexpr (SPLIT) {
+        item = unit / n_parts;
+        const int part = unit - item * n_parts, nta = tiles_of(item);
+        const int tb = (int)((long long)nta * part / n_parts), te = (int)((long long)nta * (part + 1) / n_parts);
+        nt0 = (te - tb + 1) / 2;
+        nt1 = te - tb - nt0;
+        toff = grp == 0 ? tb : tb + nt0;
+    } else {
+        nt0 = tiles_of(2 * unit);
+        nt1 = tiles_of(2 * unit + 1);
+        item = min(2 * unit + grp, total - 1);
+        valid = 2 * unit + grp < total;
+    }
     const int nt = grp == 0 ? nt0 : nt1;
     const int h = item / n_qb, b = item % n_qb;
     const int L = min(len[h], C);
@@ -233,22 +249,23 @@ __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
     };
     // ---- CONTIG: selection entries in a register, tiles by base address -------------------------------------------
     const unsigned lds_base = (unsigned)(size_t)LDS_PTR(unsigned char, lds);
-    int sel_chunk = 0;
+    int sel_chunk = toff >> 6;
     int selv = -1;   // lane l: entry 64 * sel_chunk + l of the list
     if constexpr (CONTIG) {
-        if (n_listed > 0) selv = sel_row[min(lane, n_listed - 1)];
+        if (n_listed > 0) selv = sel_row[min(64 * sel_chunk + lane, n_listed - 1)];
         asm volatile("s_waitcnt vmcnt(0)" : "+v"(selv)::"memory");
     }
     // first row of tile t (uniform; -1: no such tile or a negative entry); tiles are asked for in rising order
     auto row0_of = [&](int t) __attribute__((always_inline)) -> int {
         if (t >= nt) return -1;
-        if ((t >> 6) != sel_chunk) {
-            sel_chunk = t >> 6;
+        const int ta = t + toff;
+        if ((ta >> 6) != sel_chunk) {
+            sel_chunk = ta >> 6;
             selv = sel_row[min(64 * sel_chunk + lane, n_listed - 1)];
             // waited for here, once per 64 tiles, so that the common path carries no wait for it
             asm volatile("s_waitcnt vmcnt(0)" : "+v"(selv)::"memory");
         }
-        const int kb = __builtin_amdgcn_readlane(selv, t & 63);
+        const int kb = __builtin_amdgcn_readlane(selv, ta & 63);
         return kb >= 0 ? kb * TK : -1;
     };
     unsigned koff[IPW], voff[2];   // per-lane parts of a tile load: row within the instruction's four, swizzled chunk
@@ -300,7 +317,7 @@ __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
 
     // row tables: position p of tile `tile` (threads gtid < 64 of the group)
     auto sel_entry = [&](int tile) __attribute__((always_inline)) -> int {
-        const int entry = (tile * TK + gtid) >> bk_shift;
+        const int entry = ((tile + toff) * TK + gtid) >> bk_shift;
         return (gtid < TK && entry < n_listed) ? sel_row[entry] : -1;
     };
     auto key_of = [&](int kb, int tile) __attribute__((always_inline)) -> int {
@@ -559,11 +576,93 @@ __global__ __launch_bounds__(2 * NWG * 64, 1) void attn_bf16_d128_pp_kernel(
     }
     for (; done < n_bar; ++done) wg_barrier();
 
-    // epilogue: normalise, transpose through the group's own LDS region, store rows coalesced
     const float l_lane = l0 + l1;
-    const float l_tot = l_lane + shfl_xor(l_lane, 32);
+    float l_tot = l_lane + shfl_xor(l_lane, 32);
+    __syncthreads();   // the tiles are dead: their LDS takes what follows
+    if constexpr (SPLIT) {
+        // Each group hands the other the half of d the other will finish (group 0: columns 0..63, group 1: 64..127) as it
+        // sits in its registers, with its reference maxima and sums; any reference is as good as the true maximum.
+        constexpr int HB = D / 64;   // 32-column blocks per half
+        f32x4 *mine = (f32x4 *)gbase, *theirs = (f32x4 *)(lds + (grp ^ 1) * GROUPB);
+        float *my_ml = (float *)meta, *their_ml = (float *)((TileMeta *)(lds + 2 * GROUPB) + NMETA * (grp ^ 1));
+        static_assert(NMETA * sizeof(TileMeta) >= NWG * 64 * 2 * sizeof(float), "maxima and sums fit the row tables");
+        auto give = [&](int dst, const f32x16 &o) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 w = {o[4 * q4], o[4 * q4 + 1], o[4 * q4 + 2], o[4 * q4 + 3]};
+                mine[((gw * HB + dst) * 4 + q4) * 64 + lane] = w;
+            }
+        };
+        if (grp == 0) {
+#pragma unroll
+            for (int i = 0; i < HB; ++i) give(i, o_acc[HB + i]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < HB; ++i) give(i, o_acc[i]);
+        }
+        my_ml[gw * 64 + lane] = m_ref;
+        my_ml[(NWG + gw) * 64 + lane] = l_tot;
+        __syncthreads();
+        const float m_o = their_ml[gw * 64 + lane], l_o = their_ml[(NWG + gw) * 64 + lane];
+        const float m_all = fmaxf(m_ref, m_o);
+        const float w_mine = m_ref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_ref - m_all) * scale_log2);
+        const float w_other = m_o == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_o - m_all) * scale_log2);
+        l_tot = l_tot * w_mine + l_o * w_other;
+        f32x16 o[HB];
+#pragma unroll
+        for (int i = 0; i < HB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 w = theirs[((gw * HB + i) * 4 + q4) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float own = grp == 0 ? o_acc[i][4 * q4 + e] : o_acc[HB + i][4 * q4 + e];
+                    o[i][4 * q4 + e] = own * w_mine + w[e] * w_other;
+                }
+            }
+        if (n_parts > 1) {   // uniform: a fragment, [wavefront][db][q4][lane] of four floats, then maxima and sums
+            float *p = frag + (size_t)unit * ATTN_PART_FLOATS;
+#pragma unroll
+            for (int i = 0; i < HB; ++i)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const f32x4 w = {o[i][4 * q4], o[i][4 * q4 + 1], o[i][4 * q4 + 2], o[i][4 * q4 + 3]};
+                    ((f32x4 *)p)[((gw * (D / 32) + grp * HB + i) * 4 + q4) * 64 + lane] = w;
+                }
+            if (grp == 0) {
+                p[NWG * ATTN_PART_O_FLOATS + gw * 64 + lane] = m_all;
+                p[NWG * ATTN_PART_O_FLOATS + (NWG + gw) * 64 + lane] = l_tot;
+            }
+            return;
+        }
+        const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+        constexpr int HSTR = D / 2 + 8;   // bf16 elements per staged half row (16-byte pad)
+        unsigned short *Os = (unsigned short *)(gbase + GROUPB / 2) + (size_t)gw * 32 * HSTR;   // beyond what was handed over
+#pragma unroll
+        for (int i = 0; i < HB; ++i)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+                bf16x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[i][4 * q4 + e] * inv);
+                *(bf16x4 *)(Os + col * HSTR + 32 * i + 8 * q4 + 4 * g) = w;
+            }
+        __syncthreads();
+        const int rr = lane >> 3, cc = lane & 7;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int r = it * 8 + rr;
+            const int qi = b * (NWG * 32) + gw * 32 + r;
+            if (qi < n_q)
+                *(u32x4 *)(O + ((size_t)h * n_q + qi) * D + grp * (D / 2) + cc * 8) = *(const u32x4 *)(Os + r * HSTR + cc * 8);
+        }
+        if (lse && grp == 0 && g == 0 && q_idx < n_q)
+            lse[(size_t)h * n_q + q_idx] = l_tot > 0.0f ? (m_all * scale_log2 + __log2f(l_tot)) * LN2 : -INFINITY;
+        return;
+    }
+    // epilogue: normalise, transpose through the group's own LDS region, store rows coalesced
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-    __syncthreads();
     constexpr int OSTR = D + 8;  // bf16 elements per staged row (16-byte pad)
     unsigned short *Os = (unsigned short *)gbase + (size_t)gw * 32 * OSTR;
 #pragma unroll
@@ -597,36 +696,48 @@ int attn_d128_pp_setup() {
     using namespace d128pp;
     static DeviceOnce once;
     return once.run([](int) {
-        for (const void *f : {(const void *)attn_bf16_d128_pp_kernel<4, false, false>,
-                              (const void *)attn_bf16_d128_pp_kernel<4, true, false>,
-                              (const void *)attn_bf16_d128_pp_kernel<4, true, true>})
+        for (const void *f : {(const void *)attn_bf16_d128_pp_kernel<4, false, false, false>,
+                              (const void *)attn_bf16_d128_pp_kernel<4, true, false, false>,
+                              (const void *)attn_bf16_d128_pp_kernel<4, true, true, false>,
+                              (const void *)attn_bf16_d128_pp_kernel<4, false, false, true>,
+                              (const void *)attn_bf16_d128_pp_kernel<4, true, false, true>,
+                              (const void *)attn_bf16_d128_pp_kernel<4, true, true, true>})
             if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) != hipSuccess)
                 return FASTAR_ERR_HIP;
         return FASTAR_OK;
     });
 }
 
-// Launcher used by sparse_attn_fwd for bf16, d = 128, BQ = 128.
+// Launcher used by sparse_attn_fwd for bf16, d = 128, BQ = 128.  n_parts = 0: two query blocks per workgroup; n_parts > 0:
+// one, split over the two groups, its tiles cut into n_parts runs (more than one: ws takes n_parts fragments per block).
 int launch_attn_bf16_d128_pp(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt,
                              const int32_t *len, int H, int C, const int32_t *sel, const int32_t *nsel, int bk_shift,
-                             int n_sel, float scale_log2, void *O, float *lse, hipStream_t s) {
+                             int n_sel, float scale_log2, void *O, float *lse, int n_parts, void *ws, hipStream_t s) {
     using namespace d128pp;
     if (const int rc = attn_d128_pp_setup(); rc != FASTAR_OK) return rc;
     const int n_qb = (n_q + 127) / 128;
-    const int pairs = (n_qb * H + 1) / 2;
-    const dim3 grid((unsigned)(((pairs + 7) / 8) * 8));
-#define FASTAR_PP(CONTIG, BIAS_X)                                                                                  \
-    hipLaunchKernelGGL((attn_bf16_d128_pp_kernel<4, CONTIG, BIAS_X>), grid, dim3(512), LDS_BYTES, s,                \
+    const int units = n_parts > 0 ? n_qb * H * n_parts : (n_qb * H + 1) / 2;
+    const dim3 grid((unsigned)(((units + 7) / 8) * 8));
+#define FASTAR_PP(CONTIG, BIAS_X, SPLIT)                                                                           \
+    hipLaunchKernelGGL((attn_bf16_d128_pp_kernel<4, CONTIG, BIAS_X, SPLIT>), grid, dim3(512), LDS_BYTES, s,         \
                        (const unsigned short *)Q, (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, \
-                       nsel, n_q, C, bk_shift, n_sel, n_qb, H, scale_log2, 1.0f / scale_log2, (unsigned short *)O, lse)
+                       nsel, n_q, C, bk_shift, n_sel, n_qb, H, scale_log2, 1.0f / scale_log2, (unsigned short *)O, lse, \
+                       n_parts, (float *)ws)
     // key blocks of 64 rows: tiles by base address; K and V of all heads within reach of the 256 MB memory-side cache:
     // the bias rows are written in the matrix phase
     const bool cache_resident = (size_t)H * (size_t)C * D * 2 * 2 <= ((size_t)256 << 20);
-    if (bk_shift == 6 && cache_resident) FASTAR_PP(true, true);
-    else if (bk_shift == 6) FASTAR_PP(true, false);
-    else FASTAR_PP(false, false);
+    if (n_parts > 0) {
+        if (bk_shift == 6 && cache_resident) FASTAR_PP(true, true, true);
+        else if (bk_shift == 6) FASTAR_PP(true, false, true);
+        else FASTAR_PP(false, false, true);
+    } else {
+        if (bk_shift == 6 && cache_resident) FASTAR_PP(true, true, false);
+        else if (bk_shift == 6) FASTAR_PP(true, false, false);
+        else FASTAR_PP(false, false, false);
+    }
 #undef FASTAR_PP
     if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;
+    if (n_parts > 1) return launch_attn_combine_parts(ws, n_parts, n_q, n_qb, H, scale_log2, 0.0f, O, lse, s);
     return FASTAR_OK;
 }
 

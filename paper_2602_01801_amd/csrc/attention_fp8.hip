@@ -148,7 +148,7 @@ __device__ __forceinline__ f32x16 mfma_f8(i32x8 a, i32x8 b, f32x16 c) {
 
 // Query block b of head h over the entries t_begin <= t < t_end of its list (one entry = one tile).  part == nullptr:
 // normalised output rows and lse are written (the range must then be the whole list).  part != nullptr: the unnormalised
-// O^T accumulators ([wave][32-row block of d][register][lane]), then the reference maxima and the row sums
+// O^T accumulators ([wave][32-row block of d][register / 4][lane] of four), then the reference maxima and the row sums
 // ([wave][lane] each): the fragment layout that the combination launch of the split bf16 kernel reads.
 // All 256 threads of a workgroup; may be called again by the same workgroup for another block.
 __device__ __forceinline__ void attend_item_fp8(
@@ -338,7 +338,10 @@ __device__ __forceinline__ void attend_item_fp8(
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) part[((wave * (D / 32) + db) * 16 + v) * 64 + lane] = o_acc[db][v];
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4 w = {o_acc[db][4 * q4], o_acc[db][4 * q4 + 1], o_acc[db][4 * q4 + 2], o_acc[db][4 * q4 + 3]};
+                ((f32x4 *)part)[((wave * (D / 32) + db) * 4 + q4) * 64 + lane] = w;
+            }
         part[4 * ATTN_PART_O_FLOATS + wave * 64 + lane] = m_ref;
         part[4 * ATTN_PART_O_FLOATS + 4 * 64 + wave * 64 + lane] = l_tot;
         __syncthreads();   // the tile stages and the bookkeeping are free for the next block
@@ -420,6 +423,24 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_d128_sk_kernel(
     }
 }
 
+// Few query blocks: n_parts workgroups per block, each an equal run of its entries, which leave fragments for
+// attn_combine_parts_kernel (attention_d128.hip).
+__global__ __launch_bounds__(256, 2) void attn_fp8_d128_parts_kernel(
+    const unsigned short *__restrict__ Q, const uint8_t *__restrict__ K8, const uint8_t *__restrict__ V8T,
+    const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
+    const int32_t *__restrict__ nsel, int n_q, int C, int n_blk, int n_sel, int n_qb, int H, int n_parts, float scale_log2,
+    float inv_scale_log2, float *__restrict__ frag) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    const int units = n_qb * H * n_parts, per = (units + 7) / 8;
+    const int unit = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);   // neighbouring units on one XCD
+    if (unit >= units) return;
+    const int item = unit / n_parts, part = unit - item * n_parts;
+    const int n_listed = min(nsel[item], n_sel);
+    const int tb = (int)((long long)n_listed * part / n_parts), te = (int)((long long)n_listed * (part + 1) / n_parts);
+    attend_item_fp8(Q, K8, V8T, cnt, len, sel, nsel, n_q, C, n_blk, n_sel, n_qb, scale_log2, inv_scale_log2, nullptr, nullptr,
+                    lds, item / n_qb, item % n_qb, tb, te, frag + (size_t)unit * ATTN_PART_FLOATS);
+}
+
 }  // namespace f8
 
 int attn_fp8_setup() {
@@ -428,6 +449,8 @@ int attn_fp8_setup() {
         return hipFuncSetAttribute((const void *)f8::attn_fp8_d128_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    f8::LDS_BYTES) == hipSuccess &&
                        hipFuncSetAttribute((const void *)f8::attn_fp8_d128_sk_kernel,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, f8::LDS_BYTES) == hipSuccess &&
+                       hipFuncSetAttribute((const void *)f8::attn_fp8_d128_parts_kernel,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, f8::LDS_BYTES) == hipSuccess
                    ? FASTAR_OK
                    : FASTAR_ERR_HIP;
@@ -502,6 +525,17 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
                            (float *)ws);
         FASTAR_LAUNCH_CHECK();
         return launch_attn_combine(ws, n_q, n_qb, tm, n_sel, scale_log2, -6.0f, O, lse, (hipStream_t)stream);
+    }
+    // at most one block per compute unit: several workgroups per block where that pays (8 blocks of 96 tiles 97 -> 18 us,
+    // 156 of 48 tiles 55 -> 41 us; 3 tiles 8 us either way, then one workgroup)
+    const int n_parts = ws && n_qb * H <= 256 ? attn_parts(n_qb * H, n_sel, 1, 0.97f, 1.35f) : 1;
+    if (n_parts > 1) {
+        const int units = n_qb * H * n_parts;
+        hipLaunchKernelGGL(f8::attn_fp8_d128_parts_kernel, dim3((unsigned)(((units + 7) / 8) * 8)), dim3(256), f8::LDS_BYTES,
+                           (hipStream_t)stream, (const unsigned short *)Q, K8, V8T, cnt, len, sel, nsel, n_q, C, n_blk,
+                           n_sel, n_qb, H, n_parts, scale_log2, 1.0f / scale_log2, (float *)ws);
+        FASTAR_LAUNCH_CHECK();
+        return launch_attn_combine_parts(ws, n_parts, n_q, n_qb, H, scale_log2, -6.0f, O, lse, (hipStream_t)stream);
     }
     const dim3 grid((unsigned)(((n_qb * H + 7) / 8) * 8));
     hipLaunchKernelGGL(f8::attn_fp8_d128_kernel, grid, dim3(256), f8::LDS_BYTES, (hipStream_t)stream,

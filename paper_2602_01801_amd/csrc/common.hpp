@@ -127,6 +127,27 @@ inline int attn_split_full_per(int n_items, int n_tiles) {
         return per_xcd - tail_per;
     return 0;
 }
+// Few query blocks (at most one per compute unit): into how many runs of tiles each is cut, a workgroup (and a fragment)
+// each.  one_us / two_us: time of a workgroup per step of tiles_per_step tiles with one / two of them on a compute unit
+// (two_us = 0: only one fits).  One run costs its steps and about 4 us; several cost the longest run's steps and, measured
+// with 1 .. 224 blocks of 3 .. 192 tiles, 8 us + 0.25 us per run + 0.03 us per workgroup for the fragments, which are
+// written, read back and combined by one more launch.  At most 512 fragments: half of the workspace.
+inline int attn_parts(int n_items, int n_tiles, int tiles_per_step, float one_us, float two_us) {
+    int best = 1;
+    float best_us = 1e30f;
+    for (int p = 1; p <= 32 && p * n_items <= (two_us > 0.0f ? 512 : 256) && (p == 1 || p * tiles_per_step <= n_tiles); ++p) {
+        const int steps = (n_tiles + p * tiles_per_step - 1) / (p * tiles_per_step);
+        const float us = (p * n_items <= 256 ? one_us : two_us) * (float)steps +
+                         (p == 1 ? 4.0f : 8.0f + 0.25f * (float)p + 0.03f * (float)(p * n_items));
+        if (us < best_us) {
+            best_us = us;
+            best = p;
+        }
+    }
+    return best;
+}
+int launch_attn_combine_parts(const void *ws, int n_parts, int n_q, int n_qb, int H, float scale_log2, float lse_offset, void *O,
+                              float *lse, hipStream_t s);
 int launch_attn_combine(const void *ws, int n_q, int n_qb, TailMap tm, int NT, float scale_log2, float lse_offset, void *O,
                         float *lse, hipStream_t s);
 

@@ -1294,3 +1294,63 @@ def test_attention_with_a_workspace_runs_small_shapes_as_before_and_rejects_a_sh
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     with pytest.raises(fa.FastarError):
         fa.sparse_attn_fwd(Q, K, V, None, lens, sel, nsel, 128, 64, 0.1, ws=ws[:1024])
+
+
+@pytest.mark.parametrize("H,n_q,C,n_sel,BK,fp8", [
+    (1, 128, 64 * 12, 6, 64, False),        # the shortest list that is split over a workgroup's two groups
+    (2, 129, 64 * 40, 13, 64, False),       # odd number of tiles, a block of one query
+    (1, 300, 64 * 210, 193, 64, False),     # many runs; lists of more than 64 entries start inside a later register's worth
+    (3, 500, 64 * 80 - 17, 75, 64, False),  # last key block cut by len, runs of unequal length
+    (2, 257, 64 * 30, 43, 32, False),       # row tables instead of whole tiles, half a tile at the end
+    (17, 2048, 64 * 20, 9, 64, False),      # 272 blocks: not split
+    (16, 2048, 64 * 20, 9, 64, False),      # 256 blocks: one workgroup each, all of them
+    (1, 200, 64 * 70, 67, 64, True),
+    (3, 400, 64 * 40 - 5, 31, 64, True),
+])
+def test_attention_of_few_query_blocks_matches_the_oracle(H, n_q, C, n_sel, BK, fp8):
+    # at most 256 (head, query block) pairs: a block's tiles are split over wavefront groups and, with a workspace, over
+    # several workgroups whose fragments are combined; without one the same without fragments
+    rng = np.random.default_rng(H * 31 + n_sel)
+    g = torch.Generator(device="cuda").manual_seed(n_sel)
+    Q, K, V = (torch.randn(H, n, 128, device="cuda", generator=g).bfloat16() for n in (n_q, C, C))
+    if not fp8:
+        Q[:, ::5] *= 3.0                                       # some peaked rows
+    cnt = torch.randint(1, 6, (H, C), device="cuda", generator=g, dtype=torch.int32)
+    lens = np.full(H, C, np.int32)
+    n_qb, n_kb = -(-n_q // 128), -(-C // BK)
+    sel = np.stack([np.stack([np.sort(rng.choice(n_kb, n_sel, replace=False)) for _ in range(n_qb)]) for _ in range(H)]).astype(np.int32)
+    nsel = np.full((H, n_qb), n_sel, np.int32)
+    nsel[0, 0] = n_sel - n_sel // 3                            # a shorter list than the launch provides for
+    sel[0, 0, nsel[0, 0]:] = -1
+    if n_qb > 1:
+        nsel[-1, 1], nsel[-1, 0] = 1, 0                        # one entry, none
+        sel[-1, 1, 1:], sel[-1, 0, :] = -1, -1
+    if H > 2:
+        lens[1] = 0
+    ws = torch.empty(fa.workspace_bytes(fa.OP_ATTN, H, n_q, C), dtype=torch.uint8, device="cuda")
+    ws.fill_(0xFF)                                             # fragments are written before they are read
+    if fp8:
+        cache = fa.Cache.empty(H, C, 128, 32, torch.bfloat16)
+        cache.K.copy_(K), cache.V.copy_(V), cache.len.copy_(to_dev(lens)), cache.stamp.zero_()
+        kv8 = fa.kv8_empty(H, C, 128)
+        fa.kv_to_fp8(cache, *kv8)
+        run = lambda w: fa.sparse_attn_fwd_fp8(Q, *kv8, cnt, to_dev(lens), C, to_dev(sel), to_dev(nsel), 128, BK, 128 ** -0.5, ws=w)  # noqa: E731
+    else:
+        run = lambda w: fa.sparse_attn_fwd(Q, K, V, cnt, to_dev(lens), to_dev(sel), to_dev(nsel), 128, BK, 128 ** -0.5, ws=w)  # noqa: E731
+    outs = [tuple(to_host(x) for x in run(w)) for w in (ws, None)]
+    sync()
+    if fp8:
+        O_r, lse_r = oracle.sparse_attn_fwd_fp8(to_host(Q), to_host(kv8[0]), to_host(kv8[1]), to_host(cnt), lens, C, sel, nsel, 128,
+                                                64, 128 ** -0.5)
+    else:
+        O_r, lse_r = oracle.sparse_attn_fwd(to_host(Q), to_host(K), to_host(V), to_host(cnt), lens, sel, nsel, 128, BK, 128 ** -0.5)
+    # bf16: the rounding of P and of the output.  8-bit copy: the weights' rounding to E4M3, the bound of test_gpu_fp8.py
+    tol, tol_lse = (0.1, 0.05) if fp8 else (ATOL["bf16"], 2e-2)
+    errs = []
+    for O, lse in outs:
+        errs.append(np.abs(to_f32(O).astype(np.float64) - O_r))
+        assert errs[-1].max() <= tol
+        fin = np.isfinite(lse_r)
+        assert np.array_equal(fin, np.isfinite(lse)) and np.abs(lse[fin] - lse_r[fin]).max() <= tol_lse
+    rms = [np.sqrt((e ** 2).mean()) for e in errs]
+    assert 0.8 <= rms[0] / rms[1] <= 1.25, rms   # splitting a list loses no precision
