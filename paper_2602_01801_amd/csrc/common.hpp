@@ -58,12 +58,17 @@ __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
 }
 
 // ---- quantiser of the ANN code ----------------------------------------------------------------------
-// One float32 multiply, round half to even, saturate to [-127, 127].
-__device__ __forceinline__ int quant8(float x, float qscale) {
-    float p = __fmul_rn(x, qscale);
-    float q = rintf(p);
-    q = fminf(fmaxf(q, -127.0f), 127.0f);
-    return (int)q;
+// One float32 multiply, round half to even, saturate to [-127, 127]; four values as packed bytes.  The saturation comes
+// first (its bounds are whole numbers, so the order does not matter; a NaN becomes -127); the rounding is the addition of
+// 1.5 * 2^23, after which the low byte of the float's bits is the rounded value: three instructions per value and three
+// byte selections per word, where round, two-sided clamp, conversion and packing took seven per value.
+__device__ __forceinline__ unsigned quant8x4(float x0, float x1, float x2, float x3, float qscale) {
+    const float x[4] = {x0, x1, x2, x3};
+    unsigned u[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        u[e] = __float_as_uint(__fadd_rn(__builtin_amdgcn_fmed3f(__fmul_rn(x[e], qscale), -127.0f, 127.0f), 12582912.0f));
+    return __builtin_amdgcn_perm(u[1], u[0], 0x0C0C0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000C0Cu);
 }
 __device__ __forceinline__ unsigned pack_i8x4(int a, int b, int c, int d) {
     return (unsigned)(a & 0xFF) | ((unsigned)(b & 0xFF) << 8) | ((unsigned)(c & 0xFF) << 16) | ((unsigned)(d & 0xFF) << 24);

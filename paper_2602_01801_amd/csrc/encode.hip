@@ -5,8 +5,7 @@
 // HBM-bound: d*es bytes in, r bytes out per vector; the d x r contraction (2*d*r integer ops per
 // vector) runs on the int8 matrix cores so that it stays off the critical path.  One wavefront owns
 // 16 vectors at a time: B operand = their quantised coordinates (column = vector), A operand = R^T
-// (row = code coordinate), accumulator row 4*(lane/16)+v / column lane%16, so a lane ends up with 4
-// consecutive code bytes of one vector and stores them as one dword.
+// (rows = code coordinates, encode_dev.hpp), so a lane ends up with r / 4 consecutive code bytes of one vector.
 #include "encode_dev.hpp"
 
 namespace fastar {
@@ -17,7 +16,6 @@ __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x,
                                                      int8_t *__restrict__ code, unsigned long long *zero_fill,
                                                      int64_t zero_n) {
     constexpr int KS = D / 64;   // k-steps of 64 coordinates
-    constexpr int CB = R / 16;   // blocks of 16 code coordinates
     const int lane = lane_id();
     const int col = lane & 15, g = lane >> 4;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -37,12 +35,11 @@ __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x,
         const int64_t vload = vec < n_vec ? vec : n_vec - 1;
         const char *row = (const char *)x + (size_t)vload * row_bytes;
         i32x4 b[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) b[ks] = load_quantised<BF16>(row, ks, g, qscale);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const unsigned w = cm.code_word(b, cb, shift);
-            if (vec < n_vec) *(unsigned *)(code + vec * R + cb * 16 + 4 * g) = w;
+        load_quantised<BF16, D>(row, g, qscale, b);
+        const auto w = cm.code_words(b, shift);
+        if (vec < n_vec) {
+            if (((uintptr_t)code & 15) == 0) cm.store(code + vec * R, w, lane);   // uniform
+            else cm.template store<true>(code + vec * R, w, lane);                // the entry point asks for 4-byte alignment
         }
     }
 }
@@ -79,12 +76,13 @@ int encode_launch(const void *x, int dtype, int64_t n_vec, int d, const fastar_c
 }
 
 // ---- codes of 2 or 4 bits per entry, packed (appendix, "Quantization precision for ANN matching") -------------------
-// Same operands as encode_kernel; a lane ends with four entries of one vector = BITS / 2 bytes.
+// Same operands as encode_kernel; a lane ends with eight entries of one vector = BITS bytes.
 template <bool BF16, int D, int R, int BITS>
 __global__ __launch_bounds__(256) void encode_packed_kernel(const void *__restrict__ x, int64_t n_vec,
                                                             const int8_t *__restrict__ Rm, float qscale, int shift,
                                                             uint8_t *__restrict__ packed) {
-    constexpr int KS = D / 64, CB = R / 16;
+    static_assert(R == 32, "eight entries per lane");
+    constexpr int KS = D / 64;
     constexpr int ROWB = R * BITS / 8;
     const int lane = lane_id();
     const int col = lane & 15, g = lane >> 4;
@@ -99,16 +97,12 @@ __global__ __launch_bounds__(256) void encode_packed_kernel(const void *__restri
         const int64_t vload = vec < n_vec ? vec : n_vec - 1;
         const char *row = (const char *)x + (size_t)vload * row_bytes;
         i32x4 b[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) b[ks] = load_quantised<BF16>(row, ks, g, qscale);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const unsigned w = cm.template code_bits<BITS>(b, cb, shift);
-            if (vec < n_vec) {
-                uint8_t *dst = packed + vec * ROWB + (cb * 16 + 4 * g) * BITS / 8;
-                if (BITS == 4) *(unsigned short *)dst = (unsigned short)w;
-                else *dst = (uint8_t)w;
-            }
+        load_quantised<BF16, D>(row, g, qscale, b);
+        const unsigned w = cm.template code_bits<BITS>(b, shift);
+        if (vec < n_vec) {
+            uint8_t *dst = packed + vec * ROWB + g * BITS;
+            if (BITS == 4) *(unsigned *)dst = w;
+            else *(unsigned short *)dst = (unsigned short)w;
         }
     }
 }
@@ -147,8 +141,7 @@ __global__ __launch_bounds__(256) void encode_sign_kernel(const void *__restrict
         const int64_t vload = vec < n_vec ? vec : n_vec - 1;
         const char *row = (const char *)x + (size_t)vload * row_bytes;
         i32x4 b[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) b[ks] = load_quantised<BF16>(row, ks, g, qscale);
+        load_quantised<BF16, D>(row, g, qscale, b);
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             unsigned word = 0;

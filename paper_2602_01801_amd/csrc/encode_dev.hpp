@@ -2,8 +2,8 @@
 // match kernel that encodes its own probes:
 //   xq = clamp(rint(x * qscale), +-127);  y = R^T xq (int32);  c = clamp((y + 2^(sh-1)) >> sh, +-127)
 // One wavefront owns 16 vectors at a time: B operand = their quantised coordinates (column = vector), A operand =
-// R^T (row = code coordinate), accumulator row 4*(lane/16)+v / column lane%16, so a lane ends up with 4
-// consecutive code bytes of one vector.
+// R^T (rows = code coordinates), accumulator row 4*(lane/16)+v / column lane%16, so a lane ends up with 4 entries per
+// block of 16 rows of one vector's code.
 #pragma once
 #include "common.hpp"
 
@@ -17,78 +17,125 @@ __device__ __forceinline__ int slot_coord(int ks, int g, int e) {
     return ks * 64 + (e >> 2) * 16 + 4 * g + (e & 3);
 }
 
-// Quantised coordinates of one vector for k-step ks, as the 16 int8 k-slots of this lane.
-template <bool BF16>
-__device__ __forceinline__ i32x4 load_quantised(const void *row, int ks, int g, float qscale) {
-    i32x4 out;
-    if (BF16) {
-        const unsigned short *p = (const unsigned short *)row;
+// One lane's coordinates of one vector: raw bits while its loads are in flight, then the 16 int8 k-slots of every k-step.
+template <bool BF16, int D>
+struct RawVector {
+    static constexpr int N = BF16 ? 2 : 4;   // 16-byte loads per k-step
+    u32x4 w[D / 64][N];
+    __device__ __forceinline__ void load(const void *row, int g) {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            u32x4 w = *(const u32x4 *)(p + ks * 64 + m * 32 + 8 * g);
-            int q[8];
+        for (int ks = 0; ks < D / 64; ++ks)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                q[2 * e] = quant8(bf16_lo(w[e]), qscale);
-                q[2 * e + 1] = quant8(bf16_hi(w[e]), qscale);
-            }
-            out[2 * m] = (int)pack_i8x4(q[0], q[1], q[2], q[3]);
-            out[2 * m + 1] = (int)pack_i8x4(q[4], q[5], q[6], q[7]);
-        }
-    } else {
-        const float *p = (const float *)row;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            f32x4 w = *(const f32x4 *)(p + ks * 64 + m * 16 + 4 * g);
-            out[m] = (int)pack_i8x4(quant8(w[0], qscale), quant8(w[1], qscale), quant8(w[2], qscale), quant8(w[3], qscale));
-        }
+            for (int m = 0; m < N; ++m)
+                w[ks][m] = BF16 ? *(const u32x4 *)((const unsigned short *)row + ks * 64 + m * 32 + 8 * g)
+                                : *(const u32x4 *)((const float *)row + ks * 64 + m * 16 + 4 * g);
     }
-    return out;
+    __device__ __forceinline__ void quantise(float qscale, i32x4 (&out)[D / 64]) const {
+#pragma unroll
+        for (int ks = 0; ks < D / 64; ++ks)
+#pragma unroll
+            for (int m = 0; m < N; ++m) {
+                const u32x4 x = w[ks][m];
+                if (BF16) {
+                    out[ks][(2 * m) & 3] = (int)quant8x4(bf16_lo(x[0]), bf16_hi(x[0]), bf16_lo(x[1]), bf16_hi(x[1]), qscale);
+                    out[ks][(2 * m + 1) & 3] = (int)quant8x4(bf16_lo(x[2]), bf16_hi(x[2]), bf16_lo(x[3]), bf16_hi(x[3]), qscale);
+                } else {
+                    out[ks][m] = (int)quant8x4(__uint_as_float(x[0]), __uint_as_float(x[1]), __uint_as_float(x[2]),
+                                               __uint_as_float(x[3]), qscale);
+                }
+            }
+    }
+};
+// Quantised coordinates of one vector, loaded at once.
+template <bool BF16, int D>
+__device__ __forceinline__ void load_quantised(const void *row, int g, float qscale, i32x4 (&out)[D / 64]) {
+    RawVector<BF16, D> v;
+    v.load(row, g);
+    v.quantise(qscale, out);
 }
 
-__device__ __forceinline__ int requant(int y, int shift) {
-    int c = (y + (1 << (shift - 1))) >> shift;  // arithmetic shift = floor division
-    return min(max(c, -127), 127);
-}
-
-// A operand of one wavefront: rows of R^T for every (k-step of 64 coordinates, block of 16 code coordinates).
+// A operand of one wavefront: rows of R^T for every (k-step of 64 coordinates, block of CB rows).  Row i of block cb is
+// code coordinate CB * i + cb: a lane's CB rows are then neighbours in a row of R, which one load of CB bytes brings
+// (byte loads, 64 of them per lane at d = 128 and r = 32, were most of what an encode launch issued), and the results of
+// a lane's CB blocks interleave to 4 * CB consecutive code coordinates.
 template <bool BF16, int D, int R>
 struct CodeMatrix {
     static constexpr int KS = D / 64, CB = R / 16;
+    static_assert(CB == 2 || CB == 4, "R = 32 or 64");
     i32x4 a[KS][CB];
     __device__ __forceinline__ void load(const int8_t *__restrict__ Rm, int lane) {
         const int col = lane & 15, g = lane >> 4;
+        const bool aligned = ((uintptr_t)Rm & (CB - 1)) == 0;   // uniform
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int ks = 0; ks < KS; ++ks) {
+            unsigned w[16];   // CB neighbouring entries of 16 coordinates
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                int b[16];
+            for (int e = 0; e < 16; ++e) {
+                const int8_t *p = Rm + slot_coord<BF16>(ks, g, e) * R + CB * col;
+                if (aligned) {
+                    w[e] = CB == 2 ? (unsigned)*(const unsigned short *)p : *(const unsigned *)p;
+                } else {
+                    w[e] = 0u;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) b[e] = Rm[slot_coord<BF16>(ks, g, e) * R + cb * 16 + col];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) a[ks][cb][m] = (int)pack_i8x4(b[4 * m], b[4 * m + 1], b[4 * m + 2], b[4 * m + 3]);
+                    for (int cb = 0; cb < CB; ++cb) w[e] |= (unsigned)(uint8_t)p[cb] << (8 * cb);
+                }
             }
-    }
-    // Code bytes cb*16 + 4*(lane/16) .. +3 of the vector whose quantised coordinates are b (column lane%16).
-    __device__ __forceinline__ unsigned code_word(const i32x4 (&b)[KS], int cb, int shift) const {
-        i32x4 acc = {0, 0, 0, 0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_16x16x64(a[ks][cb], b[ks], acc);
-        return pack_i8x4(requant(acc[0], shift), requant(acc[1], shift), requant(acc[2], shift), requant(acc[3], shift));
-    }
-    // The same four entries at BITS (2 or 4) bits each, saturated to +-(2^(BITS-1) - 1), entry v in bits [BITS*v, +BITS).
-    template <int BITS>
-    __device__ __forceinline__ unsigned code_bits(const i32x4 (&b)[KS], int cb, int shift) const {
-        i32x4 acc = {0, 0, 0, 0};
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_16x16x64(a[ks][cb], b[ks], acc);
-        constexpr int LIM = (1 << (BITS - 1)) - 1;
-        unsigned w = 0;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int c = min(max((acc[v] + (1 << (shift - 1))) >> shift, -LIM), LIM);
-            w |= ((unsigned)c & ((1u << BITS) - 1u)) << (BITS * v);
+                for (int m = 0; m < 4; ++m)
+                    a[ks][cb][m] = (int)pack_i8x4((int)(w[4 * m] >> (8 * cb)), (int)(w[4 * m + 1] >> (8 * cb)),
+                                                  (int)(w[4 * m + 2] >> (8 * cb)), (int)(w[4 * m + 3] >> (8 * cb)));
         }
+    }
+    // Entries 4 * CB * (lane / 16) .. of the code of the vector whose quantised coordinates are b (column lane % 16),
+    // saturated to +-lim; f(i, c) takes entry i of them.
+    template <class F>
+    __device__ __forceinline__ void entries(const i32x4 (&b)[KS], int shift, int lim, F &&f) const {
+        i32x4 acc[CB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            acc[cb] = i32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc[cb] = mfma_i8_16x16x64(a[ks][cb], b[ks], acc[cb]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                f(CB * v + cb, min(max((acc[cb][v] + (1 << (shift - 1))) >> shift, -lim), lim));   // floor division
+    }
+    // The same as bytes: 4 * CB consecutive ones.
+    struct Words {
+        unsigned w[CB];
+    };
+    __device__ __forceinline__ Words code_words(const i32x4 (&b)[KS], int shift) const {
+        int c[4 * CB];
+        entries(b, shift, 127, [&](int i, int v) { c[i] = v; });
+        Words out;
+#pragma unroll
+        for (int k = 0; k < CB; ++k) out.w[k] = pack_i8x4(c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]);
+        return out;
+    }
+    // ... stored as this lane's part of a row of R bytes (16-byte aligned rows unless WORDS: 4-byte aligned ones)
+    template <bool WORDS = false>
+    __device__ static __forceinline__ void store(int8_t *row, const Words &x, int lane) {
+        unsigned *dst = (unsigned *)(row + 4 * CB * (lane >> 4));
+        if (WORDS) {
+#pragma unroll
+            for (int k = 0; k < CB; ++k) dst[k] = x.w[k];
+        } else if (CB == 2) {
+            *(u32x2 *)dst = u32x2{x.w[0], x.w[1]};
+        } else {
+            *(u32x4 *)dst = u32x4{x.w[0], x.w[1], x.w[2 & (CB - 1)], x.w[3 & (CB - 1)]};
+        }
+    }
+    // The same entries at BITS (2 or 4) bits each, saturated to +-(2^(BITS-1) - 1), entry i in bits [BITS*i, +BITS).
+    template <int BITS>
+    __device__ __forceinline__ unsigned code_bits(const i32x4 (&b)[KS], int shift) const {
+        static_assert(4 * CB * BITS <= 32, "one word");
+        unsigned w = 0;
+        entries(b, shift, (1 << (BITS - 1)) - 1, [&](int i, int v) { w |= ((unsigned)v & ((1u << BITS) - 1u)) << (BITS * i); });
         return w;
     }
 };

@@ -218,6 +218,9 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
 // their rows while the window's loads are in flight, leaves the codes in ck for the apply step, and clears the
 // eviction plan's scratch words (ps_all) for the launches behind it.
 constexpr int WIN_THREADS = 512;
+// dynamic LDS of the window kernel; with the static arrays of its largest instantiation with 64 tokens per workgroup
+// (r = 64, fused verify: 8.9 KB) it stays within the 160 KB of a compute unit
+constexpr size_t WINDOW_LDS_MAX = 148 * 1024;
 // What the fused tail of the window kernel needs from the verify step (defined further down).
 template <bool BF16, int D>
 struct VerifyRows;
@@ -225,7 +228,7 @@ constexpr int AGE_BINS = 1024;
 template <int UN>
 __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp,
                                                     int C, int n_new, int frame_id, unsigned *__restrict__ ps,
-                                                    int hist_word, int fut_word, unsigned *lhist);
+                                                    int hist_word, int fut_word, unsigned *lhist, int part, int n_parts);
 struct VerifyArgs {   // the verify step's arguments, for the launch that runs it as its tail
     const void *K;
     int tau2_q16;
@@ -236,22 +239,28 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 
 // With VERIFY (workspaces that every call leaves clean, see tempcache_compress) the kernel is the verify step too: once
 // the arg-max of its 64 tokens is final it runs the cosine test for them and registers the joiners; nothing is cleared
-// here (records and plan scratch are clean on entry), and every workgroup adds its slice of the age histogram.
-// TOKS: tokens per workgroup.  64 (two groups of 32 tokens, four wavefronts share each group's window scan) when the
-// call is latency-bound; 256 (eight groups, one wavefront scans the whole window for its group) when there are many
-// more workgroups than the chip holds at once: staging the window is then paid a quarter as often.
+// here (records and plan scratch are clean on entry).  The age histogram the plan wants is counted beside the match: by
+// workgroups of its own at the end of the grid's x range (n_hist of them; behind the match it cost every workgroup 2 us),
+// with 256 tokens per workgroup, where the grid fills the chip, by every workgroup as its tail (n_hist = 0).
+// TOKS: tokens per workgroup.  64 (eight wavefronts share the window scan) when the call is latency-bound; 256 (two
+// wavefronts share the scan for their 64 tokens) when there are many more workgroups than the chip holds at once:
+// staging the window is then paid a quarter as often.
+//
+// What bounds it: the chain of dependent phases of one workgroup (list, sort and staging, encode, scan, look-up, threshold
+// test).  The window's code rows are gathered straight from the list, before its order is known: they are in flight while
+// the ids are ranked.  Mean per phase at 12 heads x 1560 tokens and candidates (timestamps inside the kernel, us): list,
+// sort and staging 10.4 -> 9.7, scan 1.9 -> 1.4, look-up 2.1 -> 1.3, histogram 2.1 -> 0; launch 26 -> 20.
+// The scan was bound by the matrix units (two products per score) and the LDS (a group's codes and penalties, 5 KB, read
+// for 32 tokens): one product, and 64 or 128 tokens per read; 256 tokens x 3600 candidates 18 -> 9 us, launch at
+// 40 heads x 3600 tokens 113 -> 92.
 template <int R, bool ENC, bool BF16, int D, bool VERIFY, int TOKS>
-__global__ __launch_bounds__(WIN_THREADS) void tc_match_window_kernel(const int8_t *__restrict__ code,
-                                                              const int32_t *__restrict__ len, int C,
-                                                              const int8_t *__restrict__ cp, int n_new,
-                                                              const int32_t *__restrict__ cand, int n_cand, int metric,
-                                                              int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
-                                                              u64 *__restrict__ win, int32_t *__restrict__ grp,
-                                                              const void *__restrict__ K_new,
-                                                              const int8_t *__restrict__ Rm, float qscale, int shift,
-                                                              int8_t *__restrict__ ck, unsigned *__restrict__ ps_all,
-                                                              int ps_words, VerifyArgs va) {
+__global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc_match_window_kernel(
+    const int8_t *__restrict__ code, const int32_t *__restrict__ len, int C, const int8_t *__restrict__ cp, int n_new,
+    const int32_t *__restrict__ cand, int n_cand, int metric, int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
+    u64 *__restrict__ win, int32_t *__restrict__ grp, const void *__restrict__ K_new, const int8_t *__restrict__ Rm,
+    float qscale, int shift, int8_t *__restrict__ ck, unsigned *__restrict__ ps_all, int ps_words, int n_hist, VerifyArgs va) {
     static_assert(!VERIFY || ENC, "the fused verify step reads the probe codes this kernel encoded");
+    static_assert(TOKS == 64 || TOKS == 256, "one pair of token groups, or four");
     constexpr int KS = R / 32;
     constexpr int NCH = R / 16;  // 16-byte chunks per code
     extern __shared__ __attribute__((aligned(16))) unsigned char wlds[];
@@ -259,397 +268,379 @@ __global__ __launch_bounds__(WIN_THREADS) void tc_match_window_kernel(const int8
     i32x4 *ccode = (i32x4 *)wlds;                       // [NCH][n_pad]
     int *cslot = (int *)(wlds + (size_t)NCH * n_pad * 16);  // [n_pad]
     int *cpen = cslot + n_pad;                          // [n_pad]
-    constexpr int TG = TOKS / 32;                  // groups of 32 tokens
-    constexpr int SPLIT = (WIN_THREADS / 64) / TG; // wavefronts sharing one group of 32 tokens, each on its share of the window
-    static_assert(TG * SPLIT == WIN_THREADS / 64 && (TOKS == 64 || TOKS % 128 == 0), "token groups times window shares = wavefronts");
-    __shared__ u64 partbest[SPLIT][TG][32];
+    constexpr int NG = TOKS >= 256 ? 4 : 2;             // groups of 32 tokens a wavefront scans the window for
+    constexpr int TQ = TOKS / (32 * NG);                // such sets of groups
+    constexpr int SPLIT = (WIN_THREADS / 64) / TQ;      // wavefronts sharing one set, each on its share of the window
+    // partial arg-maxima of the scan; R before it, the verify hand-over and the age histogram after it
+    __shared__ __attribute__((aligned(16))) u64 partbest[SPLIT][TOKS];
+    static_assert(sizeof(partbest) >= AGE_BINS * sizeof(unsigned), "the histogram fits");
+    const int n_tok_wgs = (int)gridDim.x - n_hist;
+    if (VERIFY && (int)blockIdx.x >= n_tok_wgs) {       // uniform
+        age_histogram_slice<4>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)blockIdx.y * ps_words, va.hist_word,
+                               va.fut_word, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs, n_hist);
+        return;
+    }
     const int h = blockIdx.y;
     const int L = min(len[h], C);
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int col = lane & 31, g2 = lane >> 5;
-    const int tg = wave % TG, ch = wave / TG;
+    const int tq = wave % TQ, ch = wave / TQ;
     const int8_t *ch_code = code + (size_t)h * C * R;
-    // Tokens of this workgroup: [t0, t1).  64 tokens: its block.  256: an equal share of the frame (whole groups of 32
-    // tokens), taken in blocks of 256 once the window is staged; the launcher sizes the grid so that no share is empty.
-    const int per = TOKS < 256 ? TOKS : ((((n_new + (int)gridDim.x - 1) / (int)gridDim.x) + 31) & ~31);
-    const int t0 = min((int)blockIdx.x * per, n_new), t1 = min(t0 + per, n_new);
-    __shared__ __attribute__((aligned(16))) int8_t pcode[ENC ? TOKS * R : 16];
-    i32x4 bfrag[KS];
-    CodeMatrix<BF16, D, R> cm;
-    // encoding: 16 tokens per wavefront and round; 64 tokens: wavefronts 0..3 once, 256 tokens: all eight twice
-    constexpr int EROUNDS = TOKS >= 128 ? TOKS / 128 : 1;
-    const bool enc_wave = ENC && (TOKS >= 128 || wave < 4);
-    i32x4 xq[EROUNDS][D / 64];
-    if (ENC && !VERIFY)
-        for (int k = blockIdx.x * WIN_THREADS + tid; k < ps_words; k += gridDim.x * WIN_THREADS) ps_all[(size_t)h * ps_words + k] = 0u;
-    if (enc_wave) cm.load(Rm, lane);
-    // what a block of tokens needs before the window can be scanned for it: the rows to encode (ENC) or the probe
-    // codes (B operand); for the workgroup's first block these loads are in flight while the window is staged
-    auto load_block = [&](int base) {   // base: first token of the block
-        if (enc_wave) {
-#pragma unroll
-            for (int er = 0; er < EROUNDS; ++er) {
-                const int etok = base + 16 * (wave + 8 * er) + (lane & 15);  // token this lane helps to encode
-                const char *row = (const char *)K_new + ((size_t)h * n_new + min(etok, n_new - 1)) * (size_t)D * (BF16 ? 2 : 4);
-#pragma unroll
-                for (int ks = 0; ks < D / 64; ++ks) xq[er][ks] = load_quantised<BF16>(row, ks, lane >> 4, qscale);
-            }
-        } else if (!ENC) {
-            const int trow = min(base + tg * 32 + col, n_new - 1);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) bfrag[ks] = *(const i32x4 *)(cp + ((size_t)h * n_new + trow) * R + ks * 32 + 16 * g2);
-        }
-    };
-    load_block(t0);
     // The candidate list is a SET of slots and ties go to the smallest slot, so the window is staged in ascending
     // slot order without repeats: position order then is slot order, which is all the arg-max below needs.
-    //   1. every thread reads its entries of the list (ids outside [0, L) do not count) and whether the list already
-    //      ascends (then it is staged as it stands: equal neighbours are the same slot and change nothing);
-    //   2. otherwise the ids are sorted through a bitmap over the slot range they span, held where the codes will go
-    //      (several passes when the range is wider than that area): set bits, count per wavefront, expand in order;
-    //   3. the code rows of the sorted slots are gathered (one round of loads per batch, as before).
-    constexpr int CPT = 8;          // list entries per thread: the window holds at most 148 KB / (R + 8) < 3840 ids
-    constexpr int NOID = INT_MAX;   // key of an id that does not count
-    __shared__ int s_flag, s_min, s_max, s_wtot[WIN_THREADS / 64];
+    //   1. every thread reads its entries of the list (ids outside [0, L) do not count) and asks for their code rows;
+    //   2. the ids are ranked through a bitmap over the slots, held where the codes will go (several passes when the
+    //      cache is longer than that area): set bits, prefix counts per word, rank = prefix + bits below;
+    //   3. the rows go to their ranks (repeats write the same row to the same place), candidates whose penalty |code|^2 is
+    //      odd before the others: a score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus one for an odd
+    //      penalty, so with the odd ones first the earliest position that reaches the largest T is the one wanted, and the
+    //      scan needs one matrix product instead of two.
+    constexpr int CPT = ((int)(WINDOW_LDS_MAX / (R + 8)) + WIN_THREADS - 1) / WIN_THREADS;   // list entries per thread
+    // of them, rows in flight while the ids are ranked (registers); the rows beyond are loaded when their ranks are known
+    constexpr int PF = R == 32 ? (TOKS >= 256 ? CPT : BF16 ? 4 : 2) : 2;
+    // R by way of LDS, where it fits: a coalesced load per thread now, the operand's pieces from LDS later
+    constexpr bool RM_LDS = ENC && (size_t)D * R <= sizeof(partbest);
+    const bool rm_lds = RM_LDS && ((uintptr_t)Rm & 7) == 0;   // uniform
+    u64 rm_part = 0;
+    if (rm_lds && tid < D * R / 8) rm_part = ((const u64 *)Rm)[tid];
     int ce[CPT];
     {
-        bool descends = false;
-        int vmin = NOID, vmax = -1;
         const int32_t *ch_cand = cand + (size_t)h * n_cand;
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
             const int p = k * WIN_THREADS + tid;
-            int v = NOID, before = -1;
-            if (p < n_cand) {
-                const int x = ch_cand[p];
-                if (x >= 0 && x < L) v = x;
-                if (p > 0) {
-                    const int y = ch_cand[p - 1];
-                    before = (y >= 0 && y < L) ? y : NOID;
-                }
-            }
-            ce[k] = v;
-            descends |= before > v;
-            if (v != NOID) {
-                vmin = min(vmin, v);
-                vmax = max(vmax, v);
-            }
+            ce[k] = p < n_cand ? ch_cand[p] : -1;
         }
-        if (tid == 0) {
-            s_flag = 0;
-            s_min = NOID;
-            s_max = -1;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            vmin = min(vmin, shfl_xor(vmin, off));
-            vmax = max(vmax, shfl_xor(vmax, off));
-        }
-        const bool any_desc = __any(descends);
-        if (lane == 0) {
-            if (any_desc) atomicOr(&s_flag, 1);
-            if (vmax >= 0) {
-                atomicMin(&s_min, vmin);
-                atomicMax(&s_max, vmax);
-            }
-        }
-        __syncthreads();
     }
-    int n_u;   // staged candidates (positions 0 .. n_u-1 of cslot; uniform over the workgroup)
-    if (s_flag == 0) {
+    // Tokens of this workgroup: [t0, t1).  64 tokens: its block.  256: an equal share of the frame (whole groups of 32
+    // tokens), taken in blocks of 256 once the window is staged; the launcher sizes the grid so that no share is empty.
+    const int per = TOKS < 256 ? TOKS : ((((n_new + n_tok_wgs - 1) / n_tok_wgs) + 31) & ~31);
+    const int t0 = min((int)blockIdx.x * per, n_new), t1 = min(t0 + per, n_new);
+    __shared__ __attribute__((aligned(16))) int8_t pcode[ENC ? TOKS * R : 16];
+    CodeMatrix<BF16, D, R> cm;
+    // encoding: 16 tokens per wavefront and round; 64 tokens: wavefronts 0..3 once, 256 tokens: all eight twice
+    constexpr int EROUNDS = TOKS >= 128 ? TOKS / 128 : 1;
+    const bool enc_wave = ENC && (TOKS >= 128 || wave < 4);
+    RawVector<BF16, D> xr[EROUNDS];
+    if (ENC && !VERIFY)
+        for (int k = blockIdx.x * WIN_THREADS + tid; k < ps_words; k += gridDim.x * WIN_THREADS) ps_all[(size_t)h * ps_words + k] = 0u;
+    // the rows of a block of tokens to encode
+    auto load_block = [&](int base) {   // base: first token of the block
+#pragma unroll
+        for (int er = 0; er < EROUNDS; ++er) {
+            const int etok = base + 16 * (wave + 8 * er) + (lane & 15);  // token this lane helps to encode
+            xr[er].load((const char *)K_new + ((size_t)h * n_new + min(etok, n_new - 1)) * (size_t)D * (BF16 ? 2 : 4), lane >> 4);
+        }
+    };
+    constexpr bool EARLY = BF16 || TOKS == 64;   // the first block's rows in flight while the window is staged (registers)
+    if (EARLY && enc_wave) load_block(t0);
+    unsigned *bm = (unsigned *)wlds;             // bitmap of the slots, [words]
+    const int words = R * n_pad / 8;             // half of the code area; the words' prefix counts take the other half
+    unsigned *wpre = bm + words;
+    for (int w = tid; w < min((C + 31) >> 5, words); w += WIN_THREADS) bm[w] = 0u;
+    __shared__ int s_wtot[WIN_THREADS / 64];
+    __shared__ u64 s_odd[WAVE];                  // by rank in slot order: the candidates with an odd penalty
+    static_assert(WINDOW_LDS_MAX / (R + 8) <= 64 * WAVE, "one word of s_odd per lane");
+    if (tid < WAVE) s_odd[tid] = 0ull;
+    if (rm_lds && tid < D * R / 8) ((u64 *)partbest)[tid] = rm_part;
+#pragma unroll
+    for (int k = 0; k < CPT; ++k)
+        if (ce[k] < 0 || ce[k] >= L) ce[k] = -1;
+    i32x4 row[PF][NCH];
+#pragma unroll
+    for (int k = 0; k < PF; ++k)
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            i32x4 v = {0, 0, 0, 0};
+            if (ce[k] >= 0) v = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
+            row[k][c] = v;
+        }
+    int pos[CPT];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) pos[k] = -1;
+    int n_u = 0;   // staged candidates: positions 0 .. n_u-1 (uniform over the workgroup)
+    for (int lo = 0; lo < L; lo += 32 * words) {   // uniform; one pass unless the cache is long for the list
+        const int nw = min((L - lo + 31) >> 5, words);
+        if (lo > 0) {
+            __syncthreads();   // the ranks of the pass before have been read
+            for (int w = tid; w < nw; w += WIN_THREADS) bm[w] = 0u;
+        }
+        __syncthreads();
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
-            const int p = k * WIN_THREADS + tid;
-            if (p < n_pad) cslot[p] = ce[k] == NOID ? -1 : ce[k];
+            const int o = ce[k] - lo;
+            if (ce[k] >= lo && o < 32 * nw) atomicOr(&bm[o >> 5], 1u << (o & 31));
         }
-        n_u = n_cand;
         __syncthreads();
-    } else {
-        unsigned *bm = (unsigned *)wlds;                    // the code area: R * n_pad bytes
-        const int bm_bits = 8 * R * n_pad;
-        const int lo0 = s_min & ~31, hi = s_max + 1;
-        int base = 0;
-        for (int lo = lo0; lo < hi; lo += bm_bits) {       // uniform
-            const int nbits = min(hi - lo, bm_bits);
-            const int nw = (nbits + 31) >> 5;
-            for (int w = tid; w < nw; w += WIN_THREADS) bm[w] = 0u;
-            __syncthreads();
+        // a thread owns a run of consecutive words, an odd number of them (their addresses spread over the banks)
+        const int wpt = ((nw + WIN_THREADS - 1) / WIN_THREADS) | 1;
+        const int w0 = tid * wpt, w1 = min(w0 + wpt, nw);
+        int c = 0;
+        for (int w = w0; w < w1; ++w) c += __popc(bm[w]);
+        int incl = c;
 #pragma unroll
-            for (int k = 0; k < CPT; ++k) {
-                const int v = ce[k];
-                if (v != NOID && v >= lo && v - lo < nbits) atomicOr(&bm[(v - lo) >> 5], 1u << ((v - lo) & 31));
-            }
-            __syncthreads();
-            // a wavefront owns a contiguous run of words, its lanes take them 64 at a time
-            const int wpw = (nw + WIN_THREADS / 64 - 1) / (WIN_THREADS / 64);
-            const int w0 = min(wave * wpw, nw), w1 = min(w0 + wpw, nw);
-            int c = 0;
-            for (int w = w0 + lane; w < w1; w += 64) c += __popc(bm[w]);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) c += shfl_xor(c, off);
-            if (lane == 0) s_wtot[wave] = c;
-            __syncthreads();
-            int pos = base, tot = 0;
-#pragma unroll
-            for (int ww = 0; ww < WIN_THREADS / 64; ++ww) {
-                const int t = s_wtot[ww];
-                if (ww < wave) pos += t;
-                tot += t;
-            }
-            for (int wb = w0; wb < w1; wb += 64) {         // uniform over the wavefront
-                const int w = wb + lane;
-                unsigned bits = w < w1 ? bm[w] : 0u;
-                const int mine = __popc(bits);
-                int incl = mine;
-#pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int o = __shfl_up(incl, off, WAVE);
-                    if (lane >= off) incl += o;
-                }
-                int q = pos + incl - mine;
-                while (bits) {
-                    cslot[q++] = lo + 32 * w + (__ffs(bits) - 1);
-                    bits &= bits - 1;
-                }
-                pos += __shfl(incl, 63, WAVE);
-            }
-            base += tot;
-            __syncthreads();   // the bitmap may be cleared again; cslot is complete after the last pass
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, WAVE);
+            if (lane >= off) incl += o;
         }
-        n_u = base;
+        if (lane == 63) s_wtot[wave] = incl;
+        __syncthreads();
+        int run = n_u + incl - c;
+#pragma unroll
+        for (int ww = 0; ww < WIN_THREADS / 64; ++ww) {
+            const int t = s_wtot[ww];
+            if (ww < wave) run += t;
+            n_u += t;
+        }
+        for (int w = w0; w < w1; ++w) {
+            wpre[w] = (unsigned)run;
+            run += __popc(bm[w]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            const int o = ce[k] - lo;
+            if (ce[k] >= lo && o < 32 * nw) pos[k] = (int)wpre[o >> 5] + __popc(bm[o >> 5] & ((1u << (o & 31)) - 1u));
+        }
     }
     const int n_stage = (n_u + 31) & ~31;   // <= n_pad
-    // Code rows in batches of independent loads, so a batch costs one memory round trip however many rows it holds.
-    constexpr int BATCH = 128 / R;  // candidates per thread and batch (32 code registers)
-    for (int p0 = 0; p0 < n_stage; p0 += WIN_THREADS * BATCH) {
-        int sl[BATCH];
+    // stable partition by the parity of the penalty (the parity of the number of odd entries)
+    auto row_of = [&](int k, i32x4 (&rw)[NCH]) {   // list entries whose rows were not prefetched
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int p = p0 + u * WIN_THREADS + tid;
-            sl[u] = p < n_u ? cslot[p] : -1;
-        }
-        i32x4 row[BATCH][NCH];
+        for (int c = 0; c < NCH; ++c) rw[c] = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
+    };
+    auto odd_penalty = [&](const i32x4 (&rw)[NCH]) -> bool {
+        unsigned x = 0;
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u)
+        for (int c = 0; c < NCH; ++c) x ^= (unsigned)(rw[c][0] ^ rw[c][1] ^ rw[c][2] ^ rw[c][3]);
+        return __popc(x & 0x01010101u) & 1;
+    };
+    if (metric == 0) {   // uniform
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                i32x4 v = {0, 0, 0, 0};
-                if (sl[u] >= 0) v = *(const i32x4 *)(ch_code + (size_t)sl[u] * R + c * 16);
-                row[u][c] = v;
+        for (int k = 0; k < CPT; ++k) {
+            if (k >= PF && n_cand <= k * WIN_THREADS) break;   // uniform
+            if (pos[k] < 0) continue;
+            bool odd;
+            if (k < PF) {
+                odd = odd_penalty(row[k < PF ? k : 0]);
+            } else {
+                i32x4 rw[NCH];
+                row_of(k, rw);
+                odd = odd_penalty(rw);
             }
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int p = p0 + u * WIN_THREADS + tid;
-            if (p < n_stage) {
-                int nn = 0;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    ccode[c * n_pad + p] = row[u][c];
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) nn = dot4_i8((unsigned)row[u][c][m], (unsigned)row[u][c][m], nn);
-                }
-                if (p >= n_u) cslot[p] = -1;
-                cpen[p] = sl[u] >= 0 ? (metric == 0 ? -nn : 0) : MATCH_NONE;  // minus the penalty
-            }
+            if (odd) atomicOr(&s_odd[pos[k] >> 6], 1ull << (pos[k] & 63));
         }
     }
-    __shared__ int vj[TOKS], vs[TOKS];
-    for (int base = t0; base < t1; base += TOKS) {
-    const int lim = min(base + TOKS, t1);   // this block's tokens: [base, lim)
-    const int tok = base + tg * 32 + col;
-    if (base != t0) {
-        __syncthreads();   // the previous block's probe codes and arg-maxima have been read
-        load_block(base);
+    __syncthreads();                        // the bitmap is dead: its memory takes the codes
+    int n_odd;
+    {
+        const u64 mine = s_odd[lane];
+        const int cnt_odd = __popcll(mine);
+        int incl = cnt_odd;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, WAVE);
+            if (lane >= off) incl += o;
+        }
+        n_odd = __shfl(incl, 63, WAVE);
+        const int excl = incl - cnt_odd;
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            if (n_cand <= k * WIN_THREADS) break;   // uniform
+            const int p = max(pos[k], 0);
+            const unsigned lo = __shfl((int)(unsigned)mine, p >> 6, WAVE), hi = __shfl((int)(unsigned)(mine >> 32), p >> 6, WAVE);
+            const u64 w = ((u64)hi << 32) | lo;
+            const int below = __shfl(excl, p >> 6, WAVE) + __popcll(w & ((1ull << (p & 63)) - 1ull));
+            if (pos[k] >= 0) pos[k] = (w >> (p & 63)) & 1ull ? below : n_odd + p - below;
+        }
+    }
+    auto stage_row = [&](int p, int slot, const i32x4 (&rw)[NCH]) {
+        int nn = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            ccode[c * n_pad + p] = rw[c];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) nn = dot4_i8((unsigned)rw[c][m], (unsigned)rw[c][m], nn);
+        }
+        cslot[p] = slot;
+        cpen[p] = slot < 0 ? MATCH_NONE : metric == 0 ? -((nn + 1) >> 1) : 0;  // minus half the penalty, rounded up
+    };
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        if (k >= PF && n_cand <= k * WIN_THREADS) break;   // uniform
+        if (pos[k] < 0) continue;
+        if (k < PF) {
+            stage_row(pos[k], ce[k], row[k < PF ? k : 0]);
+        } else {
+            i32x4 rw[NCH];
+            row_of(k, rw);
+            stage_row(pos[k], ce[k], rw);
+        }
+    }
+    if (tid < n_stage - n_u) {   // the ragged end of the last group of 32
+        const i32x4 none[NCH] = {};
+        stage_row(n_u + tid, -1, none);
     }
     if (enc_wave) {
+        if (rm_lds) cm.load((const int8_t *)partbest, lane);   // stored before the barriers above
+        else cm.load(Rm, lane);
+    }
+    for (int base = t0; base < t1; base += TOKS) {
+    const int lim = min(base + TOKS, t1);   // this block's tokens: [base, lim)
+    if (base != t0) __syncthreads();   // the previous block's probe codes and arg-maxima have been read
+    if (enc_wave) {
+        if (!EARLY || base != t0) load_block(base);
 #pragma unroll
         for (int er = 0; er < EROUNDS; ++er) {
             const int etok = base + 16 * (wave + 8 * er) + (lane & 15);
-#pragma unroll
-            for (int cb = 0; cb < R / 16; ++cb) {
-                const unsigned w = cm.code_word(xq[er], cb, shift);
-                *(unsigned *)(pcode + (16 * (wave + 8 * er) + (lane & 15)) * R + cb * 16 + 4 * (lane >> 4)) = w;
-                if (etok < lim) *(unsigned *)(ck + ((size_t)h * n_new + etok) * R + cb * 16 + 4 * (lane >> 4)) = w;
-            }
+            i32x4 xq[D / 64];
+            xr[er].quantise(qscale, xq);
+            const auto w = cm.code_words(xq, shift);
+            cm.store(pcode + (16 * (wave + 8 * er) + (lane & 15)) * R, w, lane);
+            if (etok < lim) cm.store(ck + ((size_t)h * n_new + etok) * R, w, lane);
         }
     }
     __syncthreads();
-    if (ENC) {
+    // Scan: the second operands of this wavefront's groups of 32 tokens.
+    i32x4 bfrag[NG][KS];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) bfrag[ks] = *(const i32x4 *)(pcode + (tg * 32 + col) * R + ks * 32 + 16 * g2);
-    }
+    for (int u = 0; u < NG; ++u)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int t = (tq * NG + u) * 32 + col;
+            bfrag[u][ks] = ENC ? *(const i32x4 *)(pcode + t * R + ks * 32 + 16 * g2)
+                               : *(const i32x4 *)(cp + ((size_t)h * n_new + min(base + t, n_new - 1)) * R + ks * 32 + 16 * g2);
+        }
     // Running arg-max of a lane over the 16 scores per group its accumulators hold: only the best score and the group
     // it came from are kept in the loop (a maximum tree and one compare-select per group; a later group replaces the
     // best only on a strictly higher score, so the earliest group wins among equals); which of the group's rows it was
-    // is looked up once, after the loop, by recomputing that group's 16 scores for this lane's token.
-    int bs = INT_MIN, bg = 0;
-    // a wavefront whose 32 tokens all lie beyond the block's end scans nothing (uniform over the wavefront)
-    const int n_groups = base + tg * 32 < lim ? n_stage / 32 : 0;
-    // squared distance: 2 * dot, the product is accumulated twice; inner product: the second product is with zero
-    i32x4 bfrag2[KS];
+    // is looked up once, after the loop, by recomputing that group's scores for the token.
+    int bs[NG], bg[NG];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bfrag2[ks][e] = metric == 0 ? bfrag[ks][e] : 0;
-    if constexpr (TOKS >= 256) {
-        // Long scans (one wavefront, the whole window): two groups of 32 candidates per step in three rotating operand
-        // sets, so that the reads of step t + 2, the matrix instructions of step t + 1 and the maxima of step t are in
-        // flight together (a wavefront issues in order: without the rotation its matrix and vector phases alternate).
-        // Steps past the end repeat the last group, which changes nothing: only a strictly higher score replaces the best.
-        constexpr int UNR = 2;
+    for (int u = 0; u < NG; ++u) {
+        bs[u] = INT_MIN;
+        bg[u] = 0;
+    }
+    // a wavefront whose tokens all lie beyond the block's end scans nothing (uniform over the wavefront)
+    const int n_groups = base + tq * NG * 32 < lim ? n_stage / 32 : 0;
+    {
+        // One group of 32 candidates per step in two rotating operand sets: the reads and matrix instructions of a step are
+        // issued before the maxima of the one before it (a wavefront issues in order: without the rotation its matrix and
+        // vector phases alternate).  Steps past the end repeat the last group, which changes nothing: only a strictly
+        // higher score replaces the best.
         struct ScanSet {
-            i32x4 a[UNR][KS];
-            i32x16 acc[UNR];
+            i32x4 a[KS];
+            i32x16 pen, acc[NG];
         };
-        const int n_it = n_groups > ch * UNR ? (n_groups - ch * UNR + SPLIT * UNR - 1) / (SPLIT * UNR) : 0;
-        auto group_of = [&](int it, int u) { return min((ch + it * SPLIT) * UNR + u, n_groups - 1); };
+        const int n_it = n_groups > ch ? (n_groups - ch + SPLIT - 1) / SPLIT : 0;
+        auto group_of = [&](int it) { return min(ch + it * SPLIT, n_groups - 1); };
         auto rd = [&](ScanSet &s, int it) {
+            const int gi = group_of(it);
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const int gi = group_of(it, u);
+            for (int ks = 0; ks < KS; ++ks) s.a[ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) s.a[u][ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
+            for (int q4 = 0; q4 < 4; ++q4) {   // minus the penalty of the accumulators' rows
+                const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {   // minus the penalty of the accumulator's rows
-                    const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s.acc[u][4 * q4 + e] = np[e];
-                }
+                for (int e = 0; e < 4; ++e) s.pen[4 * q4 + e] = np[e];
             }
         };
-        auto mm = [&](ScanSet &s) {
+        auto mm = [&](ScanSet &s) {   // the matrix unit subtracts the penalty
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
+            for (int u = 0; u < NG; ++u) s.acc[u] = mfma_i8_32x32x32(s.a[0], bfrag[u][0], s.pen);
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) s.acc[u] = mfma_i8_32x32x32(s.a[u][ks], bfrag[ks], s.acc[u]);
+            for (int ks = 1; ks < KS; ++ks)
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) s.acc[u] = mfma_i8_32x32x32(s.a[u][ks], bfrag2[ks], s.acc[u]);
-            }
+                for (int u = 0; u < NG; ++u) s.acc[u] = mfma_i8_32x32x32(s.a[ks], bfrag[u][ks], s.acc[u]);
         };
         auto red = [&](const ScanSet &s, int it) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                int mx = s.acc[u][0];
+            for (int u = 0; u < NG; ++u) {
+                int mx = max(s.acc[u][0], bs[u]);
 #pragma unroll
                 for (int v = 1; v < 16; ++v) mx = max(mx, s.acc[u][v]);
-                const bool better = mx > bs;
-                bs = better ? mx : bs;
-                bg = better ? group_of(it, u) : bg;
+                bg[u] = mx > bs[u] ? group_of(it) : bg[u];
+                bs[u] = mx;
             }
         };
         if (n_it > 0) {
-            ScanSet s0, s1, s2;
+            ScanSet s0, s1;
             rd(s0, 0);
-            rd(s1, 1);
             mm(s0);
-            for (int it = 0; it < n_it; it += 3) {
-                rd(s2, it + 2);
+            rd(s1, 1);
+            for (int it = 0; it < n_it; it += 2) {
                 mm(s1);
                 red(s0, it);
-                rd(s0, it + 3);
-                mm(s2);
-                red(s1, it + 1);
-                rd(s1, it + 4);
+                rd(s0, it + 2);
                 mm(s0);
-                red(s2, it + 2);
+                red(s1, it + 1);
+                rd(s1, it + 3);
             }
         }
-    } else {
-    // Four groups of 32 candidates per step, their operand reads and matrix instructions issued together
-    // (a group repeated at the ragged end changes nothing: only a strictly higher score replaces the best).
-    constexpr int UNR = 4;
-    for (int g0 = ch * UNR; g0 < n_groups; g0 += SPLIT * UNR) {
-        i32x4 afrag[UNR][KS];
-        i32x16 acc[UNR];
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const int gi = min(g0 + u, n_groups - 1);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) afrag[u][ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
-            // the accumulator starts from minus the penalty of its rows: the matrix unit does the subtraction
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[u][4 * q4 + e] = np[e];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc[u] = mfma_i8_32x32x32(afrag[u][ks], bfrag[ks], acc[u]);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc[u] = mfma_i8_32x32x32(afrag[u][ks], bfrag2[ks], acc[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            int mx = acc[u][0];
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = max(mx, acc[u][v]);
-            const bool better = mx > bs;
-            bs = better ? mx : bs;
-            bg = better ? min(g0 + u, n_groups - 1) : bg;
-        }
     }
-    }
-    u64 mybest = 0;
-    if (bs > MATCH_VALID) {   // some real candidate was seen: the earliest row of group bg that reaches the best score
-        i32x4 pc[NCH];
-        const int8_t *prow = ENC ? pcode + (tg * 32 + col) * R : cp + ((size_t)h * n_new + min(tok, n_new - 1)) * R;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
-        int pos = -1;
-#pragma unroll
-        for (int v = 15; v >= 0; --v) {
-            const int row = bg * 32 + 8 * (v >> 2) + 4 * g2 + (v & 3);
-            int dot = 0;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const i32x4 cc = ccode[c * n_pad + row];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) dot = dot4_i8((unsigned)cc[m], (unsigned)pc[c][m], dot);
-            }
-            const int S = (metric == 0 ? 2 * dot : dot) + cpen[row];
-            pos = S == bs ? row : pos;
-        }
-        if (pos >= 0) mybest = ((u64)(unsigned)(bs + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)pos);
-    }
-    {
-        const unsigned lo = shfl_xor((unsigned)mybest, 32), hi = shfl_xor((unsigned)(mybest >> 32), 32);
+    for (int u = 0; u < NG; ++u) {   // (best score, earliest group) as one word; 0: no real candidate was seen
+        u64 key = bs[u] > MATCH_VALID ? ((u64)(unsigned)(bs[u] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)bg[u]) : 0ull;
+        const unsigned lo = shfl_xor((unsigned)key, 32), hi = shfl_xor((unsigned)(key >> 32), 32);
         const u64 other = ((u64)hi << 32) | lo;
-        if (other > mybest) mybest = other;
+        if (other > key) key = other;
+        if (g2 == 0) partbest[ch][(tq * NG + u) * 32 + col] = key;
     }
-    if (g2 == 0) partbest[ch][tg][col] = mybest;
     __syncthreads();
-    if (ch == 0 && g2 == 0) {
-        int j = -1, S = 0;
-        if (tok < lim) {
+    {
+        // Look-up, TPT threads per token: the earliest row of the best group that reaches the best score.  The threads
+        // start at different rows: the groups' rows lie at multiples of 512 bytes, all on the same banks.
+        constexpr int TPT = WIN_THREADS / TOKS, ROWS = 32 / TPT;
+        const int t = tid / TPT, sub = tid % TPT, tok = base + t;
+        u64 best = partbest[0][t];
 #pragma unroll
-            for (int c = 1; c < SPLIT; ++c) {
-                const u64 other = partbest[c][tg][col];
-                if (other > mybest) mybest = other;
+        for (int c = 1; c < SPLIT; ++c) {
+            const u64 other = partbest[c][t];
+            if (other > best) best = other;
+        }
+        const bool seen = best != 0 && tok < lim;
+        const int T = (int)(unsigned)(best >> 32) - SCORE_BIAS;
+        int at = INT_MAX;
+        if (seen) {
+            i32x4 pc[NCH];
+            const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + tok) * R;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
+            const int row0 = (int)(0xFFFFFFFFu - (unsigned)best) * 32 + sub * ROWS;
+#pragma unroll
+            for (int v = 0; v < ROWS; ++v) {
+                const int rw = row0 + ((v + t) & (ROWS - 1));
+                int dot = 0;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const i32x4 cc = ccode[c * n_pad + rw];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) dot = dot4_i8((unsigned)cc[m], (unsigned)pc[c][m], dot);
+                }
+                if (dot + cpen[rw] == T) at = min(at, rw);
             }
-            if (mybest != 0) {
-                j = cslot[(int)(0xFFFFFFFFu - (unsigned)mybest)];   // position in the window -> slot
-                S = (int)(unsigned)(mybest >> 32) - SCORE_BIAS;
-                if (!VERIFY) {
+        }
+#pragma unroll
+        for (int off = 1; off < TPT; off <<= 1) at = min(at, shfl_xor(at, off));
+        if (sub == 0) {
+            const int j = seen ? cslot[at] : -1;   // position in the window -> slot
+            const int S = !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T;
+            if (tok < lim) {
+                if (!VERIFY && seen) {
                     win[(size_t)h * C + j] = 0;
                     grp[(size_t)h * C + j] = 0;
                 }
+                jstar[(size_t)h * n_new + tok] = j;
+                sbest[(size_t)h * n_new + tok] = S;
             }
-            jstar[(size_t)h * n_new + tok] = j;
-            sbest[(size_t)h * n_new + tok] = S;
-        }
-        if (VERIFY) {
-            vj[tg * 32 + col] = j;
-            vs[tg * 32 + col] = S;
+            // for the threshold test below; only this token's own threads (of this wavefront) have read the word
+            if (VERIFY) partbest[0][t] = ((u64)(unsigned)S << 32) | (u64)(unsigned)j;
         }
     }
     if constexpr (VERIFY) {
         __syncthreads();
         constexpr int NPASS = TOKS * 16 / WIN_THREADS;   // tokens per 16-lane group
-        constexpr int PB = TOKS >= 256 ? 8 : 2;          // passes whose rows are loaded together (registers)
+        constexpr int PB = TOKS >= 256 ? (BF16 ? 8 : 4) : 2;   // passes whose rows are loaded together (registers)
 #pragma unroll
         for (int p0 = 0; p0 < NPASS; p0 += PB) {
             VerifyRows<BF16, D> vr[PB];
@@ -657,33 +648,32 @@ __global__ __launch_bounds__(WIN_THREADS) void tc_match_window_kernel(const int8
             for (int pass = 0; pass < PB; ++pass) {   // every row this group will need, in one round of loads
                 const int t = (p0 + pass) * (WIN_THREADS / 16) + (tid >> 4);
                 const int i = min(base + t, n_new - 1);
-                vr[pass].load(va.K, K_new, pcode + t * R, R, C, n_new, metric, h, i, tid & 15, vj[t]);
+                vr[pass].load(va.K, K_new, pcode + t * R, R, C, n_new, metric, h, i, tid & 15, (int)(unsigned)partbest[0][t]);
             }
 #pragma unroll
             for (int pass = 0; pass < PB; ++pass) {
                 const int t = (p0 + pass) * (WIN_THREADS / 16) + (tid >> 4);
                 const int i = base + t;
                 if (i < lim)   // whole 16-lane groups
-                    vr[pass].decide(C, n_new, qscale, metric, va.tau2_q16, win, grp, va.merged, h, i, tid & 15, vj[t], vs[t]);
+                    vr[pass].decide(C, n_new, qscale, metric, va.tau2_q16, win, grp, va.merged, h, i, tid & 15,
+                                    (int)(unsigned)partbest[0][t], (int)(unsigned)(partbest[0][t] >> 32));
             }
         }
     }
     if constexpr (TOKS < 256) break;   // one block per workgroup: the grid covers the tokens (and the compiler sees no loop)
     }   // blocks of tokens
     if constexpr (VERIFY) {
-        __shared__ unsigned lhist[AGE_BINS];
-        __syncthreads();
-        age_histogram_slice<(TOKS >= 256 ? 20 : 4)>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)h * ps_words,
-                                                    va.hist_word, va.fut_word, lhist);
+        if (n_hist == 0) {   // uniform over the launch
+            __syncthreads();
+            age_histogram_slice<(TOKS >= 256 ? 20 : 4)>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)h * ps_words,
+                                                        va.hist_word, va.fut_word, (unsigned *)partbest, (int)blockIdx.x, n_tok_wgs);
+        }
     }
 }
 static size_t match_window_lds(int n_cand, int r) { return (size_t)((n_cand + 31) & ~31) * (size_t)(r + 8); }
-// dynamic LDS of the window kernel; with the static arrays of its largest instantiation (r = 64, fused verify: 10.6 KB)
-// it stays within the 160 KB of a compute unit
-constexpr size_t WINDOW_LDS_MAX = 148 * 1024;
-// static LDS of the wide (256 tokens per workgroup) instantiations: probe codes, verify hand-over, partial results,
-// age histogram, a few words; what is left of a compute unit's 160 KB is their window
-static constexpr size_t wide_window_lds_max(int r) { return (size_t)160 * 1024 - ((size_t)256 * r + 256 * 8 + 2048 + 4096 + 256); }
+// static LDS of the wide (256 tokens per workgroup) instantiations: probe codes, partial results, under 1 KB of small
+// arrays; what is left of a compute unit's 160 KB is their window
+static constexpr size_t wide_window_lds_max(int r) { return (size_t)160 * 1024 - ((size_t)256 * r + 4 * 256 * 8 + 1024); }
 template <int R, bool ENC, bool BF16, int D, bool VERIFY, int TOKS>
 static int allow_window_lds() {
     const size_t lim = TOKS == 64 ? WINDOW_LDS_MAX : wide_window_lds_max(R);
@@ -746,12 +736,12 @@ __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ be
 
 // Per head, a histogram of the live slots' ages (frame_id - stamp, 1024 bins, the last one collecting everything
 // older) for the eviction plan: the verify launch, a whole grid, reads the stamps, where the plan has few
-// workgroups per head.  Every workgroup of the launch adds its slice of the slots.  Called by whole workgroups.
+// workgroups per head.  The calling workgroup adds slice `part` of `n_parts` of the slots.  Called by whole workgroups.
 // UN: 16-byte loads per lane in flight before the first is used (a slice read in one round trip when it fits).
 template <int UN>
 __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp,
                                                     int C, int n_new, int frame_id, unsigned *__restrict__ ps,
-                                                    int hist_word, int fut_word, unsigned *lhist) {
+                                                    int hist_word, int fut_word, unsigned *lhist, int part, int n_parts) {
     const int h = blockIdx.y;
     const int L = min(len[h], C);
     if (hist_word < 0) return;   // uniform over the launch: the plan counts the ages itself
@@ -760,8 +750,8 @@ __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ 
     __syncthreads();
     // every workgroup takes a run of slots that starts on a multiple of four, four consecutive stamps per lane and load
     // (16 bytes when the head's row is aligned), four such loads in flight before the first is used
-    const int chunk = ((L + gridDim.x - 1) / gridDim.x + 3) & ~3;
-    const int j0 = min((int)blockIdx.x * chunk, L), j1 = min(j0 + chunk, L);
+    const int chunk = ((L + n_parts - 1) / n_parts + 3) & ~3;
+    const int j0 = min(part * chunk, L), j1 = min(j0 + chunk, L);
     const int32_t *st = stamp + (size_t)h * C;
     const bool vec = (((uintptr_t)st) & 15) == 0;
     bool future = false;
@@ -922,11 +912,12 @@ struct RowPiece {
     }
 };
 
+// Sum over the 16 lanes of a group (a row of the lane crossbar), in every lane; all 16 take part.
 __device__ __forceinline__ int group16_sum(int v) {
-    v += shfl_xor(v, 1);
-    v += shfl_xor(v, 2);
-    v += shfl_xor(v, 4);
-    v += shfl_xor(v, 8);
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);   // row_half_mirror: the other four of eight
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, false);   // row_mirror: the other eight of sixteen
     return v;
 }
 
@@ -958,7 +949,7 @@ __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__
     if (i < n_new) verify_token<BF16, D>(K, K_new, cp, r, C, n_new, qscale, metric, tau2_q16, jstar, sbest, win, grp,
                                          merged, h, i, l16);  // whole 16-lane groups
     age_histogram_slice<4>(len, stamp, C, n_new, frame_id, plan_scratch + (size_t)h * scratch_words, hist_word, fut_word,
-                        lhist);
+                        lhist, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Token i of head h, matched to slot j with code score W (j < 0: no candidate); cprow = the token's probe code.
@@ -986,11 +977,12 @@ struct VerifyRows {
             RP::unpack(rb, b);
             int dot = 0, na = 0, nb = 0;
 #pragma unroll
-            for (int e = 0; e < RP::EPL; ++e) {
-                const int qa = quant8(a[e], qscale), qb = quant8(b[e], qscale);
-                dot += qa * qb;
-                na += qa * qa;
-                nb += qb * qb;
+            for (int e = 0; e < RP::EPL; e += 4) {
+                const unsigned qa = quant8x4(a[e], a[e + 1], a[e + 2], a[e + 3], qscale);
+                const unsigned qb = quant8x4(b[e], b[e + 1], b[e + 2], b[e + 3], qscale);
+                dot = dot4_i8(qa, qb, dot);
+                na = dot4_i8(qa, qa, na);
+                nb = dot4_i8(qb, qb, nb);
             }
             dot = group16_sum(dot);
             na = group16_sum(na);
@@ -1861,13 +1853,9 @@ __global__ __launch_bounds__(256) void tc_recode_kernel(const void *__restrict__
     cm.load(Rm, lane);
     const char *row = (const char *)K + ((size_t)h * C + j) * (size_t)D * (BF16 ? 2 : 4);
     i32x4 xq[D / 64];
-#pragma unroll
-    for (int ks = 0; ks < D / 64; ++ks) xq[ks] = load_quantised<BF16>(row, ks, g, qscale);
-#pragma unroll
-    for (int cb = 0; cb < R / 16; ++cb) {
-        const unsigned w = cm.code_word(xq, cb, shift);
-        if (act) *(unsigned *)(code + ((size_t)h * C + j) * R + cb * 16 + 4 * g) = w;
-    }
+    load_quantised<BF16, D>(row, g, qscale, xq);
+    const auto w = cm.code_words(xq, shift);
+    if (act) cm.store(code + ((size_t)h * C + j) * R, w, lane);
 }
 
 }  // namespace fastar
@@ -1962,14 +1950,16 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
             const int per = (((n_new + gx - 1) / gx) + 31) & ~31;
             gx = (n_new + per - 1) / per;
         }
-        const dim3 grid(gx, H);
+        // the age histogram beside the match: a workgroup per 8192 slots (one round of loads, 4 x 16 bytes per thread)
+        const int n_hist = fused_verify && !wide && !self_hist ? (C + 8191) / 8192 : 0;
+        const dim3 grid(gx + n_hist, H);
         const bool bf = dtype == FASTAR_BF16;
         const VerifyArgs va = {cache->K, tau2_q16, merged, cache->stamp, frame_id, self_hist ? -1 : PS_HIST, PS_FUT};
         int rc = FASTAR_OK;
 #define FASTAR_WIN(RR, ENC, BF, DD, VER, TT)                                                                              \
     rc = launch_match_window<RR, ENC, BF, DD, VER, TT>(grid, win_lds, s, cache->code, cache->len, C, cp, n_new, cand,      \
                                                        n_cand, metric, jstar, sbest, win, grp, K_new, codec->R,            \
-                                                       codec->qscale, codec->shift, ck, plan_scratch, (int)PS_STRIDE, va)
+                                                       codec->qscale, codec->shift, ck, plan_scratch, (int)PS_STRIDE, n_hist, va)
 #define FASTAR_WIN_ENC(RR, BF, DD)                                                      \
     do {                                                                                \
         if (fused_verify && wide) FASTAR_WIN(RR, true, BF, DD, true, 256);              \
