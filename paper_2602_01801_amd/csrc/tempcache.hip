@@ -3,8 +3,8 @@
 //   tc_match_window  (candidate list that fits LDS, probe = new key: the usual call) codes of the new keys AND the
 //                 top-1 candidate slot of every token on exact integer code scores (int8 matrix cores), final in
 //                 one launch; clears the group records of the matched slots
-//   otherwise     encode (encode.hip) -> tc_match (candidate chunks over many workgroups, 64-bit atomicMax) ->
-//                 tc_prep (unpack the match, clear the group records it will touch)
+//   otherwise     encode (encode.hip) -> tc_match_all (the whole cache, a range of slots per workgroup) or tc_match (a
+//                 longer list, in chunks), 64-bit atomicMax -> tc_prep (unpack the match, clear the group records it will touch)
 //   tc_verify     cosine test on the 8-bit quantised full-width keys as an int64 inequality; joiners
 //                 register in their slot's group record (count, best joiner); age histogram of the live slots
 //   tc_plan       per head: ranks of the unmerged tokens (ballot + prefix sum), evictions needed,
@@ -59,49 +59,17 @@ size_t compress_ws_bytes(int H, int C, int n_new, int r) {
     return compress_ws(H, C, n_new, r).total;
 }
 
-// Running arg-max of one lane over the 16 scores a 32x32 matrix instruction leaves it (rows 8(v/4) + 4(lane/32) + v%4
-// of a group of 32 candidates), with "earliest position" among equal scores at no extra cost: a score word carries
-// its position among the 16 in its low four bits (one shift-add per score), so plain maxima pick (highest score, then
-// earliest row), and a later group only replaces the best on a strictly higher score.  Callers present the
-// candidates in ascending slot order without repeats, which makes this the smallest-slot rule of the match.
-// Scores lie within +-2^21, missing candidates carry MATCH_NONE: both survive the shift by four.
 constexpr int MATCH_NONE = -(1 << 26);       // score word of a missing candidate (minus its "penalty")
 constexpr int MATCH_VALID = -(1 << 25);      // every real score is above, every missing one below
-struct LaneBest {
-    int s = INT_MIN, m = 0, g = 0;           // best score, its packed word, the group it came from
-    __device__ __forceinline__ void take(const i32x16 &acc, int group) {
-        int p[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) p[v] = (int)(((unsigned)acc[v] << 4) + (unsigned)(15 - v));
-        int mx = p[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) mx = max(mx, p[v]);
-        const int sc = mx >> 4;
-        if (sc > s) { s = sc; m = mx; g = group; }
-    }
-    // position of the best among the candidates (group * 32 + row), or -1 when no real candidate was seen
-    __device__ __forceinline__ int pos(int g2) const {
-        if (s <= MATCH_VALID) return -1;
-        const int v = 15 - (m & 15);
-        return g * 32 + 8 * (v >> 2) + 4 * g2 + (v & 3);
-    }
-    // (score, position) as one word ordered like the arg-max: higher score first, then the earlier position
-    __device__ __forceinline__ u64 key(int g2, int pos0) const {
-        const int p = pos(g2);
-        return p < 0 ? 0ull : ((u64)(unsigned)(s + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)(pos0 + p));
-    }
-};
-
-// ---- match -------------------------------------------------------------------------------------------
+// ---- match against a candidate list too long for the LDS window -------------------------------------------------
 // D = A x B: A rows = 32 candidate slots (codes gathered by slot id), B columns = 32 tokens (probe codes).
 // A lane therefore sees 16 candidates of one token per matrix instruction and keeps the best
 // (score, lowest slot) as one 64-bit key: (score + bias) << 32 | ~slot.
-// CAND_CHUNK = candidate positions scanned by one workgroup: 64 for a windowed candidate list (more, lighter
-// workgroups hide the two dependent loads better), 256 for a scan of the whole cache (fewer atomics per token).
-// Ties go to the smallest slot.  A scan of the whole cache (LIST false) visits the slots in ascending order, so the
-// cheap "earliest position" arg-max of LaneBest is that rule.  A candidate list too long for the LDS window (LIST)
-// comes in any order and may repeat ids: there every score is compared as the full (score, smallest slot) key.
-template <int R, int CAND_CHUNK, bool LIST>
+// CAND_CHUNK = candidate positions scanned by one workgroup: 64 for a shorter list (more, lighter workgroups hide the
+// two dependent loads better), 256 for a longer one (fewer atomics per token).
+// Ties go to the smallest slot; the list comes in any order and may repeat ids, so every score is compared as the full
+// (score, smallest slot) key.
+template <int R, int CAND_CHUNK>
 __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict__ code, const int32_t *__restrict__ len,
                                                        int C, const int8_t *__restrict__ cp, int n_new,
                                                        const int32_t *__restrict__ cand, int n_cand, int metric,
@@ -109,13 +77,11 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
     constexpr int KS = R / 32;
     constexpr int NIT = CAND_CHUNK / 32;  // groups of 32 candidates per workgroup
     __shared__ __attribute__((aligned(16))) int cpen[4][CAND_CHUNK];   // minus the score penalty: -|code|^2 (metric 0), 0 (metric 1); MATCH_NONE: no candidate
-    __shared__ __attribute__((aligned(16))) int cslotw[LIST ? 4 : 1][LIST ? CAND_CHUNK : 4];   // slot of every row (LIST)
+    __shared__ __attribute__((aligned(16))) int cslotw[4][CAND_CHUNK];   // slot of every row
     const int h = blockIdx.z;
     const int L = min(len[h], C);
-    const int n_pos = LIST ? n_cand : L;
     const int pos0 = blockIdx.y * CAND_CHUNK;
-    if (pos0 >= n_pos) return;  // uniform
-    const int pos1 = min(pos0 + CAND_CHUNK, n_pos);
+    const int pos1 = min(pos0 + CAND_CHUNK, n_cand);
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int col = lane & 31, g2 = lane >> 5;
     const int tok = blockIdx.x * 128 + wave * 32 + col;
@@ -135,7 +101,7 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
         const int pos = pos0 + it * 32 + col;
         int sl = -1;
         if (pos < pos1) {
-            sl = LIST ? cand[(size_t)h * n_cand + pos] : pos;
+            sl = cand[(size_t)h * n_cand + pos];
             if (sl < 0 || sl >= L) sl = -1;
         }
         slot[it] = sl;
@@ -159,11 +125,10 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
         nn += shfl_xor(nn, 32);
         if (g2 == 0) {
             cpen[wave][it * 32 + col] = slot[it] >= 0 ? (metric == 0 ? -nn : 0) : MATCH_NONE;
-            if (LIST) cslotw[wave][it * 32 + col] = slot[it];
+            cslotw[wave][it * 32 + col] = slot[it];
         }
     }
     __syncthreads();  // every wavefront reads back only its own rows; the barrier orders write and read
-    LaneBest lb;
     u64 mybest = 0;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
@@ -183,21 +148,16 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(afrag[it][ks], bfrag[ks], acc);
         }
-        if (LIST) {
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const i32x4 sl4 = *(const i32x4 *)(&cslotw[wave][it * 32 + 8 * q4 + 4 * g2]);
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const i32x4 sl4 = *(const i32x4 *)(&cslotw[wave][it * 32 + 8 * q4 + 4 * g2]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const u64 key = ((u64)(unsigned)(acc[4 * q4 + e] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)sl4[e]);
-                    if (sl4[e] >= 0 && key > mybest) mybest = key;
-                }
+            for (int e = 0; e < 4; ++e) {
+                const u64 key = ((u64)(unsigned)(acc[4 * q4 + e] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)sl4[e]);
+                if (sl4[e] >= 0 && key > mybest) mybest = key;
             }
-        } else {
-            lb.take(acc, it);
         }
     }
-    if (!LIST) mybest = lb.key(g2, pos0);   // position = slot
     {
         const unsigned lo = shfl_xor((unsigned)mybest, 32), hi = shfl_xor((unsigned)(mybest >> 32), 32);
         const u64 other = ((u64)hi << 32) | lo;
@@ -206,18 +166,325 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
     if (g2 == 0 && tok < n_new && mybest != 0) atomicMax(&best[(size_t)h * n_new + tok], mybest);
 }
 
+// ---- scan of a window of candidates held in LDS ------------------------------------------------------------
+// Shared by the kernel that stages a candidate list and the one that stages a range of the cache; eight wavefronts, TOKS
+// tokens at a time.  ccode: codes chunk-major ([16-byte chunk][candidate], conflict-free operand reads); cslot: slot ids;
+// cpen: minus half the penalty.
+// Candidates whose penalty |code|^2 is odd come first: a score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus
+// one for an odd penalty, so the earliest position that reaches the largest T is the one with the best score (and, slots
+// ascending in each half, the smallest slot), and the scan needs one matrix product instead of two.
+constexpr int WIN_THREADS = 512;
+template <int R, int TOKS>
+struct WindowScan {
+    static_assert(TOKS == 64 || TOKS == 256, "one set of token groups, or two");
+    static constexpr int KS = R / 32, NCH = R / 16;
+    static constexpr int NG = TOKS >= 256 ? 4 : 2;             // groups of 32 tokens a wavefront scans the window for
+    static constexpr int TQ = TOKS / (32 * NG);                // such sets of groups
+    static constexpr int SPLIT = (WIN_THREADS / 64) / TQ;      // wavefronts sharing one set, each on its share of the window
+    static constexpr int TPT = WIN_THREADS / TOKS;             // threads per token of the look-up
+    // parity of |code|^2 (the parity of the number of odd entries)
+    __device__ static __forceinline__ bool odd_penalty(const i32x4 (&rw)[NCH]) {
+        unsigned x = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) x ^= (unsigned)(rw[c][0] ^ rw[c][1] ^ rw[c][2] ^ rw[c][3]);
+        return __popc(x & 0x01010101u) & 1;
+    }
+    __device__ static __forceinline__ void stage(i32x4 *ccode, int *cslot, int *cpen, int n_pad, int metric, int p, int slot,
+                                                 const i32x4 (&rw)[NCH]) {
+        int nn = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            ccode[c * n_pad + p] = rw[c];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) nn = dot4_i8((unsigned)rw[c][m], (unsigned)rw[c][m], nn);
+        }
+        cslot[p] = slot;
+        cpen[p] = slot < 0 ? MATCH_NONE : metric == 0 ? -((nn + 1) >> 1) : 0;   // minus half the penalty, rounded up
+    }
+    // Running arg-max of a lane over the 16 scores per group its accumulators hold: only the best score and the group it
+    // came from are kept in the loop (a maximum tree and one select per group; a later group replaces the best only on a
+    // strictly higher score, so the earliest group wins among equals); which of the group's rows it was is looked up once,
+    // after the loop, by recomputing that group's scores for the token.
+    // Leaves (best score, earliest group) of this wavefront's share in partbest as one word per token, 0: none seen.
+    __device__ static __forceinline__ void scan(const i32x4 *ccode, const int *cpen, int n_pad, int n_groups, int tq, int ch,
+                                                const i32x4 (&bfrag)[NG][KS], u64 (*partbest)[TOKS]) {
+        const int lane = lane_id(), col = lane & 31, g2 = lane >> 5;
+        int bs[NG], bg[NG];
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            bs[u] = INT_MIN;
+            bg[u] = 0;
+        }
+        // One group of 32 candidates per step.  A wavefront issues in order, so the matrix instructions of one half of the
+        // token groups are issued before the maxima of the half before them, and the operands, in two rotating sets, are
+        // read most of a step before they are used.  Steps past the end repeat the last group, which changes nothing: only
+        // a strictly higher score replaces the best.
+        constexpr int HALF = NG / 2;
+        struct Operands {
+            i32x4 a[KS];
+            i32x16 pen;
+        };
+        const int n_it = n_groups > ch ? (n_groups - ch + SPLIT - 1) / SPLIT : 0;
+        auto group_of = [&](int it) { return min(ch + it * SPLIT, n_groups - 1); };
+        // marks the penalties as still in use: the compiler would let the last product of a step overwrite them and copy the
+        // next ones into place, 25 moves per step
+        auto keep = [](const Operands &s) { asm volatile("" ::"v"(s.pen)); };
+        auto rd = [&](Operands &s, int it) {
+            const int gi = group_of(it);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) s.a[ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {   // minus the penalty of the accumulators' rows
+                const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s.pen[4 * q4 + e] = np[e];
+            }
+        };
+        auto mm = [&](i32x16 (&acc)[HALF], const Operands &s, int u0) {   // the matrix unit subtracts the penalty
+#pragma unroll
+            for (int u = 0; u < HALF; ++u) acc[u] = mfma_i8_32x32x32(s.a[0], bfrag[u0 + u][0], s.pen);
+#pragma unroll
+            for (int ks = 1; ks < KS; ++ks)
+#pragma unroll
+                for (int u = 0; u < HALF; ++u) acc[u] = mfma_i8_32x32x32(s.a[ks], bfrag[u0 + u][ks], acc[u]);
+        };
+        auto red = [&](const i32x16 (&acc)[HALF], int it, int u0) {
+            const int gi = group_of(it);
+#pragma unroll
+            for (int u = 0; u < HALF; ++u) {
+                int mx = max(acc[u][0], bs[u0 + u]);
+#pragma unroll
+                for (int v = 1; v < 16; ++v) mx = max(mx, acc[u][v]);
+                bg[u0 + u] = mx > bs[u0 + u] ? gi : bg[u0 + u];
+                bs[u0 + u] = mx;
+            }
+        };
+        if (n_it > 0) {
+            Operands o0, o1;
+            i32x16 acc0[HALF], acc1[HALF];
+            rd(o0, 0);
+            rd(o1, 1);
+            mm(acc0, o0, 0);
+            for (int it = 0; it < n_it; it += 2) {
+                mm(acc1, o0, HALF);
+                keep(o0);
+                rd(o0, it + 2);
+                red(acc0, it, 0);
+                mm(acc0, o1, 0);
+                red(acc1, it, HALF);
+                mm(acc1, o1, HALF);
+                keep(o1);
+                rd(o1, it + 3);
+                red(acc0, it + 1, 0);
+                mm(acc0, o0, 0);
+                red(acc1, it + 1, HALF);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            u64 key = bs[u] > MATCH_VALID ? ((u64)(unsigned)(bs[u] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)bg[u]) : 0ull;
+            const unsigned lo = shfl_xor((unsigned)key, 32), hi = shfl_xor((unsigned)(key >> 32), 32);
+            const u64 other = ((u64)hi << 32) | lo;
+            if (other > key) key = other;
+            if (g2 == 0) partbest[ch][(tq * NG + u) * 32 + col] = key;
+        }
+    }
+    // Best score T of token t and the earliest position `at` that reaches it (false: no real candidate), after a barrier
+    // behind scan(); TPT neighbouring threads per token (sub = 0 .. TPT-1), all of them get the answer.  The threads start
+    // at different rows: the groups' rows lie at multiples of 512 bytes, all on the same banks.
+    __device__ static __forceinline__ bool look_up(const i32x4 *ccode, const int *cpen, int n_pad, const i32x4 (&pc)[NCH],
+                                                   bool ok, int t, int sub, const u64 (*partbest)[TOKS], int &T, int &at) {
+        constexpr int ROWS = 32 / TPT;
+        u64 best = partbest[0][t];
+#pragma unroll
+        for (int c = 1; c < SPLIT; ++c) {
+            const u64 other = partbest[c][t];
+            if (other > best) best = other;
+        }
+        const bool seen = best != 0 && ok;
+        T = (int)(unsigned)(best >> 32) - SCORE_BIAS;
+        at = INT_MAX;
+        if (seen) {
+            const int row0 = (int)(0xFFFFFFFFu - (unsigned)best) * 32 + sub * ROWS;
+#pragma unroll
+            for (int v = 0; v < ROWS; ++v) {
+                const int rw = row0 + ((v + t) & (ROWS - 1));
+                int dot = 0;
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) {
+                    const i32x4 cc = ccode[c * n_pad + rw];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) dot = dot4_i8((unsigned)cc[m], (unsigned)pc[c][m], dot);
+                }
+                if (dot + cpen[rw] == T) at = min(at, rw);
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < TPT; off <<= 1) at = min(at, shfl_xor(at, off));
+        return seen;
+    }
+};
+// Stable partition of up to 4096 ranked candidates, those marked in the bitmap s_odd (one 64-bit word per lane) first.
+// Built and used by whole wavefronts.
+struct OddFirst {
+    u64 mine;
+    int excl, n_odd;
+    __device__ __forceinline__ explicit OddFirst(const u64 *s_odd) {
+        const int lane = lane_id();
+        mine = s_odd[lane];
+        const int c = __popcll(mine);
+        int incl = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, WAVE);
+            if (lane >= off) incl += o;
+        }
+        n_odd = __shfl(incl, 63, WAVE);
+        excl = incl - c;
+    }
+    __device__ __forceinline__ int place(int p) const {
+        const unsigned lo = __shfl((int)(unsigned)mine, p >> 6, WAVE), hi = __shfl((int)(unsigned)(mine >> 32), p >> 6, WAVE);
+        const u64 w = ((u64)hi << 32) | lo;
+        const int below = __shfl(excl, p >> 6, WAVE) + __popcll(w & ((1ull << (p & 63)) - 1ull));
+        return (w >> (p & 63)) & 1ull ? below : n_odd + p - below;
+    }
+};
+
+// ---- match of the whole cache --------------------------------------------------------------------------------
+// One workgroup = one range of slots (staged in LDS once) x one share of the frame's tokens, taken in blocks of up to TOKS;
+// the best of a range goes to the token's packed (score, smallest slot) word.  What bounds it: the vector instructions of
+// the maxima, 40 cycles per 32 x 32 scores, beside 32 of the matrix product.  (A chunk of 256 slots per workgroup in
+// registers with doubled products, position words and eight times the atomic operations took 71 us at 12 heads x 1560
+// tokens x 32760 slots, this kernel 45; two workgroups per unit with 128 tokens each: 50.)
+template <int R, int TOKS>
+__global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8_t *__restrict__ code,
+                                                                      const int32_t *__restrict__ len, int C,
+                                                                      const int8_t *__restrict__ cp, int n_new, int metric,
+                                                                      int range, int share, int block,
+                                                                      u64 *__restrict__ best) {
+    typedef WindowScan<R, TOKS> WS;
+    constexpr int KS = WS::KS, NCH = WS::NCH, NG = WS::NG, TPT = WS::TPT;
+    extern __shared__ __attribute__((aligned(16))) unsigned char wlds[];
+    i32x4 *ccode = (i32x4 *)wlds;                             // [NCH][range]
+    int *cslot = (int *)(wlds + (size_t)NCH * range * 16);    // [range]
+    int *cpen = cslot + range;                                // [range]
+    __shared__ u64 partbest[WS::SPLIT][TOKS];
+    __shared__ u64 s_odd[WAVE];
+    const int h = blockIdx.z;
+    const int L = min(len[h], C);
+    const int j0 = blockIdx.x * range;
+    if (j0 >= L) return;                                      // uniform
+    const int n = min(range, L - j0), n_stage = (n + 31) & ~31;   // range is a multiple of 32
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const int col = lane & 31, g2 = lane >> 5;
+    const int swave = __builtin_amdgcn_readfirstlane(wave);   // uniform: the scan's bookkeeping stays in scalar registers
+    const int tq = swave % WS::TQ, ch = swave / WS::TQ;
+    const int t = tid / TPT, sub = tid % TPT;
+    const int t0 = min((int)blockIdx.y * share, n_new), t1 = min(t0 + share, n_new);
+    const int8_t *cph = cp + (size_t)h * n_new * R;
+    i32x4 bfrag[NG][KS], pc[NCH];
+    auto load_tokens = [&](int base) {   // second operands of the scan, and the look-up's probe code
+#pragma unroll
+        for (int u = 0; u < NG; ++u)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                bfrag[u][ks] = *(const i32x4 *)(cph + (size_t)min(base + (tq * NG + u) * 32 + col, n_new - 1) * R + ks * 32 + 16 * g2);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(cph + (size_t)min(base + t, n_new - 1) * R + 16 * c);
+    };
+    // the range's rows, a batch of four per thread at a time; the parities first when they matter
+    constexpr int PER = 4;
+    const int8_t *ch_code = code + ((size_t)h * C + j0) * R;
+    i32x4 row[PER][NCH];
+    auto load_rows = [&](int p0) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+#pragma unroll
+            for (int c = 0; c < NCH; ++c)
+                row[k][c] = *(const i32x4 *)(ch_code + (size_t)min(p0 + k * WIN_THREADS + tid, n - 1) * R + 16 * c);
+    };
+    load_rows(0);
+    load_tokens(t0);
+    if (tid < WAVE) s_odd[tid] = 0ull;
+    __syncthreads();
+    for (int p0 = 0; p0 < n_stage; p0 += PER * WIN_THREADS) {   // uniform
+        if (p0 > 0) load_rows(p0);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int p = p0 + k * WIN_THREADS + tid;           // a wavefront's 64 positions are one word
+            const u64 odd = __ballot(metric == 0 && p < n && WS::odd_penalty(row[k]));
+            if (lane == 0 && p < n) s_odd[p >> 6] = odd;
+        }
+    }
+    __syncthreads();
+    const OddFirst odd_first(s_odd);
+    const bool single = n_stage <= PER * WIN_THREADS;           // uniform: the rows are still in registers
+    for (int p0 = 0; p0 < n_stage; p0 += PER * WIN_THREADS) {
+        if (!single) load_rows(p0);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int p = p0 + k * WIN_THREADS + tid;
+            const int at = odd_first.place(min(p, n - 1));
+            if (p < n_stage) WS::stage(ccode, cslot, cpen, range, metric, p < n ? at : p, p < n ? j0 + p : -1, row[k]);
+        }
+    }
+    __syncthreads();
+    for (int base = t0; base < t1; base += block) {
+        const int lim = min(base + block, t1);
+        WS::scan(ccode, cpen, range, base + tq * NG * 32 < lim ? n_stage / 32 : 0, tq, ch, bfrag, partbest);
+        i32x4 pcur[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) pcur[c] = pc[c];
+        if (base + block < t1) load_tokens(base + block);       // in flight during the look-up
+        __syncthreads();
+        int T, at;
+        const bool seen = WS::look_up(ccode, cpen, range, pcur, base + t < lim, t, sub, partbest, T, at);
+        if (sub == 0 && seen) {
+            const int S = metric == 0 ? 2 * T + (at < odd_first.n_odd ? 1 : 0) : T;
+            atomicMax(&best[(size_t)h * n_new + base + t],
+                      ((u64)(unsigned)(S + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)cslot[at]));
+        }
+        __syncthreads();                                        // the next block's scan writes the partial results
+    }
+}
+// slots of a range at most: what fits a compute unit's LDS beside the static arrays (and 4096, OddFirst's words)
+static constexpr int match_all_range_max(int r) { return r == 32 ? 3584 : 2048; }
+template <int R, int TOKS>
+static int allow_match_all_lds() {
+    return hipFuncSetAttribute((const void *)tc_match_all_kernel<R, TOKS>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               match_all_range_max(R) * (R + 8)) == hipSuccess
+               ? FASTAR_OK
+               : FASTAR_ERR_HIP;
+}
+template <int R, int TOKS>
+static int launch_match_all(const int8_t *code, const int32_t *len, int C, const int8_t *cp, int n_new, int H, int metric,
+                            u64 *best, hipStream_t s) {
+    // One workgroup per compute unit (LDS): as few ranges as its LDS allows, the tokens shared out while workgroups are
+    // left over, then the ranges made shorter until the chip is covered.  Ranges of at least 512 slots: shorter ones are
+    // all staging and look-up.
+    constexpr int CUS = 256;
+    int ranges = (C + match_all_range_max(R) - 1) / match_all_range_max(R);
+    const int blocks = (n_new + TOKS - 1) / TOKS;
+    const int splits = std::max(1, std::min(blocks, CUS / std::max(1, ranges * H)));
+    ranges = std::max(ranges, std::min((C + 511) / 512, CUS / std::max(1, splits * H)));
+    const int range = (((C + ranges - 1) / ranges) + 31) & ~31;
+    const int share = (((n_new + splits - 1) / splits) + 31) & ~31;
+    const int n_blk = (share + TOKS - 1) / TOKS;
+    const int block = (((share + n_blk - 1) / n_blk) + 31) & ~31;
+    const dim3 grid((C + range - 1) / range, (n_new + share - 1) / share, H);
+    hipLaunchKernelGGL((tc_match_all_kernel<R, TOKS>), grid, dim3(WIN_THREADS), (size_t)range * (R + 8), s, code, len, C, cp,
+                       n_new, metric, range, share, block, best);
+    FASTAR_LAUNCH_CHECK();
+    return FASTAR_OK;
+}
+
 // ---- match against a candidate window held in LDS --------------------------------------------------------
 // For a candidate list short enough to stage in LDS (the previous frame's slots: n_cand * (R + 8) bytes), one
 // workgroup owns 64 tokens and sees every candidate, so the arg-max is final when it ends: no atomics, no packed
-// keys to unpack, and the group records of the matched slots are cleared right here.  The eight wavefronts are
-// (token half) x (quarter of the window): each takes every fourth step of 4 x 32 candidates, the partial arg-maxima
-// meet through LDS.  The epilogue per 32 x 32 scores is plain integer ALU work, so two wavefronts per SIMD (not
-// one) are what keeps the ALUs issuing.
-// LDS: codes chunk-major ([16-byte chunk][candidate], conflict-free A-operand reads), slot ids, penalties.
+// keys to unpack, and the group records of the matched slots are cleared right here.
 // With ENC the kernel also is the call's encode step for its 64 tokens (probe = new key): it quantises and projects
 // their rows while the window's loads are in flight, leaves the codes in ck for the apply step, and clears the
 // eviction plan's scratch words (ps_all) for the launches behind it.
-constexpr int WIN_THREADS = 512;
 // dynamic LDS of the window kernel; with the static arrays of its largest instantiation with 64 tokens per workgroup
 // (r = 64, fused verify: 8.9 KB) it stays within the 160 KB of a compute unit
 constexpr size_t WINDOW_LDS_MAX = 148 * 1024;
@@ -268,9 +535,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     i32x4 *ccode = (i32x4 *)wlds;                       // [NCH][n_pad]
     int *cslot = (int *)(wlds + (size_t)NCH * n_pad * 16);  // [n_pad]
     int *cpen = cslot + n_pad;                          // [n_pad]
-    constexpr int NG = TOKS >= 256 ? 4 : 2;             // groups of 32 tokens a wavefront scans the window for
-    constexpr int TQ = TOKS / (32 * NG);                // such sets of groups
-    constexpr int SPLIT = (WIN_THREADS / 64) / TQ;      // wavefronts sharing one set, each on its share of the window
+    typedef WindowScan<R, TOKS> WS;
+    constexpr int NG = WS::NG, TQ = WS::TQ, SPLIT = WS::SPLIT;
     // partial arg-maxima of the scan; R before it, the verify hand-over and the age histogram after it
     __shared__ __attribute__((aligned(16))) u64 partbest[SPLIT][TOKS];
     static_assert(sizeof(partbest) >= AGE_BINS * sizeof(unsigned), "the histogram fits");
@@ -284,17 +550,15 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     const int L = min(len[h], C);
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int col = lane & 31, g2 = lane >> 5;
-    const int tq = wave % TQ, ch = wave / TQ;
+    const int swave = __builtin_amdgcn_readfirstlane(wave);   // uniform: the scan's bookkeeping stays in scalar registers
+    const int tq = swave % TQ, ch = swave / TQ;
     const int8_t *ch_code = code + (size_t)h * C * R;
     // The candidate list is a SET of slots and ties go to the smallest slot, so the window is staged in ascending
     // slot order without repeats: position order then is slot order, which is all the arg-max below needs.
     //   1. every thread reads its entries of the list (ids outside [0, L) do not count) and asks for their code rows;
     //   2. the ids are ranked through a bitmap over the slots, held where the codes will go (several passes when the
     //      cache is longer than that area): set bits, prefix counts per word, rank = prefix + bits below;
-    //   3. the rows go to their ranks (repeats write the same row to the same place), candidates whose penalty |code|^2 is
-    //      odd before the others: a score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus one for an odd
-    //      penalty, so with the odd ones first the earliest position that reaches the largest T is the one wanted, and the
-    //      scan needs one matrix product instead of two.
+    //   3. the rows go to their ranks (repeats write the same row to the same place), odd penalties first (WindowScan).
     constexpr int CPT = ((int)(WINDOW_LDS_MAX / (R + 8)) + WIN_THREADS - 1) / WIN_THREADS;   // list entries per thread
     // of them, rows in flight while the ids are ranked (registers); the rows beyond are loaded when their ranks are known
     constexpr int PF = R == 32 ? (TOKS >= 256 ? CPT : BF16 ? 4 : 2) : 2;
@@ -409,12 +673,6 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
 #pragma unroll
         for (int c = 0; c < NCH; ++c) rw[c] = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
     };
-    auto odd_penalty = [&](const i32x4 (&rw)[NCH]) -> bool {
-        unsigned x = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) x ^= (unsigned)(rw[c][0] ^ rw[c][1] ^ rw[c][2] ^ rw[c][3]);
-        return __popc(x & 0x01010101u) & 1;
-    };
     if (metric == 0) {   // uniform
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
@@ -422,49 +680,25 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             if (pos[k] < 0) continue;
             bool odd;
             if (k < PF) {
-                odd = odd_penalty(row[k < PF ? k : 0]);
+                odd = WS::odd_penalty(row[k < PF ? k : 0]);
             } else {
                 i32x4 rw[NCH];
                 row_of(k, rw);
-                odd = odd_penalty(rw);
+                odd = WS::odd_penalty(rw);
             }
             if (odd) atomicOr(&s_odd[pos[k] >> 6], 1ull << (pos[k] & 63));
         }
     }
     __syncthreads();                        // the bitmap is dead: its memory takes the codes
-    int n_odd;
-    {
-        const u64 mine = s_odd[lane];
-        const int cnt_odd = __popcll(mine);
-        int incl = cnt_odd;
+    const OddFirst odd_first(s_odd);
+    const int n_odd = odd_first.n_odd;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, WAVE);
-            if (lane >= off) incl += o;
-        }
-        n_odd = __shfl(incl, 63, WAVE);
-        const int excl = incl - cnt_odd;
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            if (n_cand <= k * WIN_THREADS) break;   // uniform
-            const int p = max(pos[k], 0);
-            const unsigned lo = __shfl((int)(unsigned)mine, p >> 6, WAVE), hi = __shfl((int)(unsigned)(mine >> 32), p >> 6, WAVE);
-            const u64 w = ((u64)hi << 32) | lo;
-            const int below = __shfl(excl, p >> 6, WAVE) + __popcll(w & ((1ull << (p & 63)) - 1ull));
-            if (pos[k] >= 0) pos[k] = (w >> (p & 63)) & 1ull ? below : n_odd + p - below;
-        }
+    for (int k = 0; k < CPT; ++k) {
+        if (n_cand <= k * WIN_THREADS) break;   // uniform
+        const int p = odd_first.place(max(pos[k], 0));
+        if (pos[k] >= 0) pos[k] = p;
     }
-    auto stage_row = [&](int p, int slot, const i32x4 (&rw)[NCH]) {
-        int nn = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            ccode[c * n_pad + p] = rw[c];
-#pragma unroll
-            for (int m = 0; m < 4; ++m) nn = dot4_i8((unsigned)rw[c][m], (unsigned)rw[c][m], nn);
-        }
-        cslot[p] = slot;
-        cpen[p] = slot < 0 ? MATCH_NONE : metric == 0 ? -((nn + 1) >> 1) : 0;  // minus half the penalty, rounded up
-    };
+    auto stage_row = [&](int p, int slot, const i32x4 (&rw)[NCH]) { WS::stage(ccode, cslot, cpen, n_pad, metric, p, slot, rw); };
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
         if (k >= PF && n_cand <= k * WIN_THREADS) break;   // uniform
@@ -511,117 +745,18 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             bfrag[u][ks] = ENC ? *(const i32x4 *)(pcode + t * R + ks * 32 + 16 * g2)
                                : *(const i32x4 *)(cp + ((size_t)h * n_new + min(base + t, n_new - 1)) * R + ks * 32 + 16 * g2);
         }
-    // Running arg-max of a lane over the 16 scores per group its accumulators hold: only the best score and the group
-    // it came from are kept in the loop (a maximum tree and one compare-select per group; a later group replaces the
-    // best only on a strictly higher score, so the earliest group wins among equals); which of the group's rows it was
-    // is looked up once, after the loop, by recomputing that group's scores for the token.
-    int bs[NG], bg[NG];
-#pragma unroll
-    for (int u = 0; u < NG; ++u) {
-        bs[u] = INT_MIN;
-        bg[u] = 0;
-    }
     // a wavefront whose tokens all lie beyond the block's end scans nothing (uniform over the wavefront)
-    const int n_groups = base + tq * NG * 32 < lim ? n_stage / 32 : 0;
-    {
-        // One group of 32 candidates per step in two rotating operand sets: the reads and matrix instructions of a step are
-        // issued before the maxima of the one before it (a wavefront issues in order: without the rotation its matrix and
-        // vector phases alternate).  Steps past the end repeat the last group, which changes nothing: only a strictly
-        // higher score replaces the best.
-        struct ScanSet {
-            i32x4 a[KS];
-            i32x16 pen, acc[NG];
-        };
-        const int n_it = n_groups > ch ? (n_groups - ch + SPLIT - 1) / SPLIT : 0;
-        auto group_of = [&](int it) { return min(ch + it * SPLIT, n_groups - 1); };
-        auto rd = [&](ScanSet &s, int it) {
-            const int gi = group_of(it);
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) s.a[ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {   // minus the penalty of the accumulators' rows
-                const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s.pen[4 * q4 + e] = np[e];
-            }
-        };
-        auto mm = [&](ScanSet &s) {   // the matrix unit subtracts the penalty
-#pragma unroll
-            for (int u = 0; u < NG; ++u) s.acc[u] = mfma_i8_32x32x32(s.a[0], bfrag[u][0], s.pen);
-#pragma unroll
-            for (int ks = 1; ks < KS; ++ks)
-#pragma unroll
-                for (int u = 0; u < NG; ++u) s.acc[u] = mfma_i8_32x32x32(s.a[ks], bfrag[u][ks], s.acc[u]);
-        };
-        auto red = [&](const ScanSet &s, int it) {
-#pragma unroll
-            for (int u = 0; u < NG; ++u) {
-                int mx = max(s.acc[u][0], bs[u]);
-#pragma unroll
-                for (int v = 1; v < 16; ++v) mx = max(mx, s.acc[u][v]);
-                bg[u] = mx > bs[u] ? group_of(it) : bg[u];
-                bs[u] = mx;
-            }
-        };
-        if (n_it > 0) {
-            ScanSet s0, s1;
-            rd(s0, 0);
-            mm(s0);
-            rd(s1, 1);
-            for (int it = 0; it < n_it; it += 2) {
-                mm(s1);
-                red(s0, it);
-                rd(s0, it + 2);
-                mm(s0);
-                red(s1, it + 1);
-                rd(s1, it + 3);
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < NG; ++u) {   // (best score, earliest group) as one word; 0: no real candidate was seen
-        u64 key = bs[u] > MATCH_VALID ? ((u64)(unsigned)(bs[u] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)bg[u]) : 0ull;
-        const unsigned lo = shfl_xor((unsigned)key, 32), hi = shfl_xor((unsigned)(key >> 32), 32);
-        const u64 other = ((u64)hi << 32) | lo;
-        if (other > key) key = other;
-        if (g2 == 0) partbest[ch][(tq * NG + u) * 32 + col] = key;
-    }
+    WS::scan(ccode, cpen, n_pad, base + tq * NG * 32 < lim ? n_stage / 32 : 0, tq, ch, bfrag, partbest);
     __syncthreads();
     {
-        // Look-up, TPT threads per token: the earliest row of the best group that reaches the best score.  The threads
-        // start at different rows: the groups' rows lie at multiples of 512 bytes, all on the same banks.
-        constexpr int TPT = WIN_THREADS / TOKS, ROWS = 32 / TPT;
+        constexpr int TPT = WS::TPT;
         const int t = tid / TPT, sub = tid % TPT, tok = base + t;
-        u64 best = partbest[0][t];
+        i32x4 pc[NCH];
+        const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + min(tok, n_new - 1)) * R;
 #pragma unroll
-        for (int c = 1; c < SPLIT; ++c) {
-            const u64 other = partbest[c][t];
-            if (other > best) best = other;
-        }
-        const bool seen = best != 0 && tok < lim;
-        const int T = (int)(unsigned)(best >> 32) - SCORE_BIAS;
-        int at = INT_MAX;
-        if (seen) {
-            i32x4 pc[NCH];
-            const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + tok) * R;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
-            const int row0 = (int)(0xFFFFFFFFu - (unsigned)best) * 32 + sub * ROWS;
-#pragma unroll
-            for (int v = 0; v < ROWS; ++v) {
-                const int rw = row0 + ((v + t) & (ROWS - 1));
-                int dot = 0;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) {
-                    const i32x4 cc = ccode[c * n_pad + rw];
-#pragma unroll
-                    for (int m = 0; m < 4; ++m) dot = dot4_i8((unsigned)cc[m], (unsigned)pc[c][m], dot);
-                }
-                if (dot + cpen[rw] == T) at = min(at, rw);
-            }
-        }
-#pragma unroll
-        for (int off = 1; off < TPT; off <<= 1) at = min(at, shfl_xor(at, off));
+        for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
+        int T, at;
+        const bool seen = WS::look_up(ccode, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, at);
         if (sub == 0) {
             const int j = seen ? cslot[at] : -1;   // position in the window -> slot
             const int S = !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T;
@@ -685,7 +820,7 @@ static int allow_window_lds() {
 struct PlanResidency;
 static int plan_residency(PlanResidency *out);
 static int plan_residency_setup();
-// every instantiation of the window kernel may use more than the default 64 KB of dynamic LDS: requested once per device
+// every instantiation of the window and whole-cache kernels may use more than the default 64 KB of dynamic LDS: requested once per device
 int tempcache_setup() {
     if (const int rc = plan_residency_setup(); rc != FASTAR_OK) return rc;
     static DeviceOnce once;
@@ -703,6 +838,10 @@ int tempcache_setup() {
 #undef FASTAR_ALLOW
         if (rc == FASTAR_OK) rc = allow_window_lds<32, false, true, 128, false, 64>();
         if (rc == FASTAR_OK) rc = allow_window_lds<64, false, true, 128, false, 64>();
+        if (rc == FASTAR_OK) rc = allow_match_all_lds<32, 64>();
+        if (rc == FASTAR_OK) rc = allow_match_all_lds<32, 256>();
+        if (rc == FASTAR_OK) rc = allow_match_all_lds<64, 64>();
+        if (rc == FASTAR_OK) rc = allow_match_all_lds<64, 256>();
         return rc;
     });
 }
@@ -1976,23 +2115,27 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
 #undef FASTAR_WIN
         if (rc != FASTAR_OK) return rc;
     } else {
-        const int n_pos_cap = cand ? n_cand : C;
-        const int chunk = n_pos_cap <= 4096 ? 64 : 256;
-        dim3 grid((n_new + 127) / 128, (n_pos_cap + chunk - 1) / chunk, H);
-#define FASTAR_MATCH(RR, CH)                                                                                         \
-    do {                                                                                                             \
-        if (cand)                                                                                                    \
-            hipLaunchKernelGGL((tc_match_kernel<RR, CH, true>), grid, dim3(256), 0, s, cache->code, cache->len, C, cp, \
-                               n_new, cand, n_cand, metric, best);                                                   \
-        else                                                                                                         \
-            hipLaunchKernelGGL((tc_match_kernel<RR, CH, false>), grid, dim3(256), 0, s, cache->code, cache->len, C, cp, \
-                               n_new, cand, n_cand, metric, best);                                                   \
-    } while (0)
-        if (r == 32 && chunk == 64) FASTAR_MATCH(32, 64);
-        else if (r == 32) FASTAR_MATCH(32, 256);
-        else if (chunk == 64) FASTAR_MATCH(64, 64);
-        else FASTAR_MATCH(64, 256);
+        if (const int rc0 = tempcache_setup(); rc0 != FASTAR_OK) return rc0;
+        if (!cand) {
+            // frames of at most 128 tokens leave half of the wavefronts of a 256-token block without work
+            int rc;
+#define FASTAR_MATCH_ALL(RR, TT) rc = launch_match_all<RR, TT>(cache->code, cache->len, C, cp, n_new, H, metric, best, s)
+            if (n_new <= 128) { if (r == 32) FASTAR_MATCH_ALL(32, 64); else FASTAR_MATCH_ALL(64, 64); }
+            else { if (r == 32) FASTAR_MATCH_ALL(32, 256); else FASTAR_MATCH_ALL(64, 256); }
+#undef FASTAR_MATCH_ALL
+            if (rc != FASTAR_OK) return rc;
+        } else {
+            const int chunk = n_cand <= 4096 ? 64 : 256;
+            dim3 grid((n_new + 127) / 128, (n_cand + chunk - 1) / chunk, H);
+#define FASTAR_MATCH(RR, CH)                                                                                              \
+    hipLaunchKernelGGL((tc_match_kernel<RR, CH>), grid, dim3(256), 0, s, cache->code, cache->len, C, cp, n_new, cand, n_cand, \
+                       metric, best)
+            if (r == 32 && chunk == 64) FASTAR_MATCH(32, 64);
+            else if (r == 32) FASTAR_MATCH(32, 256);
+            else if (chunk == 64) FASTAR_MATCH(64, 64);
+            else FASTAR_MATCH(64, 256);
 #undef FASTAR_MATCH
+        }
         FASTAR_LAUNCH_CHECK();
         hipLaunchKernelGGL(tc_prep_kernel, dim3((n_new + 255) / 256, H), dim3(256), 0, s, best, n_new, C, cand, n_cand,
                            jstar, sbest, win, grp);

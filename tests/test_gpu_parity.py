@@ -774,16 +774,19 @@ def test_tempcache_many_workgroups_take_the_wide_window_kernel(dtype, d, r, H, T
         cand = np.ascontiguousarray(np.concatenate([mm_r, mm_r[:, : n_cand - T]], axis=1)[:, :n_cand])
 
 
-@pytest.mark.parametrize("H,T,n_cand,r,persistent,offset", [
-    (2, 130, 333, 32, True, 0), (2, 130, 333, 64, False, 0),   # 64 tokens per workgroup
-    (2, 70, 45, 32, True, 1), (2, 70, 45, 64, True, 2),        # projection matrix at an odd address / not on a word
-    (26, 1290, 3333, 32, True, 0),                             # 256 tokens per workgroup
+@pytest.mark.parametrize("H,T,C,n_cand,r,persistent,offset", [
+    (2, 130, 4096, 333, 32, True, 0), (2, 130, 4096, 333, 64, False, 0),   # 64 tokens per workgroup
+    (2, 70, 4096, 45, 32, True, 1), (2, 70, 4096, 45, 64, True, 2),        # projection matrix at an odd address / not on a word
+    (26, 1290, 4096, 3333, 32, True, 0),                                   # 256 tokens per workgroup
+    # the whole cache: several ranges and shares of tokens; one range per workgroup read in two rounds; several blocks
+    (2, 700, 4097, 0, 32, True, 0), (3, 300, 2500, 0, 64, False, 0), (130, 70, 7003, 0, 32, True, 0), (130, 290, 1030, 0, 32, True, 0),
+    (1, 1, 40, 0, 64, True, 0),
 ])
-def test_tempcache_window_scores_that_tie_or_differ_by_one(H, T, n_cand, r, persistent, offset):
+def test_tempcache_scores_that_tie_or_differ_by_one(H, T, C, n_cand, r, persistent, offset):
     # codes of a few small integers: nearly all scores tie, and scores of candidates with odd and even squared norms differ
     # by one, which the scan takes from the order it stages them in
     rng = np.random.default_rng(H + T + n_cand + r)
-    d, C = 64, 4096
+    d = 64
     codec = make_codec(0, 9, d, r)
     codec.shift = 8
     ref = oracle.Cache.empty(H, C, d, r, "bf16")
@@ -794,13 +797,13 @@ def test_tempcache_window_scores_that_tie_or_differ_by_one(H, T, n_cand, r, pers
     ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
     assert np.abs(ref.code.astype(int)).max() <= 6
     norms = (ref.code.astype(int) ** 2).sum(-1) & 1
-    assert 0.2 < norms.mean() < 0.8
+    assert 0.1 < norms.mean() < 0.9
     ref.cnt[:] = 1
     ref.stamp[:] = rng.integers(0, 9, size=(H, C))
     ref.len[:] = C - 9
     gpu = dev_cache(ref)
-    cand = rng.integers(-2, C, size=(H, n_cand)).astype(np.int32)
-    K_new = as_dt(base[:, rng.integers(0, 40, size=T)] + 0.2 * rng.standard_normal((H, T, d)))
+    cand = rng.integers(-2, C, size=(H, n_cand)).astype(np.int32) if n_cand else None
+    K_new = as_dt(base[:, rng.integers(0, 40, size=T)] + 0.1 * rng.standard_normal((H, T, d)))
     V_new = as_dt(rng.standard_normal((H, T, d)))
     dcodec = dev_codec(codec)
     if offset:
@@ -810,10 +813,10 @@ def test_tempcache_window_scores_that_tie_or_differ_by_one(H, T, n_cand, r, pers
     ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
     args = dict(tau2_q16=TAU2(0.8), frame_id=9)
     mm_r, mg_r, st_r = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
-    mm_g, mg_g, st_g = fa.tempcache_compress(gpu, dcodec, to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws,
-                                             ws_persistent=persistent, **args)
+    mm_g, mg_g, st_g = fa.tempcache_compress(gpu, dcodec, to_dev(K_new), to_dev(V_new),
+                                             cand=to_dev(cand) if n_cand else None, ws=ws, ws_persistent=persistent, **args)
     sync()
-    assert mg_r.sum() > 10
+    assert mg_r.sum() > T // 20
     assert np.array_equal(to_host(mg_g), mg_r)
     assert np.array_equal(to_host(mm_g), mm_r)
     assert np.array_equal(to_host(st_g), st_r)
