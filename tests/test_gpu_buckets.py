@@ -31,6 +31,29 @@ def test_prompt_buckets_bit_exact(H, n, n_p, r, m, span):
     assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("n_p", [31, 96, 97, 129, 161, 2047])   # below and from four prompt blocks on; ragged last blocks
+@pytest.mark.parametrize("n,r,m", [(1, 32, 1), (33, 64, 2), (129, 32, 3), (95, 32, 5), (64, 64, 8)])
+def test_prompt_buckets_at_the_edges_of_the_split_and_of_the_bucket_counts(n, n_p, r, m):
+    rng = np.random.default_rng(n * 4096 + n_p)
+    code, pcode = rand_codes(rng, -4, 4, 2, n, r), rand_codes(rng, -4, 4, 2, n_p, r)    # many ties
+    code[1], pcode[1] = 127, -127                                                          # the smallest product, all tied
+    got = to_host(fa.prompt_buckets(to_dev(code), to_dev(pcode), m))
+    assert np.array_equal(got, oracle.prompt_buckets(code, pcode, m))
+
+
+@pytest.mark.parametrize("n_qb,n_kb,m,n_p", [(1, 1, 1, 1), (8, 127, 2, 33), (9, 129, 3, 64), (17, 257, 5, 65)])
+def test_ann_select_buckets_at_the_edges_of_the_launches(n_qb, n_kb, m, n_p):
+    rng = np.random.default_rng(n_qb * n_kb)
+    H, BQ, BK, n_q, C = 2, 20, 64, n_qb * 20 - 7, n_kb * 64 - 5
+    qb = rng.integers(-1, n_p + 1, size=(H, n_q, m)).astype(np.int32)
+    kb = np.where(rng.random((H, C, m)) < 0.03, rng.integers(0, n_p, size=(H, C, m)), -1).astype(np.int32)
+    length = np.array([C, max(0, C - 70)], np.int32)
+    n_sel = max(1, n_kb // 3)
+    ref_sel, ref_nsel = oracle.ann_select_buckets(qb, kb, length, n_p, BQ, BK, n_sel, 0, 0)
+    sel, nsel = fa.ann_select_buckets(to_dev(qb), to_dev(kb), to_dev(length), n_p, BQ, BK, n_sel, 0, 0)
+    assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel)
+
+
 def test_prompt_buckets_of_listed_rows_only():
     rng = np.random.default_rng(3)
     H, C, n_p, r, m = 2, 900, 200, 32, 2
