@@ -108,67 +108,104 @@ __global__ __launch_bounds__(256) void encode_packed_kernel(const void *__restri
 }
 
 // ---- sign codes (LSH paragraph of Sec. 5.1): bit j = [ (R^T xq)_j >= 0 ] --------------------------------------
-// Same operand layout as encode_kernel; NB hash bits = NB/16 blocks of 16 rows of R^T.  A lane ends with the 4 sign
-// bits (rows 4g+v of a block) of one vector per block; two blocks and the four quarters g make one 32-bit word,
-// combined across the quarters with two lane exchanges.
+// HBM-bound: d*es bytes in, NB/8 out per vector.  Same operand layout as encode_kernel with NB/16 blocks of 16 rows of
+// R^T; row i of block cb is hash bit NB/16 * i + cb.  A lane's NB/16 neighbouring entries of a row of R are then one load
+// (byte loads, 256 of them per lane at d = 128 and 128 bits for fewer than two groups of vectors, were most of what the
+// launch issued), and the signs of its 4 * NB/16 sums are consecutive bits of one vector: one funnel shift each, no lane
+// exchange.  Few enough wavefronts that each hashes many groups with its operand, the next group's rows in flight:
+// 128 bits of 449280 bf16 vectors of d = 128 (122 MB) 51.6 -> 27 us = 4.5 TB/s, of 56160 vectors 13.1 -> 11.5 us.
 template <bool BF16, int D, int NB>
 __global__ __launch_bounds__(256) void encode_sign_kernel(const void *__restrict__ x, int64_t n_vec,
                                                           const int8_t *__restrict__ Rm, float qscale,
                                                           uint32_t *__restrict__ bits) {
     constexpr int KS = D / 64;
-    constexpr int CB = NB / 16;
-    constexpr int W = NB / 32;
+    constexpr int CB = NB / 16;      // 4, 8 or 16
     const int lane = lane_id();
     const int col = lane & 15, g = lane >> 4;
-    const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t gthreads = (int64_t)gridDim.x * blockDim.x;
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6, n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    const int64_t n_groups = (n_vec + 15) >> 4;
+    const size_t row_bytes = (size_t)D * (BF16 ? 2 : 4);
+    if (wave >= n_groups) return;
+    RawVector<BF16, D> raw;
+    auto load = [&](int64_t grp) {   // groups and vectors past the end re-read the last one
+        const int64_t vec = grp * 16 + col;
+        raw.load((const char *)x + (size_t)(vec < n_vec ? vec : n_vec - 1) * row_bytes, g);
+    };
+    load(wave);
     i32x4 a[KS][CB];
+    const bool aligned = ((uintptr_t)Rm & 3) == 0;   // uniform
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            int b[16];
+        for (int m = 0; m < 4; ++m) {
+            unsigned w[4][CB / 4];   // CB neighbouring entries of four coordinates
 #pragma unroll
-            for (int e = 0; e < 16; ++e) b[e] = Rm[slot_coord<BF16>(ks, g, e) * NB + cb * 16 + col];
+            for (int e = 0; e < 4; ++e) {
+                const int8_t *p = Rm + slot_coord<BF16>(ks, g, 4 * m + e) * NB + CB * col;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) a[ks][cb][m] = (int)pack_i8x4(b[4 * m], b[4 * m + 1], b[4 * m + 2], b[4 * m + 3]);
-        }
-    const int64_t wave = gtid >> 6, n_waves = gthreads >> 6;
-    const int64_t n_groups = (n_vec + 15) >> 4;
-    const size_t row_bytes = (size_t)D * (BF16 ? 2 : 4);
-    for (int64_t grp = wave; grp < n_groups; grp += n_waves) {
-        const int64_t vec = grp * 16 + col;
-        const int64_t vload = vec < n_vec ? vec : n_vec - 1;
-        const char *row = (const char *)x + (size_t)vload * row_bytes;
-        i32x4 b[KS];
-        load_quantised<BF16, D>(row, g, qscale, b);
+                for (int k = 0; k < CB / 4; ++k) {
+                    if (aligned) {
+                        w[e][k] = ((const unsigned *)p)[k];
+                    } else {
+                        w[e][k] = 0u;
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            unsigned word = 0;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int cb = 2 * w + half;
-                i32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_16x16x64(a[ks][cb], b[ks], acc);
-                unsigned nib = 0;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) nib |= (acc[v] >= 0 ? 1u : 0u) << v;
-                word |= nib << (16 * half + 4 * g);
+                        for (int i = 0; i < 4; ++i) w[e][k] |= (unsigned)(uint8_t)p[4 * k + i] << (8 * i);
+                    }
+                }
             }
-            word |= shfl_xor(word, 16);
-            word |= shfl_xor(word, 32);
-            if (g == 0 && vec < n_vec) bits[vec * W + w] = word;
+            // 4 x 4 bytes transposed: coordinates become the bytes of a word
+#pragma unroll
+            for (int k = 0; k < CB / 4; ++k) {
+                const unsigned lo01 = __builtin_amdgcn_perm(w[1][k], w[0][k], 0x05010400u), hi01 = __builtin_amdgcn_perm(w[1][k], w[0][k], 0x07030602u);
+                const unsigned lo23 = __builtin_amdgcn_perm(w[3][k], w[2][k], 0x05010400u), hi23 = __builtin_amdgcn_perm(w[3][k], w[2][k], 0x07030602u);
+                a[ks][4 * k + 0][m] = (int)__builtin_amdgcn_perm(lo23, lo01, 0x05040100u);
+                a[ks][4 * k + 1][m] = (int)__builtin_amdgcn_perm(lo23, lo01, 0x07060302u);
+                a[ks][4 * k + 2][m] = (int)__builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
+                a[ks][4 * k + 3][m] = (int)__builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+            }
+        }
+    for (int64_t grp = wave; grp < n_groups; grp += n_waves) {
+        i32x4 b[KS];
+        raw.quantise(qscale, b);
+        load(grp + n_waves < n_groups ? grp + n_waves : grp);
+        i32x4 acc[CB];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            acc[cb] = i32x4{0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc[cb] = mfma_i8_16x16x64(a[ks][cb], b[ks], acc[cb]);
+        }
+        const int64_t vec = grp * 16 + col;
+        if (vec < n_vec) {
+            // sum (v, cb) is bit CB * (4 g + v) + cb: 4 * CB bits of this lane, shifted in from the highest
+            if constexpr (CB == 4) {
+                unsigned neg = 0;
+#pragma unroll
+                for (int i = 15; i >= 0; --i) neg = __builtin_amdgcn_alignbit(neg, (unsigned)acc[i & 3][i >> 2], 31);
+                ((uint16_t *)(bits + vec * (NB / 32)))[g] = (uint16_t)~neg;
+            } else {
+#pragma unroll
+                for (int k = 0; k < CB / 8; ++k) {
+                    unsigned neg = 0;
+#pragma unroll
+                    for (int i = 31; i >= 0; --i)
+                        neg = __builtin_amdgcn_alignbit(neg, (unsigned)acc[(32 * k + i) % CB][(32 * k + i) / CB], 31);
+                    bits[vec * (NB / 32) + g * (CB / 8) + k] = ~neg;
+                }
+            }
         }
     }
 }
 
+constexpr int SIGN_WORKGROUPS = 768;
 template <bool BF16, int D, int NB>
 static void launch_encode_sign(const void *x, int64_t n_vec, const int8_t *R, float qscale, uint32_t *bits,
                                hipStream_t s) {
     int64_t groups = (n_vec + 15) / 16;
     int64_t blocks = (groups + 3) / 4;
-    if (blocks > 4096) blocks = 4096;
+    // more workgroups than are resident (two to four per compute unit, by the operand's registers) would only repeat
+    // the operand's set-up
+    if (blocks > SIGN_WORKGROUPS) blocks = SIGN_WORKGROUPS;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL((encode_sign_kernel<BF16, D, NB>), dim3((unsigned)blocks), dim3(256), 0, s, x, n_vec, R, qscale,
                        bits);

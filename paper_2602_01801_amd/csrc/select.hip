@@ -590,27 +590,31 @@ __global__ __launch_bounds__(256) void topk_kernel(const int32_t *__restrict__ s
 
 // ---- selection on sign codes (LSH family) -------------------------------------------------------------
 // Summaries: bit j of the summary of a run of g queries = majority of the run's bits (2 * ones >= queries).
-// One workgroup per (query block, head), one thread per hash bit; a wavefront's ballot is two words.
+// One workgroup per (query block, head), one thread per hash bit of a run, as many runs at a time as fit the workgroup
+// (one at a time: 7.5 us for 12 x 4680 queries of 128 bits, now 4.8); a wavefront's ballot is two words.
 __global__ __launch_bounds__(256) void lsh_summary_kernel(const uint32_t *__restrict__ qbits, int n_q, int W, int BQ,
                                                           int n_rep, int n_qb, uint32_t *__restrict__ rep) {
     extern __shared__ uint32_t qw[];  // the query block's codes, [BQ][W]
     const int b = blockIdx.x, h = blockIdx.y, j = threadIdx.x;
     const int g = BQ / n_rep;
-    const int lane = lane_id(), wave = j >> 6;
-    const bool mine = j < 32 * W;
+    const int lane = lane_id();
+    // a run's bits take 32 * W threads; the workgroup counts blockDim / (32 * W) runs at a time
+    const int bit = j & (32 * W - 1), wave = bit >> 6, run0 = j / (32 * W), runs = blockDim.x / (32 * W);
     const int q_lo = b * BQ, q_hi = min(q_lo + BQ, n_q);
     // one round of loads for the whole block, then the votes are counted from LDS
     for (int t = j; t < (q_hi - q_lo) * W; t += blockDim.x) qw[t] = qbits[((size_t)h * n_q + q_lo) * W + t];
     __syncthreads();
-    for (int u = 0; u < n_rep; ++u) {
+    for (int u = run0; u < n_rep; u += runs) {
         const int q0 = q_lo + u * g, q1 = min(q0 + g, n_q);
         int ones = 0;
-        if (mine)
-            for (int q = q0; q < q1; ++q) ones += (int)((qw[(q - q_lo) * W + (j >> 5)] >> (j & 31)) & 1u);
-        const unsigned long long m = __ballot(mine && q1 > q0 && 2 * ones >= q1 - q0);
+#pragma unroll 8
+        for (int q = q0; q < q1; ++q) ones += (int)((qw[(q - q_lo) * W + (bit >> 5)] >> (bit & 31)) & 1u);
+        const unsigned long long m = __ballot(q1 > q0 && 2 * ones >= q1 - q0);
         uint32_t *out = rep + ((size_t)h * n_qb * n_rep + (size_t)b * n_rep + u) * W;
-        if (lane == 0 && 2 * wave < W) out[2 * wave] = (uint32_t)m;
-        if (lane == 0 && 2 * wave + 1 < W) out[2 * wave + 1] = (uint32_t)(m >> 32);
+        if (lane == 0) {
+            out[2 * wave] = (uint32_t)m;
+            out[2 * wave + 1] = (uint32_t)(m >> 32);
+        }
     }
 }
 
@@ -717,6 +721,125 @@ __global__ __launch_bounds__(256) void lsh_score_kernel(const uint32_t *__restri
 #pragma unroll
                 for (int i = 0; i < LSH_QB; ++i)
                     if (b0 + i < n_qb) out[((size_t)h * n_qb + b0 + i) * n_kb_cap + kb] = best[i];
+            }
+        }
+    }
+}
+
+// Equal-bit ranking on the int8 matrix cores.  With the key's bits as 0 / 1 and the summary's as -1 / +1,
+// equal bits = product + number of the summary's zero bits, a constant per summary that is added after the maximum.  The
+// vector ALU form above needs 2 W + 1 instructions per (summary, 64 keys); here 32 x 32 pairs take W matrix instructions
+// and 16 maxima, the bits of a key are spread over bytes once (8 instructions per word) and the summaries once per
+// workgroup, as operand fragments in LDS (slot i of half g2 of a word: bits 4 g2 + i + 8 * {0..3} on both sides).
+// A workgroup takes up to LSH_MM_KB / W column blocks of 32 summaries (blockIdx.z), a wavefront a key block at a time.
+// 148 summaries of 128 bits against 12 x 37440 keys: 51.2 us on the vector ALU, 15.5 here (1.7 key blocks per wavefront,
+// so set-up and the first rows' latency weigh most).
+constexpr int LSH_MM_KB = 32;   // LDS for summary fragments per workgroup, in KB: several workgroups fit a compute unit
+__device__ __forceinline__ i32x4 lsh_spread(unsigned w) {
+    const unsigned m = 0x01010101u;
+    return i32x4{(int)(w & m), (int)((w >> 1) & m), (int)((w >> 2) & m), (int)((w >> 3) & m)};
+}
+template <int W>
+__global__ __launch_bounds__(256) void lsh_score_mm_kernel(const uint32_t *__restrict__ kbits, const int32_t *__restrict__ len,
+                                                           const uint32_t *__restrict__ rep, int C, int n_q, int BQ, int n_rep,
+                                                           int BK, int n_qb, int n_kb_cap, int32_t *__restrict__ out) {
+    constexpr int CC = LSH_MM_KB / W;
+    typedef unsigned __attribute__((ext_vector_type(W > 4 ? 4 : W), aligned(4))) key_words;   // rows are 4-byte aligned
+    constexpr int KW = W > 4 ? 4 : W;
+    __shared__ i32x4 frag[CC][W][64];
+    __shared__ int zeros[CC * 32];
+    const int h = blockIdx.y;
+    const int L = min(len[h], C);
+    const int n_kb = (L + BK - 1) / BK;
+    if ((int)blockIdx.x * 4 >= n_kb) return;   // uniform for the workgroup
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 31, g2 = lane >> 5;
+    const int NR = n_qb * n_rep, g = BQ / n_rep;
+    const int cb0 = blockIdx.z * CC;
+    const int ncb = min(CC, (NR + 31) / 32 - cb0);
+    const uint32_t *kb_h = kbits + (size_t)h * C * W;
+    const uint32_t *rp = rep + (size_t)h * NR * W;
+    // one thread per (summary, word): both halves' fragments
+    for (int t = threadIdx.x; t < ncb * 32 * W; t += blockDim.x) {
+        const int w = t % W, c = t / W;
+        const unsigned bits = rp[(size_t)min(cb0 * 32 + c, NR - 1) * W + w];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            i32x4 f = lsh_spread(bits >> (4 * half));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned z = (unsigned)f[i] ^ 0x01010101u;   // bytes that become -1
+                f[i] = (int)(((z << 8) - z) | (unsigned)f[i]);
+            }
+            frag[c >> 5][w][half * 32 + (c & 31)] = f;
+        }
+    }
+    for (int c = threadIdx.x; c < ncb * 32; c += blockDim.x) {
+        const int rc = cb0 * 32 + c;
+        // columns past the summaries or of a run without a query never count
+        int z = -(1 << 20);
+        if (rc < NR && (rc / n_rep) * BQ + (rc % n_rep) * g < n_q) {
+            z = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) z += __popc(~rp[(size_t)rc * W + w]);
+        }
+        zeros[c] = z;
+    }
+    __syncthreads();
+    for (int kb = blockIdx.x * 4 + wave; kb < n_kb; kb += gridDim.x * 4) {
+        int best[CC];
+#pragma unroll
+        for (int c = 0; c < CC; ++c) best[c] = -(1 << 20);
+        const int k_end = min(kb * BK + BK, L);
+        for (int k0 = kb * BK; k0 < k_end; k0 += 64) {
+            i32x4 a[2][W];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t *row = kb_h + (size_t)min(k0 + 32 * q + col, C - 1) * W;
+#pragma unroll
+                for (int p = 0; p < W / KW; ++p) {
+                    const key_words kw = *(const key_words *)(row + p * KW);
+#pragma unroll
+                    for (int w = 0; w < KW; ++w) a[q][p * KW + w] = lsh_spread(kw[w] >> (4 * g2));
+                }
+            }
+            const bool whole = k0 + 64 <= k_end;   // uniform
+#pragma unroll
+            for (int c = 0; c < CC; ++c) {
+                if (c < ncb) {   // uniform
+                    i32x16 acc0 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                    i32x16 acc1 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        const i32x4 b = frag[c][w][lane];
+                        acc0 = mfma_i8_32x32x32(a[0][w], b, acc0);
+                        acc1 = mfma_i8_32x32x32(a[1][w], b, acc1);
+                    }
+                    int m = best[c];
+                    if (whole) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) m = max(max(m, acc0[v]), acc1[v]);
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int key = k0 + 8 * (v >> 2) + 4 * g2 + (v & 3);
+                            if (key < k_end) m = max(m, acc0[v]);
+                            if (key + 32 < k_end) m = max(m, acc1[v]);
+                        }
+                    }
+                    best[c] = m;
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CC; ++c) {
+            if (c < ncb) {
+                int m = max_across_halves_i32(best[c]) + zeros[c * 32 + col];
+                if (n_rep == 4) m = max_over_quad_i32(m);   // uniform
+                else for (int off = 1; off < n_rep; off <<= 1) m = max(m, shfl_xor(m, off));
+                const int rc = (cb0 + c) * 32 + col;
+                if (g2 == 0 && (col & (n_rep - 1)) == 0 && rc < NR)
+                    out[((size_t)h * n_qb + rc / n_rep) * n_kb_cap + kb] = m;
             }
         }
     }
@@ -959,29 +1082,44 @@ static int select_lsh_impl(const uint32_t *qbits, int n_q, const uint32_t *kbits
     hipLaunchKernelGGL(lsh_summary_kernel, dim3(n_qb, H), dim3(256), (size_t)BQ * W * 4, s, qbits, n_q, W, BQ, n_rep, n_qb,
                        rep);
     FASTAR_LAUNCH_CHECK();
-    const int kb_per_round = BK >= 64 ? 1 : 64 / BK;
-    const int n_units = (n_kb_cap + kb_per_round - 1) / kb_per_round;
-    dim3 grid((n_units + 3) / 4, H);
-    int lds_words = n_qb * n_rep * W;
-    if ((size_t)lds_words * 4 > 48 * 1024) lds_words = 0;  // too many summaries (per-query form): read them from memory
-    const size_t lds_bytes = (size_t)lds_words * 4;
-    const unsigned rc = lsh_radius_addend(band, radius);
+    // equal bits of whole 64-key rounds, runs that tile the 32 columns: the matrix cores (15.5 against 51.2 us at
+    // 12 x 37440 keys); tables, shorter key blocks and other runs have no such form
+    if (band == 0 && BK % 64 == 0 && n_rep <= 32 && (n_rep & (n_rep - 1)) == 0) {
+        const int n_z = ((n_qb * n_rep + 31) / 32 + LSH_MM_KB / W - 1) / (LSH_MM_KB / W);
+        // four workgroups per compute unit: their summaries are spread once for all of their key blocks
+        const int64_t share = (1024 + (int64_t)H * n_z - 1) / ((int64_t)H * n_z);
+        dim3 grid((unsigned)std::min<int64_t>((n_kb_cap + 3) / 4, share), H, n_z);
+#define FASTAR_LSH_MM(WW) \
+    hipLaunchKernelGGL(lsh_score_mm_kernel<WW>, grid, dim3(256), 0, s, kbits, len, rep, C, n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score)
+        if (W == 2) FASTAR_LSH_MM(2);
+        else if (W == 4) FASTAR_LSH_MM(4);
+        else FASTAR_LSH_MM(8);
+#undef FASTAR_LSH_MM
+    } else {
+        const int kb_per_round = BK >= 64 ? 1 : 64 / BK;
+        const int n_units = (n_kb_cap + kb_per_round - 1) / kb_per_round;
+        dim3 grid((n_units + 3) / 4, H);
+        int lds_words = n_qb * n_rep * W;
+        if ((size_t)lds_words * 4 > 48 * 1024) lds_words = 0;  // too many summaries (per-query form): read them from memory
+        const size_t lds_bytes = (size_t)lds_words * 4;
+        const unsigned rc = lsh_radius_addend(band, radius);
 #define FASTAR_LSH(WW, BB)                                                                                             \
-    hipLaunchKernelGGL((lsh_score_kernel<WW, BB>), grid, dim3(256), lds_bytes, s, kbits, len, rep, C, n_q, BQ, n_rep, BK, \
-                       n_qb, n_kb_cap, lds_words, rc, radius, score)
+        hipLaunchKernelGGL((lsh_score_kernel<WW, BB>), grid, dim3(256), lds_bytes, s, kbits, len, rep, C, n_q, BQ, n_rep, BK, \
+                           n_qb, n_kb_cap, lds_words, rc, radius, score)
 #define FASTAR_LSH_W(BB)                        \
-    do {                                        \
-        if (W == 2) FASTAR_LSH(2, BB);          \
-        else if (W == 4) FASTAR_LSH(4, BB);     \
-        else FASTAR_LSH(8, BB);                 \
-    } while (0)
-    if (band == 0) FASTAR_LSH_W(0);
-    else if (band == 4) FASTAR_LSH_W(4);
-    else if (band == 8) FASTAR_LSH_W(8);
-    else if (band == 16) FASTAR_LSH_W(16);
-    else FASTAR_LSH_W(32);
+        do {                                        \
+            if (W == 2) FASTAR_LSH(2, BB);          \
+            else if (W == 4) FASTAR_LSH(4, BB);     \
+            else FASTAR_LSH(8, BB);                 \
+        } while (0)
+        if (band == 0) FASTAR_LSH_W(0);
+        else if (band == 4) FASTAR_LSH_W(4);
+        else if (band == 8) FASTAR_LSH_W(8);
+        else if (band == 16) FASTAR_LSH_W(16);
+        else FASTAR_LSH_W(32);
 #undef FASTAR_LSH_W
 #undef FASTAR_LSH
+    }
     FASTAR_LAUNCH_CHECK();
     // with tables only key blocks with a collision are candidates
     hipLaunchKernelGGL(topk_kernel, dim3(n_qb, H), dim3(256), (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score, n_kb_cap,

@@ -191,6 +191,44 @@ def test_encode_sign_bit_exact(dtype, d, n_bits, n):
     assert np.array_equal(as_u32(got), ref)
 
 
+@pytest.mark.parametrize("dtype,d,n_bits", [("bf16", 128, 128), ("fp32", 64, 64), ("bf16", 64, 256), ("fp32", 128, 256)])
+@pytest.mark.parametrize("n,offset", [(17, 1), (63, 2), (49153, 0), (98400, 0)])    # more groups of 16 than wavefronts; R off a word
+def test_encode_sign_many_groups_and_any_address(dtype, d, n_bits, n, offset):
+    rng = np.random.default_rng(d + n_bits + n)
+    R = rng.choice(np.array([-1, 1], np.int8), size=(d, n_bits))
+    xs = to_storage(rng.standard_normal((n, d)).astype(np.float32) * 1.5, dtype)
+    buf = torch.zeros(d * n_bits + offset, dtype=torch.int8, device="cuda")
+    buf[offset:] = to_dev(R).flatten()
+    got = fa.encode_sign(to_dev(xs), buf[offset:].view(d, n_bits), 127 / 4.5)
+    sync()
+    assert np.array_equal(as_u32(got), oracle.encode_sign(xs, R, 127 / 4.5))
+
+
+@pytest.mark.parametrize("n_bits", [64, 128, 256])
+@pytest.mark.parametrize("H,n_q,C,BQ,n_rep,BK,n_sel,lens", [
+    (2, 33, 33, 32, 1, 64, 1, [33, 1]),                 # one round that is not whole, two summaries
+    (3, 700, 1000, 64, 32, 64, 5, [1000, 95, 0]),       # a run per column block, several workgroups along the summaries
+    (1, 2100, 64 * 9 + 1, 32, 8, 64, 4, [577]),         # 528 summaries; a key block of one key
+    (2, 390, 192 * 5 - 70, 64, 2, 192, 3, [890, 193]),  # key blocks of three rounds, the last ones cut
+    (1, 129, 64 * 70, 128, 4, 64, 30, [4480]),          # runs without a query
+])
+def test_ann_select_lsh_at_the_edges_of_the_matrix_form(n_bits, H, n_q, C, BQ, n_rep, BK, n_sel, lens):
+    rng = np.random.default_rng(n_bits + n_q)
+    W = n_bits // 32
+    words = lambda n: (rng.integers(0, 1 << 32, size=(H, n, W), dtype=np.uint64) & rng.integers(0, 1 << 32, size=(H, n, W), dtype=np.uint64)).astype(np.uint32)  # noqa: E731
+    qb, kb = words(n_q), words(C)
+    qb[:, ::3], kb[:, ::5], kb[:, 1::7] = 0, 0xFFFFFFFF, 0          # no bit equal, every bit equal
+    length = np.array(lens, np.int32)
+    ref_sel, ref_nsel = oracle.ann_select_lsh(qb, kb, length, BQ, n_rep, BK, n_sel)
+    buf = torch.zeros(H * C * W + 1, dtype=torch.int32, device="cuda")
+    buf[1:] = to_dev(kb.view(np.int32)).flatten()
+    for dkb in (to_dev(kb.view(np.int32)), buf[1:].view(H, C, W)):   # rows on 16 bytes, and off them
+        sel, nsel = fa.ann_select_lsh(to_dev(qb.view(np.int32)), dkb, to_dev(length), BQ, n_rep, BK, n_sel)
+        sync()
+        assert np.array_equal(to_host(nsel), ref_nsel)
+        assert np.array_equal(to_host(sel), ref_sel)
+
+
 @pytest.mark.parametrize("H,n_q,C,n_bits,BQ,n_rep,BK,n_sel,lens,flip", [
     (2, 256, 1280, 128, 128, 4, 64, 5, [1280, 546], 0.3),            # cfg1-shaped
     (3, 300, 64 * 40, 128, 128, 4, 64, 7, [2560, 2000, 0], 0.02),     # heavy ties, ragged tail, empty head
