@@ -11,6 +11,11 @@
 // Softmax runs in fp32 in the log2 domain with a running maximum; masked keys (padding of the list,
 // slots beyond len) get a -inf bias and zeroed K/V rows.
 //
+// Few query blocks (S > 1): the workgroup has S groups of wavefronts, group i takes every S-th tile from i on in tile space
+// of its own, and group 0 adds the others' sums up at the end.  A tile costs a chain of row table, gather, staging and
+// products (about 2 us for a lone workgroup), which otherwise follow one another: 39 blocks of
+// 64 queries x 11 tiles 21.5 -> 13.5 us with four groups.
+//
 // fp32: attention_f32.hip.
 #include "common.hpp"
 
@@ -25,10 +30,9 @@ struct __attribute__((aligned(16))) TileMeta {
     float bias[TK];  // log2(cnt) of that row, -inf when masked
 };
 
-// Fill the row table of tile `t` (threads 0..63 of the workgroup).
+// Fill the row table of tile `t` (p = the thread's index in its group; threads 0..63).
 __device__ __forceinline__ void fill_meta(TileMeta &m, int t, const int32_t *__restrict__ sel_row, int n_listed,
-                                          int bk_shift, int L, const int32_t *__restrict__ cnt_h) {
-    const int p = threadIdx.x;
+                                          int bk_shift, int L, const int32_t *__restrict__ cnt_h, int p) {
     if (p < TK) {
         const int listpos = t * TK + p;
         const int entry = listpos >> bk_shift;
@@ -59,21 +63,25 @@ struct AttnCfg {
     static constexpr int K_BYTES = TK * KSTR * 2;
     static constexpr int V_BYTES = D * VSTR * 2;
     static constexpr int O_BYTES = NW * 32 * KSTR * 2;         // epilogue staging, reuses the tile space
+    static constexpr int PART_BYTES = (D / 2 + 2) * 64 * 4;    // a wavefront's accumulators, maxima and row sums
     static constexpr int TILE_BYTES = (K_BYTES + V_BYTES) > O_BYTES ? (K_BYTES + V_BYTES) : O_BYTES;
 };
 
-template <int D, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
+template <int D, int NW, int S>
+__global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
     const unsigned short *__restrict__ Q, const unsigned short *__restrict__ K, const unsigned short *__restrict__ V,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int bk_shift, int n_sel, int n_qb, int H, float scale_log2,
     unsigned short *__restrict__ O, float *__restrict__ lse) {
     typedef AttnCfg<D, NW> Cfg;
     constexpr int NT = Cfg::NT, KSTR = Cfg::KSTR, VSTR = Cfg::VSTR, CPR = Cfg::CPR;
-    __shared__ __attribute__((aligned(16))) unsigned char tile_mem[Cfg::TILE_BYTES];
-    __shared__ TileMeta meta[3];
-    unsigned short *Ks = (unsigned short *)tile_mem;
-    unsigned short *Vt = (unsigned short *)(tile_mem + Cfg::K_BYTES);
+    static_assert((S - 1) * NW * Cfg::PART_BYTES <= S * Cfg::TILE_BYTES, "the groups' sums reuse the tile space");
+    __shared__ __attribute__((aligned(16))) unsigned char tile_mem[S * Cfg::TILE_BYTES];
+    __shared__ TileMeta meta_all[S][3];
+    const int grp = S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);   // wave-uniform
+    TileMeta *meta = meta_all[grp];
+    unsigned short *Ks = (unsigned short *)(tile_mem + grp * Cfg::TILE_BYTES);
+    unsigned short *Vt = (unsigned short *)(tile_mem + grp * Cfg::TILE_BYTES + Cfg::K_BYTES);
 
     // workgroup -> (head, query block).  Workgroups are dealt round-robin to the 8 XCDs; give each
     // XCD a contiguous range of (head, block) pairs so that the K/V of a head stay in one L2.
@@ -87,7 +95,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
         h = item / n_qb;
         b = item % n_qb;
     }
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x - grp * NT, lane = tid & 63, wave = tid >> 6;   // of the group
     const int col = lane & 31, g = lane >> 5;
     const int L = min(len[h], C);
     const int n_listed = min(nsel[(size_t)h * n_qb + b], n_sel);
@@ -96,6 +104,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
     const unsigned short *Kh = K + (size_t)h * C * D;
     const unsigned short *Vh = V + (size_t)h * C * D;
     const int nt = ((n_listed << bk_shift) + TK - 1) / TK;
+    const int steps = (nt + S - 1) / S;   // the same for every group: a tile past the list is all masked rows
 
     // Q fragments of this wavefront's 32 queries (B operand: column = query, k-slots = 8 coordinates)
     const int q_idx = b * (NW * 32) + wave * 32 + col;
@@ -161,18 +170,20 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
         }
     };
 
-    if (nt > 0) {
-        fill_meta(meta[0], 0, sel_row, n_listed, bk_shift, L, cnt_h);
-        if (nt > 1) fill_meta(meta[1], 1, sel_row, n_listed, bk_shift, L, cnt_h);
+    auto fill = [&](int t) { fill_meta(meta[t % 3], t * S + grp, sel_row, n_listed, bk_shift, L, cnt_h, tid); };
+    if (steps > 0) {
+        fill(0);
+        if (steps > 1) fill(1);
         __syncthreads();
         issue_loads(meta[0]);
     }
-    for (int t = 0; t < nt; ++t) {
+    for (int t = 0; t < steps; ++t) {
         __syncthreads();  // tile t-1 fully consumed; row table of tile t+1 visible
         store_tiles();
         __syncthreads();
-        if (t + 1 < nt) issue_loads(meta[(t + 1) % 3]);
-        if (t + 2 < nt) fill_meta(meta[(t + 2) % 3], t + 2, sel_row, n_listed, bk_shift, L, cnt_h);
+        if (t + 1 < steps) issue_loads(meta[(t + 1) % 3]);
+        if (t + 2 < steps) fill(t + 2);
+        if (S > 1 && t * S + grp >= nt) break;   // uniform for the wavefront; only in the last step, no barrier is left in the loop
         const TileMeta &mt = meta[t % 3];
 
         // S^T = K Q^T : two blocks of 32 keys x 32 queries
@@ -243,10 +254,36 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
             }
     }
 
-    // epilogue: normalise, transpose through LDS, store rows coalesced
+    __syncthreads();
+    if constexpr (S > 1) {
+        // the other groups' accumulators, maxima and sums, lane by lane
+        if (grp > 0) {
+            float *part = (float *)(tile_mem + ((grp - 1) * NW + wave) * Cfg::PART_BYTES) + lane;
+#pragma unroll
+            for (int i = 0; i < D / 2; ++i) part[i * 64] = o_acc[i / 16][i % 16];
+            part[(D / 2) * 64] = m_run;
+            part[(D / 2 + 1) * 64] = l_run;
+        }
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int o = 1; o < S; ++o) {
+                const float *part = (const float *)(tile_mem + ((o - 1) * NW + wave) * Cfg::PART_BYTES) + lane;
+                const float m_o = part[(D / 2) * 64];
+                const float m_new = fmaxf(m_run, m_o), m_safe = m_new == -INFINITY ? 0.0f : m_new;
+                const float a0 = __builtin_amdgcn_exp2f(m_run - m_safe), a1 = __builtin_amdgcn_exp2f(m_o - m_safe);
+#pragma unroll
+                for (int i = 0; i < D / 2; ++i) o_acc[i / 16][i % 16] = fmaf(o_acc[i / 16][i % 16], a0, part[i * 64] * a1);
+                l_run = fmaf(l_run, a0, part[(D / 2 + 1) * 64] * a1);
+                m_run = m_new;
+            }
+        }
+        __syncthreads();
+        if (grp > 0) return;   // whole wavefronts; the last barrier orders a wavefront's own rows only
+    }
+    // epilogue: normalise, transpose through LDS (each wavefront its own rows), store rows coalesced
     const float l_tot = l_run + shfl_xor(l_run, 32);
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-    __syncthreads();
     unsigned short *Os = (unsigned short *)tile_mem + (size_t)wave * 32 * KSTR;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -256,7 +293,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
                        pack_bf16x2(o_acc[db][4 * q4 + 2] * inv, o_acc[db][4 * q4 + 3] * inv)};
             *(u32x2 *)(Os + col * KSTR + 32 * db + 8 * q4 + 4 * g) = w;
         }
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     {
         constexpr int LPR = CPR;          // lanes per row (16-byte chunks)
         constexpr int RPI = 64 / LPR;     // rows per iteration
@@ -335,8 +374,8 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
         int bk_shift = 0;
         while ((1 << bk_shift) < BK) ++bk_shift;
         const dim3 grid((unsigned)(((n_qb * H + 7) / 8) * 8));
-#define FASTAR_ATTN(DD, NW)                                                                                       \
-    hipLaunchKernelGGL((attn_bf16_kernel<DD, NW>), grid, dim3(NW * 64), 0, s, (const unsigned short *)Q,          \
+#define FASTAR_ATTN(DD, NW, S)                                                                                     \
+    hipLaunchKernelGGL((attn_bf16_kernel<DD, NW, S>), grid, dim3(S * NW * 64), 0, s, (const unsigned short *)Q,          \
                        (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, nsel, n_q, C, bk_shift, \
                        n_sel, n_qb, H, scale_log2, (unsigned short *)O, lse)
         // Two query blocks per workgroup in anti-phase (matrix | vector) on each SIMD; one workgroup fills a CU, so the
@@ -367,8 +406,16 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
                                             nullptr, s);
         if (d == 128)  // tuned path: direct-to-LDS tiles, LDS transpose loads
             return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
-        if (BQ == 128) FASTAR_ATTN(64, 4);
-        else FASTAR_ATTN(64, 2);
+        // d = 64.  At most one query block per compute unit: its tiles over several groups of wavefronts (256 blocks of 64
+        // queries x 11 tiles 22.1 -> 14.7 us, 40 tiles 70 -> 36; of 128 queries 21.9 -> 18.6 and 66 -> 49; lists of 2 tiles
+        // the same).  With 480 blocks it is already slower (2 tiles 9.7 -> 13.9, 11 tiles of 128 queries 28 -> 34).
+        if (n_items <= 256 && n_tiles > 2) {
+            if (BQ == 128) FASTAR_ATTN(64, 4, 2);
+            else FASTAR_ATTN(64, 2, 4);
+        } else {
+            if (BQ == 128) FASTAR_ATTN(64, 4, 1);
+            else FASTAR_ATTN(64, 2, 1);
+        }
 #undef FASTAR_ATTN
     } else {
         if (BQ > 128 || BK > 64) return FASTAR_ERR_UNSUPPORTED;

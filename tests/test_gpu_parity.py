@@ -1383,6 +1383,36 @@ def test_attention_with_a_workspace_runs_small_shapes_as_before_and_rejects_a_sh
         fa.sparse_attn_fwd(Q, K, V, None, lens, sel, nsel, 128, 64, 0.1, ws=ws[:1024])
 
 
+@pytest.mark.parametrize("H,n_q,C,n_sel,BQ,BK", [
+    (1, 64, 64 * 12, 3, 64, 64),         # the shortest list that is split: one group of wavefronts without a tile
+    (3, 777, 64 * 20 - 9, 11, 64, 64),   # groups of unequal numbers of tiles, the last key block cut by len
+    (2, 300, 64 * 20, 13, 128, 64),      # two groups
+    (2, 260, 640, 300, 64, 1),           # single keys, the last tile not full
+    (1, 64 * 256, 640, 5, 64, 64), (1, 64 * 257, 640, 5, 64, 64),   # the last split launch and the first that is not
+])
+def test_attention_of_64_wide_heads_split_over_groups_of_wavefronts(H, n_q, C, n_sel, BQ, BK):
+    rng = np.random.default_rng(H * 31 + n_sel)
+    g = torch.Generator(device="cuda").manual_seed(n_sel)
+    Q, K, V = (torch.randn(H, n, 64, device="cuda", generator=g).bfloat16() for n in (n_q, C, C))
+    Q[:, ::5] *= 3.0
+    cnt = torch.randint(1, 6, (H, C), device="cuda", generator=g, dtype=torch.int32)
+    lens = np.full(H, C, np.int32)
+    n_qb, n_kb = -(-n_q // BQ), -(-C // BK)
+    sel = np.stack([np.stack([np.sort(rng.choice(n_kb, n_sel, replace=False)) for _ in range(n_qb)]) for _ in range(H)]).astype(np.int32)
+    nsel = np.full((H, n_qb), n_sel, np.int32)
+    if n_qb > 3:
+        nsel[-1, 1:4] = 1, 0, 2                # lists shorter than the number of groups
+        for b, n in ((1, 1), (2, 0), (3, 2)):
+            sel[-1, b, n:] = -1
+    if H > 2:
+        lens[1] = 70                           # most of the listed blocks lie past the live rows
+    O, lse = (to_host(x) for x in fa.sparse_attn_fwd(Q, K, V, cnt, to_dev(lens), to_dev(sel), to_dev(nsel), BQ, BK, 0.125))
+    O_r, lse_r = oracle.sparse_attn_fwd(to_host(Q), to_host(K), to_host(V), to_host(cnt), lens, sel, nsel, BQ, BK, 0.125)
+    assert np.abs(to_f32(O).astype(np.float64) - O_r).max() <= ATOL["bf16"]
+    fin = np.isfinite(lse_r)
+    assert np.array_equal(fin, np.isfinite(lse)) and np.abs(lse[fin] - lse_r[fin]).max() <= 2e-2
+
+
 @pytest.mark.parametrize("H,n_q,C,n_sel,BK,fp8", [
     (1, 128, 64 * 12, 6, 64, False),        # the shortest list that is split over a workgroup's two groups
     (2, 129, 64 * 40, 13, 64, False),       # odd number of tiles, a block of one query
