@@ -562,8 +562,9 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     constexpr int CPT = ((int)(WINDOW_LDS_MAX / (R + 8)) + WIN_THREADS - 1) / WIN_THREADS;   // list entries per thread
     // of them, rows in flight while the ids are ranked (registers); the rows beyond are loaded when their ranks are known
     constexpr int PF = R == 32 ? (TOKS >= 256 ? CPT : BF16 ? 4 : 2) : 2;
-    // R by way of LDS, where it fits: a coalesced load per thread now, the operand's pieces from LDS later
-    constexpr bool RM_LDS = ENC && (size_t)D * R <= sizeof(partbest);
+    // R by way of LDS, where it fits and one 8-byte word per thread covers it (all but d = 128, r = 64): a coalesced load
+    // per thread now, the operand's pieces from LDS later
+    constexpr bool RM_LDS = ENC && (size_t)D * R <= sizeof(partbest) && D * R / 8 <= WIN_THREADS;
     const bool rm_lds = RM_LDS && ((uintptr_t)Rm & 7) == 0;   // uniform
     u64 rm_part = 0;
     if (rm_lds && tid < D * R / 8) rm_part = ((const u64 *)Rm)[tid];

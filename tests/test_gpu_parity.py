@@ -765,10 +765,13 @@ def test_tempcache_candidate_list_is_a_set_and_ties_go_to_the_smallest_slot(orde
     assert_cache_equal(host_cache(gpu), ref, VTOL["fp32"])
 
 
-@pytest.mark.parametrize("dtype,d,r,H,T,n_cand,persistent", [
-    ("bf16", 128, 32, 24, 1501, 3000, True), ("bf16", 128, 32, 24, 1501, 3000, False),
-    ("fp32", 64, 64, 22, 1530, 1800, True), ("bf16", 64, 32, 26, 1300, 3500, True)])
-def test_tempcache_many_workgroups_take_the_wide_window_kernel(dtype, d, r, H, T, n_cand, persistent):
+@pytest.mark.parametrize("dtype,d,r,H,T,n_cand,persistent,offset", [
+    ("bf16", 128, 32, 24, 1501, 3000, True, 0), ("bf16", 128, 32, 24, 1501, 3000, False, 0),
+    ("fp32", 64, 64, 22, 1530, 1800, True, 0), ("bf16", 64, 32, 26, 1300, 3500, True, 0),
+    # the projection matrix larger than one 8-byte word per thread; the same matrix off its 8-byte address
+    ("bf16", 128, 64, 22, 1530, 1800, True, 0), ("bf16", 128, 64, 22, 1530, 1800, False, 4), ("fp32", 128, 64, 22, 1530, 1800, True, 1),
+    ("fp32", 128, 64, 22, 1530, 1800, False, 0)])
+def test_tempcache_many_workgroups_take_the_wide_window_kernel(dtype, d, r, H, T, n_cand, persistent, offset):
     # more than two rounds of 64-token workgroups over the chip with a window that fills a compute unit's LDS: the
     # launcher takes the instantiation with 256 tokens per workgroup (ragged last workgroup, shuffled lists with
     # repeats and dead ids, repeated keys, two calls on one workspace)
@@ -785,6 +788,11 @@ def test_tempcache_many_workgroups_take_the_wide_window_kernel(dtype, d, r, H, T
     ref.stamp[:] = rng.integers(0, 9, size=(H, C))
     ref.len[:] = rng.integers(3800, 4400, size=H)
     gpu = dev_cache(ref)
+    dcodec = dev_codec(codec)
+    if offset:
+        buf = torch.zeros(d * r + offset, dtype=torch.int8, device="cuda")
+        buf[offset:] = dcodec.R.flatten()
+        dcodec.R = buf[offset:].view(d, r)
     ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
     cand = None
     for f in (9, 10):
@@ -801,7 +809,7 @@ def test_tempcache_many_workgroups_take_the_wide_window_kernel(dtype, d, r, H, T
             cand = np.stack([row[rng.permutation(n_cand)] for row in cand])
         args = dict(tau2_q16=TAU2(0.9), frame_id=f)
         mm_r, mg_r, st_r = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
-        mm_g, mg_g, st_g = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand),
+        mm_g, mg_g, st_g = fa.tempcache_compress(gpu, dcodec, to_dev(K_new), to_dev(V_new), cand=to_dev(cand),
                                                  ws=ws, ws_persistent=persistent, **args)
         sync()
         assert mg_r.sum() > 100 * H
