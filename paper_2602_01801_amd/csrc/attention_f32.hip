@@ -32,6 +32,12 @@ __device__ __forceinline__ f32x4 mfma_f32_16x16x4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// What masked positions (padding, rows past len, the end of the list) fetch: a row of the cache that nothing selects need not
+// be finite, and inf + -inf or 0 * inf would reach the output.  Offsets instead of row numbers in the table, so that the
+// choice costs nothing per load: 33 us at 196 groups x 15 key blocks against 32 with masked positions on row 0 (a branch that
+// clears their operands instead: 35).
+__device__ float zero_row[128];
+
 constexpr int KS = 4;     // wavefronts of a workgroup: they share one query group and split its tiles
 
 template <int D>
@@ -41,7 +47,7 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
     int BQ, int BK, int n_sel, int n_qb, int groups_per_block, int n_groups, float scale_log2, float *__restrict__ O,
     float *__restrict__ lse) {
     constexpr int CH = D / 16;   // 16-coordinate chunks of a row, and V columns per lane
-    __shared__ __attribute__((aligned(16))) int tkeys[KS][TKF];
+    __shared__ __attribute__((aligned(16))) long long tvrows[KS][TKF];
     __shared__ __attribute__((aligned(16))) float tbiases[KS][TKF];
     __shared__ float po[KS][4 * CH][64];       // partial O^T, as it sits in the registers
     __shared__ float pm[KS][QW], pl[KS][QW];   // reference maxima and row sums
@@ -58,7 +64,7 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
     const int nq_here = min(min(QW, BQ - q_in), n_q - q0);
     if (nq_here <= 0) return;                                // (uniform over the workgroup)
     const int L = min(len[h], C);
-    const int n_listed = L > 0 ? min(nsel[b_all], n_sel) : 0;   // masked positions read row 0, which is live then
+    const int n_listed = L > 0 ? min(nsel[b_all], n_sel) : 0;
     const int32_t *sel_row = sel + (size_t)b_all * n_sel;
     const int n_pos = max(n_listed, 0) * BK;
     const int nt = (n_pos + TKF - 1) / TKF;
@@ -77,53 +83,55 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
     }
     float m_run = -INFINITY, l_run = 0.0f;   // of this lane's query; l_run over this lane's keys only
 
-    // this wavefront's row table: cache row and bias of the 32 positions of a tile
-    int *tkey = tkeys[ks];
+    // this wavefront's row table: V row and bias of the 32 positions of a tile (rows as byte offsets from the head's own)
+    long long *tvrow = tvrows[ks];
     float *tbias = tbiases[ks];
-    auto lookup = [&](int t, int &key, float &bias) {   // position lane % 32 of tile t
+    struct Position {
+        long long k, v;
+        float bias;
+    };
+    const Position masked = {(const char *)zero_row - (const char *)Kh, (const char *)zero_row - (const char *)Vh, -INFINITY};
+    auto lookup = [&](int t) {   // position lane % 32 of tile t
+        Position pos = masked;
         const int p = t * TKF + (lane & 31);
-        key = 0;
-        bias = -INFINITY;
         if (p < n_pos) {
             const int e = p / BK;
             const int kb = sel_row[e];
             const int k = kb * BK + (p - e * BK);
             if (kb >= 0 && k < L) {
-                key = k;
-                bias = cnt_h ? log2f((float)cnt_h[k]) : 0.0f;
+                pos.k = pos.v = (long long)k * (D * 4);
+                pos.bias = cnt_h ? log2f((float)cnt_h[k]) : 0.0f;
             }
         }
+        return pos;
     };
     f32x4 kf[2][CH];
-    auto load_k = [&](int key) {   // the key of this lane's row of either half tile: lanes 0..31 hold positions 0..31
+    auto load_k = [&](long long krow) {   // the key of this lane's row of either half tile: lanes 0..31 hold positions 0..31
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            const int k = __shfl(key, 16 * hh + qc, WAVE);
-            const float *kp = Kh + (size_t)k * D + 4 * quarter;
+            const float *kp = (const float *)((const char *)(Kh + 4 * quarter) + __shfl(krow, 16 * hh + qc, WAVE));
 #pragma unroll
             for (int c = 0; c < CH; ++c) kf[hh][c] = *(const f32x4 *)(kp + 16 * c);
         }
     };
-    int key = 0;
-    float bias = -INFINITY;
+    Position next = masked;
     if (ks < nt) {
-        lookup(ks, key, bias);
-        load_k(key);
+        next = lookup(ks);
+        load_k(next.k);
     }
     for (int t = ks; t < nt; t += KS) {
         if (lane < TKF) {
-            tkey[lane] = key;
-            tbias[lane] = bias;
+            tvrow[lane] = next.v;
+            tbias[lane] = next.bias;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         // V rows of this lane's keys 16 hh + 4 quarter + v
         float vf[2][4][CH];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            const i32x4 vk = *(const i32x4 *)(tkey + 16 * hh + 4 * quarter);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const float *vp = Vh + (size_t)vk[v] * D + CH * qc;
+                const float *vp = (const float *)((const char *)(Vh + CH * qc) + tvrow[16 * hh + 4 * quarter + v]);
 #pragma unroll
                 for (int c = 0; c < CH; c += 4) {
                     const f32x4 w = *(const f32x4 *)(vp + c);
@@ -132,7 +140,7 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
                 }
             }
         }
-        if (t + KS < nt) lookup(t + KS, key, bias);
+        if (t + KS < nt) next = lookup(t + KS);
         f32x4 s[2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) s[hh] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -142,7 +150,7 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int hh = 0; hh < 2; ++hh) s[hh] = mfma_f32_16x16x4(kf[hh][c][e], q[c][e], s[hh]);
-        if (t + KS < nt) load_k(key);
+        if (t + KS < nt) load_k(next.k);
         float mx = -INFINITY;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {

@@ -479,6 +479,49 @@ def test_attention_skips_negative_and_dead_entries_inside_a_list():
     check_attention(Q, K, V, cnt, length, sel, nsel, BQ, BK, d ** -0.5, "bf16")
 
 
+@pytest.mark.parametrize("d,BQ,BK,n_kb,n_sel", [
+    (128, 128, 1, 900, 48),      # single keys, the list ends inside a step of 32
+    (64, 128, 1, 300, 45),
+    (128, 64, 64, 14, 5),        # key blocks, the last one cut by len
+    (64, 128, 16, 40, 7),
+])
+def test_fp32_attention_reads_nothing_of_rows_that_are_not_selected(d, BQ, BK, n_kb, n_sel):
+    # rows that no list names, row 0 among them, hold infinities and NaN; lists with padding, dead entries inside and a
+    # last step of keys that is not full.  The outputs are those of a cache with zeros there, bit for bit.
+    rng = np.random.default_rng(d + BK)
+    H, n_q, C = 2, 300, n_kb * BK
+    n_qb = -(-n_q // BQ)
+    Q, K, V = (rng.standard_normal((H, n, d)).astype(np.float32) for n in (n_q, C, C))
+    cnt = rng.integers(1, 5, size=(H, C)).astype(np.int32)
+    lens = np.array([C, C - BK // 2 - 1], np.int32)
+    named = np.sort(rng.choice(np.arange(1, n_kb), 2 * n_sel - 2, replace=False)) if 2 * n_sel <= n_kb else np.arange(2, n_kb)
+    named = np.union1d(named, [n_kb - 1])                       # the block that len cuts (or ends before)
+    sel = np.stack([np.stack([np.sort(np.append(rng.choice(named[:-1], n_sel - 1, replace=False), n_kb - 1))
+                              for _ in range(n_qb)]) for _ in range(H)]).astype(np.int32)
+    nsel = np.full((H, n_qb), n_sel, np.int32)
+    sel[0, 0, 1] = -1                                            # padding inside a list
+    nsel[1, 0] = n_sel - 2
+    sel[1, 1, :-1] = -1                                          # only the cut block is left
+    hidden = np.ones((H, C), bool)
+    for kb in named:
+        hidden[:, kb * BK:(kb + 1) * BK] = False
+    hidden |= np.arange(C)[None, :] >= lens[:, None]
+    hidden[:, 0] = True
+    outs = []
+    for poison in (False, True):
+        Kp, Vp = K.copy(), V.copy()
+        bad = np.resize(np.array([np.inf, np.nan, -np.inf, 3e38], np.float32), d)
+        Kp[hidden], Vp[hidden] = (bad, bad[::-1]) if poison else (0.0, 0.0)
+        outs.append([to_host(x) for x in fa.sparse_attn_fwd(to_dev(Q), to_dev(Kp), to_dev(Vp), to_dev(cnt), to_dev(lens),
+                                                            to_dev(sel), to_dev(nsel), BQ, BK, d ** -0.5)])
+        if not poison:
+            O_r, lse_r = oracle.sparse_attn_fwd(Q, Kp, Vp, cnt, lens, sel, nsel, BQ, BK, d ** -0.5)
+            assert np.abs(outs[0][0].astype(np.float64) - O_r).max() <= ATOL["fp32"]
+            fin = np.isfinite(lse_r)
+            assert np.array_equal(fin, np.isfinite(outs[0][1])) and np.abs(outs[0][1][fin] - lse_r[fin]).max() <= 1e-4
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+
+
 @pytest.mark.parametrize("seed", [1, 2, 3])
 def test_attention_on_seeded_random_shapes(seed):
     """bf16, d 128, key blocks of 64 rows: a dozen random shapes per seed (ragged queries and caches, capacities that are
