@@ -355,12 +355,16 @@ int sparse_attn_fwd(const void *Q, int n_q, const void *K, const void *V, const 
 
 /*
  * sparse_attn_fwd with a workspace: same arguments, same result (to the tolerance of the attention itself: a block
- * that several workgroups share is put together from their partial sums).  With more query blocks than the chip holds
- * at once, in a number that would leave a short last round of workgroups (bf16, d = 128, BQ = 128; the rule is in
- * attention.hip), the launch is split: whole rounds of query blocks are taken by one workgroup each, the blocks left
- * over are cut into equal shares of their tiles for all resident workgroups, blocks cut by a share's boundary leave
- * fragments in `ws`, and a second small launch combines them.  Other shapes run exactly as sparse_attn_fwd and leave
- * `ws` untouched.
+ * that several workgroups share is put together from their partial sums).  Two kinds of bf16, d = 128, BQ = 128 launches
+ * leave such partial sums (fragments) in `ws`, and a second small launch combines them:
+ *   - more (head, query block) pairs than the chip holds at once, in a number that would leave a short last round of
+ *     workgroups: whole rounds of query blocks are taken by one workgroup each, and the blocks left over are cut into
+ *     equal shares of their tiles for all resident workgroups;
+ *   - at most 128 pairs with more than 8 tiles of 64 listed keys each (n_sel * BK > 512): a block's tiles are cut into
+ *     runs, a workgroup each, where that is expected to be faster than one workgroup per block.
+ * Which launches these are follows from H, n_q, n_sel and BK alone (attn_split_full_per and attn_parts in common.hpp).
+ * Every other call runs exactly as sparse_attn_fwd and leaves `ws` untouched.  Calls that may be in flight at the same
+ * time (two streams, two threads) need a workspace each; one is enough for calls that follow one another on a stream.
  *   ws / ws_bytes  fastar_workspace_bytes(FASTAR_OP_ATTN, ...) bytes, 256-byte aligned; contents need not be kept
  */
 int sparse_attn_fwd_ws(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len,
@@ -398,9 +402,10 @@ int sparse_attn_fwd_fp8(const void *Q, int n_q, const uint8_t *K8, const uint8_t
 
 /*
  * sparse_attn_fwd_fp8 with a workspace, as sparse_attn_fwd_ws is to sparse_attn_fwd: same arguments, same result (to the
- * tolerance of the attention itself); a launch that would end in a short last round of workgroups is split, the query
- * blocks left over are cut into equal shares of their tiles, and a second small launch combines the fragments.  Other
- * shapes run exactly as sparse_attn_fwd_fp8 and leave `ws` untouched.
+ * tolerance of the attention itself).  The same two kinds of launches leave fragments in `ws` for a second small launch to
+ * combine: those that would end in a short last round of workgroups, and those of at most 256 (head, query block) pairs
+ * whose lists are long enough for several workgroups each.  Every other call runs exactly as sparse_attn_fwd_fp8 and
+ * leaves `ws` untouched.  Calls that may be in flight at the same time need a workspace each.
  *   ws / ws_bytes  fastar_workspace_bytes(FASTAR_OP_ATTN, ...) bytes, 256-byte aligned; contents need not be kept
  */
 int sparse_attn_fwd_fp8_ws(const void *Q, int n_q, const uint8_t *K8, const uint8_t *V8T, const int32_t *cnt,

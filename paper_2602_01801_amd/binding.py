@@ -484,7 +484,8 @@ def ann_cross_attn_fwd(Q, qcode, Kp, Vp, pcode, BQ: int, n_sel: int, scale: floa
 def sparse_attn_fwd(Q, K, V, cnt, length, sel, nsel, BQ: int, BK: int, scale: float, out=None, want_lse: bool = True,
                     ws=None):
     """Block-sparse attention.  Returns (O [H,n_q,d] in Q's dtype, lse [H,n_q] float32 or None).
-    ws: uint8 device workspace of workspace_bytes(OP_ATTN, ...) -> sparse_attn_fwd_ws (persistent kernel where it pays)."""
+    ws: uint8 device workspace of workspace_bytes(OP_ATTN, ...) -> sparse_attn_fwd_ws (several workgroups per query block
+    where that pays; calls that may be in flight at the same time need a workspace each)."""
     _dev(Q)
     _dev(K, Q.dtype)
     _dev(V, Q.dtype)
@@ -535,7 +536,7 @@ def kv_to_fp8(cache: Cache, K8: torch.Tensor, V8T: torch.Tensor, stamp_lo: int =
 def sparse_attn_fwd_fp8(Q, K8, V8T, cnt, length, C: int, sel, nsel, BQ: int, BK: int, scale: float, out=None,
                         want_lse: bool = True, ws=None):
     """Block-sparse attention over the 8-bit cache copy.  Returns (O [H,n_q,d] bf16, lse [H,n_q] float32 or None).
-    ws: workspace of workspace_bytes(OP_ATTN, ...) -> sparse_attn_fwd_fp8_ws."""
+    ws: workspace of workspace_bytes(OP_ATTN, ...) -> sparse_attn_fwd_fp8_ws (as for sparse_attn_fwd)."""
     _dev(Q, torch.bfloat16)
     _dev(K8, torch.uint8)
     _dev(V8T, torch.uint8)

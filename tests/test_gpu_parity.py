@@ -1418,7 +1418,7 @@ def test_persistent_attention_matches_the_oracle_and_the_plain_launch(H, n_q, C,
         assert np.array_equal(ok, np.isfinite(lw[h, q0:q1])) and np.abs(lw[h, q0:q1][ok] - lr[ok]).max(initial=0.0) <= 2e-2
 
 
-def test_attention_with_a_workspace_runs_small_shapes_as_before_and_rejects_a_short_workspace():
+def test_attention_with_a_workspace_runs_short_lists_as_without_and_rejects_a_short_workspace():
     rng = np.random.default_rng(5)
     H, n_q, C, n_sel = 2, 300, 640, 4
     Q, K, V = (to_dev(to_storage(rng.standard_normal((H, n, 128)).astype(np.float32), "bf16")) for n in (n_q, C, C))
@@ -1432,6 +1432,46 @@ def test_attention_with_a_workspace_runs_small_shapes_as_before_and_rejects_a_sh
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     with pytest.raises(fa.FastarError):
         fa.sparse_attn_fwd(Q, K, V, None, lens, sel, nsel, 128, 64, 0.1, ws=ws[:1024])
+
+
+@pytest.mark.parametrize("kind,H,n_q,n_sel,BQ,BK,used", [
+    ("bf16", 1, 512, 10, 128, 64, True),         # few query blocks, long lists: fragments
+    ("bf16", 32, 512, 50, 128, 64, True),        # 128 pairs, the most that are cut
+    ("bf16", 43, 384, 50, 128, 64, False),       # 129 pairs
+    ("bf16", 1, 512, 8, 128, 64, False),         # the longest lists that never are: 8 tiles
+    ("bf16", 1, 512, 512, 128, 1, False),        # the same of single keys
+    ("bf16", 8, 640, 50, 64, 64, False),         # BQ = 64
+    ("bf16_d64", 1, 512, 50, 128, 64, False),
+    ("fp32", 1, 512, 50, 128, 64, False),
+    ("fp8", 1, 512, 10, 128, 64, True),
+    ("fp8", 64, 512, 300, 128, 64, True),        # 256 pairs
+    ("fp8", 257, 100, 50, 128, 64, False),       # 257 pairs
+    ("fp8", 1, 512, 4, 128, 64, False),
+])
+def test_which_attention_launches_use_their_workspace(kind, H, n_q, n_sel, BQ, BK, used):
+    # the interface says which calls write the workspace; the others leave it as it is and give the plain call's bits
+    d, dt = 64 if kind == "bf16_d64" else 128, torch.float32 if kind == "fp32" else torch.bfloat16
+    C = n_sel * BK + 64
+    g = torch.Generator(device="cuda").manual_seed(H + n_sel)
+    Q, K, V = (torch.randn(H, n, d, device="cuda", generator=g).to(dt) for n in (n_q, C, C))
+    n_qb = -(-n_q // BQ)
+    lens = torch.full((H,), C, dtype=torch.int32, device="cuda")
+    sel = torch.arange(n_sel, dtype=torch.int32, device="cuda").expand(H, n_qb, n_sel).contiguous()
+    nsel = torch.full((H, n_qb), n_sel, dtype=torch.int32, device="cuda")
+    ws = torch.full((fa.workspace_bytes(fa.OP_ATTN, H, n_q, C),), 0xA5, dtype=torch.uint8, device="cuda")
+    if kind == "fp8":
+        cache = fa.Cache.empty(H, C, d, 32, dt)
+        cache.K.copy_(K), cache.V.copy_(V), cache.len.copy_(lens), cache.stamp.zero_()
+        kv8 = fa.kv8_empty(H, C, d)
+        fa.kv_to_fp8(cache, *kv8)
+        run = lambda w: fa.sparse_attn_fwd_fp8(Q, *kv8, None, lens, C, sel, nsel, BQ, BK, d ** -0.5, ws=w)  # noqa: E731
+    else:
+        run = lambda w: fa.sparse_attn_fwd(Q, K, V, None, lens, sel, nsel, BQ, BK, d ** -0.5, ws=w)  # noqa: E731
+    with_ws, plain = run(ws), run(None)
+    sync()
+    assert bool((ws != 0xA5).any()) == used
+    if not used:
+        assert all(torch.equal(a, b) for a, b in zip(with_ws, plain))
 
 
 @pytest.mark.parametrize("H,n_q,C,n_sel,BQ,BK", [
