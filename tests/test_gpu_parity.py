@@ -1543,9 +1543,18 @@ def test_attention_of_few_query_blocks_matches_the_oracle(H, n_q, C, n_sel, BK, 
         kv8 = fa.kv8_empty(H, C, 128)
         fa.kv_to_fp8(cache, *kv8)
         run = lambda w: fa.sparse_attn_fwd_fp8(Q, *kv8, cnt, to_dev(lens), C, to_dev(sel), to_dev(nsel), 128, BK, 128 ** -0.5, ws=w)  # noqa: E731
+        unsplit = lambda: run(None)  # noqa: E731
     else:
         run = lambda w: fa.sparse_attn_fwd(Q, K, V, cnt, to_dev(lens), to_dev(sel), to_dev(nsel), 128, BK, 128 ** -0.5, ws=w)  # noqa: E731
-    outs = [tuple(to_host(x) for x in run(w)) for w in (ws, None)]
+
+        def unsplit():
+            # the same query blocks in a launch of more than 256 pairs, which takes whole lists: the heads repeated
+            rep = 256 // (H * n_qb) + 1
+            many = lambda x: x.repeat(rep, *[1] * (x.dim() - 1))  # noqa: E731
+            O, lse = fa.sparse_attn_fwd(*(many(x) for x in (Q, K, V, cnt, to_dev(lens), to_dev(sel), to_dev(nsel))), 128, BK,
+                                        128 ** -0.5)
+            return O[:H], lse[:H]
+    outs = [tuple(to_host(x) for x in f()) for f in (lambda: run(ws), lambda: run(None), unsplit)]
     sync()
     if fp8:
         O_r, lse_r = oracle.sparse_attn_fwd_fp8(to_host(Q), to_host(kv8[0]), to_host(kv8[1]), to_host(cnt), lens, C, sel, nsel, 128,
@@ -1560,5 +1569,10 @@ def test_attention_of_few_query_blocks_matches_the_oracle(H, n_q, C, n_sel, BK, 
         assert errs[-1].max() <= tol
         fin = np.isfinite(lse_r)
         assert np.array_equal(fin, np.isfinite(lse)) and np.abs(lse[fin] - lse_r[fin]).max() <= tol_lse
+    # Splitting a list loses no precision: P is rounded against the maximum of a part of the list instead of the whole
+    # list's, everything else is fp32.  The roundings are other ones, so the two errors are two samples of the same
+    # distribution: one query's outputs share its roundings of P, N queries give N squared errors of relative variance about
+    # 2, and the ratio of two such root mean squares has a standard deviation of about sqrt(2 * 2 / N) / 2 = 1 / sqrt(N).
+    # Three of them.
     rms = [np.sqrt((e ** 2).mean()) for e in errs]
-    assert 0.8 <= rms[0] / rms[1] <= 1.25, rms   # splitting a list loses no precision
+    assert max(rms[0], rms[1]) <= (1.0 + 3.0 / np.sqrt(H * n_q)) * rms[2], rms
