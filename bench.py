@@ -448,17 +448,23 @@ def cpu_baseline(cfg, pipe, oracle_cache, oracle_prev, oracle_fid, host_chunks, 
     return info
 
 
-def attn_kernel_name(n_items, H, C, d=128, n_tiles=None):
-    """Which bf16 d = 128, BQ = 128, BK = 64 kernel sparse_attn_fwd launches for this many (head, query block) pairs
-    and this cache capacity (K and V of all heads within 256 MB: bias rows written in the matrix phase).  n_tiles: 64-key
-    tiles per query block when the call carries a workspace (then a launch with a short last round is split)."""
+def attn_kernel_name(n_items, H, C, n_tiles, ws, fp8=False, d=128):
+    """Which kernel the self-attention call launches (bf16 or the 8-bit copy, d = 128, BQ = 128, BK = 64) for this many
+    (head, query block) pairs, cache capacity (bf16: K and V of all heads within 256 MB: bias rows written in the matrix
+    phase) and 64-key tiles per query block; ws: the call carries a workspace."""
     per_xcd = (n_items + 7) // 8
     tail = per_xcd % 64
-    if n_tiles is not None and per_xcd > 64 and 0 < tail <= 24 and n_tiles * (1.2 - 0.0375 * tail) > 30.0:
-        return "attn_bf16_d128_sk_kernel + attn_combine_kernel"
+    if ws and per_xcd > 64 and 0 < tail <= 24 and n_tiles * (1.2 - 0.0375 * tail) > 30.0:   # a short last round is shared out
+        return "attn_%s_d128_sk_kernel + attn_combine_kernel" % ("fp8" if fp8 else "bf16")
+    if fp8:
+        return "attn_fp8_d128_parts_kernel + attn_combine_parts_kernel, or attn_fp8_d128_kernel" if ws and n_items <= 256 else "attn_fp8_d128_kernel"
+    pp = "attn_bf16_d128_pp_kernel<4, true, %s, " % ("true" if H * C * d * 2 * 2 <= (256 << 20) else "false")
+    if n_items <= 256 and n_tiles > 5:   # one block per workgroup, split over its two groups
+        return pp + "true>" + (" (+ attn_combine_parts_kernel where that pays)" if ws and n_items <= 128 and n_tiles > 8 else "")
+    if n_items <= 512 and n_tiles <= 5 and (n_items <= 256 or n_tiles <= 2):
+        return "attn_bf16_d128_kernel<4>"
     if n_items <= 512 or n_items % 512 == 0 or n_items % 512 >= 256:
-        resident = H * C * d * 2 * 2 <= (256 << 20)
-        return "attn_bf16_d128_pp_kernel<4, true, %s>" % ("true" if resident else "false")
+        return pp + "false>"
     return "attn_bf16_d128_kernel<4>"
 
 
@@ -727,7 +733,7 @@ def run_layer(args, workload, torch, fa, np, to_dev, to_host, steps, warmup, sta
                        "frac_of_peak": {k: round(v / PEAK_HBM_GBS, 4) for k, v in stage_gbs.items()},
                        "peak_GBs": PEAK_HBM_GBS},
         "effective_tflops": round(tflops, 2), "pct_mfma_peak": round(100 * tflops / peak_tf, 2),
-        "roofline": {"kernel": ("attn_fp8_d128_kernel" if fp8 else attn_kernel_name(cfg["H"] * pipe.n_qb, cfg["H"], C, n_tiles=(pipe.n_sel * pipe.BK + 63) // 64 if pipe.ws_a is not None else None)) + " (block-sparse self-attention)",
+        "roofline": {"kernel": attn_kernel_name(cfg["H"] * pipe.n_qb, cfg["H"], C, (pipe.n_sel * pipe.BK + 63) // 64, pipe.ws_a is not None, fp8) + " (block-sparse self-attention)",
                      "bound": "hbm" if hbm_bound else "mfma",
                      "achieved": round(gbs, 1) if hbm_bound else round(tflops, 2),
                      "peak": PEAK_HBM_GBS if hbm_bound else peak_tf, "unit": "GB/s" if hbm_bound else "TFLOP/s",

@@ -18,20 +18,34 @@ def test_more_than_one_gpu_is_refused_with_a_message():
 def test_roofline_kernel_name_follows_the_dispatch_rule():
     sys.path.insert(0, ROOT)
     import bench
+    name = bench.attn_kernel_name
     # cfg2: 37 query blocks x 12 heads fit one round of two-block workgroups; 12 x 37440 slots of K and V = 230 MB
-    assert bench.attn_kernel_name(37 * 12, 12, 37440) == "attn_bf16_d128_pp_kernel<4, true, true>"
-    assert bench.attn_kernel_name(37 * 12, 12, 196608) == "attn_bf16_d128_pp_kernel<4, true, false>"
-    # cfg5: 29 x 40 = 1160 = 2 rounds of 512 + 136 (< 256): one block per workgroup
-    assert bench.attn_kernel_name(29 * 40, 40, 230400) == "attn_bf16_d128_kernel<4>"
-    assert bench.attn_kernel_name(29 * 40, 40, 230400, n_tiles=360).startswith("attn_bf16_d128_sk_kernel")   # with a workspace: split launch
-    assert bench.attn_kernel_name(37 * 12, 12, 37440, n_tiles=52) == "attn_bf16_d128_pp_kernel<4, true, true>"
-    assert bench.attn_kernel_name(1024, 40, 230400).startswith("attn_bf16_d128_pp_kernel<4, true, false")
-    assert bench.attn_kernel_name(1024 + 256, 8, 1000).startswith("attn_bf16_d128_pp_kernel")
-    # the same rule as the launcher's source states it
-    src = open(os.path.join(ROOT, "paper_2602_01801_amd", "csrc", "attention.hip")).read()
-    assert "n_items <= 512 || n_items % 512 == 0 || n_items % 512 >= 256" in src
-    src = open(os.path.join(ROOT, "paper_2602_01801_amd", "csrc", "attention_d128_pp.hip")).read()
-    assert "(size_t)H * (size_t)C * D * 2 * 2 <= ((size_t)256 << 20)" in src
+    assert name(37 * 12, 12, 37440, 52, True) == "attn_bf16_d128_pp_kernel<4, true, true, false>"
+    assert name(37 * 12, 12, 196608, 52, False) == "attn_bf16_d128_pp_kernel<4, true, false, false>"
+    # cfg5: 29 x 40 = 1160 = 2 rounds of 512 + 136 (< 256): one block per workgroup, split with a workspace
+    assert name(29 * 40, 40, 230400, 360, False) == "attn_bf16_d128_kernel<4>"
+    assert name(29 * 40, 40, 230400, 360, True).startswith("attn_bf16_d128_sk_kernel")
+    assert name(29 * 40, 40, 230400, 360, True, fp8=True).startswith("attn_fp8_d128_sk_kernel")
+    assert name(1024, 40, 230400, 360, False) == "attn_bf16_d128_pp_kernel<4, true, false, false>"
+    assert name(1024 + 256, 8, 1000, 10, False).startswith("attn_bf16_d128_pp_kernel")
+    # at most 256 pairs: a block per workgroup; short lists: the one-block kernel
+    assert name(13 * 12, 12, 32760, 52, False) == "attn_bf16_d128_pp_kernel<4, true, true, true>"
+    assert name(128, 8, 32760, 52, True).startswith("attn_bf16_d128_pp_kernel<4, true, true, true> (+ attn_combine_parts")
+    assert name(129, 8, 32760, 52, True) == "attn_bf16_d128_pp_kernel<4, true, true, true>"
+    assert name(256, 8, 32760, 5, True) == name(444, 12, 32760, 2, True) == "attn_bf16_d128_kernel<4>"
+    assert name(444, 12, 32760, 5, True) == "attn_bf16_d128_pp_kernel<4, true, true, false>"
+    # the same rules as the launchers' sources state them, and the instantiations that are named
+    src = lambda f: open(os.path.join(ROOT, "paper_2602_01801_amd", "csrc", f)).read()  # noqa: E731
+    order = [src("attention.hip").index(rule) for rule in (
+        "if (ws && d == 128 && BQ == 128 && full_per > 0)",
+        "n_items <= 256 && n_tiles > 5)",
+        "n_items <= 512 && n_tiles <= 5 && (n_items <= 256 || n_tiles <= 2))",
+        "(n_items <= 512 || n_items % 512 == 0 || n_items % 512 >= 256))")]
+    assert order == sorted(order)
+    assert "tail_per <= 24 && (float)n_tiles * (1.2f - 0.0375f * (float)tail_per) > 30.0f" in src("common.hpp")
+    assert "ws && n_qb * H <= 256 ? attn_parts(" in src("attention_fp8.hip")
+    assert "(size_t)H * (size_t)C * D * 2 * 2 <= ((size_t)256 << 20)" in src("attention_d128_pp.hip")
+    assert "template <int NWG, bool CONTIG, bool BIAS_X, bool SPLIT>" in src("attention_d128_pp.hip")
 
 
 def test_traffic_figure_is_read_from_the_committed_profile():
