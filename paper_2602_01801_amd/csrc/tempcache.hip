@@ -509,9 +509,10 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 // here (records and plan scratch are clean on entry).  The age histogram the plan wants is counted beside the match: by
 // workgroups of its own at the end of the grid's x range (n_hist of them; behind the match it cost every workgroup 2 us),
 // with 256 tokens per workgroup, where the grid fills the chip, by every workgroup as its tail (n_hist = 0).
-// TOKS: tokens per workgroup.  64 (eight wavefronts share the window scan) when the call is latency-bound; 256 (two
-// wavefronts share the scan for their 64 tokens) when there are many more workgroups than the chip holds at once:
-// staging the window is then paid a quarter as often.
+// TOKS: tokens per workgroup.  64 (eight wavefronts share the window scan) when the call is latency-bound; 256 (four
+// wavefronts share the scan for their 128 tokens) when there are many more workgroups than the chip holds at once:
+// staging the window is then paid a quarter as often.  The wide form's prefetched rows and operands do not all fit the
+// registers: with bf16 rows of 128 it spills 100 bytes per lane (r = 32; 268 at r = 64), around the scan, not in its loop.
 //
 // What bounds it: the chain of dependent phases of one workgroup (list, sort and staging, encode, scan, look-up, threshold
 // test).  The window's code rows are gathered straight from the list, before its order is known: they are in flight while
