@@ -1083,12 +1083,13 @@ static int select_lsh_impl(const uint32_t *qbits, int n_q, const uint32_t *kbits
                        rep);
     FASTAR_LAUNCH_CHECK();
     // equal bits of whole 64-key rounds, runs that tile the 32 columns: the matrix cores (15.5 against 51.2 us at
-    // 12 x 37440 keys); tables, shorter key blocks and other runs have no such form
-    if (band == 0 && BK % 64 == 0 && n_rep <= 32 && (n_rep & (n_rep - 1)) == 0) {
-        const int n_z = ((n_qb * n_rep + 31) / 32 + LSH_MM_KB / W - 1) / (LSH_MM_KB / W);
+    // 12 x 37440 keys); tables, shorter key blocks and other runs have no such form, and more summaries than 65535
+    // workgroups take (8.4 million of 256 bits per head) would exceed what the device allows a grid's z (65536)
+    const int64_t n_z = (((int64_t)n_qb * n_rep + 31) / 32 + LSH_MM_KB / W - 1) / (LSH_MM_KB / W);
+    if (band == 0 && BK % 64 == 0 && n_rep <= 32 && (n_rep & (n_rep - 1)) == 0 && n_z <= 65535) {
         // four workgroups per compute unit: their summaries are spread once for all of their key blocks
-        const int64_t share = (1024 + (int64_t)H * n_z - 1) / ((int64_t)H * n_z);
-        dim3 grid((unsigned)std::min<int64_t>((n_kb_cap + 3) / 4, share), H, n_z);
+        const int64_t share = (1024 + H * n_z - 1) / (H * n_z);
+        dim3 grid((unsigned)std::min<int64_t>((n_kb_cap + 3) / 4, share), H, (unsigned)n_z);
 #define FASTAR_LSH_MM(WW) \
     hipLaunchKernelGGL(lsh_score_mm_kernel<WW>, grid, dim3(256), 0, s, kbits, len, rep, C, n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score)
         if (W == 2) FASTAR_LSH_MM(2);

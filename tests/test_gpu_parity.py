@@ -229,6 +229,22 @@ def test_ann_select_lsh_at_the_edges_of_the_matrix_form(n_bits, H, n_q, C, BQ, n
         assert np.array_equal(to_host(sel), ref_sel)
 
 
+@pytest.mark.parametrize("n_qb", [262140, 262141])   # the most summaries that the matrix form takes, and a run more
+def test_ann_select_lsh_with_more_summaries_than_one_grid_of_the_matrix_form(n_qb):
+    BQ, W, C, n_sel = 32, 8, 4 * 64 - 7, 2
+    g = torch.Generator(device="cuda").manual_seed(n_qb)
+    words = lambda n: torch.randint(-2 ** 31, 2 ** 31 - 1, (1, n, W), dtype=torch.int32, device="cuda", generator=g)  # noqa: E731
+    qb, kb = words(n_qb * BQ - 5), words(C)
+    length = np.array([C], np.int32)
+    sel, nsel = (to_host(x)[0] for x in fa.ann_select_lsh(qb, kb, to_dev(length), BQ, BQ, 64, n_sel))
+    sync()
+    assert (nsel == n_sel).all()
+    for b0 in (0, n_qb // 2, n_qb - 200):   # a query block's selection depends on no other block
+        part = to_host(qb[:, b0 * BQ:(b0 + 200) * BQ]).view(np.uint32)
+        ref_sel, _ = oracle.ann_select_lsh(part, to_host(kb).view(np.uint32), length, BQ, BQ, 64, n_sel)
+        assert np.array_equal(sel[b0:b0 + 200], ref_sel[0])
+
+
 @pytest.mark.parametrize("H,n_q,C,n_bits,BQ,n_rep,BK,n_sel,lens,flip", [
     (2, 256, 1280, 128, 128, 4, 64, 5, [1280, 546], 0.3),            # cfg1-shaped
     (3, 300, 64 * 40, 128, 128, 4, 64, 7, [2560, 2000, 0], 0.02),     # heavy ties, ragged tail, empty head
