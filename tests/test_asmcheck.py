@@ -1,6 +1,12 @@
 """The build-time ISA check of the attention kernels' inline-assembly LDS reads (paper_2602_01801_amd/asmcheck.py):
 it must flag a register touched between an asm read and its wait, and nothing else."""
-from paper_2602_01801_amd import asmcheck
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2602_01801_amd import asmcheck, build
 
 
 def lines(text):
@@ -81,3 +87,19 @@ def test_the_scan_ends_at_an_unconditional_jump():
 	;;#ASMEND
 """
     assert asmcheck._check_lines(lines(text), False) == 0
+
+
+def test_the_combine_kernel_has_four_fragments_in_flight(tmp_path):
+    # 16 loads of 16 bytes (four of each fragment) before the first of them is waited for: left to itself the compiler asks
+    # for a fragment when it has used up the one before, and the launch takes half as long again
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    asm = str(tmp_path / "a.s")
+    subprocess.run([hipcc, *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "attention_d128.hip"), "-o", asm],
+                   check=True, stderr=subprocess.DEVNULL)
+    text = open(asm).read()
+    body = text[re.search(r"^_ZN\S*attn_combine_kernel\S*:", text, re.M).start():]
+    body = body[:body.index(".Lfunc_end")]
+    runs = [part.count("global_load_dwordx4") for part in re.split(r"s_waitcnt vmcnt|s_barrier", body)]
+    assert max(runs) == 16, runs
