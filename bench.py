@@ -271,7 +271,8 @@ class ChunkPipeline:
         valid = (kb >= 0) & (t.arange(self.n_sel, device=sel.device)[None, None, :] < nsel[:, :, None])
         keys = t.clamp(t.minimum((kb + 1) * self.BK, L) - kb * self.BK, min=0) * valid
         es = self.cache.K.element_size()
-        return float(keys.sum().item()) * self.d * es * 2 + 2.0 * self.H * self.n_q * self.d * es
+        es_kv = 1 if self.kv8 is not None else es
+        return float(keys.sum().item()) * self.d * es_kv * 2 + 2.0 * self.H * self.n_q * self.d * es
 
     def attended_flops(self):
         """4 * d * sum over (head, query) of the live keys in the selected blocks, for the current selection."""
@@ -468,7 +469,8 @@ def attn_kernel_name(n_items, H, C, n_tiles, ws, fp8=False, d=128):
     return "attn_bf16_d128_kernel<4>"
 
 
-TRAFFIC_FILES = {"cfg2": "cfg2_chunk_step_hbm_traffic.txt", "cfg5full": "cfg5full_chunk_step_hbm_traffic.txt"}
+TRAFFIC_FILES = {"cfg2": "cfg2_chunk_step_hbm_traffic.txt", "cfg5full": "cfg5full_chunk_step_hbm_traffic.txt",
+                 "cfg5full_fp8": "cfg5full_fp8_hbm_traffic.txt"}
 
 
 def profiled_traffic(workload):
@@ -481,7 +483,7 @@ def profiled_traffic(workload):
     best = None
     try:
         for line in open(os.path.join(ROOT, "profiles", name)):
-            if "attn_bf16_d128" in line and not line.startswith("#"):
+            if ("attn_bf16_d128" in line or "attn_fp8_d128" in line) and not line.startswith("#"):
                 f = line.split()
                 total = (float(f[-2]) + float(f[-1])) * 1e6
                 best = total if best is None else max(best, total)   # of several groups of launches: the self-attention ones
@@ -699,7 +701,7 @@ def run_layer(args, workload, torch, fa, np, to_dev, to_host, steps, warmup, sta
         "compress": cf * H * T * (5 * d * es + 40 + r) + cf * H * T * r,
     }
     stage_gbs = {k: round(v / (stage_ms[k] * 1e-3) / 1e9, 1) for k, v in bytes_stage.items() if stage_ms.get(k, 0) > 0}
-    traffic, traffic_src = (None, None) if fp8 else profiled_traffic(workload)
+    traffic, traffic_src = profiled_traffic(workload + "_fp8" if fp8 else workload)
     # Which roofline binds the attention launch.  Its arithmetic intensity (128 flops per gathered byte at BQ 128) is
     # below the chip's balance point, so it is the matrix roofline only while the gathered rows are served from cache.
     # The counter summary of this workload decides: when at least half of the gathered bytes come from HBM, the launch is

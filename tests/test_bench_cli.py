@@ -57,5 +57,23 @@ def test_traffic_figure_is_read_from_the_committed_profile():
     t5, src5 = bench.profiled_traffic("cfg5full")
     assert t5 is not None and 5e9 < t5 < 14e9             # the world-model launch gathers 13.7 GB, most of it from HBM
     assert src5 == "profiles/cfg5full_chunk_step_hbm_traffic.txt"
+    t8, src8 = bench.profiled_traffic("cfg5full_fp8")
+    assert t8 is not None and 2e9 < t8 < 7e9              # half the bytes per row
+    assert src8 == "profiles/cfg5full_fp8_hbm_traffic.txt"
     # a workload without a committed counter summary reports no traffic rather than another workload's
-    assert bench.profiled_traffic("cfg5") == (None, None)
+    assert bench.profiled_traffic("cfg5") == bench.profiled_traffic("cfg2_fp8") == (None, None)
+
+
+def test_gathered_bytes_count_rows_of_the_cache_that_is_attended():
+    import types
+    import torch
+    sys.path.insert(0, ROOT)
+    import bench
+    cls = next(c for c in vars(bench).values() if isinstance(c, type) and hasattr(c, "gathered_bytes"))
+    cache = types.SimpleNamespace(K=torch.zeros(1, dtype=torch.bfloat16), len=torch.tensor([130], dtype=torch.int32))
+    sel = (torch.tensor([[[0, 2, -1]]], dtype=torch.int32), torch.tensor([[2]], dtype=torch.int32))
+    layer = dict(t=torch, sel=sel, cache=cache, BK=64, n_sel=3, H=1, n_q=100, d=128)
+    q_and_o = 2 * 100 * 128 * 2
+    for kv8, es in ((None, 2), ((None, None), 1)):
+        got = cls.gathered_bytes(types.SimpleNamespace(kv8=kv8, **layer))
+        assert got == (64 + 2) * 128 * es * 2 + q_and_o
