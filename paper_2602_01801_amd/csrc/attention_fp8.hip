@@ -10,8 +10,8 @@
 //                  key (32g + 16kb + 4q + e) sits in A row (8q + 4g + e) of half kb, so that a lane's 32 scores are
 //                  the keys 32g .. 32g+31 in the order the next product wants them;
 //   O^T = V^T P^T  A = 32 value coordinates x 64 keys from LDS, B = P rounded to E4M3, straight from the score registers;
-//   l = 1^T P^T    the row sums, by the same instruction on an operand of ones: numerator and denominator see the
-//                  same rounded P, so the output stays a convex combination of the stored values.
+//   l = 1^T P^T    the row sums, by a matrix instruction (16x16x128) on an operand of ones: numerator and denominator see
+//                  the same rounded P, so the output stays a convex combination of the stored values.
 // Softmax arithmetic as in the bf16 kernels: scores start from the keys' bias (log2 of the multiplicity, -inf for
 // dead slots), exponent in one fma, lazily updated reference maximum.  E4M3 spans 2^-9 .. 448, so P is kept near the
 // top of that range: P = 2^6 * exp2(score - reference) with the reference at most 2 octaves behind the running
@@ -40,7 +40,7 @@ __device__ __forceinline__ int sw_k(int row) { return ((row >> 1) & 1) | (((row 
 __device__ __forceinline__ int sw_v(int row) { return (row >> 2) & 3; }
 
 __device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float d) {
-    int w = 0;
+    int w = (int)__float_as_uint(a);   // both halves are written; a register that ends here anyway saves clearing one
     w = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, w, false);
     w = __builtin_amdgcn_cvt_pk_fp8_f32(c, d, w, true);
     return (unsigned)w;
@@ -125,18 +125,32 @@ __global__ __launch_bounds__(256) void kv_to_fp8_kernel(const void *__restrict__
 }
 
 // ---- attention ------------------------------------------------------------------------------------------------
-struct __attribute__((aligned(16))) TileMeta {
-    float bias[TK];  // log2(cnt) of the tile's keys in units of raw scores (divided by scale * log2 e), -inf when dead
-    int blk;         // block to load (a masked tile loads block 0, which is live)
-    int pad[3];
-};
-
+// What bounds it: on a cache that L2 serves, the issue of one wavefront (per tile 9 matrix instructions, 33 exponentials, about
+// 100 other vector instructions, 27 LDS reads and 50 scalar ones, one after the other: 1.0 us for a workgroup alone on a
+// compute unit), which other wavefronts of the SIMD overlap; on a long cache, HBM.  So the kernel is held to 168 registers
+// and three workgroups share a compute unit (two with 241 registers: 2.13 us per tile and three blocks, three: 1.77; gathered
+// from a cache of 184320 slots x 32 heads 2.42 -> 2.12, 5.9 TB/s).  That takes what a lane keeps down to the accumulators,
+// Q and half a dozen offsets: row sums from a 16x16x128 product (four accumulators, not sixteen), tile addresses in scalar
+// registers, one copy of the loop's body (unrolled over the stages it spilt).  Launch at 40 heads x 3600 queries x 360 blocks of
+// a 230400-slot cache 1.28 -> 1.13 ms.  Tiles in flight alone were not what it waited for: two workgroups per unit with three
+// tiles each on their way instead of one took the same 1.29 ms; two each is what LDS leaves to three workgroups.
+constexpr int NST = 3;                                        // stages of one K and one V tile
+constexpr int LIST = 512;                                     // entries of the selection list held in LDS (a ring of two halves)
 constexpr int OSTR = D + 8;                                   // bf16 elements per staged output row
-constexpr int STAGE_BYTES = 4 * TILEB;                        // K and V, two stages each
+constexpr int STAGE_BYTES = NST * 2 * TILEB;
 constexpr int OUT_BYTES = 4 * 32 * OSTR * 2;                  // output staging of the four wavefronts
-constexpr int META_OFF = OUT_BYTES > STAGE_BYTES ? OUT_BYTES : STAGE_BYTES;
-constexpr int LDS_BYTES = META_OFF + 3 * (int)sizeof(TileMeta);
+constexpr int LIST_OFF = OUT_BYTES > STAGE_BYTES ? OUT_BYTES : STAGE_BYTES;
+constexpr int CNT_OFF = LIST_OFF + LIST * 4;                  // multiplicities as loaded, a row of TK per tile in flight
+constexpr int BIAS_OFF = CNT_OFF + NST * TK * 4;              // log2 of them in units of raw scores, -inf when dead: two rows
+constexpr int LDS_BYTES = BIAS_OFF + 2 * TK * 4;
+static_assert(3 * LDS_BYTES <= 160 * 1024, "three workgroups per compute unit");
 
+// Workgroup barrier that leaves the tile loads in flight (the fence of __syncthreads may drain them).
+__device__ __forceinline__ void wg_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 __device__ __forceinline__ i32x8 lds_read_32(const unsigned char *p0, const unsigned char *p1) {
     const i32x4 lo = *(const i32x4 *)p0, hi = *(const i32x4 *)p1;
     i32x8 r = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
@@ -144,6 +158,15 @@ __device__ __forceinline__ i32x8 lds_read_32(const unsigned char *p0, const unsi
 }
 __device__ __forceinline__ f32x16 mfma_f8(i32x8 a, i32x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);   // both operands E4M3, no scales
+}
+__device__ __forceinline__ f32x4 mfma_row_sums(i32x8 ones, i32x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, b, c, 4, 0, 0, 0, 0, 0);   // E2M1 times E4M3, no scales
+}
+// max(x[l], x[l ^ 32]) on the vector ALU (the lane-swap instruction), without a trip through the LDS queue
+__device__ __forceinline__ float max_across_halves(float x) {
+    const unsigned u = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Query block b of head h over the entries t_begin <= t < t_end of its list (one entry = one tile).  part == nullptr:
@@ -158,9 +181,15 @@ __device__ __forceinline__ void attend_item_fp8(
     float inv_scale_log2, unsigned short *__restrict__ O, float *__restrict__ lse, unsigned char *lds, int h, int b,
     int t_begin, int t_end, float *__restrict__ part) {
     unsigned char *kbuf = lds;
-    unsigned char *vbuf = lds + 2 * TILEB;
-    TileMeta *meta = (TileMeta *)(lds + META_OFF);
-    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned char *vbuf = lds + NST * TILEB;
+    int *list = (int *)(lds + LIST_OFF);
+    int *cnt_in = (int *)(lds + CNT_OFF);
+    float *bias = (float *)(lds + BIAS_OFF);
+    // opaque here and again at the end: the compiler would keep per-lane values of the epilogue, and of the loop over blocks
+    // around this function, in registers through the loop over the tiles, and spill
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5;
     const int L = min(len[h], C);
@@ -190,116 +219,147 @@ __device__ __forceinline__ void attend_item_fp8(
             }
         }
     }
-    f32x16 o_acc[D / 32], l_acc;
+    f32x16 o_acc[D / 32];
+    f32x4 l_acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        l_acc[v] = 0.0f;
+    for (int v = 0; v < 16; ++v)
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) o_acc[db][v] = 0.0f;
-    }
-    i32x8 ones;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) ones[w] = 0x38383838;   // 1.0 in every byte
+    // The row sums come from a 16x16x128 product on the same P registers.  Lane l's weights (query l % 32, half l / 32 of the
+    // keys) are there the k-slots 16 (l / 16) .. +15 and 64 + 16 (l / 16) .. +15 of column l % 16, so that queries below 16 own
+    // the even sixteens of k and the others the odd ones.  Row i of the other operand is 1 on the sixteens of parity
+    // (i / 4) % 2 and 0 on the others; lane l's first accumulator (row 4 (l / 16), column l % 16) is then the sum of query
+    // l % 32.  That operand is in 4-bit floating point, whose lanes hold 32 k-slots in order: four registers.
+    const bool odd16 = (lane >> 2) & 1;
+    const int one_even = odd16 ? 0 : 0x22222222, one_odd = odd16 ? 0x22222222 : 0;
+    i32x8 ones = {one_even, one_even, one_odd, one_odd, 0, 0, 0, 0};
     float m_ref = -INFINITY, neg_ms = 0.0f;
     constexpr float P_OFF = 6.0f;                  // P = 2^P_OFF * exp2(score - reference)
     const float tau_raw = 2.0f * inv_scale_log2;   // the reference may lag the true maximum by 2 octaves: P <= 2^8
 
-    // direct global -> LDS loads of one tile: eight 1-KiB instructions per tensor, two per wavefront
+    // Direct global -> LDS loads of one tile: eight 1-KiB instructions per tensor, two per wavefront.  The second of the two
+    // reads and writes 1 KiB further on (its rows have the same swizzle), which the instruction's offset does for both.
+    const unsigned ksrc = (8 * 2 * wave + (lane >> 3)) * D + (((lane & 7) ^ sw_k(16 * wave + (lane >> 3))) << 4);
+    const unsigned vsrc = (16 * 2 * wave + (lane >> 2)) * TK + (((lane & 3) ^ sw_v(lane >> 2)) << 4);
     auto issue_loads = [&](int blk, int stage) {
-        const uint8_t *kt = Kh + (size_t)blk * TILEB;
+        const uint8_t *kt = Kh + (size_t)blk * TILEB;   // uniform
         const uint8_t *vt = Vh + (size_t)blk * TILEB;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int inst = 2 * wave + i;
-            const int krow = 8 * inst + (lane >> 3), kpos = lane & 7;
-            const int vrow = 16 * inst + (lane >> 2), vpos = lane & 3;
-            const uint8_t *ksrc = kt + krow * D + ((kpos ^ sw_k(krow)) << 4);
-            const uint8_t *vsrc = vt + vrow * TK + ((vpos ^ sw_v(vrow)) << 4);
-            __builtin_amdgcn_global_load_lds(ksrc, LDS_PTR8(unsigned, kbuf + stage * TILEB + inst * 1024), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(vsrc, LDS_PTR8(unsigned, vbuf + stage * TILEB + inst * 1024), 16, 0, 0);
+        unsigned char *kd = kbuf + stage * TILEB + wave * 2048, *vd = vbuf + stage * TILEB + wave * 2048;
+        // buffer instructions: the tile's address stays in scalar registers, a lane adds its 32-bit offset
+        const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc((void *)kt, 0, TILEB, 0x00020000);
+        const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc((void *)vt, 0, TILEB, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, LDS_PTR8(unsigned, kd), 16, ksrc, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(kr, LDS_PTR8(unsigned, kd), 16, ksrc, 0, 1024, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, LDS_PTR8(unsigned, vd), 16, vsrc, 0, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vr, LDS_PTR8(unsigned, vd), 16, vsrc, 0, 1024, 0);
+    };
+    // the list by way of LDS, half a ring at a time: the block to load, or -1 (loads block 0, which is live, fully masked)
+    auto load_list = [&](int from) {   // from: a multiple of LIST / 2
+        static_assert(LIST / 2 == 256, "one entry per thread");
+        if (from + tid < nt) {
+            const int kb = sel_row[from + tid];
+            list[(from + tid) % LIST] = kb >= 0 && kb < n_live_blk ? kb : -1;
         }
     };
-    // tile bookkeeping, two tiles ahead, by the first 64 threads (one per key of the tile)
-    auto sel_entry = [&](int tile) -> int { return (tid < TK && tile < nt) ? sel_row[tile] : -1; };
-    auto fill_meta = [&](TileMeta &m, int kb, int cnt_v) {
-        if (tid < TK) {
-            const bool blk_ok = kb >= 0 && kb < n_live_blk;
-            const int key = kb * TK + tid;
-            const bool live = blk_ok && key < L;
-            m.bias[tid] = live ? (cnt_h ? __log2f((float)cnt_v) * inv_scale_log2 : 0.0f) : -INFINITY;
-            if (tid == 0) m.blk = blk_ok ? kb : 0;
-        }
+    auto entry = [&](int tile) -> int { return __builtin_amdgcn_readfirstlane(list[tile % LIST]); };   // uniform
+    // The first wavefront keeps the bias rows: multiplicities are loaded one tile ahead of the tile itself, straight to LDS,
+    // and turned into the bias of a tile while the tile before it is worked on.
+    const bool counts = wave == 0 && cnt_h != nullptr;   // uniform over the wavefront
+    auto issue_counts = [&](int tile, int kb) {
+        const int key = min(max(kb, 0) * TK + lane, L - 1);
+        __builtin_amdgcn_global_load_lds(cnt_h + key, LDS_PTR8(unsigned, cnt_in + (tile % NST) * TK), 4, 0, 0);
     };
-    auto cnt_of = [&](int kb) -> int {
-        const int key = kb * TK + tid;
-        return (tid < TK && cnt_h && kb >= 0 && key < L) ? cnt_h[key] : 1;
+    auto fill_bias = [&](int tile, int kb, int n) {   // wavefront 0; n: the multiplicity read from cnt_in
+        const bool live = kb >= 0 && lane < L - kb * TK;
+        const float v = cnt_h ? __log2f((float)n) * inv_scale_log2 : 0.0f;
+        bias[(tile & 1) * TK + lane] = live ? v : -INFINITY;
     };
-    int kb_ahead = -1;
+    // Waits until this wavefront's share of tile t has landed (in the first: the multiplicities of tile t + 1, asked for
+    // right behind it, too).  Loads complete in order; behind these there are NST - 2 tiles of four loads in flight, with one
+    // load of multiplicities each, unless the list ends before.
+    auto wait_tile = [&](bool ends) {   // ends: fewer than NST - 1 tiles are behind tile t
+        constexpr int NEWER = 4 * (NST - 2), NEWER0 = 5 * (NST - 2);
+        static_assert(NEWER0 < 16, "the counter's low bits alone");
+        if (ends) __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
+        else if (counts) __builtin_amdgcn_s_waitcnt(0x0F70 | NEWER0);
+        else __builtin_amdgcn_s_waitcnt(0x0F70 | NEWER);
+        asm volatile("" ::: "memory");
+    };
+    int kb_of[NST] = {};   // entries of tiles t + 1 .. t + NST (uniform)
     if (nt > 0) {
-        const int kb0 = sel_entry(0), kb1 = sel_entry(1);
-        fill_meta(meta[0], kb0, cnt_of(kb0));
-        if (nt > 1) fill_meta(meta[1], kb1, cnt_of(kb1));
-        if (nt > 2) kb_ahead = sel_entry(2);
+        load_list(0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // the counts in wait_tile start from nothing in flight
         __syncthreads();
-        issue_loads(meta[0].blk, 0);
-    }
-    // per-lane LDS offsets of the operand reads (tile-independent)
-    unsigned koff[2][2];   // [key half kb][k-step s]: first of the two chunks; the second is that offset ^ 16
+        if (counts) issue_counts(0, entry(0));
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        const int row = 32 * ((col >> 2) & 1) + 16 * kb + 4 * (col >> 3) + (col & 3);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) koff[kb][s] = row * D + (((4 * s + 2 * g) ^ sw_k(row)) << 4);
-    }
-    unsigned voff[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
-        const int row = 32 * db + col;
-        voff[db] = row * TK + (((2 * g) ^ sw_v(row)) << 4);
-    }
-
-    auto tile_step = [&](int t, auto stage_c) {
-        constexpr int STAGE = decltype(stage_c)::value;
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wavefront's share of tile t has landed
-        __syncthreads();                     // ... and everyone else's; tile t-1 fully consumed
-        int cnt2 = 1, kb3 = -1;
-        const int kb2 = kb_ahead;
-        if (t + 2 < nt) {
-            cnt2 = cnt_of(kb2);
-            if (t + 3 < nt) kb3 = sel_entry(t + 3);
+        for (int i = 0; i < NST - 1; ++i) {
+            if (i < nt) issue_loads(max(entry(i), 0), i);
+            if (i + 1 < nt && counts) issue_counts(i + 1, entry(i + 1));
         }
-        if (t + 1 < nt) issue_loads(meta[(t + 1) % 3].blk, STAGE ^ 1);
-        const TileMeta &mt = meta[t % 3];
-        const unsigned char *ks = kbuf + STAGE * TILEB, *vs = vbuf + STAGE * TILEB;
-        // scores start from the keys' bias: register 4q+e of half kb is key 32g + 16kb + 4q + e
-        f32x16 s_acc[2];
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int i = 1; i < NST; ++i) kb_of[i - 1] = entry(min(i, nt - 1));
+        wait_tile(NST - 1 >= nt);
+        if (wave == 0) fill_bias(0, entry(0), cnt_in[lane]);
+    }
+    // Per-lane LDS offsets of the operand reads (tile-independent).  Rows 16 (K, second half of the keys) and 32 (V, next block
+    // of coordinates) further on have the same swizzle, so everything but the 16-byte chunk is a constant on top.
+    const int krow = 32 * ((col >> 2) & 1) + 4 * (col >> 3) + (col & 3);
+    const unsigned koff = krow * D + (((2 * g) ^ sw_k(krow)) << 4);   // k-step s, second chunk: ^ 64 s, ^ 16
+    const unsigned voff = col * TK + (((2 * g) ^ sw_v(col)) << 4);    // second chunk: ^ 16
+
+    int stage = 0;
+    for (int t = 0; t < nt; ++t) {
+        wait_tile(t + NST - 1 >= nt);
+        wg_barrier();   // everyone's share has landed, bias row t is written, tile t-1 is fully consumed
+        const int stage_behind = stage == 0 ? NST - 1 : stage - 1;
+        if (t + NST - 1 < nt) issue_loads(max(kb_of[NST - 2], 0), stage_behind);
+        const int cnt_next = cnt_in[(stage == NST - 1 ? 0 : stage + 1) * TK + lane];   // wavefront 0 alone uses it
+        if (t + NST < nt && (t + NST) % (LIST / 2) == 0) {   // half a ring of the list; its other half is still in use
+            load_list(t + NST);
+            __syncthreads();
+        }
+        const float *bt = bias + (t & 1) * TK;
+        const unsigned ka0 = koff + stage * TILEB, va0 = voff + stage * TILEB;
+        // The reads of an operand are issued well before its product (the scheduling fences keep them there): a wavefront
+        // waits about 130 cycles for a read that it has just issued.
+        // Scores start from the keys' bias: register 4q+e of half kb is key 32g + 16kb + 4q + e.
+        f32x16 s_acc[2];
+        auto read_bias = [&](int kb) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const f32x4 bv = *(const f32x4 *)(&mt.bias[32 * g + 16 * kb + 4 * q4]);
+                const f32x4 bv = *(const f32x4 *)(&bt[32 * g + 16 * kb + 4 * q4]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) s_acc[kb][4 * q4 + e] = bv[e];
             }
-        i32x8 ka[2][2];
+        };
+        auto k_operand = [&](int kb, int s) {
+            return lds_read_32(kbuf + (ka0 ^ (64u * s)) + 16 * kb * D, kbuf + (ka0 ^ (64u * s) ^ 16u) + 16 * kb * D);
+        };
+        auto v_operand = [&](int db) { return lds_read_32(vbuf + va0 + 32 * db * TK, vbuf + (va0 ^ 16u) + 32 * db * TK); };
+        i32x8 ka[2][2], va[D / 32];
+        read_bias(0);
+        ka[0][0] = k_operand(0, 0);
+        ka[0][1] = k_operand(0, 1);
+        ka[1][0] = k_operand(1, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        s_acc[0] = mfma_f8(ka[0][0], qf[0], s_acc[0]);
+        read_bias(1);
+        ka[1][1] = k_operand(1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        s_acc[0] = mfma_f8(ka[0][1], qf[1], s_acc[0]);
+        s_acc[1] = mfma_f8(ka[1][0], qf[0], s_acc[1]);
+        s_acc[1] = mfma_f8(ka[1][1], qf[1], s_acc[1]);
+        const int kb_raw = list[(t + NST) % LIST];   // not used beyond the end of the list
+        constexpr int VE = 1, VM = 1;   // blocks of V^T read before the row maximum, and after half of the weights
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) ka[kb][s] = lds_read_32(ks + koff[kb][s], ks + (koff[kb][s] ^ 16u));
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) s_acc[kb] = mfma_f8(ka[kb][s], qf[s], s_acc[kb]);
-        // V^T operands: issued now, they land during the softmax arithmetic
-        i32x8 va[D / 32];
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db) va[db] = lds_read_32(vs + voff[db], vs + (voff[db] ^ 16u));
+        for (int db = 0; db < VE; ++db) va[db] = v_operand(db);
+        __builtin_amdgcn_sched_barrier(0);
         float mx = s_acc[0][0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s_acc[0][v]);
 #pragma unroll
         for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s_acc[1][v]);
-        mx = fmaxf(mx, shfl_xor(mx, 32));
+        mx = max_across_halves(mx);
         if (__any(mx > m_ref + tau_raw)) {   // wave-uniform
             const float m_new = fmaxf(m_ref, mx);
             const float alpha = m_ref == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_ref - m_new) * scale_log2);
@@ -313,7 +373,7 @@ __device__ __forceinline__ void attend_item_fp8(
         }
         i32x8 pf;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 float p[4];
@@ -321,18 +381,31 @@ __device__ __forceinline__ void attend_item_fp8(
                 for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][4 * q4 + e], scale_log2, neg_ms));
                 pf[4 * kb + q4] = (int)pack_fp8x4(p[0], p[1], p[2], p[3]);
             }
-        l_acc = mfma_f8(ones, pf, l_acc);
+            if (kb == 0) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int db = VE; db < VE + VM; ++db) va[db] = v_operand(db);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int db = VE + VM; db < D / 32; ++db) va[db] = v_operand(db);
+        kb_of[NST - 1] = __builtin_amdgcn_readfirstlane(kb_raw);
+        l_acc = mfma_row_sums(ones, pf, l_acc);
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) o_acc[db] = mfma_f8(va[db], pf, o_acc[db]);
-        // bookkeeping of tile t+2
-        if (t + 2 < nt) fill_meta(meta[(t + 2) % 3], kb2, cnt2);
-        kb_ahead = kb3;
-    };
-    for (int t = 0; t < nt; t += 2) {
-        tile_step(t, std::integral_constant<int, 0>{});
-        if (t + 1 < nt) tile_step(t + 1, std::integral_constant<int, 1>{});
+        if (wave == 0) {   // multiplicities that were asked for with the tile before t + 1 (see wait_tile)
+            if (t + 1 < nt) fill_bias(t + 1, kb_of[0], cnt_next);
+            if (t + NST < nt && counts) issue_counts(t + NST, kb_of[NST - 1]);
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < NST; ++i) kb_of[i] = kb_of[i + 1];
+        stage = stage == NST - 1 ? 0 : stage + 1;
     }
 
+    int etid = threadIdx.x;
+    asm volatile("" : "+v"(etid));
+    const int elane = etid & 63, ecol = elane & 31, eg = elane >> 5, e_idx = b * 128 + wave * 32 + ecol;
     const float l_tot = l_acc[0];
     if (part) {   // a fragment: the combination launch normalises
 #pragma unroll
@@ -340,10 +413,10 @@ __device__ __forceinline__ void attend_item_fp8(
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
                 const f32x4 w = {o_acc[db][4 * q4], o_acc[db][4 * q4 + 1], o_acc[db][4 * q4 + 2], o_acc[db][4 * q4 + 3]};
-                ((f32x4 *)part)[((wave * (D / 32) + db) * 4 + q4) * 64 + lane] = w;
+                ((f32x4 *)part)[((wave * (D / 32) + db) * 4 + q4) * 64 + elane] = w;
             }
-        part[4 * ATTN_PART_O_FLOATS + wave * 64 + lane] = m_ref;
-        part[4 * ATTN_PART_O_FLOATS + 4 * 64 + wave * 64 + lane] = l_tot;
+        part[4 * ATTN_PART_O_FLOATS + wave * 64 + elane] = m_ref;
+        part[4 * ATTN_PART_O_FLOATS + 4 * 64 + wave * 64 + elane] = l_tot;
         __syncthreads();   // the tile stages and the bookkeeping are free for the next block
         return;
     }
@@ -359,11 +432,11 @@ __device__ __forceinline__ void attend_item_fp8(
             bf16x4 w;
 #pragma unroll
             for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o_acc[db][4 * q4 + e] * inv);
-            *(bf16x4 *)(Os + col * OSTR + 32 * db + 8 * q4 + 4 * g) = w;
+            *(bf16x4 *)(Os + ecol * OSTR + 32 * db + 8 * q4 + 4 * eg) = w;
         }
     __syncthreads();
     {
-        const int rr = lane >> 4, cc = lane & 15;
+        const int rr = elane >> 4, cc = elane & 15;
 #pragma unroll
         for (int it = 0; it < 8; ++it) {
             const int r = it * 4 + rr;
@@ -371,13 +444,13 @@ __device__ __forceinline__ void attend_item_fp8(
             if (qi < n_q) *(u32x4 *)(O + ((size_t)h * n_q + qi) * D + cc * 8) = *(const u32x4 *)(Os + r * OSTR + cc * 8);
         }
     }
-    if (lse && g == 0 && q_idx < n_q)
-        lse[(size_t)h * n_q + q_idx] = l_tot > 0.0f ? (m_ref * scale_log2 - 6.0f + __log2f(l_tot)) * LN2 : -INFINITY;
+    if (lse && eg == 0 && e_idx < n_q)
+        lse[(size_t)h * n_q + e_idx] = l_tot > 0.0f ? (m_ref * scale_log2 - 6.0f + __log2f(l_tot)) * LN2 : -INFINITY;
     __syncthreads();   // the staged output rows have been read: the tile stages are free for the next block
 }
 
-// One query block per workgroup; two workgroups per CU, started as slots free up.
-__global__ __launch_bounds__(256, 2) void attn_fp8_d128_kernel(
+// One query block per workgroup; three workgroups per CU, started as slots free up.
+__global__ __launch_bounds__(256, 3) void attn_fp8_d128_kernel(
     const unsigned short *__restrict__ Q, const uint8_t *__restrict__ K8, const uint8_t *__restrict__ V8T,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int n_blk, int n_sel, int n_qb, int H, float scale_log2,
@@ -395,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_d128_kernel(
 
 // The split launch (see the bf16 kernel of the same structure in attention_d128.hip): the first n_plain workgroups take one
 // whole query block each, in the plain kernel's order; the others take equal shares of the tiles of the blocks left over.
-__global__ __launch_bounds__(256, 2) void attn_fp8_d128_sk_kernel(
+__global__ __launch_bounds__(256, 3) void attn_fp8_d128_sk_kernel(
     const unsigned short *__restrict__ Q, const uint8_t *__restrict__ K8, const uint8_t *__restrict__ V8T,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int n_blk, int n_sel, int n_qb, TailMap tm, int n_plain, int NT,
@@ -425,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_d128_sk_kernel(
 
 // Few query blocks: n_parts workgroups per block, each an equal run of its entries, which leave fragments for
 // attn_combine_parts_kernel (attention_d128.hip).
-__global__ __launch_bounds__(256, 2) void attn_fp8_d128_parts_kernel(
+__global__ __launch_bounds__(256, 3) void attn_fp8_d128_parts_kernel(
     const unsigned short *__restrict__ Q, const uint8_t *__restrict__ K8, const uint8_t *__restrict__ V8T,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int n_blk, int n_sel, int n_qb, int H, int n_parts, float scale_log2,
@@ -514,7 +587,10 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
     const int n_qb = (n_q + 127) / 128;
     const int n_blk = (C + f8::TK - 1) / f8::TK;
     const float scale_log2 = scale * 1.4426950408889634f;
-    // with a workspace, a launch that would end in a short last round of workgroups is split (one entry = one tile)
+    // With a workspace, a launch that would end in a short last round of workgroups is split (one entry = one tile), by the
+    // rule of the bf16 kernel although three of these workgroups share a unit: two per unit already draw what HBM gives, so
+    // the last round is short or not by the count of 64 per XCD (1160 blocks of 360 tiles, 128 of an XCD's 145 taken whole:
+    // 1128 us; 112: 1167, 96: 1175, 136: 1199, unsplit 1167).
     const int full_per = ws ? attn_split_full_per(n_qb * H, n_sel) : 0;
     if (full_per > 0) {
         const TailMap tm = {(n_qb * H + 7) / 8, full_per, n_qb * H};

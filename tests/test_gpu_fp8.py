@@ -120,6 +120,28 @@ def test_fp8_attention_matches_the_oracle(H, n_q, C, lens, n_sel, seed):
     check_fp8_attention(Q, c, sel, nsel, d ** -0.5, use_cnt=False)
 
 
+@pytest.mark.parametrize("counts", [(1, 2, 3), (4, 5, 7), (255, 256, 257, 258, 259), (511, 512, 515, 600)])
+def test_fp8_attention_at_the_edges_of_its_pipeline(counts):
+    # lists that end while the first tiles are being asked for, and around the pieces (256 entries) in which a list goes
+    # through LDS; entries of -1 at the pieces' edges, the last block short
+    rng = np.random.default_rng(counts[0])
+    H, d, n_kb = 1, 128, 640
+    C = 64 * n_kb - 7
+    c = rand_cache(rng, H, C, d, [C], "bf16")
+    n_qb, n_sel = len(counts), max(counts)
+    Q = to_storage((rng.standard_normal((H, 128 * n_qb - 5, d)) * 1.1).astype(np.float32), "bf16")
+    sel = np.full((H, n_qb, n_sel), -1, np.int32)
+    for b, m in enumerate(counts):
+        sel[0, b, :m] = np.sort(rng.choice(n_kb - 1, size=m, replace=False))
+        sel[0, b, m - 1] = n_kb - 1
+        for edge in (0, 255, 256, 511, 512):
+            if m > 3 and edge < m - 1 and (b + edge) % 2:
+                sel[0, b, edge] = -1
+    nsel = np.array([counts], np.int32)
+    check_fp8_attention(Q, c, sel, nsel, d ** -0.5)
+    check_fp8_attention(Q, c, sel, nsel, d ** -0.5, use_cnt=False)
+
+
 @pytest.mark.parametrize("H,n_q,C,n_sel", [
     (20, 3600, 64 * 300, 150),     # 580 query blocks: 73 per XCD range, 9 of them left over by the whole round
     (33, 2048, 64 * 256, 128),     # 528 blocks: 2 per range left over
