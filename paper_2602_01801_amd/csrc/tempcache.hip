@@ -25,6 +25,8 @@ int encode_launch(const void *x, int dtype, int64_t n_vec, int d, const fastar_c
 
 constexpr int SCORE_BIAS = 1 << 23;      // makes every score positive inside the packed arg-max key
 constexpr int PLAN_SCRATCH_WORDS = 64 + 3 * 1024;  // per-head scratch of tc_plan_kernel (PS_STRIDE)
+constexpr int AGE_BINS = 1024;           // bins of an age histogram (frame_id - stamp), the last one collecting everything older
+constexpr int AGE_WORDS = AGE_BINS + 16; // a slice's histogram and, behind it, whether a stamp lies in the future
 constexpr int HS_STRIDE = 8;             // per-head scalars: oldL, n_unmerged, e, n_victims, n_dropped, newL, 3 if the workspace is not clean, clean mark
 constexpr int WS_CLEAN = 0x5A17C1EA;     // hs word 7 after a call: group records and plan scratch are all zero again
 constexpr int WS_FAILED = 0x0BADC0DE;    // hs word 7 after a call whose plan gave up for the head: records and scratch are left as they are
@@ -33,8 +35,14 @@ typedef unsigned long long u64;
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Caches of up to SETTLE_SLOTS slots on a persistent workspace: the launches behind the match are one, tc_settle_kernel.
+constexpr int SETTLE_SLICE = 8192;        // slots per slice of the age histogram
+constexpr int SETTLE_SLOTS = 65536;       // eight slices
+constexpr int SETTLE_TOKENS = 8192;       // tokens per frame (their list is held in LDS)
+__host__ __device__ static inline int settle_slices(int C) { return (C + SETTLE_SLICE - 1) / SETTLE_SLICE; }
+
 struct CompressWs {
-    size_t ck, cp, best, jstar, sbest, rank, victims, hs, ps, win, grp, total;
+    size_t ck, cp, best, jstar, sbest, rank, victims, hs, ps, win, grp, tstamp, ages, slot_age, total;
 };
 static CompressWs compress_ws(int H, int C, int n_new, int r) {
     CompressWs w;
@@ -51,6 +59,10 @@ static CompressWs compress_ws(int H, int C, int n_new, int r) {
     w.hs = o; o += align256((size_t)H * HS_STRIDE * 4);
     w.win = o; o += align256((size_t)H * C * 8);
     w.grp = o; o += align256((size_t)H * C * 4);
+    w.tstamp = o; o += align256(T * 4);
+    const size_t slices = C <= SETTLE_SLOTS ? (size_t)H * settle_slices(C) : 0;
+    w.ages = o; o += align256(slices * AGE_WORDS * 4);
+    w.slot_age = o; o += align256(slices * SETTLE_SLICE * 2);
     w.total = o;
     return w;
 }
@@ -491,7 +503,16 @@ constexpr size_t WINDOW_LDS_MAX = 148 * 1024;
 // What the fused tail of the window kernel needs from the verify step (defined further down).
 template <bool BF16, int D>
 struct VerifyRows;
-constexpr int AGE_BINS = 1024;
+// What the launch that settles a call wants of the match and verify launches besides their results (nullptr: the plan and
+// apply launches follow instead): the length, the stamps of the matched slots and the slices' age histograms.
+struct SettleOut {
+    int32_t *hs;
+    int32_t *tstamp;
+    unsigned *ages;
+    unsigned short *slot_age;
+};
+__device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
+                                          int frame_id, const SettleOut &so, unsigned *lhist, int slice);
 template <int UN>
 __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp,
                                                     int C, int n_new, int frame_id, unsigned *__restrict__ ps,
@@ -502,6 +523,7 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
     uint8_t *merged;
     const int32_t *stamp;
     int frame_id, hist_word, fut_word;
+    SettleOut so;
 };
 
 // With VERIFY (workspaces that every call leaves clean, see tempcache_compress) the kernel is the verify step too: once
@@ -543,13 +565,17 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     static_assert(sizeof(partbest) >= AGE_BINS * sizeof(unsigned), "the histogram fits");
     const int n_tok_wgs = (int)gridDim.x - n_hist;
     if (VERIFY && (int)blockIdx.x >= n_tok_wgs) {       // uniform
-        age_histogram_slice<4>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)blockIdx.y * ps_words, va.hist_word,
-                               va.fut_word, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs, n_hist);
+        if (va.so.hs)
+            age_slice(len, va.stamp, C, n_new, va.frame_id, va.so, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs);
+        else
+            age_histogram_slice<4>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)blockIdx.y * ps_words, va.hist_word,
+                                   va.fut_word, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs, n_hist);
         return;
     }
     const int h = blockIdx.y;
     const int L = min(len[h], C);
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    if (VERIFY && va.so.hs && blockIdx.x == 0 && tid == 0) va.so.hs[(size_t)h * HS_STRIDE] = L;
     const int col = lane & 31, g2 = lane >> 5;
     const int swave = __builtin_amdgcn_readfirstlane(wave);   // uniform: the scan's bookkeeping stays in scalar registers
     const int tq = swave % TQ, ch = swave / TQ;
@@ -785,7 +811,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             for (int pass = 0; pass < PB; ++pass) {   // every row this group will need, in one round of loads
                 const int t = (p0 + pass) * (WIN_THREADS / 16) + (tid >> 4);
                 const int i = min(base + t, n_new - 1);
-                vr[pass].load(va.K, K_new, pcode + t * R, R, C, n_new, metric, h, i, tid & 15, (int)(unsigned)partbest[0][t]);
+                vr[pass].load(va.K, K_new, pcode + t * R, R, C, n_new, metric, h, i, tid & 15, (int)(unsigned)partbest[0][t],
+                              va.so.tstamp ? va.stamp : nullptr);
             }
 #pragma unroll
             for (int pass = 0; pass < PB; ++pass) {
@@ -793,14 +820,14 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
                 const int i = base + t;
                 if (i < lim)   // whole 16-lane groups
                     vr[pass].decide(C, n_new, qscale, metric, va.tau2_q16, win, grp, va.merged, h, i, tid & 15,
-                                    (int)(unsigned)partbest[0][t], (int)(unsigned)(partbest[0][t] >> 32));
+                                    (int)(unsigned)partbest[0][t], (int)(unsigned)(partbest[0][t] >> 32), va.so.tstamp);
             }
         }
     }
     if constexpr (TOKS < 256) break;   // one block per workgroup: the grid covers the tokens (and the compiler sees no loop)
     }   // blocks of tokens
     if constexpr (VERIFY) {
-        if (n_hist == 0) {   // uniform over the launch
+        if (n_hist == 0 && !va.so.hs) {   // uniform over the launch
             __syncthreads();
             age_histogram_slice<(TOKS >= 256 ? 20 : 4)>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)h * ps_words,
                                                         va.hist_word, va.fut_word, (unsigned *)partbest, (int)blockIdx.x, n_tok_wgs);
@@ -949,6 +976,50 @@ __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ 
     if (__any(future) && lane_id() == 0) atomicOr(&ps[fut_word], 1u);
 }
 
+// The same for tc_settle_kernel: the histogram of one slice of SETTLE_SLICE slots, by one workgroup, stored whole (nothing
+// has to be cleared before or after), whether one of its stamps lies in the future, and every slot's bin: the launch that
+// settles the call replaces stamps while other workgroups of it still look for victims.
+__device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
+                                          int frame_id, const SettleOut &so, unsigned *lhist, int slice) {
+    const int h = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+    const int L = min(len[h], C);
+    if (L + n_new <= C) return;   // uniform over the head: no eviction can be needed
+    for (int k = tid; k < AGE_BINS; k += nt) lhist[k] = 0;
+    __syncthreads();
+    const int32_t *st = stamp + (size_t)h * C;
+    const int j0 = slice * SETTLE_SLICE, j1 = min(j0 + SETTLE_SLICE, L);
+    unsigned short *age = so.slot_age + (size_t)h * settle_slices(C) * SETTLE_SLICE;
+    int future = 0;
+    constexpr int UN = 16;   // loads in flight
+    for (int jb = j0; jb < j1; jb += nt * UN) {   // uniform trip count
+        int sv[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int j = jb + u * nt + tid;
+            sv[u] = j < j1 ? st[j] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const bool act = jb + u * nt + tid < j1;
+            const unsigned bin = min((unsigned)frame_id - (unsigned)sv[u], (unsigned)(AGE_BINS - 1));
+            if (act && sv[u] > frame_id) future = 1;
+            if (act) age[jb + u * nt + tid] = (unsigned short)bin;
+            // neighbouring slots were mostly written by the same frame: lanes of the first lane's age count together
+            const u64 m = __ballot(act);
+            if (m == 0) continue;
+            const int first = __ffsll((unsigned long long)m) - 1;
+            const unsigned fbin = (unsigned)__shfl((int)bin, first);
+            const u64 same = __ballot(act && bin == fbin);
+            if (lane_id() == first) atomicAdd(&lhist[fbin], (unsigned)__popcll(same));
+            if (act && bin != fbin) atomicAdd(&lhist[bin], 1u);
+        }
+    }
+    future = __syncthreads_or(future);
+    unsigned *out = so.ages + ((size_t)h * settle_slices(C) + slice) * AGE_WORDS;
+    for (int k = tid; k < AGE_BINS; k += nt) out[k] = lhist[k];
+    if (tid == 0) out[AGE_BINS] = (unsigned)future;
+}
+
 // ---- row pieces: 16 lanes share one row of D elements ----------------------------------------------------
 template <bool BF16, int D>
 struct RowPiece {
@@ -1069,7 +1140,7 @@ __device__ __forceinline__ void verify_token(const void *__restrict__ K, const v
                                              int metric, int tau2_q16, const int32_t *__restrict__ jstar,
                                              const int32_t *__restrict__ sbest, u64 *__restrict__ win,
                                              int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
-                                             int l16);
+                                             int l16, const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp);
 
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__ K, const void *__restrict__ K_new,
@@ -1081,14 +1152,21 @@ __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__
                                                         const int32_t *__restrict__ len,
                                                         const int32_t *__restrict__ stamp, int frame_id,
                                                         unsigned *__restrict__ plan_scratch, int hist_word,
-                                                        int fut_word, int scratch_words) {
+                                                        int fut_word, int scratch_words, int n_slices, SettleOut so) {
     typedef RowPiece<BF16, D> RP;
     __shared__ unsigned lhist[AGE_BINS];
     const int h = blockIdx.y;
+    const int n_tok_wgs = (int)gridDim.x - n_slices;
+    if ((int)blockIdx.x >= n_tok_wgs) {   // uniform
+        age_slice(len, stamp, C, n_new, frame_id, so, lhist, (int)blockIdx.x - n_tok_wgs);
+        return;
+    }
+    if (so.hs && blockIdx.x == 0 && threadIdx.x == 0) so.hs[(size_t)h * HS_STRIDE] = min(len[h], C);
     const int l16 = threadIdx.x & 15;
     const int i = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);
     if (i < n_new) verify_token<BF16, D>(K, K_new, cp, r, C, n_new, qscale, metric, tau2_q16, jstar, sbest, win, grp,
-                                         merged, h, i, l16);  // whole 16-lane groups
+                                         merged, h, i, l16, so.tstamp ? stamp : nullptr, so.tstamp);  // whole 16-lane groups
+    if (so.hs) return;
     age_histogram_slice<4>(len, stamp, C, n_new, frame_id, plan_scratch + (size_t)h * scratch_words, hist_word, fut_word,
                         lhist, (int)blockIdx.x, (int)gridDim.x);
 }
@@ -1099,8 +1177,11 @@ template <bool BF16, int D>
 struct VerifyRows {
     typename RowPiece<BF16, D>::Raw ra, rb;   // raw bits: half the registers of the float values while the loads are in flight
     unsigned cw;
+    int ts;   // stamp of the slot
     __device__ __forceinline__ void load(const void *__restrict__ K, const void *__restrict__ K_new, const int8_t *cprow,
-                                         int r, int C, int n_new, int metric, int h, int i, int l16, int j) {
+                                         int r, int C, int n_new, int metric, int h, int i, int l16, int j,
+                                         const int32_t *__restrict__ stamp) {
+        ts = stamp && l16 == 0 && j >= 0 ? stamp[(size_t)h * C + j] : 0;
         typedef RowPiece<BF16, D> RP;
         ra = RP::load_raw(K_new, (size_t)h * n_new + i, l16);
         cw = (metric == 0 && l16 < r / 4) ? ((const unsigned *)cprow)[l16] : 0u;
@@ -1108,7 +1189,7 @@ struct VerifyRows {
     }
     __device__ __forceinline__ void decide(int C, int n_new, float qscale, int metric, int tau2_q16, u64 *__restrict__ win,
                                            int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
-                                           int l16, int j, int W) const {
+                                           int l16, int j, int W, int32_t *__restrict__ tstamp) const {
         typedef RowPiece<BF16, D> RP;
         const int nn = group16_sum(dot4_i8(cw, cw, 0));  // |probe code|^2 (r <= 64: at most 16 words)
         bool is_merged = false;
@@ -1137,16 +1218,18 @@ struct VerifyRows {
             }
         }
         if (l16 == 0) merged[(size_t)h * n_new + i] = is_merged ? 1 : 0;
+        if (tstamp && l16 == 0) tstamp[(size_t)h * n_new + i] = ts;
     }
 };
 template <bool BF16, int D>
 __device__ __forceinline__ void verify_core(const void *__restrict__ K, const void *__restrict__ K_new,
                                             const int8_t *cprow, int r, int C, int n_new, float qscale, int metric,
                                             int tau2_q16, u64 *__restrict__ win, int32_t *__restrict__ grp,
-                                            uint8_t *__restrict__ merged, int h, int i, int l16, int j, int W) {
+                                            uint8_t *__restrict__ merged, int h, int i, int l16, int j, int W,
+                                            const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp) {
     VerifyRows<BF16, D> v;
-    v.load(K, K_new, cprow, r, C, n_new, metric, h, i, l16, j);
-    v.decide(C, n_new, qscale, metric, tau2_q16, win, grp, merged, h, i, l16, j, W);
+    v.load(K, K_new, cprow, r, C, n_new, metric, h, i, l16, j, stamp);
+    v.decide(C, n_new, qscale, metric, tau2_q16, win, grp, merged, h, i, l16, j, W, tstamp);
 }
 
 template <bool BF16, int D>
@@ -1155,11 +1238,11 @@ __device__ __forceinline__ void verify_token(const void *__restrict__ K, const v
                                              int metric, int tau2_q16, const int32_t *__restrict__ jstar,
                                              const int32_t *__restrict__ sbest, u64 *__restrict__ win,
                                              int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
-                                             int l16) {
+                                             int l16, const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp) {
     // everything addressed by the token first (one round trip), then the matched slot's key row
     const size_t ti = (size_t)h * n_new + i;
     verify_core<BF16, D>(K, K_new, cp + ti * r, r, C, n_new, qscale, metric, tau2_q16, win, grp, merged, h, i, l16,
-                         jstar[ti], sbest[ti]);
+                         jstar[ti], sbest[ti], stamp, tstamp);
 }
 
 // ---- plan ----------------------------------------------------------------------------------------------
@@ -1766,6 +1849,152 @@ static int plan_nb(int H, int C, PlanResidency pr) {
 }
 
 // ---- apply ---------------------------------------------------------------------------------------------
+// Token i of head h, merged into slot j: the group's representative refreshes the slot.  kraw / vraw: the token's own rows,
+// cw: its code word of this lane.  Whole 16-lane groups; sub: which of the wavefront's.
+template <bool BF16, int D>
+__device__ __forceinline__ void apply_merged_token(void *__restrict__ K, void *__restrict__ V, int8_t *__restrict__ code,
+                                                   int32_t *__restrict__ cnt, int32_t *__restrict__ stamp, int r,
+                                                   const void *__restrict__ K_new, const void *__restrict__ V_new,
+                                                   const int8_t *__restrict__ ck, int n_new, int frame_id,
+                                                   const int32_t *__restrict__ jstar, const uint8_t *__restrict__ merged,
+                                                   u64 *win, int32_t *grp, int rep_mode, size_t tb, size_t cb, int i, int j,
+                                                   int l16, int sub, const typename RowPiece<BF16, D>::Raw &kraw,
+                                                   const typename RowPiece<BF16, D>::Raw &vraw, unsigned cw) {
+    typedef RowPiece<BF16, D> RP;
+    // second round of loads, everything addressed by the slot at once: its records and multiplicity, and already
+    // its value row (and key row for the mean key), which only the group's representative goes on to use
+    const bool mean_key = rep_mode == 1;
+    float acc[RP::EPL], vn[RP::EPL], kacc[RP::EPL], kn[RP::EPL];
+    const u64 wkey = win[cb + j];
+    const int gc = grp[cb + j];
+    const int m0 = cnt[cb + j];
+    RP::load(V, cb + j, l16, acc);
+    if (mean_key) RP::load(K, cb + j, l16, kacc);
+    const int widx = (int)(0xFFFFFFFFu - (unsigned)wkey);
+    if (widx == i) {  // this token represents the group: it refreshes the slot
+        // ... and clears the group's records behind it: the other joiners only look for their own index in the
+        // record, which neither the old nor the cleared value shows them
+        if (l16 == 0) {
+            win[cb + j] = 0;
+            grp[cb + j] = 0;
+        }
+        // mean value; with rep_mode 1 also the mean key, whose stored bits feed later integer decisions: single
+        // float32 operations in a fixed order (multiplicity * old row, members in ascending token order, one division)
+#pragma unroll
+        for (int e = 0; e < RP::EPL; ++e) acc[e] *= (float)m0;
+        if (mean_key) {
+#pragma unroll
+            for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fmul_rn((float)m0, kacc[e]);
+        }
+        if (gc == 1) {
+            RP::unpack(vraw, vn);
+#pragma unroll
+            for (int e = 0; e < RP::EPL; ++e) acc[e] += vn[e];
+            if (mean_key) {
+                RP::unpack(kraw, kn);
+#pragma unroll
+                for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fadd_rn(kacc[e], kn[e]);
+            }
+        } else {  // several joiners: add their rows in ascending token order
+            for (int base = 0; base < n_new; base += 16) {
+                const int t = base + l16;
+                const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
+                unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
+                while (mm) {
+                    const int bit = __ffs(mm) - 1;
+                    mm &= mm - 1;
+                    RP::load(V_new, tb + base + bit, l16, vn);
+#pragma unroll
+                    for (int e = 0; e < RP::EPL; ++e) acc[e] += vn[e];
+                    if (mean_key) {
+                        RP::load(K_new, tb + base + bit, l16, kn);
+#pragma unroll
+                        for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fadd_rn(kacc[e], kn[e]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < RP::EPL; ++e) acc[e] = __fdiv_rn(acc[e], (float)(m0 + gc));
+        RP::store(V, cb + j, l16, acc);
+        if (mean_key) {   // the slot's code follows in tc_recode_kernel, from the stored row
+#pragma unroll
+            for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fdiv_rn(kacc[e], (float)(m0 + gc));
+            RP::store(K, cb + j, l16, kacc);
+        } else if (rep_mode == 2) {
+            // Medoid key: of {stored key (weight m0), joiners (weight 1)} the member x with the smallest
+            // cost(x) = sum_y w_y |x - y|^2 in code space = W |x|^2 + S2 - 2 x . S1 (W = sum of the weights,
+            // S1 = weighted sum of the codes, S2 = weighted sum of their squared norms): exact integers, one pass to
+            // build the sums and one to evaluate the candidates (stored key first, then tokens ascending; a later
+            // candidate wins only on a strictly smaller cost).  Lane l16 owns code word l16 (r <= 64: 16 words).
+            // A single joiner never wins: cost(stored) = |d|^2 <= m0 |d|^2 = cost(joiner).
+            if (gc > 1) {
+                const bool has_w = l16 < r / 4;
+                const unsigned ow = has_w ? ((const unsigned *)(code + (cb + j) * r))[l16] : 0u;
+                long long S1[4], S2 = (long long)m0 * dot4_i8(ow, ow, 0);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) S1[k] = (long long)m0 * (int)(signed char)(ow >> (8 * k));
+                for (int base = 0; base < n_new; base += 16) {
+                    const int t = base + l16;
+                    const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
+                    unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
+                    while (mm) {
+                        const int bit = __ffs(mm) - 1;
+                        mm &= mm - 1;
+                        const unsigned w = has_w ? ((const unsigned *)(ck + (tb + base + bit) * r))[l16] : 0u;
+                        S2 += dot4_i8(w, w, 0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) S1[k] += (int)(signed char)(w >> (8 * k));
+                    }
+                }
+                const long long W = (long long)m0 + gc;
+                auto group16_sum64 = [](long long v) -> long long {
+#pragma unroll
+                    for (int off = 1; off < 16; off <<= 1) {
+                        const unsigned lo = shfl_xor((unsigned)v, off), hi = shfl_xor((unsigned)((unsigned long long)v >> 32), off);
+                        v += (long long)(((unsigned long long)hi << 32) | lo);
+                    }
+                    return v;
+                };
+                auto cost_of = [&](unsigned w) -> long long {   // this lane's share of W |x|^2 + S2 - 2 x . S1
+                    long long c = W * dot4_i8(w, w, 0) + S2;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) c -= 2 * S1[k] * (int)(signed char)(w >> (8 * k));
+                    return c;
+                };
+                long long best_cost = group16_sum64(cost_of(ow));
+                int best = -1;   // the stored key
+                for (int base = 0; base < n_new; base += 16) {
+                    const int t = base + l16;
+                    const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
+                    unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
+                    while (mm) {
+                        const int bit = __ffs(mm) - 1;
+                        mm &= mm - 1;
+                        const unsigned w = has_w ? ((const unsigned *)(ck + (tb + base + bit) * r))[l16] : 0u;
+                        const long long c = group16_sum64(cost_of(w));
+                        if (c < best_cost) {
+                            best_cost = c;
+                            best = base + bit;
+                        }
+                    }
+                }
+                if (best >= 0) {
+                    RP::copy(K, cb + j, K_new, tb + best, l16);
+                    if (has_w) ((unsigned *)(code + (cb + j) * r))[l16] = ((const unsigned *)(ck + (tb + best) * r))[l16];
+                }
+            }
+        } else {
+            RP::store_raw(K, cb + j, l16, kraw);
+            if (l16 < r / 4) ((unsigned *)(code + (cb + j) * r))[l16] = cw;
+        }
+        if (l16 == 0) {
+            cnt[cb + j] = m0 + gc;
+            stamp[cb + j] = frame_id;
+        }
+    }
+}
+
 template <bool BF16, int D>
 __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, void *__restrict__ V, int8_t *__restrict__ code,
                                                        int32_t *__restrict__ cnt, int32_t *__restrict__ stamp, int C,
@@ -1826,138 +2055,8 @@ __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, voi
     int dst = -1;
     if (mg) {
         dst = j;
-        // second round of loads, everything addressed by the slot at once: its records and multiplicity, and already
-        // its value row (and key row for the mean key), which only the group's representative goes on to use
-        const bool mean_key = rep_mode == 1;
-        float acc[RP::EPL], vn[RP::EPL], kacc[RP::EPL], kn[RP::EPL];
-        const u64 wkey = win[cb + j];
-        const int gc = grp[cb + j];
-        const int m0 = cnt[cb + j];
-        RP::load(V, cb + j, l16, acc);
-        if (mean_key) RP::load(K, cb + j, l16, kacc);
-        const int widx = (int)(0xFFFFFFFFu - (unsigned)wkey);
-        if (widx == i) {  // this token represents the group: it refreshes the slot
-            // ... and clears the group's records behind it: the other joiners only look for their own index in the
-            // record, which neither the old nor the cleared value shows them
-            if (l16 == 0) {
-                win[cb + j] = 0;
-                grp[cb + j] = 0;
-            }
-            // mean value; with rep_mode 1 also the mean key, whose stored bits feed later integer decisions: single
-            // float32 operations in a fixed order (multiplicity * old row, members in ascending token order, one division)
-#pragma unroll
-            for (int e = 0; e < RP::EPL; ++e) acc[e] *= (float)m0;
-            if (mean_key) {
-#pragma unroll
-                for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fmul_rn((float)m0, kacc[e]);
-            }
-            if (gc == 1) {
-                RP::unpack(vraw, vn);
-#pragma unroll
-                for (int e = 0; e < RP::EPL; ++e) acc[e] += vn[e];
-                if (mean_key) {
-                    RP::unpack(kraw, kn);
-#pragma unroll
-                    for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fadd_rn(kacc[e], kn[e]);
-                }
-            } else {  // several joiners: add their rows in ascending token order
-                for (int base = 0; base < n_new; base += 16) {
-                    const int t = base + l16;
-                    const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
-                    unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
-                    while (mm) {
-                        const int bit = __ffs(mm) - 1;
-                        mm &= mm - 1;
-                        RP::load(V_new, tb + base + bit, l16, vn);
-#pragma unroll
-                        for (int e = 0; e < RP::EPL; ++e) acc[e] += vn[e];
-                        if (mean_key) {
-                            RP::load(K_new, tb + base + bit, l16, kn);
-#pragma unroll
-                            for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fadd_rn(kacc[e], kn[e]);
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < RP::EPL; ++e) acc[e] = __fdiv_rn(acc[e], (float)(m0 + gc));
-            RP::store(V, cb + j, l16, acc);
-            if (mean_key) {   // the slot's code follows in tc_recode_kernel, from the stored row
-#pragma unroll
-                for (int e = 0; e < RP::EPL; ++e) kacc[e] = __fdiv_rn(kacc[e], (float)(m0 + gc));
-                RP::store(K, cb + j, l16, kacc);
-            } else if (rep_mode == 2) {
-                // Medoid key: of {stored key (weight m0), joiners (weight 1)} the member x with the smallest
-                // cost(x) = sum_y w_y |x - y|^2 in code space = W |x|^2 + S2 - 2 x . S1 (W = sum of the weights,
-                // S1 = weighted sum of the codes, S2 = weighted sum of their squared norms): exact integers, one pass to
-                // build the sums and one to evaluate the candidates (stored key first, then tokens ascending; a later
-                // candidate wins only on a strictly smaller cost).  Lane l16 owns code word l16 (r <= 64: 16 words).
-                // A single joiner never wins: cost(stored) = |d|^2 <= m0 |d|^2 = cost(joiner).
-                if (gc > 1) {
-                    const bool has_w = l16 < r / 4;
-                    const unsigned ow = has_w ? ((const unsigned *)(code + (cb + j) * r))[l16] : 0u;
-                    long long S1[4], S2 = (long long)m0 * dot4_i8(ow, ow, 0);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) S1[k] = (long long)m0 * (int)(signed char)(ow >> (8 * k));
-                    for (int base = 0; base < n_new; base += 16) {
-                        const int t = base + l16;
-                        const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
-                        unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
-                        while (mm) {
-                            const int bit = __ffs(mm) - 1;
-                            mm &= mm - 1;
-                            const unsigned w = has_w ? ((const unsigned *)(ck + (tb + base + bit) * r))[l16] : 0u;
-                            S2 += dot4_i8(w, w, 0);
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) S1[k] += (int)(signed char)(w >> (8 * k));
-                        }
-                    }
-                    const long long W = (long long)m0 + gc;
-                    auto group16_sum64 = [](long long v) -> long long {
-#pragma unroll
-                        for (int off = 1; off < 16; off <<= 1) {
-                            const unsigned lo = shfl_xor((unsigned)v, off), hi = shfl_xor((unsigned)((unsigned long long)v >> 32), off);
-                            v += (long long)(((unsigned long long)hi << 32) | lo);
-                        }
-                        return v;
-                    };
-                    auto cost_of = [&](unsigned w) -> long long {   // this lane's share of W |x|^2 + S2 - 2 x . S1
-                        long long c = W * dot4_i8(w, w, 0) + S2;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) c -= 2 * S1[k] * (int)(signed char)(w >> (8 * k));
-                        return c;
-                    };
-                    long long best_cost = group16_sum64(cost_of(ow));
-                    int best = -1;   // the stored key
-                    for (int base = 0; base < n_new; base += 16) {
-                        const int t = base + l16;
-                        const bool member = t < n_new && merged[tb + t] && jstar[tb + t] == j;
-                        unsigned mm = (unsigned)((__ballot(member) >> (16 * sub)) & 0xFFFFull);
-                        while (mm) {
-                            const int bit = __ffs(mm) - 1;
-                            mm &= mm - 1;
-                            const unsigned w = has_w ? ((const unsigned *)(ck + (tb + base + bit) * r))[l16] : 0u;
-                            const long long c = group16_sum64(cost_of(w));
-                            if (c < best_cost) {
-                                best_cost = c;
-                                best = base + bit;
-                            }
-                        }
-                    }
-                    if (best >= 0) {
-                        RP::copy(K, cb + j, K_new, tb + best, l16);
-                        if (has_w) ((unsigned *)(code + (cb + j) * r))[l16] = ((const unsigned *)(ck + (tb + best) * r))[l16];
-                    }
-                }
-            } else {
-                RP::store_raw(K, cb + j, l16, kraw);
-                if (l16 < r / 4) ((unsigned *)(code + (cb + j) * r))[l16] = cw;
-            }
-            if (l16 == 0) {
-                cnt[cb + j] = m0 + gc;
-                stamp[cb + j] = frame_id;
-            }
-        }
+        apply_merged_token<BF16, D>(K, V, code, cnt, stamp, r, K_new, V_new, ck, n_new, frame_id, jstar, merged, win, grp,
+                                    rep_mode, tb, cb, i, j, l16, sub, kraw, vraw, cw);
     } else if (a < n_unm - n_dropped) {
         dst = a < n_victims ? victims[tb + a] : L + (a - n_victims);
         // A plan whose bounded wait ran out (stats[7] = 1) may have left victim positions unwritten: whatever they
@@ -1974,6 +2073,423 @@ __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, voi
         }
     }
     if (l16 == 0) merge_map[ti] = dst;
+}
+
+// ---- plan and apply in one launch ----------------------------------------------------------------------
+// On a persistent workspace and a cache of at most SETTLE_SLOTS slots nothing that the plan decides needs a meeting: the
+// threshold age follows from the slices' age histograms less the slots touched in this frame, and so do the numbers of
+// victims in the slices below.  Every workgroup works that out for itself (the same data, the same answer) and goes
+// straight on to its share of the rows:
+//   - workgroups below n_slices * n_reps: (slice, share).  The slice's victims in ascending order, from its stamps; the
+//     rows of every n_reps-th of them, starting with the share's, are replaced by those of the unmerged tokens of their
+//     rank.  A stamp in the future or a threshold in the last bin: the first workgroup of the head selects on the stamps
+//     themselves and replaces all of the head's victims.
+//   - the others: 32 tokens each; the merged ones refresh their slots, the unmerged ones that found no victim are
+//     appended.
+// They write what no other one reads: a slot is touched or a victim or new; tokens' flags and slots, the old length, the
+// touched slots' old stamps, every slot's age and the histograms were left by the match and verify launches.
+// What bounds it: the chain of a workgroup.  At 12 heads x 1560 tokens and 37440 slots (timestamps inside the kernel, us, of the
+// workgroups for victims): first loads 2.6, lists, bitmap and histogram 3.2, threshold 0.7, slice 1.0, rows 0.7 on average
+// and 4 at most; the token workgroups are done after 6.  Launch 16.5, where the plan (17 workgroups per head, one
+// meeting) took 13.5 and the apply launch behind it 9.3; a chunk of three such calls 325 -> 293.
+// All 888 workgroups have to be resident at once: with 99 registers they took two rounds and 23.8 us, so frames of up to
+// 2048 tokens have an instantiation of 64 (it spills 17 words, around the medoid key and the selection on stamps).
+constexpr int SETTLE_THREADS = 512;
+constexpr int SETTLE_WAVES = SETTLE_THREADS / 64;
+constexpr int SETTLE_GROUPS = SETTLE_THREADS / 16;             // 16-lane groups: rows a workgroup moves at a time
+constexpr int SETTLE_SPT = SETTLE_SLICE / SETTLE_THREADS;      // slots per thread of a slice
+static_assert(SETTLE_SPT == 16 && AGE_BINS == 2 * SETTLE_THREADS, "a thread's slots are half a bitmap word, its bins two");
+// dynamic LDS: bitmap of the touched slots, unmerged tokens by rank, victims of the slice
+static size_t settle_lds_bytes(int C, int n_new) {
+    return (size_t)((C + 63) / 64) * 8 + (size_t)((n_new + 7) & ~7) * 2 + SETTLE_SLICE * 2;
+}
+
+// Inclusive prefix over a wavefront's lanes, on the vector ALU (six shuffles by way of the LDS queue took 0.3 us).
+__device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8: prefix of 16 lanes
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast 15: rows 1 and 3 add the row below
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31: the upper half adds the lower
+    return v;
+}
+struct Pair {
+    unsigned a, b;
+};
+// Exclusive prefix over the workgroup's threads of two counts at once, and their totals.  wtot: two sets, used in turn, so that
+// one barrier is enough.
+__device__ __forceinline__ Pair settle_scan(Pair v, Pair (*wtot)[SETTLE_WAVES], int &turn, Pair &total) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const Pair incl = {wave_incl_scan(v.a), wave_incl_scan(v.b)};
+    Pair *wt = wtot[turn];
+    turn ^= 1;
+    if (lane == 63) wt[wave] = incl;
+    __syncthreads();
+    Pair pos = {incl.a - v.a, incl.b - v.b};
+    total = {0u, 0u};
+#pragma unroll
+    for (int w = 0; w < SETTLE_WAVES; ++w) {
+        const Pair c = wt[w];
+        pos.a += w < wave ? c.a : 0u;
+        pos.b += w < wave ? c.b : 0u;
+        total.a += c.a;
+        total.b += c.b;
+    }
+    return pos;
+}
+
+// TPT: tokens of the list per thread (4: frames of up to 2048 tokens; 16).
+template <bool BF16, int D, int TPT>
+__global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_settle_kernel(
+    void *__restrict__ K, void *__restrict__ V, int8_t *__restrict__ code, int32_t *__restrict__ cnt,
+    int32_t *__restrict__ stamp, int C, int r, const void *__restrict__ K_new, const void *__restrict__ V_new,
+    const int8_t *__restrict__ ck, int n_new, int frame_id, const int32_t *__restrict__ jstar, uint8_t *merged, u64 *win,
+    int32_t *grp, int32_t *hs, int32_t *__restrict__ merge_map, int32_t *__restrict__ len, int rep_mode,
+    const int32_t *__restrict__ tstamp, const unsigned *__restrict__ ages, const unsigned short *__restrict__ slot_age,
+    int n_reps, int32_t *__restrict__ stats) {
+    typedef RowPiece<BF16, D> RP;
+    extern __shared__ __attribute__((aligned(16))) unsigned char slds[];
+    __shared__ unsigned h_all[AGE_BINS], h_low[AGE_BINS];   // ages of the head's eligible slots, and of those below this slice
+    __shared__ Pair wtot[2][SETTLE_WAVES];
+    __shared__ int kcnt[TPT * SETTLE_WAVES];
+    __shared__ int sh[4];
+    int turn = 0;
+    const int h = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const int l16 = tid & 15, group = tid >> 4, sub = lane >> 4;
+    const int n_slices = settle_slices(C), n_evict_wgs = n_slices * n_reps;
+    const size_t tb = (size_t)h * n_new, cb = (size_t)h * C;
+    const int L = hs[(size_t)h * HS_STRIDE], mark = hs[(size_t)h * HS_STRIDE + 7];
+    const bool dirty = mark != 0 && mark != WS_CLEAN;   // neither zero-filled nor left by a finished call: nothing is applied
+    const bool maybe = L + n_new > C;                    // otherwise no eviction can be needed
+    unsigned *touched = (unsigned *)slds;                // [ceil(C / 64) * 2]
+    unsigned short *unm = (unsigned short *)(touched + 2 * ((C + 63) / 64));
+    unsigned short *vict = unm + ((n_new + 7) & ~7);
+    auto clear_touched = [&]() {
+        for (int w = tid; w < 2 * ((C + 63) / 64); w += SETTLE_THREADS) touched[w] = 0u;
+    };
+
+    if ((int)blockIdx.x >= n_evict_wgs) {   // ---- tokens
+        const int base = ((int)blockIdx.x - n_evict_wgs) * SETTLE_GROUPS;
+        const int i = base + group;
+        const bool ok = i < n_new;
+        const size_t ti = tb + min(i, n_new - 1);
+        // first round of loads: the token's flag, slot and rows, and everybody's flags
+        const bool mg = merged[ti] != 0;
+        const int j = jstar[ti];
+        const typename RP::Raw kraw = RP::load_raw(K_new, ti, l16), vraw = RP::load_raw(V_new, ti, l16);
+        unsigned cw = 0;
+        if (l16 < r / 4) cw = ((const unsigned *)(ck + ti * r))[l16];
+        uint8_t flag[TPT];
+#pragma unroll
+        for (int k = 0; k < TPT; ++k)
+            flag[k] = k * SETTLE_THREADS < n_new ? merged[tb + min(k * SETTLE_THREADS + tid, n_new - 1)] : 1;
+        if (dirty) {   // uniform over the head
+            if (ok && l16 == 0) {
+                merge_map[ti] = -1;
+                merged[ti] = 0;
+            }
+            if (base == 0 && tid == 0) {
+                int32_t *st = stats + (size_t)h * 8;
+                st[0] = L; st[1] = 0; st[2] = 0; st[3] = 0; st[4] = n_new; st[5] = 0; st[6] = 0; st[7] = 3;
+            }
+            return;
+        }
+        unsigned n_mine = 0, n_below = 0;   // unmerged tokens among those this thread looks at, and of them below the workgroup's
+#pragma unroll
+        for (int k = 0; k < TPT; ++k) {
+            const int t = k * SETTLE_THREADS + tid;
+            const bool u = t < n_new && flag[k] == 0;
+            n_mine += u ? 1u : 0u;
+            n_below += u && t < base ? 1u : 0u;
+        }
+        Pair tot;
+        settle_scan({n_mine, n_below}, wtot, turn, tot);
+        const int n_unm = (int)tot.a, first_rank = (int)tot.b;
+        const int e = max(0, L + n_unm - C);
+        int n_victims = e;
+        if (e > L - (n_new - n_unm)) {   // there may be fewer untouched slots than that: count the touched ones
+            clear_touched();
+            __syncthreads();
+            unsigned distinct = 0;
+            for (int t = tid; t < n_new; t += SETTLE_THREADS)
+                if (merged[tb + t]) {
+                    const int s = jstar[tb + t];
+                    distinct += (atomicOr(&touched[s >> 5], 1u << (s & 31)) >> (s & 31)) & 1u ? 0u : 1u;
+                }
+            settle_scan({distinct, 0u}, wtot, turn, tot);
+            n_victims = min(e, L - (int)tot.a);
+        }
+        const int n_dropped = e - n_victims;
+        // rank of an unmerged token: those below the workgroup's, then those before it in it
+        if (l16 == 0) kcnt[group] = ok && !mg ? 1 : 0;
+        __syncthreads();
+        int a = first_rank;
+#pragma unroll
+        for (int q = 0; q < SETTLE_GROUPS; ++q) a += q < group ? kcnt[q] : 0;
+        if (ok && mg) {
+            apply_merged_token<BF16, D>(K, V, code, cnt, stamp, r, K_new, V_new, ck, n_new, frame_id, jstar, merged, win, grp,
+                                        rep_mode, tb, cb, i, j, l16, sub, kraw, vraw, cw);
+            if (l16 == 0) merge_map[ti] = j;
+        } else if (ok && a >= n_victims) {   // appended, or dropped
+            const int dst = a < n_unm - n_dropped ? L + (a - n_victims) : -1;
+            if (dst >= 0) {
+                RP::store_raw(K, cb + dst, l16, kraw);
+                RP::store_raw(V, cb + dst, l16, vraw);
+                if (l16 < r / 4) ((unsigned *)(code + (cb + dst) * r))[l16] = cw;
+                if (l16 == 0) {
+                    cnt[cb + dst] = 1;
+                    stamp[cb + dst] = frame_id;
+                }
+            }
+            if (l16 == 0) merge_map[ti] = dst;
+        }
+        if (base == 0 && tid == 0) {
+            const int n_app = n_unm - n_dropped, newL = L + n_app - n_victims;
+            int32_t *st = stats + (size_t)h * 8;
+            st[0] = newL; st[1] = n_new - n_unm; st[2] = n_app; st[3] = n_victims; st[4] = n_dropped; st[5] = 0; st[6] = 0;
+            st[7] = 0;
+            len[h] = newL;   // the other workgroups read the length of before from hs
+            hs[(size_t)h * HS_STRIDE + 7] = WS_CLEAN;
+        }
+        return;
+    }
+
+    // ---- victims
+    const int slice = (int)blockIdx.x % n_slices, share = (int)blockIdx.x / n_slices;
+    const int32_t *st = stamp + cb;
+    const unsigned *ag = ages + (size_t)h * n_slices * AGE_WORDS;
+    // first round of loads: the tokens' flags, slots and slots' stamps, this thread's run of ages, two bins of every slice
+    int tj[TPT], ts[TPT];
+    uint8_t flag[TPT];
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const int t = min(k * SETTLE_THREADS + tid, n_new - 1);
+        tj[k] = jstar[tb + t];
+        ts[k] = tstamp[tb + t];
+        flag[k] = merged[tb + t];
+    }
+    const int s0 = slice * SETTLE_SLICE;
+    u32x4 run[2];   // ages of slots s0 + 16 tid .. +15
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        run[q] = *(const u32x4 *)(slot_age + ((size_t)h * n_slices + slice) * SETTLE_SLICE + SETTLE_SPT * tid + 8 * q);
+    constexpr int MAX_SLICES = SETTLE_SLOTS / SETTLE_SLICE;
+    u32x2 bins[MAX_SLICES];
+    unsigned fut[MAX_SLICES];
+#pragma unroll
+    for (int q = 0; q < MAX_SLICES; ++q) {
+        bins[q] = u32x2{0u, 0u};
+        fut[q] = 0u;
+        if (q < n_slices) {   // uniform
+            bins[q] = *(const u32x2 *)(ag + (size_t)q * AGE_WORDS + 2 * tid);
+            fut[q] = ag[(size_t)q * AGE_WORDS + AGE_BINS];
+        }
+    }
+    if (!maybe || dirty) return;   // uniform over the head; after the loads, which do not depend on it
+    unsigned all0 = 0, all1 = 0, low0 = 0, low1 = 0, future = 0;
+#pragma unroll
+    for (int q = 0; q < MAX_SLICES; ++q) {
+        all0 += bins[q][0]; all1 += bins[q][1];
+        low0 += q < slice ? bins[q][0] : 0u;
+        low1 += q < slice ? bins[q][1] : 0u;
+        future |= fut[q];
+    }
+    clear_touched();
+    // unmerged tokens by rank (ascending token order): counts per wavefront and round, every wavefront adds them up itself
+    unsigned tmask = 0, umask = 0;   // bit k: token k * SETTLE_THREADS + tid is merged / unmerged
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const bool in = k * SETTLE_THREADS + tid < n_new;
+        tmask |= in && flag[k] != 0 ? 1u << k : 0u;
+        umask |= in && flag[k] == 0 ? 1u << k : 0u;
+        const u64 m = __ballot((umask >> k) & 1u);
+        if (lane == 0) kcnt[k * SETTLE_WAVES + wave] = __popcll(m);
+    }
+    h_all[2 * tid] = all0; h_all[2 * tid + 1] = all1;
+    h_low[2 * tid] = low0; h_low[2 * tid + 1] = low1;
+    __syncthreads();
+    constexpr int CPL = (TPT * SETTLE_WAVES + 63) / 64;   // counts per lane
+    static_assert(CPL <= 2, "a wavefront holds all counts");
+    int kc[CPL], kbase = 0;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+        kc[q] = CPL * lane + q < TPT * SETTLE_WAVES ? kcnt[CPL * lane + q] : 0;
+        kbase += kc[q];
+    }
+    const int kincl = (int)wave_incl_scan((unsigned)kbase);
+    kbase = kincl - kbase;   // unmerged tokens before the first count of this lane
+    const int n_unm = __builtin_amdgcn_readlane(kincl, 63), e = L + n_unm - C;
+    if (e <= 0) return;   // uniform over the head
+    unsigned distinct = 0, fmask = 0;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k)   // each touched slot counts once
+        if ((tmask >> k) & 1u) fmask |= (((atomicOr(&touched[tj[k] >> 5], 1u << (tj[k] & 31)) >> (tj[k] & 31)) & 1u) ^ 1u) << k;
+#pragma unroll
+    for (int k = 0; k < TPT; ++k) {
+        const u64 m = __ballot((umask >> k) & 1u);
+        const int c = k * SETTLE_WAVES + wave;   // uniform
+        int base = __builtin_amdgcn_readlane(kbase, __builtin_amdgcn_readfirstlane(c / CPL));
+        if (CPL == 2 && (c & 1)) base += __builtin_amdgcn_readlane(kc[0], __builtin_amdgcn_readfirstlane(c / CPL));
+        if ((umask >> k) & 1u) unm[base + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)(k * SETTLE_THREADS + tid);
+        const bool first = (fmask >> k) & 1u;
+        const u64 fm = __ballot(first);
+        if (fm) {   // uniform; most of them carry the stamp of the frame before: lanes of one age count together
+            const unsigned bin = min((unsigned)frame_id - (unsigned)ts[k], (unsigned)(AGE_BINS - 1));
+            const int lead = __ffsll((unsigned long long)fm) - 1;
+            const bool same = bin == (unsigned)__builtin_amdgcn_readlane((int)bin, lead), low = tj[k] < s0;
+            const u64 sm = __ballot(first && same), lm = __ballot(first && same && low);
+            distinct += first ? 1u : 0u;
+            if (lane == lead) {
+                atomicSub(&h_all[bin], (unsigned)__popcll(sm));
+                if (lm) atomicSub(&h_low[bin], (unsigned)__popcll(lm));
+            }
+            if (first && !same) {
+                atomicSub(&h_all[bin], 1u);
+                if (low) atomicSub(&h_low[bin], 1u);
+            }
+        }
+    }
+    Pair tot;
+    settle_scan({distinct, 0u}, wtot, turn, tot);   // its barrier also publishes the lists, the bitmap and the histograms
+    const int n_el = L - (int)tot.a;
+    const bool take_all = n_el <= e;
+    const int n_victims = min(e, n_el);
+    // Threshold: the bin, from the oldest on, in which the e-th slot lies; `need` of it are taken, in slot order.  Victims: keys
+    // below T and the first `need` equal to it, a key being minus the age, or on the general path the stamp.
+    int T = INT_MAX, need = 0, low_older = 0, low_ties = 0;
+    bool fast = future == 0;
+    if (fast && !take_all) {
+        const int b1 = AGE_BINS - 1 - 2 * tid, b0 = b1 - 1;   // this thread's bins, the older one first
+        const unsigned a1 = h_all[b1], a0 = h_all[b0], l1 = h_low[b1], l0 = h_low[b0];
+        const Pair ex = settle_scan({a0 + a1, l0 + l1}, wtot, turn, tot);
+        const unsigned before = ex.a, want = (unsigned)e;
+        if (before < want && want <= before + a0 + a1) {
+            const bool in1 = want <= before + a1;
+            sh[0] = in1 ? b1 : b0;
+            sh[1] = (int)(want - before - (in1 ? 0u : a1));
+            sh[2] = (int)(ex.b + (in1 ? 0u : l1));
+            sh[3] = (int)(in1 ? l1 : l0);
+        }
+        __syncthreads();
+        const int bin = sh[0];
+        fast = bin < AGE_BINS - 1;
+        T = -bin;
+        need = sh[1];
+        low_older = sh[2];
+        low_ties = sh[3];
+    } else if (fast) {   // every eligible slot: those below this slice
+        settle_scan({h_low[2 * tid] + h_low[2 * tid + 1], 0u}, wtot, turn, tot);
+        low_older = (int)tot.a;
+    }
+    if (!fast) {   // uniform over the head
+        if (blockIdx.x != 0) return;
+        // Select on the stamps themselves, four digits of eight bits from the top (each digit's counts in h_all).
+        unsigned prefix = 0;
+        unsigned want = (unsigned)e;
+        for (int shift = 24; shift >= 0 && !take_all; shift -= 8) {
+            __syncthreads();
+            if (tid < 256) h_all[tid] = 0u;
+            __syncthreads();
+            for (int j = tid; j < L; j += SETTLE_THREADS) {
+                const unsigned u = (unsigned)st[j] ^ 0x80000000u;
+                const bool el = !((touched[j >> 5] >> (j & 31)) & 1u);
+                if (el && (shift == 24 || (u >> ((shift + 8) & 31)) == prefix)) atomicAdd(&h_all[(u >> shift) & 255u], 1u);
+            }
+            __syncthreads();
+            const unsigned c = tid < 256 ? h_all[tid] : 0u;
+            const unsigned before = settle_scan({c, 0u}, wtot, turn, tot).a;
+            if (before < want && want <= before + c) {
+                sh[0] = tid;
+                sh[1] = (int)(want - before);
+            }
+            __syncthreads();
+            prefix = (prefix << 8) | (unsigned)sh[0];
+            want = (unsigned)sh[1];
+        }
+        T = take_all ? INT_MAX : (int)(prefix ^ 0x80000000u);
+        need = (int)want;
+    }
+    // Victims of a slice, the first of rank rank0: their slots in `vict`, then the rows of every n-th from the m-th on.
+    auto evict = [&](int from, const int (&sv)[SETTLE_SPT], int rank0, int ties_before, int m, int n, int &n_here, int &ties_here) {
+        const int j0 = from + SETTLE_SPT * tid;
+        unsigned bits = j0 < C ? (~(touched[j0 >> 5] >> (j0 & 31))) & 0xFFFFu : 0u;   // eligible slots of the run
+        if (j0 + SETTLE_SPT > L) bits &= j0 < L ? (1u << (L - j0)) - 1u : 0u;
+        unsigned older = 0, ties = 0;
+#pragma unroll
+        for (int q = 0; q < SETTLE_SPT; ++q) {
+            older |= (take_all || sv[q] < T) ? 1u << q : 0u;
+            ties |= (!take_all && sv[q] == T) ? 1u << q : 0u;
+        }
+        older &= bits;
+        ties &= bits;
+        const Pair ex = settle_scan({(unsigned)__popc(older), (unsigned)__popc(ties)}, wtot, turn, tot);
+        const int take_ties = min(max(need - ties_before, 0), (int)tot.b);
+        n_here = (int)tot.a + take_ties;
+        ties_here = (int)tot.b;
+        int ties_left = take_ties - (int)ex.b, idx = (int)ex.a + min((int)ex.b, take_ties);
+        for (unsigned todo = older | (ties_left > 0 ? ties : 0u); todo; todo &= todo - 1u) {
+            const int q = __ffs(todo) - 1;
+            if ((ties >> q) & 1u) {
+                if (ties_left <= 0) continue;
+                ties_left -= 1;
+            }
+            vict[idx] = (unsigned short)(j0 + q - from);
+            idx += 1;
+        }
+        __syncthreads();
+        const int n_rows = n_here > m ? (n_here - m + n - 1) / n : 0;
+        constexpr int UN = 2;   // rows of a group in flight
+        for (int v0 = group; v0 < n_rows; v0 += SETTLE_GROUPS * UN) {
+            typename RP::Raw kr[UN], vr[UN];
+            unsigned cw[UN];
+            int tok[UN], dst[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int v = v0 + u * SETTLE_GROUPS;
+                tok[u] = -1;
+                if (v < n_rows) {
+                    const int a = rank0 + v * n + m;
+                    dst[u] = from + vict[v * n + m];
+                    tok[u] = a < n_unm ? unm[a] : -1;
+                }
+                if (tok[u] >= 0) {
+                    kr[u] = RP::load_raw(K_new, tb + tok[u], l16);
+                    vr[u] = RP::load_raw(V_new, tb + tok[u], l16);
+                    cw[u] = l16 < r / 4 ? ((const unsigned *)(ck + (tb + tok[u]) * r))[l16] : 0u;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (tok[u] >= 0) {
+                    RP::store_raw(K, cb + dst[u], l16, kr[u]);
+                    RP::store_raw(V, cb + dst[u], l16, vr[u]);
+                    if (l16 < r / 4) ((unsigned *)(code + (cb + dst[u]) * r))[l16] = cw[u];
+                    if (l16 == 0) {
+                        cnt[cb + dst[u]] = 1;
+                        stamp[cb + dst[u]] = frame_id;
+                        merge_map[tb + tok[u]] = dst[u];
+                    }
+                }
+        }
+    };
+    int key[SETTLE_SPT], n_here, ties_here;
+    if (fast) {
+#pragma unroll
+        for (int q = 0; q < SETTLE_SPT; ++q) key[q] = -(int)((run[q / 8][(q % 8) / 2] >> (16 * (q & 1))) & 0xFFFFu);
+        evict(s0, key, low_older + min(need, low_ties), low_ties, share, n_reps, n_here, ties_here);
+    } else {
+        int rank0 = 0, ties_before = 0;
+        for (int q = 0; q < n_slices && rank0 < n_victims; ++q) {   // uniform
+            const int j0 = q * SETTLE_SLICE + SETTLE_SPT * tid;
+#pragma unroll
+            for (int x = 0; x < SETTLE_SPT; ++x) key[x] = j0 + x < L ? st[j0 + x] : 0;
+            __syncthreads();   // the victims of the slice before have been read
+            evict(q * SETTLE_SLICE, key, rank0, ties_before, 0, 1, n_here, ties_here);
+            rank0 += n_here;
+            ties_before += ties_here;
+        }
+    }
 }
 
 // ---- codes of the slots whose key was replaced by a mean (rep_mode 1), from the rows tc_apply_kernel stored -----
@@ -2065,6 +2581,10 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     const bool window = cand && win_lds <= WINDOW_LDS_MAX;
     const bool fused_encode = window && !P_new;  // the match kernel encodes its own probes
     const bool fused_verify = fused_encode && ws_persistent;   // ... and verifies its matches: nothing to clear first
+    // Plan and apply in one launch: short caches, whose age histograms are small enough to be read by every workgroup, and
+    // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
+    const bool settle = ws_persistent && C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
+    const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age)} : SettleOut{};
     if (!fused_encode) {
         const int64_t zero_words = (int64_t)((w.ps - w.best) / 8) + (int64_t)H * PLAN_SCRATCH_WORDS / 2;  // best .. end of ps
         int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, best, zero_words, s);
@@ -2092,10 +2612,10 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
             gx = (n_new + per - 1) / per;
         }
         // the age histogram beside the match: a workgroup per 8192 slots (one round of loads, 4 x 16 bytes per thread)
-        const int n_hist = fused_verify && !wide && !self_hist ? (C + 8191) / 8192 : 0;
+        const int n_hist = settle ? (fused_verify ? settle_slices(C) : 0) : fused_verify && !wide && !self_hist ? (C + 8191) / 8192 : 0;
         const dim3 grid(gx + n_hist, H);
         const bool bf = dtype == FASTAR_BF16;
-        const VerifyArgs va = {cache->K, tau2_q16, merged, cache->stamp, frame_id, self_hist ? -1 : PS_HIST, PS_FUT};
+        const VerifyArgs va = {cache->K, tau2_q16, merged, cache->stamp, frame_id, self_hist ? -1 : PS_HIST, PS_FUT, so};
         int rc = FASTAR_OK;
 #define FASTAR_WIN(RR, ENC, BF, DD, VER, TT)                                                                              \
     rc = launch_match_window<RR, ENC, BF, DD, VER, TT>(grid, win_lds, s, cache->code, cache->len, C, cp, n_new, cand,      \
@@ -2143,7 +2663,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
                            jstar, sbest, win, grp);
         FASTAR_LAUNCH_CHECK();
     }
-    const dim3 tgrid((n_new + 15) / 16, H);
+    dim3 tgrid((n_new + 15) / 16, H);
     const bool bf = dtype == FASTAR_BF16;
 #define FASTAR_TC(KERNEL, ...)                                                                          \
     do {                                                                                                \
@@ -2153,11 +2673,36 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         else hipLaunchKernelGGL((KERNEL<false, 64>), tgrid, dim3(256), 0, s, __VA_ARGS__);                       \
     } while (0)
     if (!fused_verify) {
+        const int n_slices = settle ? settle_slices(C) : 0;
+        tgrid.x += n_slices;
         FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest, win,
-                  grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE);
+                  grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
+                  n_slices, so);
+        tgrid.x -= n_slices;
         FASTAR_LAUNCH_CHECK();
     }
-    {
+    if (settle) {
+        // as many workgroups for the victims as would have 64 rows each if nothing merged
+        const int n_slices = settle_slices(C), n_reps = ((n_new + 63) / 64 + n_slices - 1) / n_slices;
+        const dim3 sgrid(n_slices * n_reps + (n_new + SETTLE_GROUPS - 1) / SETTLE_GROUPS, H);
+        const size_t lds = settle_lds_bytes(C, n_new);
+#define FASTAR_SETTLE_T(BF, DD, TT)                                                                                      \
+    hipLaunchKernelGGL((tc_settle_kernel<BF, DD, TT>), sgrid, dim3(SETTLE_THREADS), lds, s, cache->K, cache->V, cache->code,    \
+                       cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new, frame_id, jstar, merged, win, grp, hs,     \
+                       merge_map, cache->len, rep_mode, so.tstamp, so.ages, so.slot_age, n_reps, stats)
+#define FASTAR_SETTLE(BF, DD)                                  \
+    do {                                                       \
+        if (n_new <= 4 * SETTLE_THREADS) FASTAR_SETTLE_T(BF, DD, 4); \
+        else FASTAR_SETTLE_T(BF, DD, 16);                      \
+    } while (0)
+        if (bf && d == 128) FASTAR_SETTLE(true, 128);
+        else if (bf) FASTAR_SETTLE(true, 64);
+        else if (d == 128) FASTAR_SETTLE(false, 128);
+        else FASTAR_SETTLE(false, 64);
+#undef FASTAR_SETTLE
+#undef FASTAR_SETTLE_T
+        FASTAR_LAUNCH_CHECK();
+    } else {
         const bool long_frame = n_new > 8 * PLAN_THREADS;
 #define FASTAR_PLAN(PM, TM)                                                                                            \
     hipLaunchKernelGGL((tc_plan_kernel<PM, TM>), dim3(nb + 1, H), dim3(PLAN_THREADS), plan_lds_bytes(C, nb), s, cache->len, \
@@ -2168,12 +2713,12 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         else if (long_frame) FASTAR_PLAN(16, 16);
         else FASTAR_PLAN(16, 8);
 #undef FASTAR_PLAN
+        FASTAR_LAUNCH_CHECK();
+        FASTAR_TC(tc_apply_kernel, cache->K, cache->V, cache->code, cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new,
+                  frame_id, jstar, merged, win, grp, rank, victims, hs, merge_map, cache->len, rep_mode, plan_scratch,
+                  (int)PS_STRIDE, stats);
+        FASTAR_LAUNCH_CHECK();
     }
-    FASTAR_LAUNCH_CHECK();
-    FASTAR_TC(tc_apply_kernel, cache->K, cache->V, cache->code, cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new,
-              frame_id, jstar, merged, win, grp, rank, victims, hs, merge_map, cache->len, rep_mode, plan_scratch,
-              (int)PS_STRIDE, stats);
-    FASTAR_LAUNCH_CHECK();
 #undef FASTAR_TC
     if (rep_mode == FASTAR_REP_MEAN) {
         const dim3 rgrid((n_new + 63) / 64, H);

@@ -991,6 +991,78 @@ def test_tempcache_plan_that_gives_up_leaves_the_cache_untouched_and_says_so(pat
         assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
 
 
+# (dtype, d, H, T, C, free slots, stamps from / to, frame id, what else): edges of the age histogram's slices (8192 slots), of
+# the list of unmerged tokens (512 tokens per round, 2048 and 8192 in all), of the cache (no eviction, some, all and too
+# few evictable slots), of the histogram (a stamp in the future, a threshold in or beyond the last bin, stamps that wrap)
+@pytest.mark.parametrize("dtype,d,H,T,C,free,lo,hi,frame,extra", [
+    ("bf16", 128, 3, 300, 1000, 0, 0, 9, 9, None),
+    ("fp32", 128, 2, 512, 8192, 7, 3, 9, 9, None),
+    ("bf16", 64, 2, 513, 8193, 0, 0, 900, 1000, None),
+    ("fp32", 64, 1, 77, 4001, 500, 0, 9, 9, None),
+    ("bf16", 128, 2, 2048, 16385, 0, 0, 60, 61, None),
+    ("bf16", 128, 1, 2049, 65536, 100, 0, 60, 61, "clustered"),
+    ("fp32", 128, 1, 8192, 40000, 0, 0, 3, 3, None),
+    ("bf16", 128, 1, 8193, 9000, 0, 0, 3, 3, None),            # longer than the list: the plan and apply launches
+    ("bf16", 128, 2, 900, 500, 0, 0, 5, 6, None),              # fewer evictable slots than are needed: tokens dropped
+    ("bf16", 128, 2, 400, 20000, 0, 0, 9, 9, "future"),
+    ("bf16", 128, 2, 400, 20000, 0, 0, 3000, 5000, None),      # threshold in the last bin
+    ("fp32", 64, 2, 400, 9000, 30, 0, 1022, 1022, None),       # ... just short of it
+    ("bf16", 128, 1, 300, 8200, 0, -2 ** 31, 2 ** 31 - 1, 2 ** 31 - 1, None),
+])
+@pytest.mark.parametrize("rep_mode", [fa.REP_LAST, fa.REP_MEAN])
+def test_tempcache_short_caches_settle_in_one_launch(dtype, d, H, T, C, free, lo, hi, frame, extra, rep_mode):
+    # on a persistent workspace (plan and apply in one launch), against the oracle and against the call without one
+    if rep_mode != fa.REP_LAST and (T > 2048 or frame == 2 ** 31 - 1):
+        pytest.skip("one mode is enough at the largest sizes")
+    rng = np.random.default_rng(C + T + d)
+    r = 32
+    codec = make_codec(0, 9, d, r)
+    as_dt = lambda a: to_storage(a.astype(np.float32), dtype)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.V[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = rng.integers(1, 4, size=(H, C))
+    ref.stamp[:] = rng.integers(lo, hi, size=(H, C))
+    if extra == "future":
+        ref.stamp[:, 17] = frame + 30
+    if extra == "clustered":       # the oldest slots lie together in one slice
+        ref.stamp[:, 30000:33000] = 0
+    ref.len[:] = C - free
+    ref.len[0] = C - free // 2
+    n_cand = min(T, 700)
+    cand = np.stack([rng.choice(C - free, size=n_cand, replace=C - free < n_cand) for _ in range(H)]).astype(np.int32)
+    K_new = rng.standard_normal((H, T, d))
+    for h in range(H):             # a third of the frame repeats candidates, some of them several times
+        rep = rng.permutation(T)[: T // 3]
+        K_new[h, rep] = to_f32(ref.K[h, cand[h, rng.integers(0, n_cand, size=rep.size)]])
+    K_new, V_new = as_dt(K_new), as_dt(rng.standard_normal((H, T, d)))
+    args = dict(tau2_q16=TAU2(0.9), frame_id=frame, rep_mode=rep_mode)
+    n_ws = fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r)
+    out = {}
+    for persistent in (True, False):
+        gpu = dev_cache(ref)
+        ws = torch.zeros(n_ws, dtype=torch.uint8, device="cuda")
+        res = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws,
+                                    ws_persistent=persistent, **args)
+        sync()
+        out[persistent] = ([to_host(x) for x in res], host_cache(gpu))
+    expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+    (got, cache), (plain, plain_cache) = out[True], out[False]
+    for a, b, c in zip(got, expect, plain):
+        assert np.array_equal(a, b)
+        if frame != 2 ** 31 - 1:   # stamps this far apart: the plan launch reports that its choice is not exact
+            assert np.array_equal(a, c)
+    assert_cache_equal(cache, ref, VTOL[dtype])
+    for name in ("K", "V", "code", "cnt", "stamp", "len"):
+        if frame != 2 ** 31 - 1:
+            assert np.array_equal(getattr(cache, name), getattr(plain_cache, name)), name
+    st = got[2]
+    assert (st[:, 1] > 0).all()
+    if free == 0:
+        assert (st[:, 3] > 0).all()
+
+
 @pytest.mark.parametrize("name,dtype,H,frames,C", [("cfg1", None, None, 6, 6 * 256), ("cfg1", "bf16", None, 6, 3 * 256),
                                                    ("cfg2", None, 2, 4, 3 * 1560)])
 def test_tempcache_mean_key_representative_bit_exact(name, dtype, H, frames, C):
