@@ -182,11 +182,17 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
 // Shared by the kernel that stages a candidate list and the one that stages a range of the cache; eight wavefronts, TOKS
 // tokens at a time.  ccode: codes chunk-major ([16-byte chunk][candidate], conflict-free operand reads); cslot: slot ids;
 // cpen: minus half the penalty.
-// Candidates whose penalty |code|^2 is odd come first: a score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus
-// one for an odd penalty, so the earliest position that reaches the largest T is the one with the best score (and, slots
-// ascending in each half, the smallest slot), and the scan needs one matrix product instead of two.
+// A score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus one where |code|^2 is odd, so the scan needs one
+// matrix product instead of two, for T.  Who wins among the candidates of the largest T (odd |code|^2 first, then the
+// smallest slot):
+//   ORDERED (a range of the cache): those with odd |code|^2 come first, slots ascending in each half, so the earliest
+//   position is the winner;
+//   otherwise (a candidate list in any order, without repeats): positions mean nothing, cslot carries the parity in its top
+//   bit (set for even), and the scan notes whether a second group of 32 reaches the largest T; the few tokens for which
+//   one does look through all candidates.
 constexpr int WIN_THREADS = 512;
-template <int R, int TOKS>
+constexpr unsigned SLOT_EVEN = 0x80000000u;
+template <int R, int TOKS, bool ORDERED>
 struct WindowScan {
     static_assert(TOKS == 64 || TOKS == 256, "one set of token groups, or two");
     static constexpr int KS = R / 32, NCH = R / 16;
@@ -210,14 +216,21 @@ struct WindowScan {
 #pragma unroll
             for (int m = 0; m < 4; ++m) nn = dot4_i8((unsigned)rw[c][m], (unsigned)rw[c][m], nn);
         }
-        cslot[p] = slot;
+        cslot[p] = ORDERED || slot < 0 ? slot : (int)((unsigned)slot | (metric == 0 && (nn & 1) ? 0u : SLOT_EVEN));
         cpen[p] = slot < 0 ? MATCH_NONE : metric == 0 ? -((nn + 1) >> 1) : 0;   // minus half the penalty, rounded up
+    }
+    // Of two (score, twice the group + tie) words the one with the better score; equal scores of two groups are a tie.
+    __device__ static __forceinline__ u64 better(u64 a, u64 b) {
+        const unsigned sa = (unsigned)(a >> 32), sb = (unsigned)(b >> 32);
+        const u64 tied = a | (u64)(((unsigned)a >> 1) != ((unsigned)b >> 1) ? 1u : (unsigned)b & 1u);
+        return sa > sb ? a : sb > sa ? b : tied;
     }
     // Running arg-max of a lane over the 16 scores per group its accumulators hold: only the best score and the group it
     // came from are kept in the loop (a maximum tree and one select per group; a later group replaces the best only on a
     // strictly higher score, so the earliest group wins among equals); which of the group's rows it was is looked up once,
     // after the loop, by recomputing that group's scores for the token.
-    // Leaves (best score, earliest group) of this wavefront's share in partbest as one word per token, 0: none seen.
+    // Leaves (best score, earliest group) of this wavefront's share in partbest as one word per token, 0: none seen; not
+    // ORDERED: (best score, twice the group, plus one if another group reaches that score).
     __device__ static __forceinline__ void scan(const i32x4 *ccode, const int *cpen, int n_pad, int n_groups, int tq, int ch,
                                                 const i32x4 (&bfrag)[NG][KS], u64 (*partbest)[TOKS]) {
         const int lane = lane_id(), col = lane & 31, g2 = lane >> 5;
@@ -262,13 +275,23 @@ struct WindowScan {
         };
         auto red = [&](const i32x16 (&acc)[HALF], int it, int u0) {
             const int gi = group_of(it);
+            if (!ORDERED && it >= n_it) return;   // uniform: the last group again would look like a second one
 #pragma unroll
             for (int u = 0; u < HALF; ++u) {
-                int mx = max(acc[u][0], bs[u0 + u]);
+                if constexpr (ORDERED) {
+                    int mx = max(acc[u][0], bs[u0 + u]);
 #pragma unroll
-                for (int v = 1; v < 16; ++v) mx = max(mx, acc[u][v]);
-                bg[u0 + u] = mx > bs[u0 + u] ? gi : bg[u0 + u];
-                bs[u0 + u] = mx;
+                    for (int v = 1; v < 16; ++v) mx = max(mx, acc[u][v]);
+                    bg[u0 + u] = mx > bs[u0 + u] ? gi : bg[u0 + u];
+                    bs[u0 + u] = mx;
+                } else {
+                    int mx = acc[u][0];
+#pragma unroll
+                    for (int v = 1; v < 16; ++v) mx = max(mx, acc[u][v]);
+                    const int tied = mx == bs[u0 + u] ? bg[u0 + u] | 1 : bg[u0 + u];
+                    bg[u0 + u] = mx > bs[u0 + u] ? 2 * gi : tied;
+                    bs[u0 + u] = max(mx, bs[u0 + u]);
+                }
             }
         };
         if (n_it > 0) {
@@ -294,10 +317,11 @@ struct WindowScan {
         }
 #pragma unroll
         for (int u = 0; u < NG; ++u) {
-            u64 key = bs[u] > MATCH_VALID ? ((u64)(unsigned)(bs[u] + SCORE_BIAS) << 32) | (u64)(0xFFFFFFFFu - (unsigned)bg[u]) : 0ull;
+            u64 key = bs[u] > MATCH_VALID ? ((u64)(unsigned)(bs[u] + SCORE_BIAS) << 32) | (u64)(ORDERED ? 0xFFFFFFFFu - (unsigned)bg[u] : (unsigned)bg[u]) : 0ull;
             const unsigned lo = shfl_xor((unsigned)key, 32), hi = shfl_xor((unsigned)(key >> 32), 32);
             const u64 other = ((u64)hi << 32) | lo;
-            if (other > key) key = other;
+            if (ORDERED) { if (other > key) key = other; }
+            else key = better(key, other);
             if (g2 == 0) partbest[ch][(tq * NG + u) * 32 + col] = key;
         }
     }
@@ -307,6 +331,7 @@ struct WindowScan {
     __device__ static __forceinline__ bool look_up(const i32x4 *ccode, const int *cpen, int n_pad, const i32x4 (&pc)[NCH],
                                                    bool ok, int t, int sub, const u64 (*partbest)[TOKS], int &T, int &at) {
         constexpr int ROWS = 32 / TPT;
+        static_assert(ORDERED, "position order decides");
         u64 best = partbest[0][t];
 #pragma unroll
         for (int c = 1; c < SPLIT; ++c) {
@@ -334,6 +359,42 @@ struct WindowScan {
 #pragma unroll
         for (int off = 1; off < TPT; off <<= 1) at = min(at, shfl_xor(at, off));
         return seen;
+    }
+    // The same for candidates in any order: best score T of token t and the winner's cslot word among its group (0xFFFFFFFF:
+    // no candidate); tie: another group reaches T too.
+    __device__ static __forceinline__ unsigned find(const i32x4 *ccode, const int *cslot, const int *cpen, int n_pad,
+                                                    const i32x4 (&pc)[NCH], bool ok, int t, int sub,
+                                                    const u64 (*partbest)[TOKS], int &T, bool &tie) {
+        static_assert(!ORDERED, "position order decides");
+        constexpr int ROWS = 32 / TPT;
+        u64 best = partbest[0][t];
+#pragma unroll
+        for (int c = 1; c < SPLIT; ++c) best = better(best, partbest[c][t]);
+        T = (int)(unsigned)(best >> 32) - SCORE_BIAS;
+        const bool seen = best != 0 && ok;
+        tie = seen && ((unsigned)best & 1u);
+        unsigned winner = 0xFFFFFFFFu;
+        if (seen) {
+            const int row0 = (int)((unsigned)best >> 1) * 32 + sub * ROWS;
+#pragma unroll
+            for (int v = 0; v < ROWS; ++v) {
+                const int rw = row0 + ((v + t) & (ROWS - 1));
+                if (score(ccode, cpen, n_pad, pc, rw) == T) winner = min(winner, (unsigned)cslot[rw]);
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < TPT; off <<= 1) winner = min(winner, (unsigned)shfl_xor((int)winner, off));
+        return winner;
+    }
+    __device__ static __forceinline__ int score(const i32x4 *ccode, const int *cpen, int n_pad, const i32x4 (&pc)[NCH], int rw) {
+        int dot = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const i32x4 cc = ccode[c * n_pad + rw];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) dot = dot4_i8((unsigned)cc[m], (unsigned)pc[c][m], dot);
+        }
+        return dot + cpen[rw];
     }
 };
 // Stable partition of up to 4096 ranked candidates, those marked in the bitmap s_odd (one 64-bit word per lane) first.
@@ -374,7 +435,7 @@ __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8
                                                                       const int8_t *__restrict__ cp, int n_new, int metric,
                                                                       int range, int share, int block,
                                                                       u64 *__restrict__ best) {
-    typedef WindowScan<R, TOKS> WS;
+    typedef WindowScan<R, TOKS, true> WS;
     constexpr int KS = WS::KS, NCH = WS::NCH, NG = WS::NG, TPT = WS::TPT;
     extern __shared__ __attribute__((aligned(16))) unsigned char wlds[];
     i32x4 *ccode = (i32x4 *)wlds;                             // [NCH][range]
@@ -536,10 +597,11 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 // staging the window is then paid a quarter as often.  The wide form's prefetched rows and operands do not all fit the
 // registers: with bf16 rows of 128 it spills 100 bytes per lane (r = 32; 268 at r = 64), around the scan, not in its loop.
 //
-// What bounds it: the chain of dependent phases of one workgroup (list, sort and staging, encode, scan, look-up, threshold
-// test).  The window's code rows are gathered straight from the list, before its order is known: they are in flight while
-// the ids are ranked.  Mean per phase at 12 heads x 1560 tokens and candidates (timestamps inside the kernel, us): list,
-// sort and staging 10.4 -> 9.7, scan 1.9 -> 1.4, look-up 2.1 -> 1.3, histogram 2.1 -> 0; launch 26 -> 20.
+// What bounds it: the chain of dependent phases of one workgroup.  Mean per phase at 12 heads x 1560 tokens and candidates
+// (timestamps inside the kernel, us): list 3.5, repeats 0.7, encode 1.7 and staging 1.0 (the code rows are in flight
+// meanwhile), scan 2.0, look-up 1.7, threshold test 2.3.  Staged in slot order (ids ranked through the bitmap, odd norms
+// first), so that position decides ties, list to staging took 8.1 and the encode another 2.1; the scan now pays 0.2 for
+// noting ties and the look-up 0.6 for settling them.  Launch 21 -> 18, chunk of three calls 293 -> 285.
 // The scan was bound by the matrix units (two products per score) and the LDS (a group's codes and penalties, 5 KB, read
 // for 32 tokens): one product, and 64 or 128 tokens per read; 256 tokens x 3600 candidates 18 -> 9 us, launch at
 // 40 heads x 3600 tokens 113 -> 92.
@@ -558,7 +620,7 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     i32x4 *ccode = (i32x4 *)wlds;                       // [NCH][n_pad]
     int *cslot = (int *)(wlds + (size_t)NCH * n_pad * 16);  // [n_pad]
     int *cpen = cslot + n_pad;                          // [n_pad]
-    typedef WindowScan<R, TOKS> WS;
+    typedef WindowScan<R, TOKS, false> WS;
     constexpr int NG = WS::NG, TQ = WS::TQ, SPLIT = WS::SPLIT;
     // partial arg-maxima of the scan; R before it, the verify hand-over and the age histogram after it
     __shared__ __attribute__((aligned(16))) u64 partbest[SPLIT][TOKS];
@@ -580,12 +642,12 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     const int swave = __builtin_amdgcn_readfirstlane(wave);   // uniform: the scan's bookkeeping stays in scalar registers
     const int tq = swave % TQ, ch = swave / TQ;
     const int8_t *ch_code = code + (size_t)h * C * R;
-    // The candidate list is a SET of slots and ties go to the smallest slot, so the window is staged in ascending
-    // slot order without repeats: position order then is slot order, which is all the arg-max below needs.
-    //   1. every thread reads its entries of the list (ids outside [0, L) do not count) and asks for their code rows;
-    //   2. the ids are ranked through a bitmap over the slots, held where the codes will go (several passes when the
-    //      cache is longer than that area): set bits, prefix counts per word, rank = prefix + bits below;
-    //   3. the rows go to their ranks (repeats write the same row to the same place), odd penalties first (WindowScan).
+    // The candidate list is a SET of slots: a repeat counts once (a bitmap over the slots, held where the codes will go, in
+    // several passes when the cache is longer than that area, tells who came first), ids outside [0, L) not at all; ties
+    // go to the smallest slot, which the look-up decides, so the window is staged in the order of the list:
+    //   1. every thread reads its entries of the list and asks for their code rows;
+    //   2. while these are in flight, repeats are struck out and the first block of tokens is encoded;
+    //   3. the rows go to their positions.
     constexpr int CPT = ((int)(WINDOW_LDS_MAX / (R + 8)) + WIN_THREADS - 1) / WIN_THREADS;   // list entries per thread
     // of them, rows in flight while the ids are ranked (registers); the rows beyond are loaded when their ranks are known
     constexpr int PF = R == 32 ? (TOKS >= 256 ? CPT : BF16 ? 4 : 2) : 2;
@@ -593,6 +655,7 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     // per thread now, the operand's pieces from LDS later
     constexpr bool RM_LDS = ENC && (size_t)D * R <= sizeof(partbest) && D * R / 8 <= WIN_THREADS;
     const bool rm_lds = RM_LDS && ((uintptr_t)Rm & 7) == 0;   // uniform
+    __shared__ int n_tied;
     u64 rm_part = 0;
     if (rm_lds && tid < D * R / 8) rm_part = ((const u64 *)Rm)[tid];
     int ce[CPT];
@@ -627,13 +690,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     constexpr bool EARLY = BF16 || TOKS == 64;   // the first block's rows in flight while the window is staged (registers)
     if (EARLY && enc_wave) load_block(t0);
     unsigned *bm = (unsigned *)wlds;             // bitmap of the slots, [words]
-    const int words = R * n_pad / 8;             // half of the code area; the words' prefix counts take the other half
-    unsigned *wpre = bm + words;
+    const int words = R * n_pad / 4;             // the code area
     for (int w = tid; w < min((C + 31) >> 5, words); w += WIN_THREADS) bm[w] = 0u;
-    __shared__ int s_wtot[WIN_THREADS / 64];
-    __shared__ u64 s_odd[WAVE];                  // by rank in slot order: the candidates with an odd penalty
-    static_assert(WINDOW_LDS_MAX / (R + 8) <= 64 * WAVE, "one word of s_odd per lane");
-    if (tid < WAVE) s_odd[tid] = 0ull;
     if (rm_lds && tid < D * R / 8) ((u64 *)partbest)[tid] = rm_part;
 #pragma unroll
     for (int k = 0; k < CPT; ++k)
@@ -647,111 +705,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             if (ce[k] >= 0) v = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
             row[k][c] = v;
         }
-    int pos[CPT];
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) pos[k] = -1;
-    int n_u = 0;   // staged candidates: positions 0 .. n_u-1 (uniform over the workgroup)
-    for (int lo = 0; lo < L; lo += 32 * words) {   // uniform; one pass unless the cache is long for the list
-        const int nw = min((L - lo + 31) >> 5, words);
-        if (lo > 0) {
-            __syncthreads();   // the ranks of the pass before have been read
-            for (int w = tid; w < nw; w += WIN_THREADS) bm[w] = 0u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int o = ce[k] - lo;
-            if (ce[k] >= lo && o < 32 * nw) atomicOr(&bm[o >> 5], 1u << (o & 31));
-        }
-        __syncthreads();
-        // a thread owns a run of consecutive words, an odd number of them (their addresses spread over the banks)
-        const int wpt = ((nw + WIN_THREADS - 1) / WIN_THREADS) | 1;
-        const int w0 = tid * wpt, w1 = min(w0 + wpt, nw);
-        int c = 0;
-        for (int w = w0; w < w1; ++w) c += __popc(bm[w]);
-        int incl = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, WAVE);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) s_wtot[wave] = incl;
-        __syncthreads();
-        int run = n_u + incl - c;
-#pragma unroll
-        for (int ww = 0; ww < WIN_THREADS / 64; ++ww) {
-            const int t = s_wtot[ww];
-            if (ww < wave) run += t;
-            n_u += t;
-        }
-        for (int w = w0; w < w1; ++w) {
-            wpre[w] = (unsigned)run;
-            run += __popc(bm[w]);
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int o = ce[k] - lo;
-            if (ce[k] >= lo && o < 32 * nw) pos[k] = (int)wpre[o >> 5] + __popc(bm[o >> 5] & ((1u << (o & 31)) - 1u));
-        }
-    }
-    const int n_stage = (n_u + 31) & ~31;   // <= n_pad
-    // stable partition by the parity of the penalty (the parity of the number of odd entries)
-    auto row_of = [&](int k, i32x4 (&rw)[NCH]) {   // list entries whose rows were not prefetched
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) rw[c] = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
-    };
-    if (metric == 0) {   // uniform
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            if (k >= PF && n_cand <= k * WIN_THREADS) break;   // uniform
-            if (pos[k] < 0) continue;
-            bool odd;
-            if (k < PF) {
-                odd = WS::odd_penalty(row[k < PF ? k : 0]);
-            } else {
-                i32x4 rw[NCH];
-                row_of(k, rw);
-                odd = WS::odd_penalty(rw);
-            }
-            if (odd) atomicOr(&s_odd[pos[k] >> 6], 1ull << (pos[k] & 63));
-        }
-    }
-    __syncthreads();                        // the bitmap is dead: its memory takes the codes
-    const OddFirst odd_first(s_odd);
-    const int n_odd = odd_first.n_odd;
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        if (n_cand <= k * WIN_THREADS) break;   // uniform
-        const int p = odd_first.place(max(pos[k], 0));
-        if (pos[k] >= 0) pos[k] = p;
-    }
-    auto stage_row = [&](int p, int slot, const i32x4 (&rw)[NCH]) { WS::stage(ccode, cslot, cpen, n_pad, metric, p, slot, rw); };
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        if (k >= PF && n_cand <= k * WIN_THREADS) break;   // uniform
-        if (pos[k] < 0) continue;
-        if (k < PF) {
-            stage_row(pos[k], ce[k], row[k < PF ? k : 0]);
-        } else {
-            i32x4 rw[NCH];
-            row_of(k, rw);
-            stage_row(pos[k], ce[k], rw);
-        }
-    }
-    if (tid < n_stage - n_u) {   // the ragged end of the last group of 32
-        const i32x4 none[NCH] = {};
-        stage_row(n_u + tid, -1, none);
-    }
-    if (enc_wave) {
-        if (rm_lds) cm.load((const int8_t *)partbest, lane);   // stored before the barriers above
-        else cm.load(Rm, lane);
-    }
-    for (int base = t0; base < t1; base += TOKS) {
-    const int lim = min(base + TOKS, t1);   // this block's tokens: [base, lim)
-    if (base != t0) __syncthreads();   // the previous block's probe codes and arg-maxima have been read
-    if (enc_wave) {
-        if (!EARLY || base != t0) load_block(base);
+    // encodes the tokens [base, lim) of a block from the rows that load_block asked for
+    auto encode_block = [&](int base, int lim) {
 #pragma unroll
         for (int er = 0; er < EROUNDS; ++er) {
             const int etok = base + 16 * (wave + 8 * er) + (lane & 15);
@@ -760,6 +715,51 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             const auto w = cm.code_words(xq, shift);
             cm.store(pcode + (16 * (wave + 8 * er) + (lane & 15)) * R, w, lane);
             if (etok < lim) cm.store(ck + ((size_t)h * n_new + etok) * R, w, lane);
+        }
+    };
+    for (int lo = 0; lo < L; lo += 32 * words) {   // uniform; one pass unless the cache is long for the list
+        const int nw = min((L - lo + 31) >> 5, words);
+        if (lo > 0) {
+            __syncthreads();   // everyone is done with the pass before
+            for (int w = tid; w < nw; w += WIN_THREADS) bm[w] = 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            if (n_cand <= k * WIN_THREADS) break;   // uniform
+            const int o = ce[k] - lo;
+            if (ce[k] >= lo && o < 32 * nw && ((atomicOr(&bm[o >> 5], 1u << (o & 31)) >> (o & 31)) & 1u)) ce[k] = -1;   // below every later lo
+        }
+    }
+    if (L <= 0) __syncthreads();   // R has been stored
+    if (enc_wave) {
+        if (rm_lds) cm.load((const int8_t *)partbest, lane);
+        else cm.load(Rm, lane);
+        if (!EARLY) load_block(t0);
+        encode_block(t0, min(t0 + TOKS, t1));
+    }
+    __syncthreads();   // the bitmap is dead: its memory takes the codes
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        if (n_cand <= k * WIN_THREADS) break;   // uniform
+        const int p = k * WIN_THREADS + tid;
+        if (p >= n_pad) continue;
+        i32x4 rw[NCH];
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            rw[c] = i32x4{0, 0, 0, 0};
+            if (k < PF) rw[c] = row[k < PF ? k : 0][c];
+            else if (ce[k] >= 0) rw[c] = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
+        }
+        WS::stage(ccode, cslot, cpen, n_pad, metric, p, ce[k], rw);
+    }
+    for (int base = t0; base < t1; base += TOKS) {
+    const int lim = min(base + TOKS, t1);   // this block's tokens: [base, lim)
+    if (base != t0) {
+        __syncthreads();   // the previous block's probe codes and arg-maxima have been read
+        if (enc_wave) {
+            load_block(base);
+            encode_block(base, lim);
         }
     }
     __syncthreads();
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
                                : *(const i32x4 *)(cp + ((size_t)h * n_new + min(base + t, n_new - 1)) * R + ks * 32 + 16 * g2);
         }
     // a wavefront whose tokens all lie beyond the block's end scans nothing (uniform over the wavefront)
-    WS::scan(ccode, cpen, n_pad, base + tq * NG * 32 < lim ? n_stage / 32 : 0, tq, ch, bfrag, partbest);
+    WS::scan(ccode, cpen, n_pad, base + tq * NG * 32 < lim ? n_pad / 32 : 0, tq, ch, bfrag, partbest);
     __syncthreads();
     {
         constexpr int TPT = WS::TPT;
@@ -783,11 +783,40 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + min(tok, n_new - 1)) * R;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
-        int T, at;
-        const bool seen = WS::look_up(ccode, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, at);
+        int T;
+        bool tie;
+        unsigned winner = WS::find(ccode, cslot, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, tie);
+        // A tied token's threads would go through all candidates for longer than the whole scan takes, and one token in a
+        // thousand is enough for the launch to wait: the workgroup does it together.
+        if (__syncthreads_or(tie)) {   // the scan's words are done with: (T, winner) per token, then the list of tied ones
+            static_assert(SPLIT >= 3, "three rows of words");
+            unsigned *best_of = (unsigned *)partbest[1], *tied = (unsigned *)partbest[2];
+            if (tid == 0) n_tied = 0;
+            __syncthreads();
+            if (tie && sub == 0) {
+                best_of[2 * t] = winner;
+                best_of[2 * t + 1] = (unsigned)T;
+                tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
+            }
+            __syncthreads();
+            const int n = n_tied;
+            for (int q = 0; q < n; ++q) {
+                const int tt = (int)tied[q];
+                const int8_t *trow = ENC ? pcode + tt * R : cp + ((size_t)h * n_new + min(base + tt, n_new - 1)) * R;
+                i32x4 tc[NCH];
+#pragma unroll
+                for (int c = 0; c < NCH; ++c) tc[c] = *(const i32x4 *)(trow + 16 * c);
+                for (int rw = tid; rw < n_pad; rw += WIN_THREADS)
+                    if (WS::score(ccode, cpen, n_pad, tc, rw) == (int)best_of[2 * tt + 1]) atomicMin(&best_of[2 * tt], (unsigned)cslot[rw]);
+            }
+            __syncthreads();
+            if (tie) winner = best_of[2 * t];
+            __syncthreads();   // the words are handed on below
+        }
         if (sub == 0) {
-            const int j = seen ? cslot[at] : -1;   // position in the window -> slot
-            const int S = !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T;
+            const bool seen = winner != 0xFFFFFFFFu;
+            const int j = seen ? (int)(winner & ~SLOT_EVEN) : -1;
+            const int S = !seen ? 0 : metric == 0 ? 2 * T + (winner & SLOT_EVEN ? 0 : 1) : T;
             if (tok < lim) {
                 if (!VERIFY && seen) {
                     win[(size_t)h * C + j] = 0;

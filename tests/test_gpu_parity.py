@@ -991,6 +991,37 @@ def test_tempcache_plan_that_gives_up_leaves_the_cache_untouched_and_says_so(pat
         assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
 
 
+@pytest.mark.parametrize("H,T,C,n_cand,metric,wide", [(2, 100, 3000, 1600, 0, False), (2, 65, 500, 33, 1, False),
+                                                      (70, 700, 800, 2400, 0, True)])
+def test_tempcache_candidates_that_all_tie_go_to_the_smallest_slot(H, T, C, n_cand, metric, wide):
+    # keys of two values only: every token ties with half of a list that comes in any order, with repeats and ids that
+    # do not count, so no token's best group is the only one
+    rng = np.random.default_rng(C + n_cand)
+    d, r, dtype = 128, 32, "bf16"
+    codec = make_codec(0, 9, d, r)
+    two = rng.standard_normal((2, d)).astype(np.float32)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = to_storage(two[rng.integers(0, 2, size=(H, C))], dtype)
+    ref.V[:] = to_storage(rng.standard_normal((H, C, d)).astype(np.float32), dtype)
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(0, 9, size=(H, C))
+    ref.len[:] = C - 9
+    gpu = dev_cache(ref)
+    cand = rng.integers(-2, C, size=(H, n_cand)).astype(np.int32)
+    K_new = to_storage(two[rng.integers(0, 2, size=(H, T))], dtype)
+    V_new = to_storage(rng.standard_normal((H, T, d)).astype(np.float32), dtype)
+    ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
+    args = dict(tau2_q16=TAU2(0.9), frame_id=9, metric=metric)
+    expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+    got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws,
+                                ws_persistent=True, **args)
+    sync()
+    for a, b in zip(got, expect):
+        assert np.array_equal(to_host(a), b)
+    assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 # (dtype, d, H, T, C, free slots, stamps from / to, frame id, what else): edges of the age histogram's slices (8192 slots), of
 # the list of unmerged tokens (512 tokens per round, 2048 and 8192 in all), of the cache (no eviction, some, all and too
 # few evictable slots), of the histogram (a stamp in the future, a threshold in or beyond the last bin, stamps that wrap)
