@@ -218,9 +218,8 @@ __global__ __launch_bounds__(256) void bucket_topk_kernel(const int32_t *__restr
     const int b = blockIdx.x, h = blockIdx.y;
     const int n = min((min(len[h], C) + BK - 1) / BK, n_kb_cap);
     const int32_t *row = score + ((size_t)h * n_qb + b) * n_kb_cap;
-    const int n_cand = count_candidates(row, n, n_sink, n_local, 1);
-    topk_row(row, n, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, keys, n_sink, n_local,
-             n_cand);
+    __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
+    topk_row(row, n, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, keys, scratch, n_sink, n_local, 1);
 }
 
 struct BucketWs {

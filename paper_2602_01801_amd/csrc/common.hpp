@@ -87,6 +87,27 @@ __device__ __forceinline__ int dot4_i8(unsigned a, unsigned b, int acc) {
     return __builtin_amdgcn_sdot4((int)a, (int)b, acc, false);
 }
 
+// Inclusive prefix over a wavefront's lanes, on the vector ALU (six shuffles by way of the LDS queue took 0.3 us).
+__device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8: prefix of 16 lanes
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast 15: rows 1 and 3 add the row below
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31: the upper half adds the lower
+    return v;
+}
+// Maximum over a wavefront's lanes, in its last lane.
+__device__ __forceinline__ unsigned wave_max_last(unsigned v) {
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));
+    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));
+    return v;
+}
+
 // One-time set-up per device (kernel attributes, symbol addresses), safe to reach from several host threads: run(f)
 // calls f once per device ordinal, with that device current, and remembers a success.  It is the only process-wide data
 // the library keeps, and it never influences a result.

@@ -2133,16 +2133,6 @@ static size_t settle_lds_bytes(int C, int n_new) {
     return (size_t)((C + 63) / 64) * 8 + (size_t)((n_new + 7) & ~7) * 2 + SETTLE_SLICE * 2;
 }
 
-// Inclusive prefix over a wavefront's lanes, on the vector ALU (six shuffles by way of the LDS queue took 0.3 us).
-__device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8: prefix of 16 lanes
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast 15: rows 1 and 3 add the row below
-    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31: the upper half adds the lower
-    return v;
-}
 struct Pair {
     unsigned a, b;
 };

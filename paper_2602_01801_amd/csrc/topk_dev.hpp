@@ -10,27 +10,234 @@ namespace fastar {
 constexpr int TOPK_LDS_CAP = 8192; // row entries cached in LDS by the callers of topk_row
 constexpr int TOPK_KPT = 16;       // rows of up to 256 * TOPK_KPT entries are selected from registers
 
+constexpr int TOPK_DIGIT = 9;                        // bits per pass over the keys
+constexpr int TOPK_BINS = 1 << TOPK_DIGIT;
+constexpr int TOPK_SCRATCH = 2 * TOPK_BINS + 20;     // two histograms, a few words per wavefront
+
+// Rows of up to 4096 entries.  Every thread holds a run of KPT consecutive entries in registers (key + 1, 0: no entry).
+// What bounds it is the chain of barriers, and of same-address additions where the keys' leading bits are alike.  So the
+// row's range comes first (one barrier), the digits are those of its span, every wavefront reads the threshold digit off the
+// histogram itself (one barrier per pass), and once the threshold's bin holds at most 64 entries, as a rule after the
+// first pass, every wavefront ranks those (one barrier); one more for the positions.   Selection of 64 out of 512 / 2048 scores 4.9 / 9.5 -> 3.0 / 5.9 us (before: three fixed
+// digits with three barriers each and a compaction with three per 256 entries; 23 rounds of counting, a barrier each).
+// Digits of ten bits: no faster, and their 16 bins per lane cost registers.
+template <int KPT, typename KeyOf>
+__device__ __forceinline__ void topk_from_registers(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
+                                                    int32_t *__restrict__ nsel_out, unsigned *keys, int forced,
+                                                    unsigned cand_key, KeyOf &&key_of, unsigned *scratch) {
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    unsigned *hist = scratch, *wsum = scratch + 2 * TOPK_BINS;   // wsum: [4] max, [4] ~min, [4] candidates, [4] counts, list length
+    constexpr unsigned FORCED = (1u << 22) + 1u;                 // key + 1 of a forced entry
+    int kpt = (n + 255) / 256;
+    if (kpt < KPT) kpt |= 1;   // an odd stride: the threads' runs start on different banks
+    unsigned my[KPT];
+    if (keys != nullptr) {   // row in global memory: coalesced loads, all in flight at once, staged through LDS
+        int32_t v[KPT];
+#pragma unroll
+        for (int e = 0; e < KPT; ++e) {
+            const int t = e * 256 + tid;
+            v[e] = t < n ? row[t] : 0;
+        }
+        for (int t = tid; t < 2 * TOPK_BINS; t += 256) hist[t] = 0u;
+#pragma unroll
+        for (int e = 0; e < KPT; ++e) {
+            const int t = e * 256 + tid;
+            if (t < n) keys[t] = key_of(t, v[e]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < KPT; ++e) {
+            const int i = tid * kpt + e;
+            my[e] = (e < kpt && i < n) ? keys[i] + 1u : 0u;
+        }
+    } else {
+        for (int t = tid; t < 2 * TOPK_BINS; t += 256) hist[t] = 0u;
+#pragma unroll
+        for (int e = 0; e < KPT; ++e) {
+            const int i = tid * kpt + e;
+            my[e] = (e < kpt && i < n) ? key_of(i, row[i]) + 1u : 0u;
+        }
+    }
+    unsigned hi = 0u, nlo = 0u, n_cand = 0u;   // largest key + 1 and the complement of the smallest, forced entries aside; candidates
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+        if (e >= kpt) break;
+        const bool in = my[e] != 0u && my[e] != FORCED;
+        hi = max(hi, in ? my[e] : 0u);
+        nlo = max(nlo, in ? ~my[e] : 0u);
+        n_cand += (unsigned)__popcll(__ballot(my[e] > cand_key));
+    }
+    hi = wave_max_last(hi);
+    nlo = wave_max_last(nlo);
+    if (lane == 63) {
+        wsum[wave] = hi;
+        wsum[4 + wave] = nlo;
+        wsum[8 + wave] = n_cand;
+    }
+    if (tid == 0) wsum[16] = 0u;
+    __syncthreads();   // also: the histograms are clear
+    const int k = min(n_sel, (int)(wsum[8] + wsum[9] + wsum[10] + wsum[11]));
+    if (tid == 0) *nsel_out = k;
+    for (int t = k + tid; t < n_sel; t += 256) out[t] = -1;
+    if (k == 0) return;   // uniform
+    unsigned T, need;   // threshold key + 1 and how many of the entries equal to it belong to the selection
+    if (forced >= k) {  // uniform
+        T = FORCED;
+        need = (unsigned)k;
+    } else {
+        hi = max(max(wsum[0], wsum[1]), max(wsum[2], wsum[3]));
+        const unsigned lo = ~max(max(wsum[4], wsum[5]), max(wsum[6], wsum[7]));
+        need = (unsigned)(k - forced);
+        int shift = hi == lo ? 0 : 32 - __clz(hi - lo);   // bits of the span still undecided
+        unsigned prefix = 0;
+        bool whole = false;
+        for (int pass = 0; shift > 0 && !whole; ++pass) {   // uniform: at most three passes
+            const int width = min(TOPK_DIGIT, shift);
+            unsigned *h = hist + (pass & 1) * TOPK_BINS;
+            if (pass == 2) {   // every wavefront is past the pass before, and so past the first one's counts
+                for (int t = tid; t < TOPK_BINS; t += 256) h[t] = 0u;
+                __syncthreads();
+            }
+#pragma unroll
+            for (int e = 0; e < KPT; ++e) {
+                if (e >= kpt) break;   // uniform, here and below
+                const unsigned rel = my[e] - lo;
+                if (my[e] != 0u && my[e] != FORCED && (rel >> shift) == prefix)
+                    atomicAdd(&h[(rel >> (shift - width)) & ((1u << width) - 1u)], 1u);
+            }
+            __syncthreads();
+            // lane l owns the bins 511 - 8 l .. 504 - 8 l: where does the running count from the top reach `need`?
+            constexpr int BPL = TOPK_BINS / 64;
+            unsigned c[BPL], sum = 0;   // descending
+#pragma unroll
+            for (int q = 0; q < BPL / 4; ++q) {
+                const u32x4 w = ((const u32x4 *)h)[(BPL / 4) * (63 - lane) + BPL / 4 - 1 - q];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    c[4 * q + e] = w[3 - e];
+                    sum += w[3 - e];
+                }
+            }
+            const unsigned incl = wave_incl_scan(sum);
+            unsigned before = incl - sum, bin = 0, left = 0, count = 0;
+            const bool mine = before < need && need <= incl;
+#pragma unroll
+            for (int q = 0; q < BPL; ++q) {
+                const bool here = mine && before < need && need <= before + c[q];
+                bin = here ? (unsigned)(TOPK_BINS - 1 - BPL * lane - q) : bin;
+                left = here ? need - before : left;
+                count = here ? c[q] : count;
+                before += c[q];
+            }
+            const int src = __ffsll((unsigned long long)__ballot(mine)) - 1;   // exactly one lane
+            bin = (unsigned)__builtin_amdgcn_readlane((int)bin, src);
+            need = (unsigned)__builtin_amdgcn_readlane((int)left, src);
+            count = (unsigned)__builtin_amdgcn_readlane((int)count, src);
+            whole = need == count;   // all of the bin: no finer threshold needed
+            shift -= width;
+            prefix = (prefix << width) | bin;
+            if (!whole && shift > 0 && count <= 64u) {   // uniform: rank the bin's entries
+                unsigned *list = hist + ((pass & 1) ^ 1) * TOPK_BINS;   // not in use, or no longer
+#pragma unroll
+                for (int e = 0; e < KPT; ++e) {
+                    if (e >= kpt) break;
+                    if (my[e] != 0u && my[e] != FORCED && ((my[e] - lo) >> shift) == prefix) list[atomicAdd(&wsum[16], 1u)] = my[e];
+                }
+                if (tid < 3) list[count + tid] = 0u;   // the last four are read together
+                __syncthreads();
+                const unsigned mine = lane < (int)count ? list[lane] : 0u;
+                unsigned gt = 0;   // entries above this lane's
+                for (unsigned j = 0; j < count; j += 4) {
+                    const u32x4 other = *(const u32x4 *)(list + j);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) gt += other[q] > mine ? 1u : 0u;
+                }
+                // the smallest entry with fewer than `need` above it is the threshold
+                const unsigned most = (unsigned)__builtin_amdgcn_readlane((int)wave_max_last(gt < need ? gt + 1u : 0u), 63) - 1u;
+                const int at = __ffsll((unsigned long long)__ballot(gt == most && mine != 0u)) - 1;
+                need -= most;
+                prefix = (unsigned)__builtin_amdgcn_readlane((int)mine, at) - lo;
+                shift = 0;
+            }
+        }
+        T = lo + (prefix << shift);
+        if (whole) {   // everything from the bin's lower edge on
+            T -= 1u;
+            need = 0u;
+        }
+    }
+    unsigned n_gt = 0, n_eq = 0;
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+        if (e >= kpt) break;
+        n_gt += my[e] > T ? 1u : 0u;
+        n_eq += my[e] == T ? 1u : 0u;
+    }
+    const unsigned packed = (n_gt << 16) | n_eq;   // both totals stay below 4097
+    const unsigned incl = wave_incl_scan(packed);
+    if (lane == 63) wsum[12 + wave] = incl;
+    __syncthreads();
+    unsigned excl = incl - packed;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+        if (w < wave) excl += wsum[12 + w];
+    unsigned eq_rank = excl & 0xFFFFu;
+    unsigned pos = (excl >> 16) + min(eq_rank, need);
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+        if (e >= kpt) break;
+        const bool take = my[e] > T || (my[e] != 0u && my[e] == T && eq_rank < need);
+        if (my[e] == T) eq_rank += 1;
+        if (take) out[pos++] = tid * kpt + e;
+    }
+}
+
+// Entries of a row that are candidates: score >= cand_min, or forced (first n_sink / last n_local).  All 256 threads.
+__device__ __forceinline__ int count_candidates(const int32_t *row, int n, int n_sink, int n_local, int cand_min) {
+    __shared__ int cand_w[4];
+    int c = 0;
+    for (int base = 0; base < n; base += 256) {   // uniform trip count
+        const int t = base + threadIdx.x;
+        const bool is_cand = t < n && (row[t] >= cand_min || t < n_sink || t >= n - n_local);
+        c += __popcll(__ballot(is_cand));
+    }
+    if (lane_id() == 0) cand_w[threadIdx.x >> 6] = c;
+    __syncthreads();
+    return cand_w[0] + cand_w[1] + cand_w[2] + cand_w[3];
+}
+
 // ---- exact top-k per row ----------------------------------------------------------------------------
 // A row of n scores (row may point to global memory or to LDS).  The k = min(n_sel, n) largest are selected
 // (ties: lowest index) and their indices written ascending to out[0..k), the rest of out[0..n_sel) padded with
 // -1; *nsel_out = k.  Called by all 256 threads of a workgroup.
 // keys: LDS staging for up to TOPK_LDS_CAP entries of a row in global memory, or nullptr (row read in place).
-// k_cap: at most that many are selected (callers that admit only some entries as candidates pass their number; the
-// others must score below every candidate).
+// cand_min > INT_MIN: only entries that score at least that much (or are forced) may be selected, and k is at most their
+// number.
 // n_sink / n_local: the first / last entries of the row are forced (sink and local key blocks of AnnSA): they rank
 // ahead of every real score, so they are always among the selected ones while n_sink + n_local <= n_sel.
+// scratch: TOPK_SCRATCH words of LDS, 16-byte aligned (the caller's own use of them must be over on entry, behind a barrier).
 __device__ __forceinline__ void topk_row(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
-                                         int32_t *__restrict__ nsel_out, unsigned *keys, int n_sink = 0, int n_local = 0,
-                                         int k_cap = INT_MAX) {
+                                         int32_t *__restrict__ nsel_out, unsigned *keys, unsigned *scratch, int n_sink = 0,
+                                         int n_local = 0, int cand_min = INT_MIN) {
     // Scores are sums of at most 64 products of 8-bit codes (or counts of equal hash bits): |score| < 2^21, and
     // anything below (the INT_MIN of a block without a live key) is clamped there, so an order-preserving key has
     // 22 bits: three passes over 8-bit digits (the first has 6 significant bits) select exactly.
-    __shared__ unsigned hist[256];
-    __shared__ unsigned sh_bin, sh_remaining;
-    __shared__ unsigned wtot_a[4], wtot_b[4];
+    auto to_key0 = [](int32_t sc) -> unsigned { return (unsigned)(max(sc, -(1 << 21)) + (1 << 21)); };
+    // key of entry t with score sc: real scores stay below 2^22, forced entries sit exactly there
+    auto key_of = [&](int t, int32_t sc) -> unsigned {
+        return (t < n_sink || t >= n - n_local) ? (1u << 22) : to_key0(sc);
+    };
+    if (n <= TOPK_KPT * 256) {
+        // Forced entries rank ahead of all others: the k - forced largest of the others are to be found.
+        const int first = min(n, max(n_sink, 0)), forced = first + min(max(n_local, 0), n - first);
+        const unsigned cand_key = cand_min > INT_MIN ? to_key0(cand_min) : 0u;   // candidates: key + 1 > cand_key
+        if (n <= 4 * 256) topk_from_registers<5>(row, n, n_sel, out, nsel_out, keys, forced, cand_key, key_of, scratch);
+        else topk_from_registers<TOPK_KPT>(row, n, n_sel, out, nsel_out, keys, forced, cand_key, key_of, scratch);
+        return;
+    }
     const int tid = threadIdx.x;
     const int lane = lane_id(), wave = tid >> 6;
-    const int k = min(min(n_sel, n), k_cap);
+    const int k = min(min(n_sel, n), cand_min > INT_MIN ? count_candidates(row, n, n_sink, n_local, cand_min) : n);
     if (tid == 0) *nsel_out = k;
     for (int t = k + tid; t < n_sel; t += 256) out[t] = -1;
     if (k == 0) return;
@@ -38,90 +245,9 @@ __device__ __forceinline__ void topk_row(const int32_t *row, int n, int n_sel, i
         for (int t = tid; t < n; t += 256) out[t] = t;
         return;
     }
-    auto to_key0 = [](int32_t sc) -> unsigned { return (unsigned)(max(sc, -(1 << 21)) + (1 << 21)); };
-    // key of entry t with score sc: real scores stay below 2^22, forced entries sit exactly there
-    auto key_of = [&](int t, int32_t sc) -> unsigned {
-        return (t < n_sink || t >= n - n_local) ? (1u << 22) : to_key0(sc);
-    };
-    if (n > 1024 && n <= TOPK_KPT * 256) {
-        // Rows of 1025 to 4096 scores (shorter ones are done sooner by the three radix passes below, which take a
-        // barrier per 256 entries in their compaction; longer ones do not fit the registers): each thread owns a run of consecutive entries and keeps
-        // their keys in registers (key + 1, so that 0 stands for "no entry").  The k-th largest key is built bit by
-        // bit (23 rounds of "how many keys reach this value": one compare per key, the wavefront's count through
-        // scalar bit counts of the compare masks, one barrier per round), then one block scan of the per-thread
-        // (greater, equal) counts places every selected index: 26 barriers in all, no atomics.
-        const int kpt = (n + 255) / 256;
-        unsigned my[TOPK_KPT];
-        if (keys != nullptr) {   // row in global memory: coalesced loads, all in flight at once, staged through LDS
-            int32_t v[TOPK_KPT];
-#pragma unroll
-            for (int e = 0; e < TOPK_KPT; ++e) {
-                const int t = e * 256 + tid;
-                v[e] = t < n ? row[t] : 0;
-            }
-#pragma unroll
-            for (int e = 0; e < TOPK_KPT; ++e) {
-                const int t = e * 256 + tid;
-                if (t < n) keys[t] = key_of(t, v[e]);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < TOPK_KPT; ++e) {
-                const int i = tid * kpt + e;
-                my[e] = (e < kpt && i < n) ? keys[i] + 1u : 0u;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < TOPK_KPT; ++e) {
-                const int i = tid * kpt + e;
-                my[e] = (e < kpt && i < n) ? key_of(i, row[i]) + 1u : 0u;
-            }
-        }
-        __shared__ unsigned cnt_w[2][4];
-        auto count_ge = [&](unsigned cand, int buf) -> unsigned {   // entries with key + 1 >= cand, over the workgroup
-            unsigned c = 0;
-#pragma unroll
-            for (int e = 0; e < TOPK_KPT; ++e) c += (unsigned)__popcll(__ballot(my[e] >= cand));
-            if (lane == 0) cnt_w[buf][wave] = c;
-            __syncthreads();
-            return cnt_w[buf][0] + cnt_w[buf][1] + cnt_w[buf][2] + cnt_w[buf][3];
-        };
-        unsigned T = 0;
-        int round = 0;
-        for (int bit = 22; bit >= 0; --bit, ++round) {
-            const unsigned cand = T | (1u << bit);
-            if (count_ge(cand, round & 1) >= (unsigned)k) T = cand;
-        }
-        const unsigned need = (unsigned)k - count_ge(T + 1u, round & 1);   // ties at T that belong to the selection
-        unsigned n_gt = 0, n_eq = 0;
-#pragma unroll
-        for (int e = 0; e < TOPK_KPT; ++e) {
-            n_gt += my[e] > T ? 1u : 0u;
-            n_eq += my[e] == T ? 1u : 0u;
-        }
-        const unsigned packed = (n_gt << 16) | n_eq;   // both totals stay below 4097
-        unsigned incl = packed;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const unsigned o = __shfl_up(incl, off, WAVE);
-            if (lane >= off) incl += o;
-        }
-        if (lane == 63) wtot_a[wave] = incl;
-        __syncthreads();
-        unsigned excl = incl - packed;
-#pragma unroll
-        for (int w = 0; w < 4; ++w)
-            if (w < wave) excl += wtot_a[w];
-        unsigned eq_rank = excl & 0xFFFFu;
-        unsigned pos = (excl >> 16) + min(eq_rank, need);
-#pragma unroll
-        for (int e = 0; e < TOPK_KPT; ++e) {
-            const bool take = my[e] > T || (my[e] == T && eq_rank < need);
-            if (my[e] == T) eq_rank += 1;
-            if (take) out[pos++] = tid * kpt + e;
-        }
-        return;
-    }
+    // Longer rows: three digits of eight bits, the row read again for each.
+    unsigned *hist = scratch, *wtot_a = scratch + 256, *wtot_b = scratch + 260;
+    unsigned &sh_bin = scratch[264], &sh_remaining = scratch[265];
     const bool cached = keys != nullptr && n <= TOPK_LDS_CAP;
     if (cached) {
         for (int t0 = 0; t0 < n; t0 += 4 * 256) {   // four loads in flight per thread
@@ -236,20 +362,6 @@ __device__ __forceinline__ void topk_row(const int32_t *row, int n, int n_sel, i
         out_before += take_total;
         __syncthreads();  // wtot_a / wtot_b are rewritten by the next chunk
     }
-}
-
-// Entries of a row that are candidates: score >= cand_min, or forced (first n_sink / last n_local).  All 256 threads.
-__device__ __forceinline__ int count_candidates(const int32_t *row, int n, int n_sink, int n_local, int cand_min) {
-    __shared__ int cand_w[4];
-    int c = 0;
-    for (int base = 0; base < n; base += 256) {   // uniform trip count
-        const int t = base + threadIdx.x;
-        const bool is_cand = t < n && (row[t] >= cand_min || t < n_sink || t >= n - n_local);
-        c += __popcll(__ballot(is_cand));
-    }
-    if (lane_id() == 0) cand_w[threadIdx.x >> 6] = c;
-    __syncthreads();
-    return cand_w[0] + cand_w[1] + cand_w[2] + cand_w[3];
 }
 
 }  // namespace fastar

@@ -107,6 +107,36 @@ def test_ann_select_self_with_forced_sink_and_local_blocks(H, n_q, C, lens, n_se
         fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), 128, 4, 64, 4, n_sink=3, n_local=2)
 
 
+# rows at the edges of the top-k's register forms (256 entries per round, 1024, 4096), selections from one entry to all
+@pytest.mark.parametrize("n", [2, 33, 256, 257, 769, 1024, 1025, 3840, 3841, 4096, 4097])
+@pytest.mark.parametrize("scores", ["spread", "narrow", "equal", "two_values", "outlier"])
+def test_topk_of_rows_of_every_form_and_distribution(n, scores):
+    # the range's digits: scores that span up to 2^20, all alike, in two lumps, in one lump below a single large one
+    # (the first pass then leaves most of the row in one bin)
+    rng = np.random.default_rng(n)
+    r, BQ = 32, 64
+    pc = rand_codes(rng, -127, 127, 1, n, r) if scores == "spread" else rand_codes(rng, -2, 2, 1, n, r)
+    qc = rand_codes(rng, -127, 127, 1, 150, r) if scores == "spread" else rand_codes(rng, -3, 3, 1, 150, r)
+    if scores == "equal":
+        pc[:] = pc[:, :1]
+    elif scores == "two_values":
+        pc[:] = pc[:, rng.integers(0, 2, size=n)]
+    elif scores == "outlier":
+        pc[0, n // 2] = 127
+        qc[:] = np.abs(qc) + 60
+    length = np.array([32 * n - 5], np.int32)
+    kc = np.repeat(pc, 32, axis=1)[:, : 32 * n]
+    for n_sel in sorted({1, max(1, n // 10), max(1, n // 2), n - 1, n, n + 3}):
+        ref_sel, ref_nsel = oracle.ann_select_cross(qc, pc, BQ, n_sel)
+        sel, nsel = fa.ann_select_cross(to_dev(qc), to_dev(pc), BQ, n_sel)
+        assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel), n_sel
+        if n_sel in (max(1, n // 10), n):   # the rows of key blocks, read from memory
+            for forced in ((0, 0), (n_sel - n_sel // 2, n_sel // 2)):
+                ref_sel, ref_nsel = oracle.ann_select_self(qc, kc, length, BQ, 2, 32, n_sel, *forced)
+                sel, nsel = fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), BQ, 2, 32, n_sel, n_sink=forced[0], n_local=forced[1])
+                assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel), (n_sel, forced)
+
+
 @pytest.mark.parametrize("H,n_q,n_p,r,BQ,n_sel,span", [
     (2, 256, 64, 32, 128, 16, 60), (2, 4680, 512, 32, 128, 64, 50), (1, 300, 2048, 32, 128, 64, 4),
     (2, 100, 97, 64, 64, 10, 30), (1, 50, 20, 32, 128, 64, 30),
