@@ -48,79 +48,94 @@ __device__ __forceinline__ unsigned pack_fp8x4(float a, float b, float c, float 
 __device__ __forceinline__ float clamp_f8(float x) { return fminf(fmaxf(x, -F8_MAX), F8_MAX); }
 
 // ---- the 8-bit copy of the cache ------------------------------------------------------------------------------
-// One workgroup per (block of 64 slots, head).  A block that holds no live slot stamped >= stamp_lo is left alone;
-// otherwise it is rewritten whole: live slots with the codes of the stored rows, dead slots with zero.
+// A block of 64 slots that holds no live slot stamped >= stamp_lo is left alone; any other is rewritten whole: live slots with
+// the codes of the stored rows, dead slots with zero.  What bounds it: a frame leaves most of a long cache alone, so with a
+// workgroup per block the launch was bound by starting them (144000 at 40 heads x 230400 slots, 86 us; 47 now);
+// a workgroup looks at CPB blocks, gridDim.x apart, so that a run of slots that one frame wrote is spread over many.
+constexpr int CPB = 16;
 template <bool BF16>
 __global__ __launch_bounds__(256) void kv_to_fp8_kernel(const void *__restrict__ K, const void *__restrict__ V,
                                                         const int32_t *__restrict__ stamp, const int32_t *__restrict__ len,
                                                         int C, int n_blk, int stamp_lo, uint8_t *__restrict__ K8,
                                                         uint8_t *__restrict__ V8T) {
     __shared__ __attribute__((aligned(16))) uint8_t vt[D][TK + 16];   // transposed values of the block (padded rows)
-    __shared__ int dirty;
-    const int blk = blockIdx.x, h = blockIdx.y;
-    const int tid = threadIdx.x;
+    __shared__ unsigned dirty_of[4];                                   // per wavefront: its blocks that are to be rewritten
+    const int h = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int L = min(len[h], C);
-    if (tid == 0) dirty = 0;
-    __syncthreads();
-    if (tid < TK) {
-        const int slot = blk * TK + tid;
-        if (slot < L && stamp[(size_t)h * C + slot] >= stamp_lo) dirty = 1;
+    {
+        int st[CPB / 4];
+#pragma unroll
+        for (int e = 0; e < CPB / 4; ++e) {   // a wavefront per block: block 4 e + wave of the workgroup's
+            const long long slot = ((long long)blockIdx.x + (long long)(4 * e + wave) * gridDim.x) * TK + lane;
+            st[e] = slot < L ? stamp[(size_t)h * C + slot] : INT_MIN;
+        }
+        unsigned mine = 0;
+#pragma unroll
+        for (int e = 0; e < CPB / 4; ++e) {
+            const long long slot = ((long long)blockIdx.x + (long long)(4 * e + wave) * gridDim.x) * TK + lane;
+            if (__ballot(slot < L && st[e] >= stamp_lo)) mine |= 1u << (4 * e + wave);
+        }
+        if (lane == 0) dirty_of[wave] = mine;
     }
     __syncthreads();
-    if (!dirty) return;   // uniform
-    const int j = tid >> 2, part = tid & 3;   // slot of the block, quarter of its row (32 coordinates)
-    const int slot = blk * TK + j;
-    const size_t Cp = (size_t)n_blk * TK;
-    unsigned kw[8], vw[8];
+    for (unsigned dirty = dirty_of[0] | dirty_of[1] | dirty_of[2] | dirty_of[3]; dirty; dirty &= dirty - 1u) {   // uniform
+        const int blk = (int)blockIdx.x + (__ffs(dirty) - 1) * (int)gridDim.x;
+        const int j = tid >> 2, part = tid & 3;   // slot of the block, quarter of its row (32 coordinates)
+        const int slot = blk * TK + j;
+        const size_t Cp = (size_t)n_blk * TK;
+        unsigned kw[8], vw[8];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) kw[w] = vw[w] = 0u;
-    if (slot < L) {
-        float kf[32], vf[32];
-        if (BF16) {
-            const unsigned short *kr = (const unsigned short *)K + ((size_t)h * C + slot) * D + 32 * part;
-            const unsigned short *vr = (const unsigned short *)V + ((size_t)h * C + slot) * D + 32 * part;
+        for (int w = 0; w < 8; ++w) kw[w] = vw[w] = 0u;
+        if (slot < L) {
+            float kf[32], vf[32];
+            if (BF16) {
+                const unsigned short *kr = (const unsigned short *)K + ((size_t)h * C + slot) * D + 32 * part;
+                const unsigned short *vr = (const unsigned short *)V + ((size_t)h * C + slot) * D + 32 * part;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const u32x4 a = *(const u32x4 *)(kr + 8 * q), b = *(const u32x4 *)(vr + 8 * q);
+                for (int q = 0; q < 4; ++q) {
+                    const u32x4 a = *(const u32x4 *)(kr + 8 * q), b = *(const u32x4 *)(vr + 8 * q);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    kf[8 * q + 2 * e] = bf16_lo(a[e]); kf[8 * q + 2 * e + 1] = bf16_hi(a[e]);
-                    vf[8 * q + 2 * e] = bf16_lo(b[e]); vf[8 * q + 2 * e + 1] = bf16_hi(b[e]);
+                    for (int e = 0; e < 4; ++e) {
+                        kf[8 * q + 2 * e] = bf16_lo(a[e]); kf[8 * q + 2 * e + 1] = bf16_hi(a[e]);
+                        vf[8 * q + 2 * e] = bf16_lo(b[e]); vf[8 * q + 2 * e + 1] = bf16_hi(b[e]);
+                    }
+                }
+            } else {
+                const float *kr = (const float *)K + ((size_t)h * C + slot) * D + 32 * part;
+                const float *vr = (const float *)V + ((size_t)h * C + slot) * D + 32 * part;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const f32x4 a = *(const f32x4 *)(kr + 4 * q), b = *(const f32x4 *)(vr + 4 * q);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { kf[4 * q + e] = a[e]; vf[4 * q + e] = b[e]; }
                 }
             }
-        } else {
-            const float *kr = (const float *)K + ((size_t)h * C + slot) * D + 32 * part;
-            const float *vr = (const float *)V + ((size_t)h * C + slot) * D + 32 * part;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const f32x4 a = *(const f32x4 *)(kr + 4 * q), b = *(const f32x4 *)(vr + 4 * q);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { kf[4 * q + e] = a[e]; vf[4 * q + e] = b[e]; }
+            for (int w = 0; w < 8; ++w) {
+                kw[w] = pack_fp8x4(clamp_f8(kf[4 * w]), clamp_f8(kf[4 * w + 1]), clamp_f8(kf[4 * w + 2]), clamp_f8(kf[4 * w + 3]));
+                vw[w] = pack_fp8x4(clamp_f8(vf[4 * w]), clamp_f8(vf[4 * w + 1]), clamp_f8(vf[4 * w + 2]), clamp_f8(vf[4 * w + 3]));
             }
         }
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            kw[w] = pack_fp8x4(clamp_f8(kf[4 * w]), clamp_f8(kf[4 * w + 1]), clamp_f8(kf[4 * w + 2]), clamp_f8(kf[4 * w + 3]));
-            vw[w] = pack_fp8x4(clamp_f8(vf[4 * w]), clamp_f8(vf[4 * w + 1]), clamp_f8(vf[4 * w + 2]), clamp_f8(vf[4 * w + 3]));
+        {
+            uint8_t *dst = K8 + ((size_t)h * Cp + slot) * D + 32 * part;
+            u32x4 lo = {kw[0], kw[1], kw[2], kw[3]}, hi = {kw[4], kw[5], kw[6], kw[7]};
+            *(u32x4 *)dst = lo;
+            *(u32x4 *)(dst + 16) = hi;
         }
-    }
-    {
-        uint8_t *dst = K8 + ((size_t)h * Cp + slot) * D + 32 * part;
-        u32x4 lo = {kw[0], kw[1], kw[2], kw[3]}, hi = {kw[4], kw[5], kw[6], kw[7]};
-        *(u32x4 *)dst = lo;
-        *(u32x4 *)(dst + 16) = hi;
-    }
 #pragma unroll
-    for (int w = 0; w < 8; ++w)
+        for (int w = 0; w < 8; ++w)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) vt[32 * part + 4 * w + b][j] = (uint8_t)(vw[w] >> (8 * b));
-    __syncthreads();
-    {
-        // 128 rows of 64 bytes: thread -> row tid/2, half tid%2 (32 bytes)
-        const int row = tid >> 1, half = tid & 1;
-        uint8_t *dst = V8T + (((size_t)h * n_blk + blk) * D + row) * TK + 32 * half;
-        *(u32x4 *)dst = *(const u32x4 *)(&vt[row][32 * half]);
-        *(u32x4 *)(dst + 16) = *(const u32x4 *)(&vt[row][32 * half + 16]);
+            for (int b = 0; b < 4; ++b) vt[32 * part + 4 * w + b][j] = (uint8_t)(vw[w] >> (8 * b));
+        __syncthreads();
+        {
+            // 128 rows of 64 bytes: thread -> row tid/2, half tid%2 (32 bytes)
+            const int row = tid >> 1, half = tid & 1;
+            uint8_t *dst = V8T + (((size_t)h * n_blk + blk) * D + row) * TK + 32 * half;
+            *(u32x4 *)dst = *(const u32x4 *)(&vt[row][32 * half]);
+            *(u32x4 *)(dst + 16) = *(const u32x4 *)(&vt[row][32 * half + 16]);
+        }
+        __syncthreads();   // vt has been read
     }
 }
 
@@ -544,7 +559,7 @@ extern "C" int fastar_kv_to_fp8(const fastar_cache *cache, int32_t stamp_lo, uin
     if (((uintptr_t)cache->K & 15) || ((uintptr_t)cache->V & 15) || ((uintptr_t)K8 & 15) || ((uintptr_t)V8T & 15))
         return FASTAR_ERR_INVALID_ARG;
     const int n_blk = (C + f8::TK - 1) / f8::TK;
-    const dim3 grid(n_blk, H);
+    const dim3 grid((n_blk + f8::CPB - 1) / f8::CPB, H);
     if (cache->dtype == FASTAR_BF16)
         hipLaunchKernelGGL(f8::kv_to_fp8_kernel<true>, grid, dim3(256), 0, (hipStream_t)stream, cache->K, cache->V,
                            cache->stamp, cache->len, C, n_blk, stamp_lo, K8, V8T);

@@ -90,6 +90,26 @@ def check_fp8_attention(Q, c, sel, nsel, scale, use_cnt=True):
     return err.max(), err.mean()
 
 
+@pytest.mark.parametrize("n_blk,cut", [(1, 0), (15, 3), (16, 0), (17, 63), (33, 1), (50, 0)])
+def test_kv_to_fp8_finds_the_blocks_a_frame_wrote(n_blk, cut):
+    # a workgroup looks at 16 blocks, a grid apart: counts at its edges; a run of written slots, single ones, none
+    rng = np.random.default_rng(n_blk)
+    H, d, C = 3, 128, 64 * n_blk - cut
+    c = rand_cache(rng, H, C, d, [C, max(1, C - 70), C], "bf16")
+    c.stamp[:] = 3
+    c.stamp[0, C // 3: C // 3 + 200] = 7
+    c.stamp[0, C - 1] = c.stamp[1, 0] = 7
+    c.stamp[1, C - 1] = 7                      # beyond the head's length: not looked at (C > 70)
+    K8r, V8r = oracle.kv8_empty(H, C, d)
+    K8r[:], V8r[:] = 0x22, 0x33
+    K8, V8 = to_dev(K8r), to_dev(V8r)
+    oracle.kv_to_fp8(c, K8r, V8r, stamp_lo=7)
+    fa.kv_to_fp8(dev_cache(c), K8, V8, stamp_lo=7)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host(K8), K8r) and np.array_equal(to_host(V8), V8r)
+    assert (K8r[2] == 0x22).all()              # a head in which nothing was written stays as it is
+
+
 @pytest.mark.parametrize("H,n_q,C,lens,n_sel,seed", [
     (2, 256, 1280, [1280, 546], 5, 0),            # ragged last block, cfg1-like sizes at d = 128
     (3, 300, 64 * 40, [2560, 2000, 0], 9, 1),     # ragged queries, an empty head
