@@ -75,6 +75,13 @@ __global__ void rep_kernel(const int8_t *__restrict__ qcode, int n_q, int r, int
         const int up = 32 - BITS * (j % PER + 1);   // shift that puts the entry at the top of a word, then arithmetic shift down
         const int n = q1 - q0;
         int q = 0;
+        for (; q + 32 <= n; q += 32) {   // the usual run whole: a load costs a microsecond behind the launch that wrote it
+            int v[32];
+#pragma unroll
+            for (int e = 0; e < 32; ++e) v[e] = col[(size_t)(q + e) * rb];
+#pragma unroll
+            for (int e = 0; e < 32; ++e) s += BITS == 8 ? v[e] : ((int)((unsigned)v[e] << up) >> (32 - BITS));
+        }
         for (; q + 8 <= n; q += 8) {   // eight independent loads in flight
             int v[8];
 #pragma unroll
@@ -91,6 +98,25 @@ __global__ void rep_kernel(const int8_t *__restrict__ qcode, int n_q, int r, int
         if (s % g != 0 && s < 0) m -= 1;
         rep[((size_t)h * n_qb * n_rep + (size_t)b * n_rep + u) * r + (j & ~15) + summary_slot<BITS>(j & 15)] = (int8_t)m;
     }
+}
+
+// Lane exchanges of the scoring epilogue without a trip through LDS.
+__device__ __forceinline__ int max_across_halves_i32(int x) {   // max with lane ^ 32
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+    return max((int)r[0], (int)r[1]);
+}
+__device__ __forceinline__ int max_over_quad_i32(int x) {       // max over the four lanes 4k .. 4k+3
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+    return max(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+}
+// max over the n_rep (a power of two up to 32) neighbouring lanes that hold the summaries of one query block
+__device__ __forceinline__ int max_over_reps_i32(int x, int n_rep) {
+    if (n_rep >= 2) x = max(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
+    if (n_rep >= 4) x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
+    if (n_rep >= 8) x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, false));   // row_half_mirror
+    if (n_rep >= 16) x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x140, 0xF, 0xF, false));  // row_mirror
+    if (n_rep >= 32) x = max(x, shfl_xor(x, 16));
+    return x;
 }
 
 // ---- AnnSA scoring -----------------------------------------------------------------------------------
@@ -112,7 +138,8 @@ __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restric
     const int col = lane & 31, g2 = lane >> 5;
     const int NR = n_qb * n_rep;
     const int NCB = (NR + 31) / 32;
-    const int g = BQ / n_rep;
+    const int rep_shift = __ffs(n_rep) - 1;   // n_rep is a power of two
+    const int g = BQ >> rep_shift;
     constexpr int RB = R * BITS / 8;   // bytes per key row
     const int8_t *kc = kcode + (size_t)h * C * RB;
     const int8_t *rp = rep + (size_t)h * NR * R;
@@ -121,6 +148,7 @@ __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restric
         i32x4 bfrag[COL_CHUNK][KS];
 #pragma unroll
         for (int c = 0; c < COL_CHUNK; ++c) {
+            if (cb0 + c >= NCB) continue;   // uniform
             const int rc = min((cb0 + c) * 32 + col, NR - 1);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) bfrag[c][ks] = *(const i32x4 *)(rp + (size_t)rc * R + ks * 32 + 16 * g2);
@@ -180,11 +208,11 @@ __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restric
 #pragma unroll
             for (int c = 0; c < COL_CHUNK; ++c) {
                 if (cb0 + c < NCB) {
-                    int m = max(best[c], shfl_xor(best[c], 32));
+                    int m = max_across_halves_i32(best[c]);
                     const int rc = (cb0 + c) * 32 + col;
-                    const int b = rc / n_rep, u = rc % n_rep;
+                    const int b = rc >> rep_shift, u = rc & (n_rep - 1);
                     if (rc >= NR || b * BQ + u * g >= n_q) m = INT_MIN;
-                    for (int off = 1; off < n_rep; off <<= 1) m = max(m, shfl_xor(m, off));
+                    m = max_over_reps_i32(m, n_rep);
                     if (g2 == 0 && u == 0 && rc < NR) tile[b * KB_PER_WG + kl] = m;
                 }
             }
@@ -196,16 +224,6 @@ __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restric
         const int b = t / KB_PER_WG, kl = t % KB_PER_WG;
         if (kl < n_here) out[((size_t)h * n_qb + b) * n_kb_cap + kb0 + kl] = tile[t];
     }
-}
-
-// Lane exchanges of the scoring epilogue without a trip through LDS.
-__device__ __forceinline__ int max_across_halves_i32(int x) {   // max with lane ^ 32
-    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
-    return max((int)r[0], (int)r[1]);
-}
-__device__ __forceinline__ int max_over_quad_i32(int x) {       // max over the four lanes 4k .. 4k+3
-    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-    return max(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
 }
 
 // The same scores for long caches.  What bounds this kernel is how the memory system is addressed: workgroups that
