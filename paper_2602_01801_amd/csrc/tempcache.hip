@@ -911,7 +911,13 @@ static int launch_match_window(dim3 grid, size_t lds, hipStream_t s, Args... arg
 }
 
 // ---- prep (only behind the chunked match, which leaves packed arg-max keys) ---------------------------------
-// Unpacks the match and clears the per-slot group records it will touch.
+// A packed (score, smallest slot) word: the low word counts down with the slot.  0: no candidate.
+__device__ __forceinline__ void unpack_match(u64 key, int &j, int &S) {
+    j = key != 0 ? (int)(0xFFFFFFFFu - (unsigned)key) : -1;
+    S = key != 0 ? (int)(unsigned)(key >> 32) - SCORE_BIAS : 0;
+}
+// Unpacks the match and clears the per-slot group records it will touch.  Not needed on a persistent workspace, where the
+// records are clear and the verify launch unpacks the match itself.
 __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ best, int n_new, int C,
                                                       const int32_t *__restrict__ cand, int n_cand,
                                                       int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
@@ -919,11 +925,9 @@ __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ be
     const int h = blockIdx.y;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_new) return;
-    const u64 key = best[(size_t)h * n_new + i];
-    int j = -1, S = 0;
-    if (key != 0) {
-        j = (int)(0xFFFFFFFFu - (unsigned)key);   // the low word counts down with the slot: ties went to the smallest
-        S = (int)(unsigned)(key >> 32) - SCORE_BIAS;
+    int j, S;
+    unpack_match(best[(size_t)h * n_new + i], j, S);
+    if (j >= 0) {
         win[(size_t)h * C + j] = 0;
         grp[(size_t)h * C + j] = 0;
     }
@@ -1019,7 +1023,7 @@ __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const
     const int j0 = slice * SETTLE_SLICE, j1 = min(j0 + SETTLE_SLICE, L);
     unsigned short *age = so.slot_age + (size_t)h * settle_slices(C) * SETTLE_SLICE;
     int future = 0;
-    constexpr int UN = 16;   // loads in flight
+    constexpr int UN = 16;   // loads in flight (32 in the verify launch: 107 registers there, and no faster)
     for (int jb = j0; jb < j1; jb += nt * UN) {   // uniform trip count
         int sv[UN];
 #pragma unroll
@@ -1166,8 +1170,9 @@ __device__ __forceinline__ int group16_sum(int v) {
 template <bool BF16, int D>
 __device__ __forceinline__ void verify_token(const void *__restrict__ K, const void *__restrict__ K_new,
                                              const int8_t *__restrict__ cp, int r, int C, int n_new, float qscale,
-                                             int metric, int tau2_q16, const int32_t *__restrict__ jstar,
-                                             const int32_t *__restrict__ sbest, u64 *__restrict__ win,
+                                             int metric, int tau2_q16, int32_t *__restrict__ jstar,
+                                             const int32_t *__restrict__ sbest, const u64 *__restrict__ best,
+                                             u64 *__restrict__ win,
                                              int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
                                              int l16, const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp);
 
@@ -1175,8 +1180,9 @@ template <bool BF16, int D>
 __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__ K, const void *__restrict__ K_new,
                                                         const int8_t *__restrict__ cp, int r, int C, int n_new,
                                                         float qscale, int metric, int tau2_q16,
-                                                        const int32_t *__restrict__ jstar,
-                                                        const int32_t *__restrict__ sbest, u64 *__restrict__ win,
+                                                        int32_t *__restrict__ jstar,
+                                                        const int32_t *__restrict__ sbest, const u64 *__restrict__ best,
+                                                        u64 *__restrict__ win,
                                                         int32_t *__restrict__ grp, uint8_t *__restrict__ merged,
                                                         const int32_t *__restrict__ len,
                                                         const int32_t *__restrict__ stamp, int frame_id,
@@ -1193,7 +1199,7 @@ __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__
     if (so.hs && blockIdx.x == 0 && threadIdx.x == 0) so.hs[(size_t)h * HS_STRIDE] = min(len[h], C);
     const int l16 = threadIdx.x & 15;
     const int i = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);
-    if (i < n_new) verify_token<BF16, D>(K, K_new, cp, r, C, n_new, qscale, metric, tau2_q16, jstar, sbest, win, grp,
+    if (i < n_new) verify_token<BF16, D>(K, K_new, cp, r, C, n_new, qscale, metric, tau2_q16, jstar, sbest, best, win, grp,
                                          merged, h, i, l16, so.tstamp ? stamp : nullptr, so.tstamp);  // whole 16-lane groups
     if (so.hs) return;
     age_histogram_slice<4>(len, stamp, C, n_new, frame_id, plan_scratch + (size_t)h * scratch_words, hist_word, fut_word,
@@ -1264,14 +1270,23 @@ __device__ __forceinline__ void verify_core(const void *__restrict__ K, const vo
 template <bool BF16, int D>
 __device__ __forceinline__ void verify_token(const void *__restrict__ K, const void *__restrict__ K_new,
                                              const int8_t *__restrict__ cp, int r, int C, int n_new, float qscale,
-                                             int metric, int tau2_q16, const int32_t *__restrict__ jstar,
-                                             const int32_t *__restrict__ sbest, u64 *__restrict__ win,
+                                             int metric, int tau2_q16, int32_t *__restrict__ jstar,
+                                             const int32_t *__restrict__ sbest, const u64 *__restrict__ best,
+                                             u64 *__restrict__ win,
                                              int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
                                              int l16, const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp) {
     // everything addressed by the token first (one round trip), then the matched slot's key row
     const size_t ti = (size_t)h * n_new + i;
-    verify_core<BF16, D>(K, K_new, cp + ti * r, r, C, n_new, qscale, metric, tau2_q16, win, grp, merged, h, i, l16,
-                         jstar[ti], sbest[ti], stamp, tstamp);
+    int j, S;
+    if (best) {   // the match as its launch left it (uniform; see unpack_match)
+        unpack_match(best[ti], j, S);
+        if (l16 == 0) jstar[ti] = j;
+    } else {
+        j = jstar[ti];
+        S = sbest[ti];
+    }
+    verify_core<BF16, D>(K, K_new, cp + ti * r, r, C, n_new, qscale, metric, tau2_q16, win, grp, merged, h, i, l16, j, S, stamp,
+                         tstamp);
 }
 
 // ---- plan ----------------------------------------------------------------------------------------------
@@ -2678,9 +2693,11 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
 #undef FASTAR_MATCH
         }
         FASTAR_LAUNCH_CHECK();
-        hipLaunchKernelGGL(tc_prep_kernel, dim3((n_new + 255) / 256, H), dim3(256), 0, s, best, n_new, C, cand, n_cand,
-                           jstar, sbest, win, grp);
-        FASTAR_LAUNCH_CHECK();
+        if (!ws_persistent) {
+            hipLaunchKernelGGL(tc_prep_kernel, dim3((n_new + 255) / 256, H), dim3(256), 0, s, best, n_new, C, cand, n_cand,
+                               jstar, sbest, win, grp);
+            FASTAR_LAUNCH_CHECK();
+        }
     }
     dim3 tgrid((n_new + 15) / 16, H);
     const bool bf = dtype == FASTAR_BF16;
@@ -2694,8 +2711,8 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     if (!fused_verify) {
         const int n_slices = settle ? settle_slices(C) : 0;
         tgrid.x += n_slices;
-        FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest, win,
-                  grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
+        FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest,
+                  !window && ws_persistent ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
                   n_slices, so);
         tgrid.x -= n_slices;
         FASTAR_LAUNCH_CHECK();
