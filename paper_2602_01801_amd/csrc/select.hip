@@ -8,6 +8,7 @@
 //   topk                exact top-n_sel per row by radix select, ties to the lowest index, written in
 //                       ascending order by ballot + prefix-sum compaction (a kernel of its own for AnnSA,
 //                       the tail of the scoring kernel for AnnCA, where one workgroup owns a whole row)
+// Short caches: all three in one launch (select_short_kernel).
 #include <limits.h>
 
 #include <algorithm>
@@ -19,6 +20,11 @@ namespace fastar {
 
 constexpr int KB_PER_WG = 4;      // key blocks scored by one workgroup of score_self_kernel
 constexpr size_t LONG_CACHE_BLOCKS = 16 * 4096;   // key blocks over all heads from which the streaming kernel pays
+// Slots per head up to which one workgroup per query block scores them all (select_short_kernel); three launches against
+// one, us: r = 32, 2 x 2 query blocks, 4096 slots 9.3 -> 6.6, 9360 9.3 -> 8.9, 12288 9.6 -> 9.3; 12 x 21, 4096 11.1 -> 7.4,
+// 9360 11.7 -> 10.2, 12288 11.7 -> 12.2; r = 64, 6 x 21, 1024 11.7 -> 7.0, 4096 11.7 -> 9.3, 8192 11.8 -> 13.1.
+constexpr int short_keys(int r) { return r == 32 ? 10240 : 4096; }
+constexpr int SHORT_WGS = 256;     // its workgroups: no more than compute units (a second round: 11 us like the launches it replaces)
 constexpr int COL_CHUNK = 8;       // summary column blocks (of 32) kept in registers at a time
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -611,6 +617,95 @@ __global__ __launch_bounds__(256) void topk_kernel(const int32_t *__restrict__ s
              n_local, cand_min);
 }
 
+// ---- AnnSA selection in one launch, short caches -------------------------------------------------------
+// One workgroup = one query block: its summaries, the scores of every live key block and the top-k of the row, which
+// never leaves LDS.  The summaries are the rows of the products (row i: summary i mod n_rep, so eight rows hold them all)
+// and the keys the columns, so a lane keeps four of its sixteen results.  Nothing is masked: a run without queries is
+// replaced by the block's first one, and keys beyond the live ones by the last of them, which lies in the same key block.
+// What bounds it: a chain of latencies (keys and queries, summaries, a round of keys per 4096 of them, top-k) in place of
+// three launches; 4 heads x 780 queries x 4096 slots 9.9 -> 6.9 us, x 9360 10.2 -> 9.3.
+constexpr int SHORT_THREADS = 1024;
+template <int R>
+__global__ __launch_bounds__(SHORT_THREADS) void select_short_kernel(
+    const int8_t *__restrict__ qcode, int n_q, const int8_t *__restrict__ kcode, const int32_t *__restrict__ len, int C, int BQ,
+    int n_rep, int BK, int n_qb, int n_kb_cap, int n_sel, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int n_sink,
+    int n_local) {
+    constexpr int KS = R / 32, WAVES = SHORT_THREADS / 64;
+    constexpr int KB = R == 32 ? 4 : 2;   // key blocks in flight per wavefront (four rows of 64 bytes: 16 registers spilled)
+    extern __shared__ __attribute__((aligned(16))) unsigned char slds[];
+    int32_t *smax = (int32_t *)slds;                              // [n_kb_cap]
+    unsigned *qrow = (unsigned *)(slds + ((size_t)n_kb_cap * 4 + 15) / 16 * 16);   // [BQ][R] bytes
+    __shared__ __attribute__((aligned(16))) int8_t srep[8 * R];
+    __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
+    const int b = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g2 = lane >> 5;
+    const int g = BQ / n_rep;
+    const int q_lo = b * BQ, n_here = min(BQ, n_q - q_lo);
+    const unsigned *qc = (const unsigned *)(qcode + ((size_t)h * n_q + q_lo) * R);
+    for (int t = tid; t < n_here * (R / 4); t += SHORT_THREADS) qrow[t] = qc[t];
+    const int L = min(len[h], C);
+    const int n_kb = (L + BK - 1) / BK;
+    const int8_t *kc = kcode + (size_t)h * C * R;
+    i32x4 kf[KB][2][KS];
+    // two groups of 32 keys of each of the wavefront's next key blocks; the last group again where there is no second one
+    auto load = [&](int kb0, int sg0) {
+#pragma unroll
+        for (int q = 0; q < KB; ++q)
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const int k = min((kb0 + q * WAVES) * BK + min(sg0 + 32 * w, BK - 32) + col, L - 1);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) kf[q][w][ks] = *(const i32x4 *)(kc + (size_t)k * R + ks * 32 + 16 * g2);
+            }
+    };
+    if (wave < n_kb) load(wave, 0);
+    __syncthreads();
+    for (int t = tid; t < n_rep * R; t += SHORT_THREADS) {   // as rep_kernel
+        const int u = t / R, j = t % R;
+        const int q0 = u * g, q1 = min(q0 + g, n_here);
+        int s = g / 2;
+        for (int q = q0; q < q1; ++q) s += ((const int8_t *)qrow)[q * R + j];
+        int m = s / g;
+        if (s % g != 0 && s < 0) m -= 1;
+        srep[t] = (int8_t)m;
+    }
+    __syncthreads();
+    int u = col & (n_rep - 1);
+    if (u * g >= n_here) u = 0;
+    i32x4 rf[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) rf[ks] = *(const i32x4 *)(srep + u * R + ks * 32 + 16 * g2);
+    constexpr int BIAS = 1 << 21;   // |score| <= 64 * 127 * 127
+    for (int kb0 = wave; kb0 < n_kb; kb0 += KB * WAVES) {
+        int best[KB];
+#pragma unroll
+        for (int q = 0; q < KB; ++q) best[q] = INT_MIN;
+        for (int sg0 = 0; sg0 < BK; sg0 += 64) {
+            if (kb0 != wave || sg0 != 0) load(kb0, sg0);
+#pragma unroll
+            for (int q = 0; q < KB; ++q)
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    i32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(rf[ks], kf[q][w][ks], acc);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) best[q] = max(best[q], acc[v]);   // rows 4 g2 + v
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < KB; ++q) {
+            const int m = (int)wave_max_last((unsigned)(best[q] + BIAS)) - BIAS;
+            if (lane == 63 && kb0 + q * WAVES < n_kb) smax[kb0 + q * WAVES] = m;
+        }
+    }
+    __syncthreads();
+    if (wave >= 4) return;   // the selection is four wavefronts' work; barriers count those that are left
+    topk_row(smax, n_kb, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, nullptr, scratch, n_sink,
+             n_local);
+}
+
 // ---- selection on sign codes (LSH family) -------------------------------------------------------------
 // Summaries: bit j of the summary of a run of g queries = majority of the run's bits (2 * ones >= queries).
 // One workgroup per (query block, head), one thread per hash bit of a run, as many runs at a time as fit the workgroup
@@ -952,6 +1047,19 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
     const SelfWs w = self_ws(H, n_q, C, r, BQ, BK, n_rep);
     if (ws_bytes < w.total) return FASTAR_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
+    // Short caches, query blocks that fill the chip at most once: one launch instead of three.
+    if (bits == 8 && n_rep <= 8 && C <= short_keys(r) && BQ <= 256 && (int64_t)n_qb * H <= SHORT_WGS) {
+        const size_t lds = ((size_t)n_kb_cap * 4 + 15) / 16 * 16 + (size_t)BQ * r;
+        const dim3 qgrid(n_qb, H);
+        if (r == 32)
+            hipLaunchKernelGGL(select_short_kernel<32>, qgrid, dim3(SHORT_THREADS), lds, s, qcode, n_q, kcode, len, C, BQ, n_rep,
+                               BK, n_qb, n_kb_cap, n_sel, sel, nsel, n_sink, n_local);
+        else
+            hipLaunchKernelGGL(select_short_kernel<64>, qgrid, dim3(SHORT_THREADS), lds, s, qcode, n_q, kcode, len, C, BQ, n_rep,
+                               BK, n_qb, n_kb_cap, n_sel, sel, nsel, n_sink, n_local);
+        FASTAR_LAUNCH_CHECK();
+        return FASTAR_OK;
+    }
     int8_t *rep = (int8_t *)ws + w.rep_off;
     int32_t *score = (int32_t *)((char *)ws + w.score_off);
     const dim3 grid((n_kb_cap + KB_PER_WG - 1) / KB_PER_WG, H);

@@ -107,6 +107,29 @@ def test_ann_select_self_with_forced_sink_and_local_blocks(H, n_q, C, lens, n_se
         fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), 128, 4, 64, 4, n_sink=3, n_local=2)
 
 
+# one workgroup per query block up to 10240 slots (4096 at r = 64), 256 query blocks and 8 runs per block; the general path beyond
+@pytest.mark.parametrize("H,n_q,C,r,BQ,n_rep,BK,n_sel,lens,forced", [
+    (2, 100, 1, 32, 128, 4, 64, 1, [1, 0], (0, 0)),                    # one key, none; the block's last run has no query
+    (2, 129, 10240, 32, 128, 4, 64, 40, [10240, 10209], (0, 0)),       # the longest cache; one query in the last block
+    (2, 129, 10241, 32, 128, 4, 64, 40, [10241, 10240], (0, 0)),       # one slot more
+    (3, 200, 10240, 32, 128, 1, 32, 50, [10240, 4097, 31], (2, 3)),    # rows of 320 blocks
+    (2, 130, 4096, 64, 64, 8, 96, 11, [4095, 2209], (0, 0)),           # three groups per key block, the last one short
+    (2, 130, 4097, 64, 64, 8, 64, 11, [4097, 4096], (0, 0)),           # one slot more at r = 64
+    (2, 130, 6000, 32, 64, 2, 160, 38, [6000, 161], (1, 0)),           # five groups
+    (1, 511, 4160, 32, 256, 8, 64, 9, [4159], (0, 0)),                 # the largest query blocks, more than one round of blocks
+    (4, 64 * 64, 700, 32, 64, 4, 64, 5, [700, 640, 65, 1], (0, 0)),    # 256 query blocks
+    (1, 257 * 32, 700, 32, 32, 4, 64, 5, [699], (0, 0)),               # 257
+    (2, 70, 900, 32, 32, 16, 64, 5, [900, 70], (0, 0))])               # 16 runs per block
+def test_ann_select_self_at_the_edges_of_the_one_launch_form(H, n_q, C, r, BQ, n_rep, BK, n_sel, lens, forced):
+    rng = np.random.default_rng(n_q + C + BQ)
+    qc, kc = rand_codes(rng, -20, 20, H, n_q, r), rand_codes(rng, -128, 127, H, C, r)
+    length = np.array(lens, np.int32)
+    ref_sel, ref_nsel = oracle.ann_select_self(qc, kc, length, BQ, n_rep, BK, n_sel, *forced)
+    sel, nsel = fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), BQ, n_rep, BK, n_sel, n_sink=forced[0], n_local=forced[1])
+    assert np.array_equal(to_host(nsel), ref_nsel)
+    assert np.array_equal(to_host(sel), ref_sel)
+
+
 # rows at the edges of the top-k's register forms (256 entries per round, 1024, 4096), selections from one entry to all
 @pytest.mark.parametrize("n", [2, 33, 256, 257, 769, 1024, 1025, 3840, 3841, 4096, 4097])
 @pytest.mark.parametrize("scores", ["spread", "narrow", "equal", "two_values", "outlier"])
