@@ -254,7 +254,8 @@ int ann_select_lsh_buckets(const uint32_t *qbits, int n_q, const uint32_t *kbits
  *   ws / ws_bytes              workspace of fastar_workspace_bytes(FASTAR_OP_COMPRESS, ...), 256-byte aligned
  *   ws_persistent              0: the workspace may hold anything (the call clears what it needs: one launch more).
  *                              1: the caller zero-filled the workspace once and since then only calls of this
- *                              function on this cache have written to it; every call leaves it as clean as a
+ *                              function on this cache have written to it (frames may differ in length: the workspace
+ *                              is then sized for the longest); every call leaves it as clean as a
  *                              zero-filled one, so the match can go straight on to the threshold test (for candidate
  *                              lists that fit LDS with P_new NULL; other calls ignore the flag).  The library still
  *                              keeps no state of its own: the state is the caller's buffer.

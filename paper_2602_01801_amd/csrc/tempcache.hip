@@ -41,24 +41,27 @@ constexpr int SETTLE_SLOTS = 65536;       // eight slices
 constexpr int SETTLE_TOKENS = 8192;       // tokens per frame (their list is held in LDS)
 __host__ __device__ static inline int settle_slices(int C) { return (C + SETTLE_SLICE - 1) / SETTLE_SLICE; }
 
+// What a call leaves clean for the next one (group records, per-head scalars, plan scratch) lies in front and has sizes that
+// depend on the cache alone, so frames of any length share a persistent workspace.  Behind it is what every call writes before
+// it reads it; its offsets move with the frame's length.
 struct CompressWs {
-    size_t ck, cp, best, jstar, sbest, rank, victims, hs, ps, win, grp, tstamp, ages, slot_age, total;
+    size_t hs, win, grp, ps, best, ck, cp, jstar, sbest, rank, victims, tstamp, ages, slot_age, total;
 };
 static CompressWs compress_ws(int H, int C, int n_new, int r) {
     CompressWs w;
     size_t o = 0;
     const size_t T = (size_t)H * (n_new > 0 ? n_new : 1);
+    w.hs = o; o += align256((size_t)H * HS_STRIDE * 4);
+    w.win = o; o += align256((size_t)H * C * 8);
+    w.grp = o; o += align256((size_t)H * C * 4);
+    w.ps = o; o += align256((size_t)H * PLAN_SCRATCH_WORDS * 4);   // directly before best: one zero fill covers both
+    w.best = o; o += align256(T * 8);
     w.ck = o; o += align256(T * r);
     w.cp = o; o += align256(T * r);
-    w.best = o; o += align256(T * 8);
-    w.ps = o; o += align256((size_t)H * PLAN_SCRATCH_WORDS * 4);   // directly behind best: one zero fill covers both
     w.jstar = o; o += align256(T * 4);
     w.sbest = o; o += align256(T * 4);
     w.rank = o; o += align256(T * 4);
     w.victims = o; o += align256(T * 4);
-    w.hs = o; o += align256((size_t)H * HS_STRIDE * 4);
-    w.win = o; o += align256((size_t)H * C * 8);
-    w.grp = o; o += align256((size_t)H * C * 4);
     w.tstamp = o; o += align256(T * 4);
     const size_t slices = C <= SETTLE_SLOTS ? (size_t)H * settle_slices(C) : 0;
     w.ages = o; o += align256(slices * AGE_WORDS * 4);
@@ -2620,8 +2623,8 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     const bool settle = ws_persistent && C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
     const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age)} : SettleOut{};
     if (!fused_encode) {
-        const int64_t zero_words = (int64_t)((w.ps - w.best) / 8) + (int64_t)H * PLAN_SCRATCH_WORDS / 2;  // best .. end of ps
-        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, best, zero_words, s);
+        const int64_t zero_words = (int64_t)(w.best - w.ps) / 8 + T;   // ps and best
+        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)plan_scratch, zero_words, s);
         if (rc != FASTAR_OK) return rc;
         if (P_new) {
             rc = encode_launch(P_new, dtype, T, d, codec, r, cp, nullptr, 0, s);

@@ -1327,6 +1327,45 @@ def test_tempcache_persistent_workspace_mixes_with_the_other_paths_and_reports_a
     assert (to_host(st)[:, 7] == 3).all()
 
 
+# frames that grow a little, shrink a little, grow a lot, shrink a lot; which match each takes (a list of the previous frame's
+# slots, a list longer than LDS, the whole cache); caches of both settling paths.  Every frame evicts.
+@pytest.mark.parametrize("matches", [("window",) * 6, ("window", "long", "all", "window", "all", "window")])
+@pytest.mark.parametrize("H,C,r", [(3, 3000, 32), (2, 2500, 64), (1, 66000, 32)])
+def test_tempcache_frames_of_different_lengths_share_a_persistent_workspace(H, C, r, matches):
+    rng = np.random.default_rng(C + len(set(matches)))
+    d, dtype, lens = 128, "bf16", (300, 420, 400, 1000, 64, 420)
+    codec = make_codec(0, 9, d, r)
+    as_dt = lambda a: to_storage(a.astype(np.float32), dtype)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.V[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(0, 9, size=(H, C))
+    ref.len[:] = C
+    gpu = dev_cache(ref)
+    ws = torch.zeros(max(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r) for T in lens), dtype=torch.uint8, device="cuda")
+    for f, (T, match) in enumerate(zip(lens, matches)):
+        n_cand = {"window": T, "long": 4200, "all": 0}[match]
+        cand = np.stack([rng.choice(C, size=n_cand, replace=n_cand > C) for _ in range(H)]).astype(np.int32) if n_cand else None
+        if cand is not None:
+            cand[:, -40:] = np.arange(C - 40, C)               # the last slots too: their records end the arrays
+        K_new = as_dt(rng.standard_normal((H, T, d)))
+        for h in range(H):                                     # half of the frame repeats candidates, some of them several times
+            src = np.arange(C - 40, C) if cand is None else cand[h]
+            K_new[h, : T // 2] = ref.K[h, np.concatenate([src[-20:], rng.choice(src, size=T // 2 - 20)])]
+        V_new = as_dt(rng.standard_normal((H, T, d)))
+        args = dict(tau2_q16=TAU2(0.9), frame_id=9 + f)
+        expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+        got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=None if cand is None else to_dev(cand),
+                                    ws=ws, ws_persistent=True, **args)
+        sync()
+        assert (expect[2][:, 1] > 0).all() and (expect[2][:, 3] > 0).all()     # merges and evictions
+        for a, b in zip(got, expect):
+            assert np.array_equal(to_host(a), b), (f, T, match)
+        assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 def test_tempcache_whole_cache_match_and_inner_product_probe():
     run_rollout("cfg1", 4, 5 * 256, 0.9, windowed=False)
     run_rollout("cfg1", 4, 5 * 256, 0.9, windowed=True, metric=1, probe_queries=True)
