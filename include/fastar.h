@@ -256,9 +256,12 @@ int ann_select_lsh_buckets(const uint32_t *qbits, int n_q, const uint32_t *kbits
  *                              1: the caller zero-filled the workspace once and since then only calls of this
  *                              function on this cache have written to it (frames may differ in length: the workspace
  *                              is then sized for the longest); every call leaves it as clean as a
- *                              zero-filled one, so the match can go straight on to the threshold test (for candidate
- *                              lists that fit LDS with P_new NULL; other calls ignore the flag).  The library still
- *                              keeps no state of its own: the state is the caller's buffer.
+ *                              zero-filled one, so the match can go straight on to the threshold test (candidate
+ *                              lists that fit LDS, P_new NULL) and short caches are settled in one launch.  A
+ *                              workspace whose per-head marks say otherwise is reported (status 3) by every such
+ *                              call; of the rest of its contents, calls without a list, with one that does not fit
+ *                              LDS or with P_new clear what they need.  The library still keeps no state of its own:
+ *                              the state is the caller's buffer.
  * The cache struct and the codec struct are host structs; cache->len is updated on the device.
  * Supported: d in {64,128}, r in {32,64}; C up to about 393 000 * min(16, 1024 / H) slots per head (the eviction
  *            plan runs on that many workgroups per head and each keeps a bitmap of its share of the slots in LDS):

@@ -41,6 +41,14 @@ constexpr int SETTLE_SLOTS = 65536;       // eight slices
 constexpr int SETTLE_TOKENS = 8192;       // tokens per frame (their list is held in LDS)
 __host__ __device__ static inline int settle_slices(int C) { return (C + SETTLE_SLICE - 1) / SETTLE_SLICE; }
 
+// Calls without a window on a persistent workspace have the encode launch clear all of the cache's group records while those
+// are few, which saves the launch that would clear the matched slots' ones.  By slots per token, since a workgroup of that launch
+// clears its share by itself (call with the launch -> without, us): 12 heads x 500 tokens x 30000 slots 37.8 -> 36.5,
+// 12 x 100 x 60000 34.0 -> 38.8; and by their size: 24 x 1560 x 37440 (11 MB) 174.6 -> 172.6, 40 x 1560 x 37440 (18 MB)
+// 191.6 -> 193.1, 12 x 1560 x 99840 (14 MB) 167.3 -> 168.7.
+constexpr int CLEAR_SLOTS_PER_TOKEN = 64;
+constexpr size_t CLEAR_RECORDS_MAX = (size_t)12 << 20;
+
 // What a call leaves clean for the next one (group records, per-head scalars, plan scratch) lies in front and has sizes that
 // depend on the cache alone, so frames of any length share a persistent workspace.  Behind it is what every call writes before
 // it reads it; its offsets move with the frame's length.
@@ -919,8 +927,8 @@ __device__ __forceinline__ void unpack_match(u64 key, int &j, int &S) {
     j = key != 0 ? (int)(0xFFFFFFFFu - (unsigned)key) : -1;
     S = key != 0 ? (int)(unsigned)(key >> 32) - SCORE_BIAS : 0;
 }
-// Unpacks the match and clears the per-slot group records it will touch.  Not needed on a persistent workspace, where the
-// records are clear and the verify launch unpacks the match itself.
+// Unpacks the match and clears the per-slot group records it will touch.  Not needed where the encode launch cleared them all
+// (CLEAR_RECORDS_MAX); the verify launch then unpacks the match itself.
 __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ best, int n_new, int C,
                                                       const int32_t *__restrict__ cand, int n_cand,
                                                       int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
@@ -2622,9 +2630,12 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
     const bool settle = ws_persistent && C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
     const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age)} : SettleOut{};
+    // Calls without a window do not rely on clean group records (see fastar.h).
+    const bool clear_all = !window && ws_persistent && w.ps - w.win <= CLEAR_RECORDS_MAX && C / CLEAR_SLOTS_PER_TOKEN <= n_new;
     if (!fused_encode) {
-        const int64_t zero_words = (int64_t)(w.best - w.ps) / 8 + T;   // ps and best
-        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)plan_scratch, zero_words, s);
+        const size_t zero_from = clear_all ? w.win : w.ps;
+        const int64_t zero_words = (int64_t)(w.best - zero_from) / 8 + T;   // ps and best, the records in front of them
+        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)(base + zero_from), zero_words, s);
         if (rc != FASTAR_OK) return rc;
         if (P_new) {
             rc = encode_launch(P_new, dtype, T, d, codec, r, cp, nullptr, 0, s);
@@ -2696,7 +2707,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
 #undef FASTAR_MATCH
         }
         FASTAR_LAUNCH_CHECK();
-        if (!ws_persistent) {
+        if (!clear_all) {
             hipLaunchKernelGGL(tc_prep_kernel, dim3((n_new + 255) / 256, H), dim3(256), 0, s, best, n_new, C, cand, n_cand,
                                jstar, sbest, win, grp);
             FASTAR_LAUNCH_CHECK();
@@ -2715,7 +2726,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         const int n_slices = settle ? settle_slices(C) : 0;
         tgrid.x += n_slices;
         FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest,
-                  !window && ws_persistent ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
+                  clear_all ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
                   n_slices, so);
         tgrid.x -= n_slices;
         FASTAR_LAUNCH_CHECK();

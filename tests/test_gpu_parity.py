@@ -1366,6 +1366,40 @@ def test_tempcache_frames_of_different_lengths_share_a_persistent_workspace(H, C
         assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
 
 
+@pytest.mark.parametrize("H,T,C,n_cand", [(2, 200, 3000, 0), (2, 200, 5000, 4200), (2, 40, 5000, 0), (1, 300, 66000, 0)])
+def test_tempcache_calls_without_a_window_clear_the_group_records_they_need(H, T, C, n_cand):
+    # A workspace that held anything and was left by a call with ws_persistent = 0: its marks are those of a finished call, the
+    # records of slots which that call did not touch are not clean.
+    rng = np.random.default_rng(C + T)
+    d, r, dtype = 64, 32, "bf16"
+    codec = make_codec(0, 9, d, r)
+    as_dt = lambda a: to_storage(a.astype(np.float32), dtype)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.V[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(0, 9, size=(H, C))
+    ref.len[:] = C
+    gpu = dev_cache(ref)
+    ws = torch.full((fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r),), 0x5B, dtype=torch.uint8, device="cuda")
+    for f in range(3):
+        cand = np.stack([rng.choice(C, size=n_cand, replace=False) for _ in range(H)]).astype(np.int32) if n_cand else None
+        K_new = as_dt(rng.standard_normal((H, T, d)))
+        for h in range(H):
+            K_new[h, : T // 2] = ref.K[h, rng.choice(C if cand is None else cand[h], size=T // 2)]
+        V_new = as_dt(rng.standard_normal((H, T, d)))
+        args = dict(tau2_q16=TAU2(0.9), frame_id=9 + f)
+        expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+        got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=None if cand is None else to_dev(cand),
+                                    ws=ws, ws_persistent=f > 0, **args)
+        sync()
+        assert (expect[2][:, 1] > 0).all() and (expect[2][:, 3] > 0).all()
+        for a, b in zip(got, expect):
+            assert np.array_equal(to_host(a), b), f
+        assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 def test_tempcache_whole_cache_match_and_inner_product_probe():
     run_rollout("cfg1", 4, 5 * 256, 0.9, windowed=False)
     run_rollout("cfg1", 4, 5 * 256, 0.9, windowed=True, metric=1, probe_queries=True)
