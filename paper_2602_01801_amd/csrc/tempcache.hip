@@ -26,7 +26,7 @@ int encode_launch(const void *x, int dtype, int64_t n_vec, int d, const fastar_c
 constexpr int SCORE_BIAS = 1 << 23;      // makes every score positive inside the packed arg-max key
 constexpr int PLAN_SCRATCH_WORDS = 64 + 3 * 1024;  // per-head scratch of tc_plan_kernel (PS_STRIDE)
 constexpr int AGE_BINS = 1024;           // bins of an age histogram (frame_id - stamp), the last one collecting everything older
-constexpr int AGE_WORDS = AGE_BINS + 16; // a slice's histogram and, behind it, whether a stamp lies in the future
+constexpr int AGE_WORDS = AGE_BINS + 16; // a slice's histogram (bins of age_bin) and, behind it, its largest stamp as a key
 constexpr int HS_STRIDE = 8;             // per-head scalars: oldL, n_unmerged, e, n_victims, n_dropped, newL, 3 if the workspace is not clean, clean mark
 constexpr int WS_CLEAN = 0x5A17C1EA;     // hs word 7 after a call: group records and plan scratch are all zero again
 constexpr int WS_FAILED = 0x0BADC0DE;    // hs word 7 after a call whose plan gave up for the head: records and scratch are left as they are
@@ -53,7 +53,7 @@ constexpr size_t CLEAR_RECORDS_MAX = (size_t)12 << 20;
 // depend on the cache alone, so frames of any length share a persistent workspace.  Behind it is what every call writes before
 // it reads it; its offsets move with the frame's length.
 struct CompressWs {
-    size_t hs, win, grp, ps, best, ck, cp, jstar, sbest, rank, victims, tstamp, ages, slot_age, total;
+    size_t hs, win, grp, ps, best, ck, cp, jstar, sbest, rank, victims, tstamp, ages, slot_age, slot_stamp, total;
 };
 static CompressWs compress_ws(int H, int C, int n_new, int r) {
     CompressWs w;
@@ -74,6 +74,7 @@ static CompressWs compress_ws(int H, int C, int n_new, int r) {
     const size_t slices = C <= SETTLE_SLOTS ? (size_t)H * settle_slices(C) : 0;
     w.ages = o; o += align256(slices * AGE_WORDS * 4);
     w.slot_age = o; o += align256(slices * SETTLE_SLICE * 2);
+    w.slot_stamp = o; o += align256(slices * SETTLE_SLICE * 4);
     w.total = o;
     return w;
 }
@@ -582,6 +583,7 @@ struct SettleOut {
     int32_t *tstamp;
     unsigned *ages;
     unsigned short *slot_age;
+    int32_t *slot_stamp;
 };
 __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
                                           int frame_id, const SettleOut &so, unsigned *lhist, int slice);
@@ -1021,19 +1023,39 @@ __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ 
 }
 
 // The same for tc_settle_kernel: the histogram of one slice of SETTLE_SLICE slots, by one workgroup, stored whole (nothing
-// has to be cleared before or after), whether one of its stamps lies in the future, and every slot's bin: the launch that
-// settles the call replaces stamps while other workgroups of it still look for victims.
+// has to be cleared before or after), and every slot's bin: the launch that settles the call replaces stamps while other
+// workgroups of it still look for victims.  Ages below AGE_EXACT have a bin each; older ones eight bins per octave.  A stamp in
+// the future counts as age 0.  Bins that may hold more than one stamp, those and the first, have their slots' stamps kept too.
+constexpr int AGE_EXACT = 832;                    // 13 * 2^6
+static_assert(AGE_EXACT + (31 - 9) * 8 + 7 - 5 < AGE_BINS, "the last octave's bins");
+__device__ __forceinline__ unsigned stamp_key(int32_t stamp) { return (unsigned)stamp ^ 0x80000000u; }   // ascending
+__device__ __forceinline__ unsigned age_bin(int frame_id, int32_t stamp) {
+    if (stamp > frame_id) return 0u;
+    const unsigned age = (unsigned)frame_id - (unsigned)stamp;
+    if (age < (unsigned)AGE_EXACT) return age;
+    const int e = 31 - __clz(age);                // 9 .. 31; the three bits below the leading one
+    return (unsigned)(AGE_EXACT - 5 + 8 * (e - 9)) + ((age >> (e - 3)) & 7u);
+}
+// smallest and largest age of a bin from AGE_EXACT on
+__device__ __forceinline__ void age_bin_range(int bin, unsigned &lo, unsigned &hi) {
+    const int i = bin - (AGE_EXACT - 5), e = 9 + (i >> 3);
+    lo = (unsigned)(8 + (i & 7)) << (e - 3);
+    hi = lo + ((1u << (e - 3)) - 1u);
+}
 __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
                                           int frame_id, const SettleOut &so, unsigned *lhist, int slice) {
+    __shared__ unsigned s_max;
     const int h = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
     const int L = min(len[h], C);
     if (L + n_new <= C) return;   // uniform over the head: no eviction can be needed
     for (int k = tid; k < AGE_BINS; k += nt) lhist[k] = 0;
+    if (tid == 0) s_max = 0u;
     __syncthreads();
     const int32_t *st = stamp + (size_t)h * C;
     const int j0 = slice * SETTLE_SLICE, j1 = min(j0 + SETTLE_SLICE, L);
     unsigned short *age = so.slot_age + (size_t)h * settle_slices(C) * SETTLE_SLICE;
-    int future = 0;
+    int32_t *kept = so.slot_stamp + (size_t)h * settle_slices(C) * SETTLE_SLICE;
+    unsigned kmax = 0u;
     constexpr int UN = 16;   // loads in flight (32 in the verify launch: 107 registers there, and no faster)
     for (int jb = j0; jb < j1; jb += nt * UN) {   // uniform trip count
         int sv[UN];
@@ -1045,9 +1067,12 @@ __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const bool act = jb + u * nt + tid < j1;
-            const unsigned bin = min((unsigned)frame_id - (unsigned)sv[u], (unsigned)(AGE_BINS - 1));
-            if (act && sv[u] > frame_id) future = 1;
-            if (act) age[jb + u * nt + tid] = (unsigned short)bin;
+            const unsigned bin = age_bin(frame_id, sv[u]);
+            if (act) {
+                kmax = max(kmax, stamp_key(sv[u]));
+                age[jb + u * nt + tid] = (unsigned short)bin;
+                if (bin == 0u || bin >= (unsigned)AGE_EXACT) kept[jb + u * nt + tid] = sv[u];
+            }
             // neighbouring slots were mostly written by the same frame: lanes of the first lane's age count together
             const u64 m = __ballot(act);
             if (m == 0) continue;
@@ -1058,10 +1083,12 @@ __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const
             if (act && bin != fbin) atomicAdd(&lhist[bin], 1u);
         }
     }
-    future = __syncthreads_or(future);
+    kmax = wave_max_last(kmax);
+    if (lane_id() == 63) atomicMax(&s_max, kmax);
+    __syncthreads();
     unsigned *out = so.ages + ((size_t)h * settle_slices(C) + slice) * AGE_WORDS;
     for (int k = tid; k < AGE_BINS; k += nt) out[k] = lhist[k];
-    if (tid == 0) out[AGE_BINS] = (unsigned)future;
+    if (tid == 0) out[AGE_BINS] = s_max;
 }
 
 // ---- row pieces: 16 lanes share one row of D elements ----------------------------------------------------
@@ -2135,10 +2162,11 @@ __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, voi
 // threshold age follows from the slices' age histograms less the slots touched in this frame, and so do the numbers of
 // victims in the slices below.  Every workgroup works that out for itself (the same data, the same answer) and goes
 // straight on to its share of the rows:
-//   - workgroups below n_slices * n_reps: (slice, share).  The slice's victims in ascending order, from its stamps; the
+//   - workgroups below n_slices * n_reps: (slice, share).  The slice's victims in ascending order, from its slots' ages; the
 //     rows of every n_reps-th of them, starting with the share's, are replaced by those of the unmerged tokens of their
-//     rank.  A stamp in the future or a threshold in the last bin: the first workgroup of the head selects on the stamps
-//     themselves and replaces all of the head's victims.
+//     rank.  Where the threshold's bin may hold several stamps (age_bin), they select among the bin's stamps first, each for
+//     itself and from the copies that the match launch left: ages of 2000 and more, call at 12 heads x 1560 tokens x 37440
+//     slots 160 us by one workgroup on the stamps themselves (53 with the plan's meetings) -> 51; one stamp in the future 168 -> 33.
 //   - the others: 32 tokens each; the merged ones refresh their slots, the unmerged ones that found no victim are
 //     appended.
 // They write what no other one reads: a slot is touched or a victim or new; tokens' flags and slots, the old length, the
@@ -2148,7 +2176,7 @@ __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, voi
 // and 4 at most; the token workgroups are done after 6.  Launch 16.5, where the plan (17 workgroups per head, one
 // meeting) took 13.5 and the apply launch behind it 9.3; a chunk of three such calls 325 -> 293.
 // All 888 workgroups have to be resident at once: with 99 registers they took two rounds and 23.8 us, so frames of up to
-// 2048 tokens have an instantiation of 64 (it spills 17 words, around the medoid key and the selection on stamps).
+// 2048 tokens have an instantiation of 64 (it spills 4 words).
 constexpr int SETTLE_THREADS = 512;
 constexpr int SETTLE_WAVES = SETTLE_THREADS / 64;
 constexpr int SETTLE_GROUPS = SETTLE_THREADS / 16;             // 16-lane groups: rows a workgroup moves at a time
@@ -2192,7 +2220,7 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
     const int8_t *__restrict__ ck, int n_new, int frame_id, const int32_t *__restrict__ jstar, uint8_t *merged, u64 *win,
     int32_t *grp, int32_t *hs, int32_t *__restrict__ merge_map, int32_t *__restrict__ len, int rep_mode,
     const int32_t *__restrict__ tstamp, const unsigned *__restrict__ ages, const unsigned short *__restrict__ slot_age,
-    int n_reps, int32_t *__restrict__ stats) {
+    const int32_t *__restrict__ slot_stamp, int n_reps, int32_t *__restrict__ stats) {
     typedef RowPiece<BF16, D> RP;
     extern __shared__ __attribute__((aligned(16))) unsigned char slds[];
     __shared__ unsigned h_all[AGE_BINS], h_low[AGE_BINS];   // ages of the head's eligible slots, and of those below this slice
@@ -2302,7 +2330,6 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
 
     // ---- victims
     const int slice = (int)blockIdx.x % n_slices, share = (int)blockIdx.x / n_slices;
-    const int32_t *st = stamp + cb;
     const unsigned *ag = ages + (size_t)h * n_slices * AGE_WORDS;
     // first round of loads: the tokens' flags, slots and slots' stamps, this thread's run of ages, two bins of every slice
     int tj[TPT], ts[TPT];
@@ -2321,24 +2348,24 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
         run[q] = *(const u32x4 *)(slot_age + ((size_t)h * n_slices + slice) * SETTLE_SLICE + SETTLE_SPT * tid + 8 * q);
     constexpr int MAX_SLICES = SETTLE_SLOTS / SETTLE_SLICE;
     u32x2 bins[MAX_SLICES];
-    unsigned fut[MAX_SLICES];
+    unsigned newest[MAX_SLICES];
 #pragma unroll
     for (int q = 0; q < MAX_SLICES; ++q) {
         bins[q] = u32x2{0u, 0u};
-        fut[q] = 0u;
+        newest[q] = 0u;
         if (q < n_slices) {   // uniform
             bins[q] = *(const u32x2 *)(ag + (size_t)q * AGE_WORDS + 2 * tid);
-            fut[q] = ag[(size_t)q * AGE_WORDS + AGE_BINS];
+            newest[q] = ag[(size_t)q * AGE_WORDS + AGE_BINS];
         }
     }
     if (!maybe || dirty) return;   // uniform over the head; after the loads, which do not depend on it
-    unsigned all0 = 0, all1 = 0, low0 = 0, low1 = 0, future = 0;
+    unsigned all0 = 0, all1 = 0, low0 = 0, low1 = 0, kmax = 0;
 #pragma unroll
     for (int q = 0; q < MAX_SLICES; ++q) {
         all0 += bins[q][0]; all1 += bins[q][1];
         low0 += q < slice ? bins[q][0] : 0u;
         low1 += q < slice ? bins[q][1] : 0u;
-        future |= fut[q];
+        kmax = max(kmax, newest[q]);
     }
     clear_touched();
     // unmerged tokens by rank (ascending token order): counts per wavefront and round, every wavefront adds them up itself
@@ -2380,7 +2407,7 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
         const bool first = (fmask >> k) & 1u;
         const u64 fm = __ballot(first);
         if (fm) {   // uniform; most of them carry the stamp of the frame before: lanes of one age count together
-            const unsigned bin = min((unsigned)frame_id - (unsigned)ts[k], (unsigned)(AGE_BINS - 1));
+            const unsigned bin = age_bin(frame_id, ts[k]);
             const int lead = __ffsll((unsigned long long)fm) - 1;
             const bool same = bin == (unsigned)__builtin_amdgcn_readlane((int)bin, lead), low = tj[k] < s0;
             const u64 sm = __ballot(first && same), lm = __ballot(first && same && low);
@@ -2399,12 +2426,15 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
     settle_scan({distinct, 0u}, wtot, turn, tot);   // its barrier also publishes the lists, the bitmap and the histograms
     const int n_el = L - (int)tot.a;
     const bool take_all = n_el <= e;
-    const int n_victims = min(e, n_el);
-    // Threshold: the bin, from the oldest on, in which the e-th slot lies; `need` of it are taken, in slot order.  Victims: keys
-    // below T and the first `need` equal to it, a key being minus the age, or on the general path the stamp.
-    int T = INT_MAX, need = 0, low_older = 0, low_ties = 0;
-    bool fast = future == 0;
-    if (fast && !take_all) {
+    // Threshold: the bin, from the oldest on, in which the e-th slot lies; `need` of it are taken.  Victims: the slots of older
+    // bins, and of this one those with the smallest stamps, ties in slot order.  low_*: how many of them lie below this slice.
+    int bin = 0, need = 0, low_older = 0, low_ties = 0;
+    bool exact = true;          // one stamp per bin
+    unsigned tkey = 0u;         // otherwise the threshold among the bin's stamps
+    if (take_all) {
+        settle_scan({h_low[2 * tid] + h_low[2 * tid + 1], 0u}, wtot, turn, tot);
+        low_older = (int)tot.a;
+    } else {
         const int b1 = AGE_BINS - 1 - 2 * tid, b0 = b1 - 1;   // this thread's bins, the older one first
         const unsigned a1 = h_all[b1], a0 = h_all[b0], l1 = h_low[b1], l0 = h_low[b0];
         const Pair ex = settle_scan({a0 + a1, l0 + l1}, wtot, turn, tot);
@@ -2417,123 +2447,154 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
             sh[3] = (int)(in1 ? l1 : l0);
         }
         __syncthreads();
-        const int bin = sh[0];
-        fast = bin < AGE_BINS - 1;
-        T = -bin;
+        bin = sh[0];
         need = sh[1];
         low_older = sh[2];
         low_ties = sh[3];
-    } else if (fast) {   // every eligible slot: those below this slice
-        settle_scan({h_low[2 * tid] + h_low[2 * tid + 1], 0u}, wtot, turn, tot);
-        low_older = (int)tot.a;
+        exact = bin < AGE_EXACT && (bin > 0 || kmax <= stamp_key(frame_id));
     }
-    if (!fast) {   // uniform over the head
-        if (blockIdx.x != 0) return;
-        // Select on the stamps themselves, four digits of eight bits from the top (each digit's counts in h_all).
-        unsigned prefix = 0;
-        unsigned want = (unsigned)e;
-        for (int shift = 24; shift >= 0 && !take_all; shift -= 8) {
-            __syncthreads();
-            if (tid < 256) h_all[tid] = 0u;
-            __syncthreads();
-            for (int j = tid; j < L; j += SETTLE_THREADS) {
-                const unsigned u = (unsigned)st[j] ^ 0x80000000u;
-                const bool el = !((touched[j >> 5] >> (j & 31)) & 1u);
-                if (el && (shift == 24 || (u >> ((shift + 8) & 31)) == prefix)) atomicAdd(&h_all[(u >> shift) & 255u], 1u);
-            }
-            __syncthreads();
-            const unsigned c = tid < 256 ? h_all[tid] : 0u;
-            const unsigned before = settle_scan({c, 0u}, wtot, turn, tot).a;
-            if (before < want && want <= before + c) {
-                sh[0] = tid;
-                sh[1] = (int)(want - before);
-            }
-            __syncthreads();
-            prefix = (prefix << 8) | (unsigned)sh[0];
-            want = (unsigned)sh[1];
-        }
-        T = take_all ? INT_MAX : (int)(prefix ^ 0x80000000u);
-        need = (int)want;
-    }
-    // Victims of a slice, the first of rank rank0: their slots in `vict`, then the rows of every n-th from the m-th on.
-    auto evict = [&](int from, const int (&sv)[SETTLE_SPT], int rank0, int ties_before, int m, int n, int &n_here, int &ties_here) {
-        const int j0 = from + SETTLE_SPT * tid;
-        unsigned bits = j0 < C ? (~(touched[j0 >> 5] >> (j0 & 31))) & 0xFFFFu : 0u;   // eligible slots of the run
-        if (j0 + SETTLE_SPT > L) bits &= j0 < L ? (1u << (L - j0)) - 1u : 0u;
-        unsigned older = 0, ties = 0;
+    const size_t ab = (size_t)h * n_slices * SETTLE_SLICE + SETTLE_SPT * tid;   // this thread's run in slice 0
+    auto ages_of = [&](const u32x4 (&w)[2], unsigned &older, unsigned &ties) {   // of a run, by bins
+        older = ties = 0u;
 #pragma unroll
         for (int q = 0; q < SETTLE_SPT; ++q) {
-            older |= (take_all || sv[q] < T) ? 1u << q : 0u;
-            ties |= (!take_all && sv[q] == T) ? 1u << q : 0u;
-        }
-        older &= bits;
-        ties &= bits;
-        const Pair ex = settle_scan({(unsigned)__popc(older), (unsigned)__popc(ties)}, wtot, turn, tot);
-        const int take_ties = min(max(need - ties_before, 0), (int)tot.b);
-        n_here = (int)tot.a + take_ties;
-        ties_here = (int)tot.b;
-        int ties_left = take_ties - (int)ex.b, idx = (int)ex.a + min((int)ex.b, take_ties);
-        for (unsigned todo = older | (ties_left > 0 ? ties : 0u); todo; todo &= todo - 1u) {
-            const int q = __ffs(todo) - 1;
-            if ((ties >> q) & 1u) {
-                if (ties_left <= 0) continue;
-                ties_left -= 1;
-            }
-            vict[idx] = (unsigned short)(j0 + q - from);
-            idx += 1;
-        }
-        __syncthreads();
-        const int n_rows = n_here > m ? (n_here - m + n - 1) / n : 0;
-        constexpr int UN = 2;   // rows of a group in flight
-        for (int v0 = group; v0 < n_rows; v0 += SETTLE_GROUPS * UN) {
-            typename RP::Raw kr[UN], vr[UN];
-            unsigned cw[UN];
-            int tok[UN], dst[UN];
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int v = v0 + u * SETTLE_GROUPS;
-                tok[u] = -1;
-                if (v < n_rows) {
-                    const int a = rank0 + v * n + m;
-                    dst[u] = from + vict[v * n + m];
-                    tok[u] = a < n_unm ? unm[a] : -1;
-                }
-                if (tok[u] >= 0) {
-                    kr[u] = RP::load_raw(K_new, tb + tok[u], l16);
-                    vr[u] = RP::load_raw(V_new, tb + tok[u], l16);
-                    cw[u] = l16 < r / 4 ? ((const unsigned *)(ck + (tb + tok[u]) * r))[l16] : 0u;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < UN; ++u)
-                if (tok[u] >= 0) {
-                    RP::store_raw(K, cb + dst[u], l16, kr[u]);
-                    RP::store_raw(V, cb + dst[u], l16, vr[u]);
-                    if (l16 < r / 4) ((unsigned *)(code + (cb + dst[u]) * r))[l16] = cw[u];
-                    if (l16 == 0) {
-                        cnt[cb + dst[u]] = 1;
-                        stamp[cb + dst[u]] = frame_id;
-                        merge_map[tb + tok[u]] = dst[u];
-                    }
-                }
+            const int age = (int)((w[q / 8][(q % 8) / 2] >> (16 * (q & 1))) & 0xFFFFu);
+            older |= (take_all || age > bin) ? 1u << q : 0u;
+            ties |= (!take_all && age == bin) ? 1u << q : 0u;
         }
     };
-    int key[SETTLE_SPT], n_here, ties_here;
-    if (fast) {
+    auto eligible = [&](int j0) -> unsigned {   // live and untouched slots of the run from j0 on
+        const unsigned bits = j0 < C ? (~(touched[j0 >> 5] >> (j0 & 31))) & 0xFFFFu : 0u;
+        return j0 + SETTLE_SPT <= L ? bits : j0 < L ? bits & ((1u << (L - j0)) - 1u) : 0u;
+    };
+    if (!exact) {   // uniform over the head: digits of ten bits of the bin's stamps, over their range
+        unsigned age_lo = 0u, age_hi = 0u;
+        if (bin > 0) age_bin_range(bin, age_lo, age_hi);
+        const unsigned now = stamp_key(frame_id), top = bin > 0 ? now - age_lo : kmax;   // the age occurs: no wrap
+        tkey = now - min(age_hi, now);
+        const unsigned span = top - tkey;
+        for (int shift = span ? 32 - __clz(span) : 0; shift > 0;) {   // uniform
+            const int width = min(10, shift);
+            shift -= width;
+            __syncthreads();   // the counts before have been read
+            h_all[2 * tid] = h_all[2 * tid + 1] = 0u;
+            h_low[2 * tid] = h_low[2 * tid + 1] = 0u;
+            __syncthreads();
+            for (int q = 0; q < n_slices; ++q) {
+                if (ag[(size_t)q * AGE_WORDS + bin] == 0u) continue;   // uniform
+                unsigned older, ties;
+                const size_t at = ab + (size_t)q * SETTLE_SLICE;
+                const u32x4 w[2] = {*(const u32x4 *)(slot_age + at), *(const u32x4 *)(slot_age + at + 8)};
+                ages_of(w, older, ties);
+                ties &= eligible(q * SETTLE_SLICE + SETTLE_SPT * tid);
+                if (!ties) continue;
+                u32x4 sv[SETTLE_SPT / 4];
 #pragma unroll
-        for (int q = 0; q < SETTLE_SPT; ++q) key[q] = -(int)((run[q / 8][(q % 8) / 2] >> (16 * (q & 1))) & 0xFFFFu);
-        evict(s0, key, low_older + min(need, low_ties), low_ties, share, n_reps, n_here, ties_here);
-    } else {
-        int rank0 = 0, ties_before = 0;
-        for (int q = 0; q < n_slices && rank0 < n_victims; ++q) {   // uniform
-            const int j0 = q * SETTLE_SLICE + SETTLE_SPT * tid;
+                for (int x = 0; x < SETTLE_SPT / 4; ++x) sv[x] = *(const u32x4 *)(slot_stamp + at + 4 * x);
+                unsigned run_digit = 0u, run_n = 0u;   // a run of one digit is one addition
+                auto flush = [&]() {
+                    if (run_n) {
+                        atomicAdd(&h_all[run_digit], run_n);
+                        if (q < slice) atomicAdd(&h_low[run_digit], run_n);
+                    }
+                };
 #pragma unroll
-            for (int x = 0; x < SETTLE_SPT; ++x) key[x] = j0 + x < L ? st[j0 + x] : 0;
-            __syncthreads();   // the victims of the slice before have been read
-            evict(q * SETTLE_SLICE, key, rank0, ties_before, 0, 1, n_here, ties_here);
-            rank0 += n_here;
-            ties_before += ties_here;
+                for (int x = 0; x < SETTLE_SPT; ++x) {
+                    const unsigned digit = (stamp_key((int)sv[x / 4][x % 4]) - tkey) >> shift;
+                    if (!((ties >> x) & 1u) || (digit >> width)) continue;   // below or above what is left of the range
+                    if (digit != run_digit) {
+                        flush();
+                        run_n = 0u;
+                    }
+                    run_digit = digit;
+                    run_n += 1u;
+                }
+                flush();
+            }
+            __syncthreads();
+            const unsigned a0 = h_all[2 * tid], a1 = h_all[2 * tid + 1], l0 = h_low[2 * tid], l1 = h_low[2 * tid + 1];
+            const Pair ex = settle_scan({a0 + a1, l0 + l1}, wtot, turn, tot);
+            const unsigned before = ex.a, want = (unsigned)need;
+            if (before < want && want <= before + a0 + a1) {
+                const bool in0 = want <= before + a0;
+                sh[0] = 2 * tid + (in0 ? 0 : 1);
+                sh[1] = (int)(want - before - (in0 ? 0u : a0));
+                sh[2] = (int)(ex.b + (in0 ? 0u : l0));
+                sh[3] = (int)(in0 ? l0 : l1);
+            }
+            __syncthreads();
+            tkey += (unsigned)sh[0] << shift;
+            need = sh[1];
+            low_older += sh[2];
+            low_ties = sh[3];
         }
+    }
+    // The slice's victims in ascending order, and the rows of every n_reps-th of them
+    unsigned older, ties;
+    ages_of(run, older, ties);
+    if (!exact && ties) {
+        const size_t at = ab + (size_t)slice * SETTLE_SLICE;
+        const unsigned of_bin = ties;
+        ties = 0u;
+        for (unsigned todo = of_bin; todo; todo &= todo - 1u) {
+            const int q = __ffs(todo) - 1;
+            const unsigned key = stamp_key(slot_stamp[at + q]);
+            older |= key < tkey ? 1u << q : 0u;
+            ties |= key == tkey ? 1u << q : 0u;
+        }
+    }
+    {
+        const unsigned bits = eligible(s0 + SETTLE_SPT * tid);
+        older &= bits;
+        ties &= bits;
+    }
+    const Pair ex = settle_scan({(unsigned)__popc(older), (unsigned)__popc(ties)}, wtot, turn, tot);
+    const int take_ties = min(max(need - low_ties, 0), (int)tot.b);
+    const int n_here = (int)tot.a + take_ties, rank0 = low_older + min(need, low_ties);
+    int ties_left = take_ties - (int)ex.b, idx = (int)ex.a + min((int)ex.b, take_ties);
+    for (unsigned todo = older | (ties_left > 0 ? ties : 0u); todo; todo &= todo - 1u) {
+        const int q = __ffs(todo) - 1;
+        if ((ties >> q) & 1u) {
+            if (ties_left <= 0) continue;
+            ties_left -= 1;
+        }
+        vict[idx] = (unsigned short)(SETTLE_SPT * tid + q);
+        idx += 1;
+    }
+    __syncthreads();
+    const int n_rows = n_here > share ? (n_here - share + n_reps - 1) / n_reps : 0;
+    constexpr int UN = 2;   // rows of a group in flight
+    for (int v0 = group; v0 < n_rows; v0 += SETTLE_GROUPS * UN) {
+        typename RP::Raw kr[UN], vr[UN];
+        unsigned cw[UN];
+        int tok[UN], dst[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int v = v0 + u * SETTLE_GROUPS;
+            tok[u] = -1;
+            if (v < n_rows) {
+                const int a = rank0 + v * n_reps + share;
+                dst[u] = s0 + vict[v * n_reps + share];
+                tok[u] = a < n_unm ? unm[a] : -1;
+            }
+            if (tok[u] >= 0) {
+                kr[u] = RP::load_raw(K_new, tb + tok[u], l16);
+                vr[u] = RP::load_raw(V_new, tb + tok[u], l16);
+                cw[u] = l16 < r / 4 ? ((const unsigned *)(ck + (tb + tok[u]) * r))[l16] : 0u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+            if (tok[u] >= 0) {
+                RP::store_raw(K, cb + dst[u], l16, kr[u]);
+                RP::store_raw(V, cb + dst[u], l16, vr[u]);
+                if (l16 < r / 4) ((unsigned *)(code + (cb + dst[u]) * r))[l16] = cw[u];
+                if (l16 == 0) {
+                    cnt[cb + dst[u]] = 1;
+                    stamp[cb + dst[u]] = frame_id;
+                    merge_map[tb + tok[u]] = dst[u];
+                }
+            }
     }
 }
 
@@ -2629,7 +2690,8 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     // Plan and apply in one launch: short caches, whose age histograms are small enough to be read by every workgroup, and
     // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
     const bool settle = ws_persistent && C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
-    const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age)} : SettleOut{};
+    const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age),
+                                          (int32_t *)(base + w.slot_stamp)} : SettleOut{};
     // Calls without a window do not rely on clean group records (see fastar.h).
     const bool clear_all = !window && ws_persistent && w.ps - w.win <= CLEAR_RECORDS_MAX && C / CLEAR_SLOTS_PER_TOKEN <= n_new;
     if (!fused_encode) {
@@ -2739,7 +2801,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
 #define FASTAR_SETTLE_T(BF, DD, TT)                                                                                      \
     hipLaunchKernelGGL((tc_settle_kernel<BF, DD, TT>), sgrid, dim3(SETTLE_THREADS), lds, s, cache->K, cache->V, cache->code,    \
                        cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new, frame_id, jstar, merged, win, grp, hs,     \
-                       merge_map, cache->len, rep_mode, so.tstamp, so.ages, so.slot_age, n_reps, stats)
+                       merge_map, cache->len, rep_mode, so.tstamp, so.ages, so.slot_age, so.slot_stamp, n_reps, stats)
 #define FASTAR_SETTLE(BF, DD)                                  \
     do {                                                       \
         if (n_new <= 4 * SETTLE_THREADS) FASTAR_SETTLE_T(BF, DD, 4); \

@@ -1147,6 +1147,43 @@ def test_tempcache_short_caches_settle_in_one_launch(dtype, d, H, T, C, free, lo
         assert (st[:, 3] > 0).all()
 
 
+# where an age does not tell the stamp: the threshold among stamps in the future, alone or beside the frame's own and older ones,
+# among ages of 1023 and more in one, two and four digits of their range, at both ends of the numbers; frames of both list sizes
+@pytest.mark.parametrize("dtype,H,T,C,lo,hi,step,frame", [
+    ("bf16", 2, 400, 9000, 50, 90, 1, 9), ("fp32", 2, 300, 17000, 5, 14, 1, 10), ("bf16", 2, 300, 8192, 10, 300000, 1, 10),
+    ("bf16", 2, 400, 20000, 0, 900, 1, 2200), ("bf16", 2, 400, 20000, 0, 24, 2000, 48000), ("fp32", 1, 2500, 12000, 0, 24, 2 ** 26, 2 ** 31 - 1),
+    ("bf16", 3, 257, 3000, -2 ** 31, 2 ** 31, 1, 0), ("bf16", 1, 3000, 30000, -2 ** 31, -2 ** 31 + 4000, 1, -2 ** 31 + 3000)])
+def test_tempcache_settles_by_the_stamps_where_ages_do_not_tell(dtype, H, T, C, lo, hi, step, frame):
+    rng = np.random.default_rng(C + T)
+    d, r = 64, 32
+    codec = make_codec(0, 9, d, r)
+    as_dt = lambda a: to_storage(a.astype(np.float32), dtype)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.V[:] = as_dt(rng.standard_normal((H, C, d)))
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(lo, hi, size=(H, C)) * step
+    ref.len[:] = C
+    ref.len[0] = C - 3
+    gpu = dev_cache(ref)
+    ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
+    for f in range(3):
+        cand = np.stack([rng.choice(C - 3, size=T, replace=False) for _ in range(H)]).astype(np.int32)
+        K_new = as_dt(rng.standard_normal((H, T, d)))
+        for h in range(H):
+            K_new[h, : T // 3] = ref.K[h, cand[h, : T // 3]]
+        V_new = as_dt(rng.standard_normal((H, T, d)))
+        args = dict(tau2_q16=TAU2(0.9), frame_id=frame)
+        expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+        got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws, ws_persistent=True, **args)
+        sync()
+        assert (expect[2][:, 1] > 0).all() and (expect[2][:, 3] > 0).all()
+        for a, b in zip(got, expect):
+            assert np.array_equal(to_host(a), b), f
+        assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 @pytest.mark.parametrize("name,dtype,H,frames,C", [("cfg1", None, None, 6, 6 * 256), ("cfg1", "bf16", None, 6, 3 * 256),
                                                    ("cfg2", None, 2, 4, 3 * 1560)])
 def test_tempcache_mean_key_representative_bit_exact(name, dtype, H, frames, C):
