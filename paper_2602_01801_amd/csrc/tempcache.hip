@@ -586,7 +586,7 @@ struct SettleOut {
     int32_t *slot_stamp;
 };
 __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
-                                          int frame_id, const SettleOut &so, unsigned *lhist, int slice);
+                                          int frame_id, const SettleOut &so, unsigned *lhist, int h, int slice);
 template <int UN>
 __device__ __forceinline__ void age_histogram_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp,
                                                     int C, int n_new, int frame_id, unsigned *__restrict__ ps,
@@ -597,6 +597,7 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
     uint8_t *merged;
     const int32_t *stamp;
     int frame_id, hist_word, fut_word;
+    int H;
     SettleOut so;
 };
 
@@ -604,7 +605,10 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 // the arg-max of its 64 tokens is final it runs the cosine test for them and registers the joiners; nothing is cleared
 // here (records and plan scratch are clean on entry).  The age histogram the plan wants is counted beside the match: by
 // workgroups of its own at the end of the grid's x range (n_hist of them; behind the match it cost every workgroup 2 us),
-// with 256 tokens per workgroup, where the grid fills the chip, by every workgroup as its tail (n_hist = 0).
+// with 256 tokens per workgroup, where the grid fills the chip, by every workgroup as its tail (n_hist = 0).  The slices of
+// tc_settle_kernel are counted, with 256 tokens per workgroup, in rows of the grid behind the heads': they run where tokens leave
+// a unit idle, or after them.  Call at 40 heads x 3600 tokens x 64800 slots 256 us with the slices among each head's workgroups
+// (each takes a whole unit's LDS, and the last heads' tokens waited), 208 as their tail, 206 behind; 24 x 2048 x 63488 85, 69, 64.
 // TOKS: tokens per workgroup.  64 (eight wavefronts share the window scan) when the call is latency-bound; 256 (four
 // wavefronts share the scan for their 128 tokens) when there are many more workgroups than the chip holds at once:
 // staging the window is then paid a quarter as often.  The wide form's prefetched rows and operands do not all fit the
@@ -639,9 +643,15 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     __shared__ __attribute__((aligned(16))) u64 partbest[SPLIT][TOKS];
     static_assert(sizeof(partbest) >= AGE_BINS * sizeof(unsigned), "the histogram fits");
     const int n_tok_wgs = (int)gridDim.x - n_hist;
+    if (VERIFY && TOKS >= 256 && (int)blockIdx.y >= va.H) {   // uniform: age slices behind everyone's tokens
+        const int at = ((int)blockIdx.y - va.H) * (int)gridDim.x + (int)blockIdx.x, n_slices = settle_slices(C);
+        if (at < va.H * n_slices)
+            age_slice(len, va.stamp, C, n_new, va.frame_id, va.so, (unsigned *)partbest, at / n_slices, at % n_slices);
+        return;
+    }
     if (VERIFY && (int)blockIdx.x >= n_tok_wgs) {       // uniform
         if (va.so.hs)
-            age_slice(len, va.stamp, C, n_new, va.frame_id, va.so, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs);
+            age_slice(len, va.stamp, C, n_new, va.frame_id, va.so, (unsigned *)partbest, blockIdx.y, (int)blockIdx.x - n_tok_wgs);
         else
             age_histogram_slice<4>(len, va.stamp, C, n_new, va.frame_id, ps_all + (size_t)blockIdx.y * ps_words, va.hist_word,
                                    va.fut_word, (unsigned *)partbest, (int)blockIdx.x - n_tok_wgs, n_hist);
@@ -1043,9 +1053,9 @@ __device__ __forceinline__ void age_bin_range(int bin, unsigned &lo, unsigned &h
     hi = lo + ((1u << (e - 3)) - 1u);
 }
 __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const int32_t *__restrict__ stamp, int C, int n_new,
-                                          int frame_id, const SettleOut &so, unsigned *lhist, int slice) {
+                                          int frame_id, const SettleOut &so, unsigned *lhist, int h, int slice) {
     __shared__ unsigned s_max;
-    const int h = blockIdx.y, tid = threadIdx.x, nt = blockDim.x;
+    const int tid = threadIdx.x, nt = blockDim.x;
     const int L = min(len[h], C);
     if (L + n_new <= C) return;   // uniform over the head: no eviction can be needed
     for (int k = tid; k < AGE_BINS; k += nt) lhist[k] = 0;
@@ -1231,7 +1241,7 @@ __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__
     const int h = blockIdx.y;
     const int n_tok_wgs = (int)gridDim.x - n_slices;
     if ((int)blockIdx.x >= n_tok_wgs) {   // uniform
-        age_slice(len, stamp, C, n_new, frame_id, so, lhist, (int)blockIdx.x - n_tok_wgs);
+        age_slice(len, stamp, C, n_new, frame_id, so, lhist, h, (int)blockIdx.x - n_tok_wgs);
         return;
     }
     if (so.hs && blockIdx.x == 0 && threadIdx.x == 0) so.hs[(size_t)h * HS_STRIDE] = min(len[h], C);
@@ -2722,10 +2732,11 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
             gx = (n_new + per - 1) / per;
         }
         // the age histogram beside the match: a workgroup per 8192 slots (one round of loads, 4 x 16 bytes per thread)
-        const int n_hist = settle ? (fused_verify ? settle_slices(C) : 0) : fused_verify && !wide && !self_hist ? (C + 8191) / 8192 : 0;
-        const dim3 grid(gx + n_hist, H);
+        const int n_hist = !fused_verify || wide ? 0 : settle ? settle_slices(C) : !self_hist ? (C + 8191) / 8192 : 0;
+        const int hist_rows = settle && fused_verify && wide ? (settle_slices(C) * H + gx - 1) / gx : 0;   // behind the heads' rows
+        const dim3 grid(gx + n_hist, H + hist_rows);
         const bool bf = dtype == FASTAR_BF16;
-        const VerifyArgs va = {cache->K, tau2_q16, merged, cache->stamp, frame_id, self_hist ? -1 : PS_HIST, PS_FUT, so};
+        const VerifyArgs va = {cache->K, tau2_q16, merged, cache->stamp, frame_id, self_hist ? -1 : PS_HIST, PS_FUT, H, so};
         int rc = FASTAR_OK;
 #define FASTAR_WIN(RR, ENC, BF, DD, VER, TT)                                                                              \
     rc = launch_match_window<RR, ENC, BF, DD, VER, TT>(grid, win_lds, s, cache->code, cache->len, C, cp, n_new, cand,      \

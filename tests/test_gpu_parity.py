@@ -1147,6 +1147,40 @@ def test_tempcache_short_caches_settle_in_one_launch(dtype, d, H, T, C, free, lo
         assert (st[:, 3] > 0).all()
 
 
+# Many workgroups: the age slices behind the tokens of the wide window match; both sides of the lines beyond which the plan and
+# apply launches settle frames of more than 2048 (2048 workgroups of the one launch) and 4096 tokens (4096); each kind of key.
+@pytest.mark.parametrize("H,T,C,n_cand,rep_mode", [
+    (48, 700, 9000, 2400, fa.REP_LAST), (36, 900, 16400, 2000, fa.REP_MEDOID),
+    (20, 2100, 3000, 700, fa.REP_MEAN), (21, 2100, 3000, 700, fa.REP_MEAN), (20, 2100, 3000, 2200, fa.REP_MEDOID),
+    (21, 4097, 6000, 500, fa.REP_MEDOID), (22, 4097, 6000, 500, fa.REP_LAST)])
+def test_tempcache_settles_large_grids(H, T, C, n_cand, rep_mode):
+    rng = np.random.default_rng(C + H)
+    d, r, dtype = 64, 32, "bf16"
+    codec = make_codec(0, 9, d, r)
+    normal = lambda *shape: to_storage(rng.standard_normal(shape, dtype=np.float32), dtype)
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:], ref.V[:] = normal(H, C, d), normal(H, C, d)
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(0, 9, size=(H, C))
+    ref.len[:] = C
+    gpu = dev_cache(ref)
+    ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
+    for f in range(2):
+        cand = np.stack([rng.choice(C, size=n_cand, replace=False) for _ in range(H)]).astype(np.int32)
+        K_new, V_new = normal(H, T, d), normal(H, T, d)
+        for h in range(H):             # half of the frame repeats candidates, some of them several times
+            K_new[h, : T // 2] = ref.K[h, rng.choice(cand[h], size=T // 2)]
+        args = dict(tau2_q16=TAU2(0.9), frame_id=9 + f, rep_mode=rep_mode)
+        expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+        got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws, ws_persistent=True, **args)
+        sync()
+        assert (expect[2][:, 1] > 0).all() and (expect[2][:, 3] > 0).all()
+        for a, b in zip(got, expect):
+            assert np.array_equal(to_host(a), b), f
+        assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 # where an age does not tell the stamp: the threshold among stamps in the future, alone or beside the frame's own and older ones,
 # among ages of 1023 and more in one, two and four digits of their range, at both ends of the numbers; frames of both list sizes
 @pytest.mark.parametrize("dtype,H,T,C,lo,hi,step,frame", [
