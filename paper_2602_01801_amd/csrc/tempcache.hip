@@ -637,7 +637,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     i32x4 *ccode = (i32x4 *)wlds;                       // [NCH][n_pad]
     int *cslot = (int *)(wlds + (size_t)NCH * n_pad * 16);  // [n_pad]
     int *cpen = cslot + n_pad;                          // [n_pad]
-    typedef WindowScan<R, TOKS, false> WS;
+    constexpr bool ORDERED = TOKS >= 256;               // how the window is staged
+    typedef WindowScan<R, TOKS, ORDERED> WS;
     constexpr int NG = WS::NG, TQ = WS::TQ, SPLIT = WS::SPLIT;
     // partial arg-maxima of the scan; R before it, the verify hand-over and the age histogram after it
     __shared__ __attribute__((aligned(16))) u64 partbest[SPLIT][TOKS];
@@ -665,12 +666,15 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     const int swave = __builtin_amdgcn_readfirstlane(wave);   // uniform: the scan's bookkeeping stays in scalar registers
     const int tq = swave % TQ, ch = swave / TQ;
     const int8_t *ch_code = code + (size_t)h * C * R;
-    // The candidate list is a SET of slots: a repeat counts once (a bitmap over the slots, held where the codes will go, in
-    // several passes when the cache is longer than that area, tells who came first), ids outside [0, L) not at all; ties
-    // go to the smallest slot, which the look-up decides, so the window is staged in the order of the list:
-    //   1. every thread reads its entries of the list and asks for their code rows;
-    //   2. while these are in flight, repeats are struck out and the first block of tokens is encoded;
-    //   3. the rows go to their positions.
+    // The candidate list is a SET of slots: ids outside [0, L) do not count and a repeat only once, and ties go to the smallest
+    // slot.  A bitmap over the slots, held where the codes will go (in several passes when the cache is longer than that area),
+    // tells repeats.
+    //   64 tokens: the window is staged in the order of the list and the look-up decides ties.
+    //   256 tokens (ORDERED): a workgroup stages once for several blocks, so there it pays to rank the ids (set bits, prefix
+    //   counts per word) and stage the rows in slot order, odd penalties first (WindowScan): position order then is all that the
+    //   arg-max needs, the scan notes no ties, and repeats are not scanned.  Call at 40 heads x 3600 tokens x 230400 slots 162 us
+    //   in list order, 152 ranked; 5 x 3600 (64 tokens) 54, 61.
+    // The candidates' code rows are in flight meanwhile, and the first block of tokens is encoded.
     constexpr int CPT = ((int)(WINDOW_LDS_MAX / (R + 8)) + WIN_THREADS - 1) / WIN_THREADS;   // list entries per thread
     // of them, rows in flight while the ids are ranked (registers); the rows beyond are loaded when their ranks are known
     constexpr int PF = R == 32 ? (TOKS >= 256 ? CPT : BF16 ? 4 : 2) : 2;
@@ -713,8 +717,13 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     constexpr bool EARLY = BF16 || TOKS == 64;   // the first block's rows in flight while the window is staged (registers)
     if (EARLY && enc_wave) load_block(t0);
     unsigned *bm = (unsigned *)wlds;             // bitmap of the slots, [words]
-    const int words = R * n_pad / 4;             // the code area
+    const int words = R * n_pad / (ORDERED ? 8 : 4);   // the code area; ordered, prefix counts of the words take half of it
+    unsigned *wpre = bm + words;
     for (int w = tid; w < min((C + 31) >> 5, words); w += WIN_THREADS) bm[w] = 0u;
+    __shared__ int s_wtot[WIN_THREADS / 64];
+    __shared__ u64 s_odd[WAVE];                  // by rank in slot order: the candidates with an odd penalty
+    static_assert(WINDOW_LDS_MAX / (R + 8) <= 64 * WAVE, "one word of s_odd per lane");
+    if (ORDERED && tid < WAVE) s_odd[tid] = 0ull;
     if (rm_lds && tid < D * R / 8) ((u64 *)partbest)[tid] = rm_part;
 #pragma unroll
     for (int k = 0; k < CPT; ++k)
@@ -740,6 +749,10 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
             if (etok < lim) cm.store(ck + ((size_t)h * n_new + etok) * R, w, lane);
         }
     };
+    int pos[CPT];
+    int n_u = 0;   // ordered: staged candidates, positions 0 .. n_u-1 (uniform over the workgroup)
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) pos[k] = ORDERED ? -1 : k * WIN_THREADS + tid;
     for (int lo = 0; lo < L; lo += 32 * words) {   // uniform; one pass unless the cache is long for the list
         const int nw = min((L - lo + 31) >> 5, words);
         if (lo > 0) {
@@ -749,9 +762,45 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
-            if (n_cand <= k * WIN_THREADS) break;   // uniform
+            if (n_cand <= k * WIN_THREADS) break;   // uniform, here and below
             const int o = ce[k] - lo;
-            if (ce[k] >= lo && o < 32 * nw && ((atomicOr(&bm[o >> 5], 1u << (o & 31)) >> (o & 31)) & 1u)) ce[k] = -1;   // below every later lo
+            if (ce[k] >= lo && o < 32 * nw) {
+                const unsigned old = atomicOr(&bm[o >> 5], 1u << (o & 31));
+                if (!ORDERED && ((old >> (o & 31)) & 1u)) ce[k] = -1;   // below every later lo
+            }
+        }
+        if constexpr (ORDERED) {
+            __syncthreads();
+            // a thread owns a run of consecutive words, an odd number of them (their addresses spread over the banks); the
+            // counts are those of the bits below within the wavefront's words
+            const int wpt = ((nw + WIN_THREADS - 1) / WIN_THREADS) | 1;
+            const int w0 = tid * wpt, w1 = min(w0 + wpt, nw);
+            int c = 0;
+            for (int w = w0; w < w1; ++w) c += __popc(bm[w]);
+            const int incl = (int)wave_incl_scan((unsigned)c);
+            if (lane == 63) s_wtot[wave] = incl;
+            int run = incl - c;
+            for (int w = w0; w < w1; ++w) {
+                wpre[w] = (unsigned)run;
+                run += __popc(bm[w]);
+            }
+            __syncthreads();
+            int wtot[WIN_THREADS / 64];
+#pragma unroll
+            for (int q = 0; q < WIN_THREADS / 64; ++q) wtot[q] = s_wtot[q];
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) {
+                if (n_cand <= k * WIN_THREADS) break;
+                const int o = ce[k] - lo, w = o >> 5;
+                if (ce[k] >= lo && o < 32 * nw) {
+                    int below = n_u + (int)wpre[w] + __popc(bm[w] & ((1u << (o & 31)) - 1u));
+#pragma unroll
+                    for (int q = 0; q + 1 < WIN_THREADS / 64; ++q) below += w >= 64 * wpt * (q + 1) ? wtot[q] : 0;
+                    pos[k] = below;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < WIN_THREADS / 64; ++q) n_u += wtot[q];
         }
     }
     if (L <= 0) __syncthreads();   // R has been stored
@@ -761,20 +810,49 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         if (!EARLY) load_block(t0);
         encode_block(t0, min(t0 + TOKS, t1));
     }
-    __syncthreads();   // the bitmap is dead: its memory takes the codes
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-        if (n_cand <= k * WIN_THREADS) break;   // uniform
-        const int p = k * WIN_THREADS + tid;
-        if (p >= n_pad) continue;
-        i32x4 rw[NCH];
+    // the code row of list entry k, where it was not asked for in advance
+    auto row_of = [&](int k, i32x4 (&rw)[NCH]) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             rw[c] = i32x4{0, 0, 0, 0};
             if (k < PF) rw[c] = row[k < PF ? k : 0][c];
             else if (ce[k] >= 0) rw[c] = *(const i32x4 *)(ch_code + (size_t)ce[k] * R + c * 16);
         }
-        WS::stage(ccode, cslot, cpen, n_pad, metric, p, ce[k], rw);
+    };
+    if (ORDERED && metric == 0) {   // uniform: stable partition by the parity of the penalty
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            if (n_cand <= k * WIN_THREADS) break;
+            if (pos[k] < 0) continue;
+            i32x4 rw[NCH];
+            row_of(k, rw);
+            if (WS::odd_penalty(rw)) atomicOr(&s_odd[pos[k] >> 6], 1ull << (pos[k] & 63));
+        }
+    }
+    __syncthreads();   // the bitmap is dead: its memory takes the codes
+    int n_odd = 0;
+    if constexpr (ORDERED) {
+        const OddFirst odd_first(s_odd);
+        n_odd = odd_first.n_odd;
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) {
+            if (n_cand <= k * WIN_THREADS) break;
+            const int p = odd_first.place(max(pos[k], 0));   // whole wavefronts
+            if (pos[k] >= 0) pos[k] = p;
+        }
+    }
+    const int n_stage = ORDERED ? (n_u + 31) & ~31 : n_pad;   // <= n_pad
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        if (n_cand <= k * WIN_THREADS) break;
+        if (pos[k] < 0 || pos[k] >= n_pad) continue;
+        i32x4 rw[NCH];
+        row_of(k, rw);
+        WS::stage(ccode, cslot, cpen, n_pad, metric, pos[k], ce[k], rw);
+    }
+    if (ORDERED && tid < n_stage - n_u) {   // the ragged end of the last group of 32
+        const i32x4 none[NCH] = {};
+        WS::stage(ccode, cslot, cpen, n_pad, metric, n_u + tid, -1, none);
     }
     for (int base = t0; base < t1; base += TOKS) {
     const int lim = min(base + TOKS, t1);   // this block's tokens: [base, lim)
@@ -797,7 +875,7 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
                                : *(const i32x4 *)(cp + ((size_t)h * n_new + min(base + t, n_new - 1)) * R + ks * 32 + 16 * g2);
         }
     // a wavefront whose tokens all lie beyond the block's end scans nothing (uniform over the wavefront)
-    WS::scan(ccode, cpen, n_pad, base + tq * NG * 32 < lim ? n_pad / 32 : 0, tq, ch, bfrag, partbest);
+    WS::scan(ccode, cpen, n_pad, base + tq * NG * 32 < lim ? n_stage / 32 : 0, tq, ch, bfrag, partbest);
     __syncthreads();
     {
         constexpr int TPT = WS::TPT;
@@ -806,42 +884,49 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + min(tok, n_new - 1)) * R;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
-        int T;
-        bool tie;
-        unsigned winner = WS::find(ccode, cslot, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, tie);
-        // A tied token's threads would go through all candidates for longer than the whole scan takes, and one token in a
-        // thousand is enough for the launch to wait: the workgroup does it together.
-        if (__syncthreads_or(tie)) {   // the scan's words are done with: (T, winner) per token, then the list of tied ones
-            static_assert(SPLIT >= 3, "three rows of words");
-            unsigned *best_of = (unsigned *)partbest[1], *tied = (unsigned *)partbest[2];
-            if (tid == 0) n_tied = 0;
-            __syncthreads();
-            if (tie && sub == 0) {
-                best_of[2 * t] = winner;
-                best_of[2 * t + 1] = (unsigned)T;
-                tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
-            }
-            __syncthreads();
-            const int n = n_tied;
-            for (int q = 0; q < n; ++q) {
-                const int tt = (int)tied[q];
-                const int8_t *trow = ENC ? pcode + tt * R : cp + ((size_t)h * n_new + min(base + tt, n_new - 1)) * R;
-                i32x4 tc[NCH];
+        int T, j, S;   // best score, slot (-1: none), score with the parity
+        if constexpr (ORDERED) {
+            int at;
+            const bool seen = WS::look_up(ccode, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, at);
+            j = seen ? cslot[at] : -1;
+            S = !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T;
+        } else {
+            bool tie;
+            unsigned winner = WS::find(ccode, cslot, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, tie);
+            // A tied token's threads would go through all candidates for longer than the whole scan takes, and one token in a
+            // thousand is enough for the launch to wait: the workgroup does it together.
+            if (__syncthreads_or(tie)) {   // the scan's words are done with: (T, winner) per token, then the list of tied ones
+                static_assert(SPLIT >= 3, "three rows of words");
+                unsigned *best_of = (unsigned *)partbest[1], *tied = (unsigned *)partbest[2];
+                if (tid == 0) n_tied = 0;
+                __syncthreads();
+                if (tie && sub == 0) {
+                    best_of[2 * t] = winner;
+                    best_of[2 * t + 1] = (unsigned)T;
+                    tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
+                }
+                __syncthreads();
+                const int n = n_tied;
+                for (int q = 0; q < n; ++q) {
+                    const int tt = (int)tied[q];
+                    const int8_t *trow = ENC ? pcode + tt * R : cp + ((size_t)h * n_new + min(base + tt, n_new - 1)) * R;
+                    i32x4 tc[NCH];
 #pragma unroll
-                for (int c = 0; c < NCH; ++c) tc[c] = *(const i32x4 *)(trow + 16 * c);
-                for (int rw = tid; rw < n_pad; rw += WIN_THREADS)
-                    if (WS::score(ccode, cpen, n_pad, tc, rw) == (int)best_of[2 * tt + 1]) atomicMin(&best_of[2 * tt], (unsigned)cslot[rw]);
+                    for (int c = 0; c < NCH; ++c) tc[c] = *(const i32x4 *)(trow + 16 * c);
+                    for (int rw = tid; rw < n_pad; rw += WIN_THREADS)
+                        if (WS::score(ccode, cpen, n_pad, tc, rw) == (int)best_of[2 * tt + 1]) atomicMin(&best_of[2 * tt], (unsigned)cslot[rw]);
+                }
+                __syncthreads();
+                if (tie) winner = best_of[2 * t];
+                __syncthreads();   // the words are handed on below
             }
-            __syncthreads();
-            if (tie) winner = best_of[2 * t];
-            __syncthreads();   // the words are handed on below
+            const bool seen = winner != 0xFFFFFFFFu;
+            j = seen ? (int)(winner & ~SLOT_EVEN) : -1;
+            S = !seen ? 0 : metric == 0 ? 2 * T + (winner & SLOT_EVEN ? 0 : 1) : T;
         }
         if (sub == 0) {
-            const bool seen = winner != 0xFFFFFFFFu;
-            const int j = seen ? (int)(winner & ~SLOT_EVEN) : -1;
-            const int S = !seen ? 0 : metric == 0 ? 2 * T + (winner & SLOT_EVEN ? 0 : 1) : T;
             if (tok < lim) {
-                if (!VERIFY && seen) {
+                if (!VERIFY && j >= 0) {
                     win[(size_t)h * C + j] = 0;
                     grp[(size_t)h * C + j] = 0;
                 }
