@@ -398,6 +398,44 @@ struct WindowScan {
         for (int off = 1; off < TPT; off <<= 1) winner = min(winner, (unsigned)shfl_xor((int)winner, off));
         return winner;
     }
+    // A second scan for candidates in any order, of which the best score is known (best_of: (winner so far, score) per token):
+    // the smallest cslot word among those that reach it.
+    __device__ static __forceinline__ void settle(const i32x4 *ccode, const int *cslot, const int *cpen, int n_pad, int n_groups,
+                                                  int tq, int ch, const i32x4 (&bfrag)[NG][KS], unsigned *best_of) {
+        const int lane = lane_id(), col = lane & 31, g2 = lane >> 5;
+        int best[NG];
+        unsigned w[NG];
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            best[u] = (int)best_of[2 * ((tq * NG + u) * 32 + col) + 1];
+            w[u] = 0xFFFFFFFFu;
+        }
+        for (int gi = ch; gi < n_groups; gi += SPLIT) {
+            i32x4 a[KS], sl[4];
+            i32x16 pen;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) a[ks] = ccode[(2 * ks + g2) * n_pad + gi * 32 + col];
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const i32x4 np = *(const i32x4 *)(&cpen[gi * 32 + 8 * q4 + 4 * g2]);
+                sl[q4] = *(const i32x4 *)(&cslot[gi * 32 + 8 * q4 + 4 * g2]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pen[4 * q4 + e] = np[e];
+            }
+#pragma unroll
+            for (int u = 0; u < NG; ++u) {
+                i32x16 acc = pen;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(a[ks], bfrag[u][ks], acc);
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    w[u] = min(w[u], acc[v] == best[u] ? (unsigned)sl[v >> 2][v & 3] : 0xFFFFFFFFu);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < NG; ++u)
+            if (w[u] != 0xFFFFFFFFu) atomicMin(&best_of[2 * ((tq * NG + u) * 32 + col)], w[u]);
+    }
     __device__ static __forceinline__ int score(const i32x4 *ccode, const int *cpen, int n_pad, const i32x4 (&pc)[NCH], int rw) {
         int dot = 0;
 #pragma unroll
@@ -893,28 +931,40 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         } else {
             bool tie;
             unsigned winner = WS::find(ccode, cslot, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, tie);
-            // A tied token's threads would go through all candidates for longer than the whole scan takes, and one token in a
-            // thousand is enough for the launch to wait: the workgroup does it together.
-            if (__syncthreads_or(tie)) {   // the scan's words are done with: (T, winner) per token, then the list of tied ones
+            // Ties between groups are settled by the workgroup: one token in a thousand has one on drawn data, most of them on a
+            // picture with flat areas.  (winner so far, T) per token, and a list of the tied ones.  Up to MANY of them share
+            // the wavefronts, which go through all candidates; more, and all go through the matrix products once more.  Launch at 12 heads x
+            // 1560 tokens, share of tokens and candidates that take one of two values 0 / 2 / 10 / 50 / 100 %, us: 19 / 22 / 32 / 132 /
+            // 344 with the workgroup on one token after the other; now 18 / 21 / 24 / 24 / 23.
+            if (__syncthreads_or(tie)) {   // the scan's words are done with
                 static_assert(SPLIT >= 3, "three rows of words");
+                constexpr int MANY = WIN_THREADS / 64;
                 unsigned *best_of = (unsigned *)partbest[1], *tied = (unsigned *)partbest[2];
                 if (tid == 0) n_tied = 0;
                 __syncthreads();
-                if (tie && sub == 0) {
+                if (sub == 0) {
                     best_of[2 * t] = winner;
-                    best_of[2 * t + 1] = (unsigned)T;
-                    tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
+                    best_of[2 * t + 1] = (unsigned)(tie ? T : INT_MAX);   // INT_MAX: no candidate scores that
+                    if (tie) tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
                 }
                 __syncthreads();
                 const int n = n_tied;
-                for (int q = 0; q < n; ++q) {
-                    const int tt = (int)tied[q];
+                if (n > MANY) {   // uniform
+                    WS::settle(ccode, cslot, cpen, n_pad, n_pad / 32, tq, ch, bfrag, best_of);
+                } else {
+                    const int share = n > 4 ? 1 : n > 2 ? 2 : n > 1 ? 4 : 8;   // wavefronts per token
+                    const int q = min(swave / share, n - 1);                    // the last token's repeat their work
+                    const int tt = (int)tied[q], best = (int)best_of[2 * tt + 1];
                     const int8_t *trow = ENC ? pcode + tt * R : cp + ((size_t)h * n_new + min(base + tt, n_new - 1)) * R;
                     i32x4 tc[NCH];
 #pragma unroll
                     for (int c = 0; c < NCH; ++c) tc[c] = *(const i32x4 *)(trow + 16 * c);
-                    for (int rw = tid; rw < n_pad; rw += WIN_THREADS)
-                        if (WS::score(ccode, cpen, n_pad, tc, rw) == (int)best_of[2 * tt + 1]) atomicMin(&best_of[2 * tt], (unsigned)cslot[rw]);
+                    unsigned w = 0xFFFFFFFFu;
+#pragma unroll 4
+                    for (int rw = 64 * (swave & (share - 1)) + lane; rw < n_pad; rw += 64 * share)
+                        if (WS::score(ccode, cpen, n_pad, tc, rw) == best) w = min(w, (unsigned)cslot[rw]);
+                    w = ~wave_max_last(~w);
+                    if (lane == 63) atomicMin(&best_of[2 * tt], w);
                 }
                 __syncthreads();
                 if (tie) winner = best_of[2 * t];

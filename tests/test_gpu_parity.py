@@ -1075,6 +1075,41 @@ def test_tempcache_candidates_that_all_tie_go_to_the_smallest_slot(H, T, C, n_ca
     assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
 
 
+@pytest.mark.parametrize("T,n_cand,r,share,metric", [(64, 700, 32, 0.08, 0), (130, 1560, 32, 0.25, 0), (64, 3700, 32, 0.9, 0),
+                                                     (100, 1000, 64, 0.15, 0), (100, 1000, 64, 0.6, 1), (64, 40, 32, 0.5, 1)])
+def test_tempcache_some_candidates_tie_and_their_slots_come_in_any_order(T, n_cand, r, share, metric):
+    # one to a dozen values that a share of the keys takes, so that a block of 64 tokens has anything from no tied token to all:
+    # a wavefront for each up to eight of them, another pass over the products beyond
+    rng = np.random.default_rng(T + n_cand)
+    H, C, d, dtype = 6, 5000, 64, "bf16"
+    codec = make_codec(0, 9, d, r)
+    values = rng.standard_normal((12, d)).astype(np.float32)
+
+    def keys(*shape):
+        k = rng.standard_normal((*shape, d)).astype(np.float32)
+        few = np.minimum(rng.integers(0, 12, size=shape), np.arange(shape[0])[:, None] * 2)
+        return to_storage(np.where((rng.random(shape) < share)[..., None], values[few], k), dtype)
+
+    ref = oracle.Cache.empty(H, C, d, r, dtype)
+    ref.K[:] = keys(H, C)
+    ref.V[:] = to_storage(rng.standard_normal((H, C, d)).astype(np.float32), dtype)
+    ref.code[:] = oracle.encode(ref.K, codec.R, codec.qscale, codec.shift)
+    ref.cnt[:] = 1
+    ref.stamp[:] = rng.integers(0, 9, size=(H, C))
+    ref.len[:] = C - 9
+    gpu = dev_cache(ref)
+    cand = rng.integers(-2, C, size=(H, n_cand)).astype(np.int32)
+    K_new, V_new = keys(H, T), to_storage(rng.standard_normal((H, T, d)).astype(np.float32), dtype)
+    args = dict(tau2_q16=TAU2(0.9), frame_id=9, metric=metric)
+    ws = torch.zeros(fa.workspace_bytes(fa.OP_COMPRESS, H, T, C, r), dtype=torch.uint8, device="cuda")
+    expect = oracle.tempcache_compress(ref, codec.R, codec.qscale, codec.shift, K_new, V_new, cand=cand, **args)
+    got = fa.tempcache_compress(gpu, dev_codec(codec), to_dev(K_new), to_dev(V_new), cand=to_dev(cand), ws=ws, ws_persistent=True, **args)
+    sync()
+    for a, b in zip(got, expect):
+        assert np.array_equal(to_host(a), b)
+    assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
+
+
 # (dtype, d, H, T, C, free slots, stamps from / to, frame id, what else): edges of the age histogram's slices (8192 slots), of
 # the list of unmerged tokens (512 tokens per round, 2048 and 8192 in all), of the cache (no eviction, some, all and too
 # few evictable slots), of the histogram (a stamp in the future, a threshold in or beyond the last bin, stamps that wrap)
@@ -1152,7 +1187,8 @@ def test_tempcache_short_caches_settle_in_one_launch(dtype, d, H, T, C, free, lo
 @pytest.mark.parametrize("H,T,C,n_cand,rep_mode", [
     (48, 700, 9000, 2400, fa.REP_LAST), (36, 900, 16400, 2000, fa.REP_MEDOID),
     (20, 2100, 3000, 700, fa.REP_MEAN), (21, 2100, 3000, 700, fa.REP_MEAN), (20, 2100, 3000, 2200, fa.REP_MEDOID),
-    (21, 4097, 6000, 500, fa.REP_MEDOID), (22, 4097, 6000, 500, fa.REP_LAST)])
+    (21, 4097, 6000, 500, fa.REP_MEDOID), (22, 4097, 6000, 500, fa.REP_LAST),
+    (24, 15360, 17000, 120, fa.REP_LAST)])   # the wide match's bitmap of the slots in two passes
 def test_tempcache_settles_large_grids(H, T, C, n_cand, rep_mode):
     rng = np.random.default_rng(C + H)
     d, r, dtype = 64, 32, "bf16"
