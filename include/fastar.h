@@ -247,8 +247,9 @@ int ann_select_lsh_buckets(const uint32_t *qbits, int n_q, const uint32_t *kbits
  *                              token of the head is reported dropped (merge_map -1, merged 0, n_dropped = n_new), and a
  *                              persistent workspace has to be zero-filled again before its next use; 2 if the stamps
  *                              of the evictable slots span 2^20 frames or more: the choice of victims is then not
- *                              guaranteed to be the oldest-first one.  With ws_persistent, C <= 65536 and n_new <= 8192
- *                              neither occurs: nothing waits there, and the choice is exact for any stamps;
+ *                              guaranteed to be the oldest-first one.  With ws_persistent, C <= 65536 and n_new <= 2048
+ *                              neither occurs: nothing waits there, and the choice is exact for any stamps (frames of
+ *                              up to 8192 tokens too while the heads are few);
  *                              3 if ws_persistent was set for a workspace that is neither zero-filled nor left by
  *                              a finished call: nothing is applied either (as for status 1)
  *   ws / ws_bytes              workspace of fastar_workspace_bytes(FASTAR_OP_COMPRESS, ...), 256-byte aligned

@@ -32,7 +32,7 @@ int fastar_probe_copy(const void *src, void *dst, size_t bytes, void *stream);
  * every such wait by `spin_limit` polls (negative: the built-in limit) and wait for `extra_arrivals` arrivals more than
  * will ever come (0: none), so a test can make the waits run out while every workgroup still finishes; the call then
  * reports status 1 for the heads concerned and leaves their cache untouched (see tempcache_compress).  Calls on a
- * persistent workspace with C <= 65536 and n_new <= 8192 have no such wait.
+ * persistent workspace with C <= 65536 and n_new <= 2048 have no such wait (see there).
  * fastar_debug_plan_wait(-1, 0) restores the normal behaviour.  Host state only; FASTAR_ERR_INVALID_ARG for a negative
  * extra_arrivals.
  */

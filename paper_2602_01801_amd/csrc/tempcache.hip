@@ -2332,6 +2332,32 @@ static size_t settle_lds_bytes(int C, int n_new) {
     return (size_t)((C + 63) / 64) * 8 + (size_t)((n_new + 7) & ~7) * 2 + SETTLE_SLICE * 2;
 }
 
+// Workgroups of tc_settle_kernel, per head, and whether it is the better way.  Shares of a slice's victims: as many as would have
+// 64 rows each if nothing merged; every one of them reads the frame's lists, so 128 rows in the form for frames of more than
+// 2048 tokens once its workgroups are more than reside at once (512).  Beyond that it is a question of how many times over:
+// plan and apply launches against the one, us per call, bf16, d = 128 (workgroups):
+//   up to 2048 tokens, at any size measured: 40 heads x 1560 x 37440 slots (2960) 72 -> 70, 40 x 2048 x 63488 (4800) 99 -> 99,
+//     12 x 1560 x 37440 (888) 39 -> 33, fp32 24 x 2048 x 49152 (2496) 83 -> 69;
+//   up to 4096: 5 x 3600 x 64800 (885) 59 -> 54, 14 x 3600 x 57600 (2030) 78 -> 74, 16 x 3600 x 57600 (2320) 85 -> 84,
+//     16 x 4096 x 61440 (2560) 146 -> 152, 40 x 2100 x 42000 (3360) 97 -> 104, 40 x 3600 x 21600 (5720) 144 -> 166;
+//   longer ones, which the plan reads again and again: 4 x 8000 x 64000 160 -> 119, 20 x 8000 x 64000 (6280) 462 -> 448,
+//     30 x 6000 x 30000 (7080) 411 -> 417, 40 x 8000 x 24000 (12520) 838 -> 868.
+struct SettleGrid {
+    int n_reps, wgs;   // shares per slice; workgroups per head
+    bool better;
+};
+static SettleGrid settle_grid(int H, int C, int n_new) {
+    const int n_slices = settle_slices(C), tok_wgs = (n_new + SETTLE_GROUPS - 1) / SETTLE_GROUPS;
+    SettleGrid g;
+    for (int rows = 64; rows <= 128; rows *= 2) {
+        g.n_reps = ((n_new + rows - 1) / rows + n_slices - 1) / n_slices;
+        g.wgs = n_slices * g.n_reps + tok_wgs;
+        if (n_new <= 2048 || (int64_t)g.wgs * H <= 512) break;
+    }
+    g.better = n_new <= 2048 || (int64_t)g.wgs * H <= (n_new <= 4096 ? 2400 : 6400);
+    return g;
+}
+
 struct Pair {
     unsigned a, b;
 };
@@ -2834,7 +2860,9 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     const bool fused_verify = fused_encode && ws_persistent;   // ... and verifies its matches: nothing to clear first
     // Plan and apply in one launch: short caches, whose age histograms are small enough to be read by every workgroup, and
     // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
-    const bool settle = ws_persistent && C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
+    const bool fits = C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
+    const SettleGrid sg = fits ? settle_grid(H, C, n_new) : SettleGrid{};
+    const bool settle = ws_persistent && fits && sg.better;
     const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age),
                                           (int32_t *)(base + w.slot_stamp)} : SettleOut{};
     // Calls without a window do not rely on clean group records (see fastar.h).
@@ -2940,14 +2968,12 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         FASTAR_LAUNCH_CHECK();
     }
     if (settle) {
-        // as many workgroups for the victims as would have 64 rows each if nothing merged
-        const int n_slices = settle_slices(C), n_reps = ((n_new + 63) / 64 + n_slices - 1) / n_slices;
-        const dim3 sgrid(n_slices * n_reps + (n_new + SETTLE_GROUPS - 1) / SETTLE_GROUPS, H);
+        const dim3 sgrid(sg.wgs, H);
         const size_t lds = settle_lds_bytes(C, n_new);
 #define FASTAR_SETTLE_T(BF, DD, TT)                                                                                      \
     hipLaunchKernelGGL((tc_settle_kernel<BF, DD, TT>), sgrid, dim3(SETTLE_THREADS), lds, s, cache->K, cache->V, cache->code,    \
                        cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new, frame_id, jstar, merged, win, grp, hs,     \
-                       merge_map, cache->len, rep_mode, so.tstamp, so.ages, so.slot_age, so.slot_stamp, n_reps, stats)
+                       merge_map, cache->len, rep_mode, so.tstamp, so.ages, so.slot_age, so.slot_stamp, sg.n_reps, stats)
 #define FASTAR_SETTLE(BF, DD)                                  \
     do {                                                       \
         if (n_new <= 4 * SETTLE_THREADS) FASTAR_SETTLE_T(BF, DD, 4); \

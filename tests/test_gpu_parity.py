@@ -1183,11 +1183,11 @@ def test_tempcache_short_caches_settle_in_one_launch(dtype, d, H, T, C, free, lo
 
 
 # Many workgroups: the age slices behind the tokens of the wide window match; both sides of the lines beyond which the plan and
-# apply launches settle frames of more than 2048 (2048 workgroups of the one launch) and 4096 tokens (4096); each kind of key.
+# apply launches settle frames of more than 2048 (2400 workgroups of the one launch) and 4096 tokens (6400); each kind of key.
 @pytest.mark.parametrize("H,T,C,n_cand,rep_mode", [
     (48, 700, 9000, 2400, fa.REP_LAST), (36, 900, 16400, 2000, fa.REP_MEDOID),
-    (20, 2100, 3000, 700, fa.REP_MEAN), (21, 2100, 3000, 700, fa.REP_MEAN), (20, 2100, 3000, 2200, fa.REP_MEDOID),
-    (21, 4097, 6000, 500, fa.REP_MEDOID), (22, 4097, 6000, 500, fa.REP_LAST),
+    (28, 2100, 3000, 700, fa.REP_MEAN), (29, 2100, 3000, 700, fa.REP_MEAN), (5, 2100, 3000, 2200, fa.REP_MEDOID),
+    (39, 4097, 6000, 500, fa.REP_MEDOID), (40, 4097, 6000, 500, fa.REP_LAST),
     (24, 15360, 17000, 120, fa.REP_LAST)])   # the wide match's bitmap of the slots in two passes
 def test_tempcache_settles_large_grids(H, T, C, n_cand, rep_mode):
     rng = np.random.default_rng(C + H)
