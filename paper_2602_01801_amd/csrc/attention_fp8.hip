@@ -49,11 +49,10 @@ __device__ __forceinline__ float clamp_f8(float x) { return fminf(fmaxf(x, -F8_M
 
 // ---- the 8-bit copy of the cache ------------------------------------------------------------------------------
 // A block of 64 slots that holds no live slot stamped >= stamp_lo is left alone; any other is rewritten whole: live slots with
-// the codes of the stored rows, dead slots with zero.  What bounds it: a frame leaves most of a long cache alone, so with a
-// workgroup per block the launch was bound by starting them (144000 at 40 heads x 230400 slots, 86 us; 47 now);
-// a workgroup looks at CPB blocks, gridDim.x apart, so that a run of slots that one frame wrote is spread over many.
-constexpr int CPB = 16;
-template <bool BF16>
+// the codes of the stored rows, dead slots with zero.  What bounds it: the rows that are rewritten, and on a long cache, of
+// which a frame leaves most alone, the starting of workgroups.  A workgroup looks at PER blocks, gridDim.x apart so that a run of
+// slots that one frame wrote is spread over many, and rewrites its own one after the other.
+template <bool BF16, int PER>
 __global__ __launch_bounds__(256) void kv_to_fp8_kernel(const void *__restrict__ K, const void *__restrict__ V,
                                                         const int32_t *__restrict__ stamp, const int32_t *__restrict__ len,
                                                         int C, int n_blk, int stamp_lo, uint8_t *__restrict__ K8,
@@ -63,24 +62,32 @@ __global__ __launch_bounds__(256) void kv_to_fp8_kernel(const void *__restrict__
     const int h = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int L = min(len[h], C);
-    {
-        int st[CPB / 4];
+    if constexpr (PER == 1) {   // the first wavefront looks; the others, and most workgroups, are done at the barrier
+        if (tid == 0) dirty_of[0] = 0u;
+        __syncthreads();
+        if (tid < TK) {
+            const int slot = blockIdx.x * TK + tid;
+            if (slot < L && stamp[(size_t)h * C + slot] >= stamp_lo) dirty_of[0] = 1u;
+        }
+    } else {
+        constexpr int EACH = (PER + 3) / 4;   // a wavefront looks at blocks 4 e + wave of the workgroup's
+        int st[EACH];
+        bool live[EACH];
 #pragma unroll
-        for (int e = 0; e < CPB / 4; ++e) {   // a wavefront per block: block 4 e + wave of the workgroup's
-            const long long slot = ((long long)blockIdx.x + (long long)(4 * e + wave) * gridDim.x) * TK + lane;
-            st[e] = slot < L ? stamp[(size_t)h * C + slot] : INT_MIN;
+        for (int e = 0; e < EACH; ++e) {
+            const int64_t slot = ((int64_t)blockIdx.x + (int64_t)(4 * e + wave) * gridDim.x) * TK + lane;
+            live[e] = 4 * e + wave < PER && slot < L;
+            st[e] = live[e] ? stamp[(size_t)h * C + slot] : INT_MIN;
         }
         unsigned mine = 0;
 #pragma unroll
-        for (int e = 0; e < CPB / 4; ++e) {
-            const long long slot = ((long long)blockIdx.x + (long long)(4 * e + wave) * gridDim.x) * TK + lane;
-            if (__ballot(slot < L && st[e] >= stamp_lo)) mine |= 1u << (4 * e + wave);
-        }
+        for (int e = 0; e < EACH; ++e)
+            if (__ballot(live[e] && st[e] >= stamp_lo)) mine |= 1u << (4 * e + wave);
         if (lane == 0) dirty_of[wave] = mine;
     }
     __syncthreads();
-    for (unsigned dirty = dirty_of[0] | dirty_of[1] | dirty_of[2] | dirty_of[3]; dirty; dirty &= dirty - 1u) {   // uniform
-        const int blk = (int)blockIdx.x + (__ffs(dirty) - 1) * (int)gridDim.x;
+    for (unsigned dirty = PER == 1 ? dirty_of[0] : dirty_of[0] | dirty_of[1] | dirty_of[2] | dirty_of[3]; dirty; dirty &= dirty - 1u) {
+        const int blk = PER == 1 ? (int)blockIdx.x : (int)blockIdx.x + (__ffs(dirty) - 1) * (int)gridDim.x;   // uniform
         const int j = tid >> 2, part = tid & 3;   // slot of the block, quarter of its row (32 coordinates)
         const int slot = blk * TK + j;
         const size_t Cp = (size_t)n_blk * TK;
@@ -135,6 +142,7 @@ __global__ __launch_bounds__(256) void kv_to_fp8_kernel(const void *__restrict__
             *(u32x4 *)dst = *(const u32x4 *)(&vt[row][32 * half]);
             *(u32x4 *)(dst + 16) = *(const u32x4 *)(&vt[row][32 * half + 16]);
         }
+        if constexpr (PER == 1) return;
         __syncthreads();   // vt has been read
     }
 }
@@ -559,13 +567,27 @@ extern "C" int fastar_kv_to_fp8(const fastar_cache *cache, int32_t stamp_lo, uin
     if (((uintptr_t)cache->K & 15) || ((uintptr_t)cache->V & 15) || ((uintptr_t)K8 & 15) || ((uintptr_t)V8T & 15))
         return FASTAR_ERR_INVALID_ARG;
     const int n_blk = (C + f8::TK - 1) / f8::TK;
-    const dim3 grid((n_blk + f8::CPB - 1) / f8::CPB, H);
-    if (cache->dtype == FASTAR_BF16)
-        hipLaunchKernelGGL(f8::kv_to_fp8_kernel<true>, grid, dim3(256), 0, (hipStream_t)stream, cache->K, cache->V,
-                           cache->stamp, cache->len, C, n_blk, stamp_lo, K8, V8T);
-    else
-        hipLaunchKernelGGL(f8::kv_to_fp8_kernel<false>, grid, dim3(256), 0, (hipStream_t)stream, cache->K, cache->V,
-                           cache->stamp, cache->len, C, n_blk, stamp_lo, K8, V8T);
+    // Blocks per workgroup: one while there are few workgroups to start (or all blocks are to be rewritten), then as many as
+    // keep the grid at 16384 or more.  Us per call by 1 / 2 / 4 / 8 / 16 blocks after a frame with 4/5 of its tokens merged:
+    // 40 heads x 230400 slots (144000 blocks) 136 / 127 / 112 / 106 / 106, 40 x 115200 126 / 126 / 124 / 127 / 127, 40 x 57600
+    // 60 / 60 / 57 / 59 / 60, 12 x 37440 13 / 14 / 15 / 17 / 18, 5 x 28000 7 / 8 / 8 / 11 / 11; all blocks of 40 x 230400
+    // 1265 / 1280 / 1303 / 1329 / 1350, of 5 x 28000 18 / 19 / 22 / 25 / 32.
+    const int64_t blocks = (int64_t)n_blk * H;
+    const int per = stamp_lo == INT_MIN ? 1 : blocks >= 8 * 16384 ? 8 : blocks >= 4 * 16384 ? 4 : blocks >= 2 * 16384 ? 2 : 1;
+#define FASTAR_KV8(BF, PER)                                                                                                 \
+    hipLaunchKernelGGL((f8::kv_to_fp8_kernel<BF, PER>), dim3((n_blk + PER - 1) / PER, H), dim3(256), 0, (hipStream_t)stream, \
+                       cache->K, cache->V, cache->stamp, cache->len, C, n_blk, stamp_lo, K8, V8T)
+#define FASTAR_KV8_PER(BF)                   \
+    do {                                     \
+        if (per == 8) FASTAR_KV8(BF, 8);     \
+        else if (per == 4) FASTAR_KV8(BF, 4); \
+        else if (per == 2) FASTAR_KV8(BF, 2); \
+        else FASTAR_KV8(BF, 1);              \
+    } while (0)
+    if (cache->dtype == FASTAR_BF16) FASTAR_KV8_PER(true);
+    else FASTAR_KV8_PER(false);
+#undef FASTAR_KV8_PER
+#undef FASTAR_KV8
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }

@@ -92,7 +92,7 @@ def check_fp8_attention(Q, c, sel, nsel, scale, use_cnt=True):
 
 @pytest.mark.parametrize("n_blk,cut", [(1, 0), (15, 3), (16, 0), (17, 63), (33, 1), (50, 0)])
 def test_kv_to_fp8_finds_the_blocks_a_frame_wrote(n_blk, cut):
-    # a workgroup looks at 16 blocks, a grid apart: counts at its edges; a run of written slots, single ones, none
+    # a workgroup per block: a run of written slots, single ones, none
     rng = np.random.default_rng(n_blk)
     H, d, C = 3, 128, 64 * n_blk - cut
     c = rand_cache(rng, H, C, d, [C, max(1, C - 70), C], "bf16")
@@ -108,6 +108,36 @@ def test_kv_to_fp8_finds_the_blocks_a_frame_wrote(n_blk, cut):
     torch.cuda.synchronize()
     assert np.array_equal(to_host(K8), K8r) and np.array_equal(to_host(V8), V8r)
     assert (K8r[2] == 0x22).all()              # a head in which nothing was written stays as it is
+
+
+@pytest.mark.parametrize("H,n_blk,cut", [(3, 10923, 0), (3, 10925, 63), (3, 21847, 5), (4, 32771, 1)])
+def test_kv_to_fp8_of_long_caches_finds_the_blocks_a_frame_wrote(H, n_blk, cut):
+    # two, four and eight blocks per workgroup, a grid apart, from 32768, 65536 and 131072 blocks on (and one just below),
+    # against a rebuild, which takes a workgroup per block at any size
+    g = torch.Generator(device="cuda").manual_seed(n_blk)
+    d, C = 128, 64 * n_blk - cut
+    normal = lambda: torch.randn((H, C, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    cache = fa.Cache.empty(H, C, d, 32, torch.bfloat16)
+    cache.K[:], cache.V[:] = normal(), normal()
+    cache.stamp.fill_(3)
+    cache.len.fill_(C)
+    cache.len[1] = C - 200
+    cache.stamp[0, C // 3: C // 3 + 5000] = 7
+    cache.stamp[:, -1] = 7                                    # beyond the second head's length
+    cache.stamp.view(-1)[torch.randint(0, H * C, (n_blk // 3,), generator=g, device="cuda")] = 7
+    whole = [torch.full_like(t, 0x55) for t in fa.kv8_empty(H, C, d)]
+    fa.kv_to_fp8(cache, *whole)
+    part = [torch.full_like(t, 0x55) for t in whole]
+    fa.kv_to_fp8(cache, *part, stamp_lo=7)
+    torch.cuda.synchronize()
+    live = torch.arange(C, device="cuda")[None, :] < cache.len[:, None]
+    written = torch.zeros((H, 64 * n_blk), dtype=torch.bool, device="cuda")
+    written[:, :C] = (cache.stamp >= 7) & live
+    dirty = written.view(H, n_blk, 64).any(2)
+    assert 0 < int(dirty.sum()) < H * n_blk // 2
+    for got, want in zip(part, whole):
+        got, want = got.view(H, n_blk, -1), want.view(H, n_blk, -1)
+        assert (got[~dirty] == 0x55).all() and torch.equal(got[dirty], want[dirty])
 
 
 @pytest.mark.parametrize("H,n_q,C,lens,n_sel,seed", [
