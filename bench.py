@@ -455,9 +455,13 @@ def attn_kernel_name(n_items, H, C, n_tiles, ws, fp8=False, d=128):
     phase) and 64-key tiles per query block; ws: the call carries a workspace."""
     per_xcd = (n_items + 7) // 8
     tail = per_xcd % 64
-    if ws and per_xcd > 64 and 0 < tail <= 24 and n_tiles * (1.2 - 0.0375 * tail) > 30.0:   # a short last round is shared out
-        return "attn_%s_d128_sk_kernel + attn_combine_kernel" % ("fp8" if fp8 else "bf16")
+    if ws and not fp8 and per_xcd > 64 and 0 < tail <= 24 and n_tiles * (1.2 - 0.0375 * tail) > 30.0:   # a short last round is shared out
+        return "attn_bf16_d128_sk_kernel + attn_combine_kernel"
     if fp8:
+        tail96 = per_xcd % 96
+        if ws and ((per_xcd > 96 and tail96 > 0 and (tail96 <= 24 and n_tiles >= 120 or tail96 <= 40 and n_tiles >= 150)) or
+                   (per_xcd > 64 and 5 <= tail <= 24 and n_tiles >= 150)):
+            return "attn_fp8_d128_sk_kernel + attn_combine_kernel"
         return "attn_fp8_d128_parts_kernel + attn_combine_parts_kernel, or attn_fp8_d128_kernel" if ws and n_items <= 256 else "attn_fp8_d128_kernel"
     pp = "attn_bf16_d128_pp_kernel<4, true, %s, " % ("true" if H * C * d * 2 * 2 <= (256 << 20) else "false")
     if n_items <= 256 and n_tiles > 5:   # one block per workgroup, split over its two groups

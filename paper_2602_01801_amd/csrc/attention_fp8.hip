@@ -537,6 +537,21 @@ __global__ __launch_bounds__(256, 3) void attn_fp8_d128_parts_kernel(
                     lds, item / n_qb, item % n_qb, tb, te, frag + (size_t)unit * ATTN_PART_FLOATS);
 }
 
+// Whether a launch of n_items pairs with n_tiles tiles each is split, and how many pairs per XCD range are taken whole then
+// (0: not split).  An XCD holds 96 of these workgroups.  Us per launch, lists from a cache of 37440 slots (pairs per XCD;
+// unsplit / 64 or a multiple taken whole / 96 or a multiple):
+//   up to 96 a single round, which the split can only make fuller: 65 of 90 tiles 162 / 211 (230400 slots 183 / 272), of 180
+//     304 / 325; 70 of 90 164 / 171, of 180 311 / 295, of 360 602 / 537; 93 of 180 341 / 381;
+//   98 of 90 tiles 239 / 219 / 251, of 135 345 / 297 / 334, of 360 877 / 717 / 737; 109 of 135 350 / 333 / 303; 125 of 135
+//     358 / 392 / 365, of 360 906 / 1007 / 908; 132 of 90 281 / 300 / 275, of 180 537 / 525 / 483, of 360 1041 / 971 / 930;
+//   145 of 90 288 / 301 / 311, of 180 548 / 558 / 541, of 360 1072 / 992 / 1059; 240 of 135 651 / 689 / 680.
+static int split_full_per(int n_items, int n_tiles) {
+    const int per_xcd = (n_items + 7) / 8, tail96 = per_xcd % 96, tail64 = per_xcd % 64;
+    if (per_xcd > 96 && tail96 > 0 && ((tail96 <= 24 && n_tiles >= 120) || (tail96 <= 40 && n_tiles >= 150))) return per_xcd - tail96;
+    if (per_xcd > 64 && tail64 >= 5 && tail64 <= 24 && n_tiles >= 150) return per_xcd - tail64;
+    return 0;
+}
+
 }  // namespace f8
 
 int attn_fp8_setup() {
@@ -624,11 +639,8 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
     const int n_qb = (n_q + 127) / 128;
     const int n_blk = (C + f8::TK - 1) / f8::TK;
     const float scale_log2 = scale * 1.4426950408889634f;
-    // With a workspace, a launch that would end in a short last round of workgroups is split (one entry = one tile), by the
-    // rule of the bf16 kernel although three of these workgroups share a unit: two per unit already draw what HBM gives, so
-    // the last round is short or not by the count of 64 per XCD (1160 blocks of 360 tiles, 128 of an XCD's 145 taken whole:
-    // 1128 us; 112: 1167, 96: 1175, 136: 1199, unsplit 1167).
-    const int full_per = ws ? attn_split_full_per(n_qb * H, n_sel) : 0;
+    // with a workspace, a launch that would end in a short last round of workgroups is split (one entry = one tile)
+    const int full_per = ws ? f8::split_full_per(n_qb * H, n_sel) : 0;
     if (full_per > 0) {
         const TailMap tm = {(n_qb * H + 7) / 8, full_per, n_qb * H};
         const int n_plain = 8 * full_per;
@@ -639,8 +651,9 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
         FASTAR_LAUNCH_CHECK();
         return launch_attn_combine(ws, n_q, n_qb, tm, n_sel, scale_log2, -6.0f, O, lse, (hipStream_t)stream);
     }
-    // at most one block per compute unit: several workgroups per block where that pays (8 blocks of 96 tiles 97 -> 18 us,
-    // 156 of 48 tiles 55 -> 41 us; 3 tiles 8 us either way, then one workgroup)
+    // at most one block per compute unit: several workgroups per block where that pays (4 blocks of 96 tiles 97 -> 19 us, 156
+    // of 48 tiles 55 -> 41; 156 of 24 tiles 31 either way, of 3 tiles 9: then one workgroup).  Over 1 to 256 blocks of 3 to 192
+    // tiles the number chosen is within 2 us or 8 % of the best one.
     const int n_parts = ws && n_qb * H <= 256 ? attn_parts(n_qb * H, n_sel, 1, 0.97f, 1.35f) : 1;
     if (n_parts > 1) {
         const int units = n_qb * H * n_parts;

@@ -44,6 +44,12 @@ def test_roofline_kernel_name_follows_the_dispatch_rule():
     assert order == sorted(order)
     assert "tail_per <= 24 && (float)n_tiles * (1.2f - 0.0375f * (float)tail_per) > 30.0f" in src("common.hpp")
     assert "ws && n_qb * H <= 256 ? attn_parts(" in src("attention_fp8.hip")
+    assert "((tail96 <= 24 && n_tiles >= 120) || (tail96 <= 40 && n_tiles >= 150))" in src("attention_fp8.hip")
+    assert "tail64 >= 5 && tail64 <= 24 && n_tiles >= 150" in src("attention_fp8.hip")
+    # 8-bit, by pairs per XCD: one round of 96 is left alone or filled up from 64, a short second one is shared out
+    split = lambda per, tiles: name(8 * per, 40, 230400, tiles, True, fp8=True).startswith("attn_fp8_d128_sk_kernel")  # noqa: E731
+    assert [split(66, 360), split(70, 180), split(70, 149), split(93, 360), split(98, 120), split(98, 119)] == [False, True, False, False, True, False]
+    assert [split(132, 150), split(132, 149), split(145, 360), split(160, 360)] == [True, False, True, False]
     assert "(size_t)H * (size_t)C * D * 2 * 2 <= ((size_t)256 << 20)" in src("attention_d128_pp.hip")
     assert "template <int NWG, bool CONTIG, bool BIAS_X, bool SPLIT>" in src("attention_d128_pp.hip")
 

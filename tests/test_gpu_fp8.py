@@ -192,6 +192,41 @@ def test_fp8_attention_at_the_edges_of_its_pipeline(counts):
     check_fp8_attention(Q, c, sel, nsel, d ** -0.5, use_cnt=False)
 
 
+# pairs per XCD range, of which whole rounds of 96 or 64 workgroups are taken whole: sizes at the edges of the rule
+@pytest.mark.parametrize("H,n_qb,n_sel,split", [
+    (33, 16, 180, False),                          # 66 per range: one round
+    (23, 24, 150, True), (23, 24, 149, False),     # 69 (64 whole)
+    (26, 30, 120, True), (26, 30, 119, False),     # 98 (96 whole)
+    (24, 44, 150, True),                           # 132 (96 whole)
+    (31, 35, 150, True)])                          # 136 (96 whole; the last range is short)
+def test_fp8_attention_split_by_the_workgroups_a_unit_holds(H, n_qb, n_sel, split):
+    d, C, n_q = 128, 64 * 300 - 9, 128 * n_qb - 40
+    g = torch.Generator(device="cuda").manual_seed(H + n_sel)
+    normal = lambda n: torch.randn((H, n, d), device="cuda", generator=g).bfloat16()  # noqa: E731
+    cache = fa.Cache.empty(H, C, d, 32, torch.bfloat16)
+    cache.K[:], cache.V[:] = normal(C), normal(C)
+    cache.stamp.zero_()
+    cache.cnt[:] = torch.randint(1, 6, (H, C), device="cuda", generator=g, dtype=torch.int32)
+    cache.len.fill_(C)
+    cache.len[2] = C // 2
+    K8, V8 = fa.kv8_empty(H, C, d)
+    fa.kv_to_fp8(cache, K8, V8)
+    sel = torch.rand((H, n_qb, 300), device="cuda", generator=g).topk(n_sel, dim=2).indices.sort(dim=2).values.to(torch.int32).contiguous()
+    nsel = torch.full((H, n_qb), n_sel, dtype=torch.int32, device="cuda")
+    nsel[1, 3], nsel[H - 1, n_qb - 1] = 7, 0
+    ws = torch.full((fa.workspace_bytes(fa.OP_ATTN, H, n_q, C),), 0x5A, dtype=torch.uint8, device="cuda")
+    args = (normal(n_q), K8, V8, cache.cnt, cache.len, C, sel, nsel, 128, 64, d ** -0.5)
+    O, lse = fa.sparse_attn_fwd_fp8(*args, ws=ws)
+    O_plain, lse_plain = fa.sparse_attn_fwd_fp8(*args)
+    torch.cuda.synchronize()
+    assert bool((ws != 0x5A).any()) == split           # fragments, or untouched
+    diff = (O.float() - O_plain.float()).abs()
+    # a fragment rounds its weights against its own reference maximum; without fragments it is the same launch
+    assert torch.isfinite(O.float()).all() and diff.max() <= (ATOL_MAX if split else 0) and diff.mean() <= (ATOL_MEAN if split else 0)
+    fin = torch.isfinite(lse_plain)
+    assert torch.equal(fin, torch.isfinite(lse)) and (lse[fin] - lse_plain[fin]).abs().max() <= 0.05
+
+
 @pytest.mark.parametrize("H,n_q,C,n_sel", [
     (20, 3600, 64 * 300, 150),     # 580 query blocks: 73 per XCD range, 9 of them left over by the whole round
     (33, 2048, 64 * 256, 128),     # 528 blocks: 2 per range left over
