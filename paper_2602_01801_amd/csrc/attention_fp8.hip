@@ -653,7 +653,7 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
     }
     // at most one block per compute unit: several workgroups per block where that pays (4 blocks of 96 tiles 97 -> 19 us, 156
     // of 48 tiles 55 -> 41; 156 of 24 tiles 31 either way, of 3 tiles 9: then one workgroup).  Over 1 to 256 blocks of 3 to 192
-    // tiles the number chosen is within 2 us or 8 % of the best one.
+    // tiles the number chosen is within 2 us or 9 % of the best one.
     const int n_parts = ws && n_qb * H <= 256 ? attn_parts(n_qb * H, n_sel, 1, 0.97f, 1.35f) : 1;
     if (n_parts > 1) {
         const int units = n_qb * H * n_parts;

@@ -41,13 +41,10 @@ constexpr int SETTLE_SLOTS = 65536;       // eight slices
 constexpr int SETTLE_TOKENS = 8192;       // tokens per frame (their list is held in LDS)
 __host__ __device__ static inline int settle_slices(int C) { return (C + SETTLE_SLICE - 1) / SETTLE_SLICE; }
 
-// Calls without a window on a persistent workspace have the encode launch clear all of the cache's group records while those
-// are few, which saves the launch that would clear the matched slots' ones.  By slots per token, since a workgroup of that launch
-// clears its share by itself (call with the launch -> without, us): 12 heads x 500 tokens x 30000 slots 37.8 -> 36.5,
-// 12 x 100 x 60000 34.0 -> 38.8; and by their size: 24 x 1560 x 37440 (11 MB) 174.6 -> 172.6, 40 x 1560 x 37440 (18 MB)
-// 191.6 -> 193.1, 12 x 1560 x 99840 (14 MB) 167.3 -> 168.7.
-constexpr int CLEAR_SLOTS_PER_TOKEN = 64;
-constexpr size_t CLEAR_RECORDS_MAX = (size_t)12 << 20;
+// The match of the whole cache clears the group records of all live slots, which saves the launch that would clear the matched
+// ones', while those are few (call with that launch -> without, us): 4 heads x 9360 slots 27.3 -> 26.6, 12 x 32760 73.5 -> 72.7,
+// 24 x 37440 174.6 -> 174.7; 40 x 37440 191.6 -> 195.0, 40 x 64000 172 -> 178.
+constexpr int64_t CLEAR_SLOTS_MAX = 1 << 20;
 
 // What a call leaves clean for the next one (group records, per-head scalars, plan scratch) lies in front and has sizes that
 // depend on the cache alone, so frames of any length share a persistent workspace.  Behind it is what every call writes before
@@ -484,7 +481,8 @@ __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8
                                                                       const int32_t *__restrict__ len, int C,
                                                                       const int8_t *__restrict__ cp, int n_new, int metric,
                                                                       int range, int share, int block,
-                                                                      u64 *__restrict__ best) {
+                                                                      u64 *__restrict__ best, u64 *__restrict__ win,
+                                                                      int32_t *__restrict__ grp) {
     typedef WindowScan<R, TOKS, true> WS;
     constexpr int KS = WS::KS, NCH = WS::NCH, NG = WS::NG, TPT = WS::TPT;
     extern __shared__ __attribute__((aligned(16))) unsigned char wlds[];
@@ -529,6 +527,10 @@ __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8
     load_rows(0);
     load_tokens(t0);
     if (tid < WAVE) s_odd[tid] = 0ull;
+    for (int p = (int)blockIdx.y * WIN_THREADS + tid; win && p < n; p += (int)gridDim.y * WIN_THREADS) {   // the live slots' group records
+        win[(size_t)h * C + j0 + p] = 0;
+        grp[(size_t)h * C + j0 + p] = 0;
+    }
     __syncthreads();
     for (int p0 = 0; p0 < n_stage; p0 += PER * WIN_THREADS) {   // uniform
         if (p0 > 0) load_rows(p0);
@@ -581,7 +583,7 @@ static int allow_match_all_lds() {
 }
 template <int R, int TOKS>
 static int launch_match_all(const int8_t *code, const int32_t *len, int C, const int8_t *cp, int n_new, int H, int metric,
-                            u64 *best, hipStream_t s) {
+                            u64 *best, u64 *win, int32_t *grp, hipStream_t s) {
     // One workgroup per compute unit (LDS): as few ranges as its LDS allows, the tokens shared out while workgroups are
     // left over, then the ranges made shorter until the chip is covered.  Ranges of at least 512 slots: shorter ones are
     // all staging and look-up.
@@ -596,7 +598,7 @@ static int launch_match_all(const int8_t *code, const int32_t *len, int C, const
     const int block = (((share + n_blk - 1) / n_blk) + 31) & ~31;
     const dim3 grid((C + range - 1) / range, (n_new + share - 1) / share, H);
     hipLaunchKernelGGL((tc_match_all_kernel<R, TOKS>), grid, dim3(WIN_THREADS), (size_t)range * (R + 8), s, code, len, C, cp,
-                       n_new, metric, range, share, block, best);
+                       n_new, metric, range, share, block, best, win, grp);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }
@@ -1074,8 +1076,8 @@ __device__ __forceinline__ void unpack_match(u64 key, int &j, int &S) {
     j = key != 0 ? (int)(0xFFFFFFFFu - (unsigned)key) : -1;
     S = key != 0 ? (int)(unsigned)(key >> 32) - SCORE_BIAS : 0;
 }
-// Unpacks the match and clears the per-slot group records it will touch.  Not needed where the encode launch cleared them all
-// (CLEAR_RECORDS_MAX); the verify launch then unpacks the match itself.
+// Unpacks the match and clears the per-slot group records it will touch.  Not needed where the match of the whole cache cleared
+// them all (CLEAR_SLOTS_MAX); the verify launch then unpacks it.
 __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ best, int n_new, int C,
                                                       const int32_t *__restrict__ cand, int n_cand,
                                                       int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
@@ -1461,7 +1463,7 @@ __device__ __forceinline__ void verify_token(const void *__restrict__ K, const v
     // everything addressed by the token first (one round trip), then the matched slot's key row
     const size_t ti = (size_t)h * n_new + i;
     int j, S;
-    if (best) {   // the match as its launch left it (uniform; see unpack_match)
+    if (best) {   // the match of the whole cache as its launch left it (uniform; see unpack_match)
         unpack_match(best[ti], j, S);
         if (l16 == 0) jstar[ti] = j;
     } else {
@@ -2861,16 +2863,14 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     // Plan and apply in one launch: short caches, whose age histograms are small enough to be read by every workgroup, and
     // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
     const bool fits = C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
+    const bool cleared = !cand && (int64_t)H * C <= CLEAR_SLOTS_MAX;
     const SettleGrid sg = fits ? settle_grid(H, C, n_new) : SettleGrid{};
     const bool settle = ws_persistent && fits && sg.better;
     const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age),
                                           (int32_t *)(base + w.slot_stamp)} : SettleOut{};
-    // Calls without a window do not rely on clean group records (see fastar.h).
-    const bool clear_all = !window && ws_persistent && w.ps - w.win <= CLEAR_RECORDS_MAX && C / CLEAR_SLOTS_PER_TOKEN <= n_new;
     if (!fused_encode) {
-        const size_t zero_from = clear_all ? w.win : w.ps;
-        const int64_t zero_words = (int64_t)(w.best - zero_from) / 8 + T;   // ps and best, the records in front of them
-        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)(base + zero_from), zero_words, s);
+        const int64_t zero_words = (int64_t)(w.best - w.ps) / 8 + T;   // ps and best
+        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)plan_scratch, zero_words, s);
         if (rc != FASTAR_OK) return rc;
         if (P_new) {
             rc = encode_launch(P_new, dtype, T, d, codec, r, cp, nullptr, 0, s);
@@ -2925,7 +2925,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         if (!cand) {
             // frames of at most 128 tokens leave half of the wavefronts of a 256-token block without work
             int rc;
-#define FASTAR_MATCH_ALL(RR, TT) rc = launch_match_all<RR, TT>(cache->code, cache->len, C, cp, n_new, H, metric, best, s)
+#define FASTAR_MATCH_ALL(RR, TT) rc = launch_match_all<RR, TT>(cache->code, cache->len, C, cp, n_new, H, metric, best, cleared ? win : nullptr, grp, s)
             if (n_new <= 128) { if (r == 32) FASTAR_MATCH_ALL(32, 64); else FASTAR_MATCH_ALL(64, 64); }
             else { if (r == 32) FASTAR_MATCH_ALL(32, 256); else FASTAR_MATCH_ALL(64, 256); }
 #undef FASTAR_MATCH_ALL
@@ -2943,7 +2943,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
 #undef FASTAR_MATCH
         }
         FASTAR_LAUNCH_CHECK();
-        if (!clear_all) {
+        if (!cleared) {
             hipLaunchKernelGGL(tc_prep_kernel, dim3((n_new + 255) / 256, H), dim3(256), 0, s, best, n_new, C, cand, n_cand,
                                jstar, sbest, win, grp);
             FASTAR_LAUNCH_CHECK();
@@ -2962,7 +2962,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         const int n_slices = settle ? settle_slices(C) : 0;
         tgrid.x += n_slices;
         FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest,
-                  clear_all ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
+                  cleared ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
                   n_slices, so);
         tgrid.x -= n_slices;
         FASTAR_LAUNCH_CHECK();

@@ -1473,7 +1473,7 @@ def test_tempcache_frames_of_different_lengths_share_a_persistent_workspace(H, C
         assert_cache_equal(host_cache(gpu), ref, VTOL[dtype])
 
 
-@pytest.mark.parametrize("H,T,C,n_cand", [(2, 200, 3000, 0), (2, 200, 5000, 4200), (2, 40, 5000, 0), (1, 300, 66000, 0)])
+@pytest.mark.parametrize("H,T,C,n_cand", [(2, 200, 3000, 0), (2, 200, 5000, 4200), (2, 40, 5000, 0), (1, 300, 66000, 0), (17, 60, 62000, 0)])
 def test_tempcache_calls_without_a_window_clear_the_group_records_they_need(H, T, C, n_cand):
     # A workspace that held anything and was left by a call with ws_persistent = 0: its marks are those of a finished call, the
     # records of slots which that call did not touch are not clean.
