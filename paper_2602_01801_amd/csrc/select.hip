@@ -24,6 +24,10 @@ constexpr size_t LONG_CACHE_BLOCKS = 16 * 4096;   // key blocks over all heads f
 // one, us: r = 32, 2 x 2 query blocks, 4096 slots 9.3 -> 6.6, 9360 9.3 -> 8.9, 12288 9.6 -> 9.3; 12 x 21, 4096 11.1 -> 7.4,
 // 9360 11.7 -> 10.2, 12288 11.7 -> 12.2; r = 64, 6 x 21, 1024 11.7 -> 7.0, 4096 11.7 -> 9.3, 8192 11.8 -> 13.1.
 constexpr int short_keys(int r) { return r == 32 ? 10240 : 4096; }
+// What it reads from beyond L2: the blocks of a head lie on as many XCDs, which fetch the head's codes each (three launches against
+// one, us): 8 heads x 32 query blocks x 10240 slots (20 MB) 11.5 -> 10.1, 40 x 3 x 10240 (37 MB) 12.5 -> 11.0, 16 x 16 x 8192
+// (32 MB) 10.9 -> 9.5, x 10240 (40 MB) 11.2 -> 12.7, 24 x 8 x 8192 (48 MB) 10.8 -> 12.6, 32 x 8 x 10240 (80 MB) 11.5 -> 16.7.
+constexpr int64_t SHORT_BYTES = 38 << 20;
 constexpr int SHORT_WGS = 256;     // its workgroups: no more than compute units (a second round: 11 us like the launches it replaces)
 constexpr int COL_CHUNK = 8;       // summary column blocks (of 32) kept in registers at a time
 
@@ -1047,8 +1051,9 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
     const SelfWs w = self_ws(H, n_q, C, r, BQ, BK, n_rep);
     if (ws_bytes < w.total) return FASTAR_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    // Short caches, query blocks that fill the chip at most once: one launch instead of three.
-    if (bits == 8 && n_rep <= 8 && C <= short_keys(r) && BQ <= 256 && (int64_t)n_qb * H <= SHORT_WGS) {
+    // Short caches, query blocks that fill the chip at most once, codes that the XCDs fetch soon enough: one launch instead of three.
+    if (bits == 8 && n_rep <= 8 && C <= short_keys(r) && BQ <= 256 && (int64_t)n_qb * H <= SHORT_WGS &&
+        (int64_t)std::min(n_qb, 8) * H * C * r <= SHORT_BYTES) {
         const size_t lds = ((size_t)n_kb_cap * 4 + 15) / 16 * 16 + (size_t)BQ * r;
         const dim3 qgrid(n_qb, H);
         if (r == 32)

@@ -107,7 +107,8 @@ def test_ann_select_self_with_forced_sink_and_local_blocks(H, n_q, C, lens, n_se
         fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), 128, 4, 64, 4, n_sink=3, n_local=2)
 
 
-# one workgroup per query block up to 10240 slots (4096 at r = 64), 256 query blocks and 8 runs per block; the general path beyond
+# one workgroup per query block up to 10240 slots (4096 at r = 64), 256 query blocks, 38 MB of codes by XCD and 8 runs per block;
+# the general path beyond
 @pytest.mark.parametrize("H,n_q,C,r,BQ,n_rep,BK,n_sel,lens,forced", [
     (2, 100, 1, 32, 128, 4, 64, 1, [1, 0], (0, 0)),                    # one key, none; the block's last run has no query
     (2, 129, 10240, 32, 128, 4, 64, 40, [10240, 10209], (0, 0)),       # the longest cache; one query in the last block
@@ -119,7 +120,9 @@ def test_ann_select_self_with_forced_sink_and_local_blocks(H, n_q, C, lens, n_se
     (1, 511, 4160, 32, 256, 8, 64, 9, [4159], (0, 0)),                 # the largest query blocks, more than one round of blocks
     (4, 64 * 64, 700, 32, 64, 4, 64, 5, [700, 640, 65, 1], (0, 0)),    # 256 query blocks
     (1, 257 * 32, 700, 32, 32, 4, 64, 5, [699], (0, 0)),               # 257
-    (2, 70, 900, 32, 32, 16, 64, 5, [900, 70], (0, 0))])               # 16 runs per block
+    (2, 70, 900, 32, 32, 16, 64, 5, [900, 70], (0, 0)),                # 16 runs per block
+    (15, 1024, 10240, 32, 128, 4, 64, 9, [10240] * 14 + [77], (0, 0)),  # as many codes as 8 XCDs fetch in that form
+    (16, 1024, 10240, 32, 128, 4, 64, 9, [10240] * 15 + [77], (1, 1))])  # more
 def test_ann_select_self_at_the_edges_of_the_one_launch_form(H, n_q, C, r, BQ, n_rep, BK, n_sel, lens, forced):
     rng = np.random.default_rng(n_q + C + BQ)
     qc, kc = rand_codes(rng, -20, 20, H, n_q, r), rand_codes(rng, -128, 127, H, C, r)
