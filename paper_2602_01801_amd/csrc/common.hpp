@@ -108,6 +108,14 @@ __device__ __forceinline__ unsigned wave_max_last(unsigned v) {
     return v;
 }
 
+// Group records of the live slots (tempcache_compress), for workgroups of the encode launch to clear; win = nullptr: none.
+struct ClearRecords {
+    unsigned long long *win;
+    int32_t *grp;
+    const int32_t *len;
+    int H, C;
+};
+
 // One-time set-up per device (kernel attributes, symbol addresses), safe to reach from several host threads: run(f)
 // calls f once per device ordinal, with that device current, and remembers a success.  It is the only process-wide data
 // the library keeps, and it never influences a result.

@@ -10,16 +10,27 @@
 
 namespace fastar {
 
+constexpr int CLEAR_RUN = 4096;   // slots per workgroup that clears group records
 template <bool BF16, int D, int R>
 __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x, int64_t n_vec,
                                                      const int8_t *__restrict__ Rm, float qscale, int shift,
                                                      int8_t *__restrict__ code, unsigned long long *zero_fill,
-                                                     int64_t zero_n) {
+                                                     int64_t zero_n, unsigned enc_blocks, ClearRecords clear) {
+    if (blockIdx.x >= enc_blocks) {   // uniform: the records of a run of slots
+        const int per_head = (clear.C + CLEAR_RUN - 1) / CLEAR_RUN, at = (int)(blockIdx.x - enc_blocks);
+        const int h = at / per_head, j0 = (at - h * per_head) * CLEAR_RUN;
+        const int j1 = min(j0 + CLEAR_RUN, min(clear.len[h], clear.C));
+        for (int j = j0 + (int)threadIdx.x; j < j1; j += 256) {
+            clear.win[(size_t)h * clear.C + j] = 0ull;
+            clear.grp[(size_t)h * clear.C + j] = 0;
+        }
+        return;
+    }
     constexpr int KS = D / 64;   // k-steps of 64 coordinates
     const int lane = lane_id();
     const int col = lane & 15, g = lane >> 4;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t gthreads = (int64_t)gridDim.x * blockDim.x;
+    const int64_t gthreads = (int64_t)enc_blocks * blockDim.x;
     // optional: clear a 64-bit array for a later kernel of the same call
     for (int64_t i = gtid; i < zero_n; i += gthreads) zero_fill[i] = 0ull;
 
@@ -46,25 +57,26 @@ __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x,
 
 template <bool BF16, int D, int R>
 static void launch_encode(const void *x, int64_t n_vec, const fastar_codec *codec, int8_t *code,
-                          unsigned long long *zero_fill, int64_t zero_n, hipStream_t s) {
+                          unsigned long long *zero_fill, int64_t zero_n, hipStream_t s, ClearRecords clear) {
     int64_t groups = (n_vec + 15) / 16;
     int64_t blocks = (groups + 3) / 4;
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL((encode_kernel<BF16, D, R>), dim3((unsigned)blocks), dim3(256), 0, s, x, n_vec, codec->R,
-                       codec->qscale, codec->shift, code, zero_fill, zero_n);
+    const int64_t clearing = clear.win ? (int64_t)clear.H * ((clear.C + CLEAR_RUN - 1) / CLEAR_RUN) : 0;
+    hipLaunchKernelGGL((encode_kernel<BF16, D, R>), dim3((unsigned)(blocks + clearing)), dim3(256), 0, s, x, n_vec, codec->R,
+                       codec->qscale, codec->shift, code, zero_fill, zero_n, (unsigned)blocks, clear);
 }
 
 // Internal launcher shared with tempcache_compress: encodes and optionally zero-fills an array.
 int encode_launch(const void *x, int dtype, int64_t n_vec, int d, const fastar_codec *codec, int r, int8_t *code,
-                  unsigned long long *zero_fill, int64_t zero_n, hipStream_t s) {
+                  unsigned long long *zero_fill, int64_t zero_n, hipStream_t s, ClearRecords clear = {}) {
     if (!x || !codec || !codec->R || !code || n_vec < 0) return FASTAR_ERR_INVALID_ARG;
     if (dtype != FASTAR_F32 && dtype != FASTAR_BF16) return FASTAR_ERR_INVALID_ARG;
     if (codec->shift < 1 || codec->shift > 16) return FASTAR_ERR_INVALID_ARG;
     if ((d != 64 && d != 128) || (r != 32 && r != 64)) return FASTAR_ERR_UNSUPPORTED;
     if (((uintptr_t)x & 15) || ((uintptr_t)code & 3)) return FASTAR_ERR_INVALID_ARG;
     if (n_vec == 0 && zero_n == 0) return FASTAR_OK;
-#define FASTAR_ENC(B, DD, RR) launch_encode<B, DD, RR>(x, n_vec, codec, code, zero_fill, zero_n, s)
+#define FASTAR_ENC(B, DD, RR) launch_encode<B, DD, RR>(x, n_vec, codec, code, zero_fill, zero_n, s, clear)
     const bool bf = dtype == FASTAR_BF16;
     if (d == 64 && r == 32) { if (bf) FASTAR_ENC(true, 64, 32); else FASTAR_ENC(false, 64, 32); }
     else if (d == 64 && r == 64) { if (bf) FASTAR_ENC(true, 64, 64); else FASTAR_ENC(false, 64, 64); }

@@ -21,7 +21,8 @@
 namespace fastar {
 
 int encode_launch(const void *x, int dtype, int64_t n_vec, int d, const fastar_codec *codec, int r, int8_t *code,
-                  unsigned long long *zero_fill, int64_t zero_n, hipStream_t s);
+                  unsigned long long *zero_fill, int64_t zero_n, hipStream_t s,
+                  ClearRecords clear = {});
 
 constexpr int SCORE_BIAS = 1 << 23;      // makes every score positive inside the packed arg-max key
 constexpr int PLAN_SCRATCH_WORDS = 64 + 3 * 1024;  // per-head scratch of tc_plan_kernel (PS_STRIDE)
@@ -38,12 +39,13 @@ static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Caches of up to SETTLE_SLOTS slots on a persistent workspace: the launches behind the match are one, tc_settle_kernel.
 constexpr int SETTLE_SLICE = 8192;        // slots per slice of the age histogram
 constexpr int SETTLE_SLOTS = 65536;       // eight slices
+constexpr int SETTLE_THREADS = 512;
 constexpr int SETTLE_TOKENS = 8192;       // tokens per frame (their list is held in LDS)
 __host__ __device__ static inline int settle_slices(int C) { return (C + SETTLE_SLICE - 1) / SETTLE_SLICE; }
 
-// The match of the whole cache clears the group records of all live slots, which saves the launch that would clear the matched
-// ones', while those are few (call with that launch -> without, us): 4 heads x 9360 slots 27.3 -> 26.6, 12 x 32760 73.5 -> 72.7,
-// 24 x 37440 174.6 -> 174.7; 40 x 37440 191.6 -> 195.0, 40 x 64000 172 -> 178.
+// Without a window, workgroups of the encode launch clear the group records of all live slots while these are few, which saves the
+// launch that would clear the matched slots' ones (call with that launch -> without, us): 4 heads x 780 tokens x 9360 slots 28.4 ->
+// 26.1, 12 x 1560 x 32760 75.2 -> 72.5, 24 x 1560 x 37440 176.8 -> 174.7; 40 x 1560 x 37440 196.0 -> 197.3, 40 x 100 x 150000 115 -> 130.
 constexpr int64_t CLEAR_SLOTS_MAX = 1 << 20;
 
 // What a call leaves clean for the next one (group records, per-head scalars, plan scratch) lies in front and has sizes that
@@ -481,8 +483,7 @@ __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8
                                                                       const int32_t *__restrict__ len, int C,
                                                                       const int8_t *__restrict__ cp, int n_new, int metric,
                                                                       int range, int share, int block,
-                                                                      u64 *__restrict__ best, u64 *__restrict__ win,
-                                                                      int32_t *__restrict__ grp) {
+                                                                      u64 *__restrict__ best) {
     typedef WindowScan<R, TOKS, true> WS;
     constexpr int KS = WS::KS, NCH = WS::NCH, NG = WS::NG, TPT = WS::TPT;
     extern __shared__ __attribute__((aligned(16))) unsigned char wlds[];
@@ -527,10 +528,6 @@ __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8
     load_rows(0);
     load_tokens(t0);
     if (tid < WAVE) s_odd[tid] = 0ull;
-    for (int p = (int)blockIdx.y * WIN_THREADS + tid; win && p < n; p += (int)gridDim.y * WIN_THREADS) {   // the live slots' group records
-        win[(size_t)h * C + j0 + p] = 0;
-        grp[(size_t)h * C + j0 + p] = 0;
-    }
     __syncthreads();
     for (int p0 = 0; p0 < n_stage; p0 += PER * WIN_THREADS) {   // uniform
         if (p0 > 0) load_rows(p0);
@@ -583,7 +580,7 @@ static int allow_match_all_lds() {
 }
 template <int R, int TOKS>
 static int launch_match_all(const int8_t *code, const int32_t *len, int C, const int8_t *cp, int n_new, int H, int metric,
-                            u64 *best, u64 *win, int32_t *grp, hipStream_t s) {
+                            u64 *best, hipStream_t s) {
     // One workgroup per compute unit (LDS): as few ranges as its LDS allows, the tokens shared out while workgroups are
     // left over, then the ranges made shorter until the chip is covered.  Ranges of at least 512 slots: shorter ones are
     // all staging and look-up.
@@ -598,7 +595,7 @@ static int launch_match_all(const int8_t *code, const int32_t *len, int C, const
     const int block = (((share + n_blk - 1) / n_blk) + 31) & ~31;
     const dim3 grid((C + range - 1) / range, (n_new + share - 1) / share, H);
     hipLaunchKernelGGL((tc_match_all_kernel<R, TOKS>), grid, dim3(WIN_THREADS), (size_t)range * (R + 8), s, code, len, C, cp,
-                       n_new, metric, range, share, block, best, win, grp);
+                       n_new, metric, range, share, block, best);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }
@@ -1076,8 +1073,8 @@ __device__ __forceinline__ void unpack_match(u64 key, int &j, int &S) {
     j = key != 0 ? (int)(0xFFFFFFFFu - (unsigned)key) : -1;
     S = key != 0 ? (int)(unsigned)(key >> 32) - SCORE_BIAS : 0;
 }
-// Unpacks the match and clears the per-slot group records it will touch.  Not needed where the match of the whole cache cleared
-// them all (CLEAR_SLOTS_MAX); the verify launch then unpacks it.
+// Unpacks the match and clears the per-slot group records it will touch.  Not needed where the encode launch cleared them all
+// (CLEAR_SLOTS_MAX); the verify launch then unpacks the match.
 __global__ __launch_bounds__(256) void tc_prep_kernel(const u64 *__restrict__ best, int n_new, int C,
                                                       const int32_t *__restrict__ cand, int n_cand,
                                                       int32_t *__restrict__ jstar, int32_t *__restrict__ sbest,
@@ -1221,12 +1218,9 @@ __device__ __forceinline__ void age_slice(const int32_t *__restrict__ len, const
                 if (bin == 0u || bin >= (unsigned)AGE_EXACT) kept[jb + u * nt + tid] = sv[u];
             }
             // neighbouring slots were mostly written by the same frame: lanes of the first lane's age count together
-            const u64 m = __ballot(act);
-            if (m == 0) continue;
-            const int first = __ffsll((unsigned long long)m) - 1;
-            const unsigned fbin = (unsigned)__shfl((int)bin, first);
+            const unsigned fbin = (unsigned)__builtin_amdgcn_readfirstlane((int)bin);   // the first lane is in range if any is
             const u64 same = __ballot(act && bin == fbin);
-            if (lane_id() == first) atomicAdd(&lhist[fbin], (unsigned)__popcll(same));
+            if (act && lane_id() == 0) atomicAdd(&lhist[fbin], (unsigned)__popcll(same));
             if (act && bin != fbin) atomicAdd(&lhist[bin], 1u);
         }
     }
@@ -1361,8 +1355,8 @@ __device__ __forceinline__ void verify_token(const void *__restrict__ K, const v
                                              int32_t *__restrict__ grp, uint8_t *__restrict__ merged, int h, int i,
                                              int l16, const int32_t *__restrict__ stamp, int32_t *__restrict__ tstamp);
 
-template <bool BF16, int D>
-__global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__ K, const void *__restrict__ K_new,
+template <bool BF16, int D, bool SETTLE>
+__global__ __launch_bounds__(SETTLE ? SETTLE_THREADS : 256) void tc_verify_kernel(const void *__restrict__ K, const void *__restrict__ K_new,
                                                         const int8_t *__restrict__ cp, int r, int C, int n_new,
                                                         float qscale, int metric, int tau2_q16,
                                                         int32_t *__restrict__ jstar,
@@ -1376,17 +1370,19 @@ __global__ __launch_bounds__(256) void tc_verify_kernel(const void *__restrict__
     typedef RowPiece<BF16, D> RP;
     __shared__ unsigned lhist[AGE_BINS];
     const int h = blockIdx.y;
-    const int n_tok_wgs = (int)gridDim.x - n_slices;
-    if ((int)blockIdx.x >= n_tok_wgs) {   // uniform
-        age_slice(len, stamp, C, n_new, frame_id, so, lhist, h, (int)blockIdx.x - n_tok_wgs);
-        return;
+    if constexpr (SETTLE) {
+        const int n_tok_wgs = (int)gridDim.x - n_slices;
+        if ((int)blockIdx.x >= n_tok_wgs) {   // uniform
+            age_slice(len, stamp, C, n_new, frame_id, so, lhist, h, (int)blockIdx.x - n_tok_wgs);
+            return;
+        }
+        if (blockIdx.x == 0 && threadIdx.x == 0) so.hs[(size_t)h * HS_STRIDE] = min(len[h], C);
     }
-    if (so.hs && blockIdx.x == 0 && threadIdx.x == 0) so.hs[(size_t)h * HS_STRIDE] = min(len[h], C);
     const int l16 = threadIdx.x & 15;
     const int i = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);
     if (i < n_new) verify_token<BF16, D>(K, K_new, cp, r, C, n_new, qscale, metric, tau2_q16, jstar, sbest, best, win, grp,
-                                         merged, h, i, l16, so.tstamp ? stamp : nullptr, so.tstamp);  // whole 16-lane groups
-    if (so.hs) return;
+                                         merged, h, i, l16, SETTLE ? stamp : nullptr, SETTLE ? so.tstamp : nullptr);  // whole 16-lane groups
+    if constexpr (SETTLE) return;
     age_histogram_slice<4>(len, stamp, C, n_new, frame_id, plan_scratch + (size_t)h * scratch_words, hist_word, fut_word,
                         lhist, (int)blockIdx.x, (int)gridDim.x);
 }
@@ -1463,7 +1459,7 @@ __device__ __forceinline__ void verify_token(const void *__restrict__ K, const v
     // everything addressed by the token first (one round trip), then the matched slot's key row
     const size_t ti = (size_t)h * n_new + i;
     int j, S;
-    if (best) {   // the match of the whole cache as its launch left it (uniform; see unpack_match)
+    if (best) {   // the match as its launch left it (uniform; see unpack_match)
         unpack_match(best[ti], j, S);
         if (l16 == 0) jstar[ti] = j;
     } else {
@@ -2324,7 +2320,6 @@ __global__ __launch_bounds__(256) void tc_apply_kernel(void *__restrict__ K, voi
 // meeting) took 13.5 and the apply launch behind it 9.3; a chunk of three such calls 325 -> 293.
 // All 888 workgroups have to be resident at once: with 99 registers they took two rounds and 23.8 us, so frames of up to
 // 2048 tokens have an instantiation of 64 (it spills 4 words).
-constexpr int SETTLE_THREADS = 512;
 constexpr int SETTLE_WAVES = SETTLE_THREADS / 64;
 constexpr int SETTLE_GROUPS = SETTLE_THREADS / 16;             // 16-lane groups: rows a workgroup moves at a time
 constexpr int SETTLE_SPT = SETTLE_SLICE / SETTLE_THREADS;      // slots per thread of a slice
@@ -2863,14 +2858,15 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
     // Plan and apply in one launch: short caches, whose age histograms are small enough to be read by every workgroup, and
     // calls of a rollout (the others pay for a clearing launch as it is, and keep the plan and its waits).
     const bool fits = C <= SETTLE_SLOTS && n_new <= SETTLE_TOKENS;
-    const bool cleared = !cand && (int64_t)H * C <= CLEAR_SLOTS_MAX;
+    const bool cleared = !window && (int64_t)H * C <= CLEAR_SLOTS_MAX;
     const SettleGrid sg = fits ? settle_grid(H, C, n_new) : SettleGrid{};
     const bool settle = ws_persistent && fits && sg.better;
     const SettleOut so = settle ? SettleOut{hs, (int32_t *)(base + w.tstamp), (unsigned *)(base + w.ages), (unsigned short *)(base + w.slot_age),
                                           (int32_t *)(base + w.slot_stamp)} : SettleOut{};
     if (!fused_encode) {
         const int64_t zero_words = (int64_t)(w.best - w.ps) / 8 + T;   // ps and best
-        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)plan_scratch, zero_words, s);
+        int rc = encode_launch(K_new, dtype, T, d, codec, r, ck, (u64 *)plan_scratch, zero_words, s,
+                               cleared ? ClearRecords{win, grp, cache->len, H, C} : ClearRecords{});
         if (rc != FASTAR_OK) return rc;
         if (P_new) {
             rc = encode_launch(P_new, dtype, T, d, codec, r, cp, nullptr, 0, s);
@@ -2925,7 +2921,7 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         if (!cand) {
             // frames of at most 128 tokens leave half of the wavefronts of a 256-token block without work
             int rc;
-#define FASTAR_MATCH_ALL(RR, TT) rc = launch_match_all<RR, TT>(cache->code, cache->len, C, cp, n_new, H, metric, best, cleared ? win : nullptr, grp, s)
+#define FASTAR_MATCH_ALL(RR, TT) rc = launch_match_all<RR, TT>(cache->code, cache->len, C, cp, n_new, H, metric, best, s)
             if (n_new <= 128) { if (r == 32) FASTAR_MATCH_ALL(32, 64); else FASTAR_MATCH_ALL(64, 64); }
             else { if (r == 32) FASTAR_MATCH_ALL(32, 256); else FASTAR_MATCH_ALL(64, 256); }
 #undef FASTAR_MATCH_ALL
@@ -2949,22 +2945,29 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
             FASTAR_LAUNCH_CHECK();
         }
     }
-    dim3 tgrid((n_new + 15) / 16, H);
+    const dim3 tgrid((n_new + 15) / 16, H);
     const bool bf = dtype == FASTAR_BF16;
-#define FASTAR_TC(KERNEL, ...)                                                                          \
-    do {                                                                                                \
-        if (bf && d == 128) hipLaunchKernelGGL((KERNEL<true, 128>), tgrid, dim3(256), 0, s, __VA_ARGS__);      \
-        else if (bf) hipLaunchKernelGGL((KERNEL<true, 64>), tgrid, dim3(256), 0, s, __VA_ARGS__);               \
-        else if (d == 128) hipLaunchKernelGGL((KERNEL<false, 128>), tgrid, dim3(256), 0, s, __VA_ARGS__);       \
-        else hipLaunchKernelGGL((KERNEL<false, 64>), tgrid, dim3(256), 0, s, __VA_ARGS__);                       \
+#define FASTAR_TC(KERNEL, GRID, THREADS, ...)                                                                          \
+    do {                                                                                                               \
+        if (bf && d == 128) hipLaunchKernelGGL((KERNEL(true, 128)), GRID, dim3(THREADS), 0, s, __VA_ARGS__);           \
+        else if (bf) hipLaunchKernelGGL((KERNEL(true, 64)), GRID, dim3(THREADS), 0, s, __VA_ARGS__);                   \
+        else if (d == 128) hipLaunchKernelGGL((KERNEL(false, 128)), GRID, dim3(THREADS), 0, s, __VA_ARGS__);           \
+        else hipLaunchKernelGGL((KERNEL(false, 64)), GRID, dim3(THREADS), 0, s, __VA_ARGS__);                          \
     } while (0)
+#define FASTAR_VERIFY(BF, DD) tc_verify_kernel<BF, DD, false>
+#define FASTAR_VERIFY_SETTLE(BF, DD) tc_verify_kernel<BF, DD, true>
+#define FASTAR_APPLY(BF, DD) tc_apply_kernel<BF, DD>
     if (!fused_verify) {
-        const int n_slices = settle ? settle_slices(C) : 0;
-        tgrid.x += n_slices;
-        FASTAR_TC(tc_verify_kernel, cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest,
-                  cleared ? best : nullptr, win, grp, merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE,
-                  n_slices, so);
-        tgrid.x -= n_slices;
+        // twice the threads where the launch also counts the ages: a slice is then one round of loads (11.6 -> 9 us at 12 heads x
+        // 1560 tokens x 32760 slots)
+        const int threads = settle ? SETTLE_THREADS : 256, n_slices = settle ? settle_slices(C) : 0;
+        const dim3 vgrid((n_new + threads / 16 - 1) / (threads / 16) + n_slices, H);
+#define FASTAR_VERIFY_ARGS                                                                                              \
+    cache->K, K_new, cp, r, C, n_new, codec->qscale, metric, tau2_q16, jstar, sbest, cleared ? best : nullptr, win, grp,  \
+        merged, cache->len, cache->stamp, frame_id, plan_scratch, self_hist ? -1 : PS_HIST, PS_FUT, PS_STRIDE, n_slices, so
+        if (settle) FASTAR_TC(FASTAR_VERIFY_SETTLE, vgrid, threads, FASTAR_VERIFY_ARGS);
+        else FASTAR_TC(FASTAR_VERIFY, vgrid, threads, FASTAR_VERIFY_ARGS);
+#undef FASTAR_VERIFY_ARGS
         FASTAR_LAUNCH_CHECK();
     }
     if (settle) {
@@ -2998,12 +3001,15 @@ extern "C" int tempcache_compress(const fastar_cache *cache, const fastar_codec 
         else FASTAR_PLAN(16, 8);
 #undef FASTAR_PLAN
         FASTAR_LAUNCH_CHECK();
-        FASTAR_TC(tc_apply_kernel, cache->K, cache->V, cache->code, cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new,
+        FASTAR_TC(FASTAR_APPLY, tgrid, 256, cache->K, cache->V, cache->code, cache->cnt, cache->stamp, C, r, K_new, V_new, ck, n_new,
                   frame_id, jstar, merged, win, grp, rank, victims, hs, merge_map, cache->len, rep_mode, plan_scratch,
                   (int)PS_STRIDE, stats);
         FASTAR_LAUNCH_CHECK();
     }
 #undef FASTAR_TC
+#undef FASTAR_VERIFY
+#undef FASTAR_VERIFY_SETTLE
+#undef FASTAR_APPLY
     if (rep_mode == FASTAR_REP_MEAN) {
         const dim3 rgrid((n_new + 63) / 64, H);
 #define FASTAR_RECODE(BF, DD, RR)                                                                                     \
