@@ -5,9 +5,9 @@
 //   score_*_kernel      int8 matrix-core scoring of summaries x key codes, reduced on the fly to one
 //                       int32 per (query block, key block) [AnnSA] or per (query block, prompt token)
 //                       [AnnCA]; HBM-bound: every key code is streamed exactly once
-//   topk                exact top-n_sel per row by radix select, ties to the lowest index, written in
-//                       ascending order by ballot + prefix-sum compaction (a kernel of its own for AnnSA,
-//                       the tail of the scoring kernel for AnnCA, where one workgroup owns a whole row)
+//   topk                exact top-n_sel per row, ties to the lowest index, written in ascending order
+//                       (topk_dev.hpp; a kernel of its own for AnnSA, the tail of the scoring kernel for
+//                       AnnCA, where one workgroup owns a whole row)
 // Short caches: all three in one launch (select_short_kernel).
 #include <limits.h>
 

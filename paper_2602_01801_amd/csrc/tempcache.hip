@@ -196,11 +196,10 @@ __global__ __launch_bounds__(256) void tc_match_kernel(const int8_t *__restrict_
 // A score 2 dot - |code|^2 is twice T = dot - ceil(|code|^2 / 2), plus one where |code|^2 is odd, so the scan needs one
 // matrix product instead of two, for T.  Who wins among the candidates of the largest T (odd |code|^2 first, then the
 // smallest slot):
-//   ORDERED (a range of the cache): those with odd |code|^2 come first, slots ascending in each half, so the earliest
-//   position is the winner;
+//   ORDERED (a range of the cache, or a list ranked into slot order): those with odd |code|^2 come first, slots ascending in
+//   each half, so the earliest position is the winner;
 //   otherwise (a candidate list in any order, without repeats): positions mean nothing, cslot carries the parity in its top
-//   bit (set for even), and the scan notes whether a second group of 32 reaches the largest T; the few tokens for which
-//   one does look through all candidates.
+//   bit (set for even), and the scan notes whether a second group of 32 reaches the largest T, for the caller to settle.
 constexpr int WIN_THREADS = 512;
 constexpr unsigned SLOT_EVEN = 0x80000000u;
 template <int R, int TOKS, bool ORDERED>
@@ -253,8 +252,8 @@ struct WindowScan {
         }
         // One group of 32 candidates per step.  A wavefront issues in order, so the matrix instructions of one half of the
         // token groups are issued before the maxima of the half before them, and the operands, in two rotating sets, are
-        // read most of a step before they are used.  Steps past the end repeat the last group, which changes nothing: only
-        // a strictly higher score replaces the best.
+        // read most of a step before they are used.  Steps past the end repeat the last group: ORDERED, that changes nothing (only
+        // a strictly higher score replaces the best); otherwise they are left out of the maxima, as they would look like ties.
         constexpr int HALF = NG / 2;
         struct Operands {
             i32x4 a[KS];
@@ -474,10 +473,11 @@ struct OddFirst {
 
 // ---- match of the whole cache --------------------------------------------------------------------------------
 // One workgroup = one range of slots (staged in LDS once) x one share of the frame's tokens, taken in blocks of up to TOKS;
-// the best of a range goes to the token's packed (score, smallest slot) word.  What bounds it: the vector instructions of
-// the maxima, 40 cycles per 32 x 32 scores, beside 32 of the matrix product.  (A chunk of 256 slots per workgroup in
-// registers with doubled products, position words and eight times the atomic operations took 71 us at 12 heads x 1560
-// tokens x 32760 slots, this kernel 45; two workgroups per unit with 128 tokens each: 50.)
+// the best of a range goes to the token's packed (score, smallest slot) word.  What bounds it is not shown: at 12 heads x 1560
+// tokens x 32760 slots the maxima (40 cycles per 32 x 32 scores) and the matrix products (32) are 11 to 20 us of the launch's 47;
+// a workgroup's last block of tokens (780 in blocks of 224) leaves half of its wavefronts without work.  (A chunk of 256 slots
+// per workgroup in registers with doubled products, position words and eight times the atomic operations took 71 us there; two
+// workgroups per unit with 128 tokens each 50.)
 template <int R, int TOKS>
 __global__ __launch_bounds__(WIN_THREADS, 2) void tc_match_all_kernel(const int8_t *__restrict__ code,
                                                                       const int32_t *__restrict__ len, int C,
@@ -648,14 +648,14 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 // (each takes a whole unit's LDS, and the last heads' tokens waited), 208 as their tail, 206 behind; 24 x 2048 x 63488 85, 69, 64.
 // TOKS: tokens per workgroup.  64 (eight wavefronts share the window scan) when the call is latency-bound; 256 (four
 // wavefronts share the scan for their 128 tokens) when there are many more workgroups than the chip holds at once:
-// staging the window is then paid a quarter as often.  The wide form's prefetched rows and operands do not all fit the
-// registers: with bf16 rows of 128 it spills 100 bytes per lane (r = 32; 268 at r = 64), around the scan, not in its loop.
+// staging the window is then paid a quarter as often.  The wide form's prefetched rows and operands take 252 registers (r = 32);
+// at r = 64 with rows of 128 it spills 144 bytes per lane, around the scan, not in its loop.
 //
 // What bounds it: the chain of dependent phases of one workgroup.  Mean per phase at 12 heads x 1560 tokens and candidates
 // (timestamps inside the kernel, us): list 3.5, repeats 0.7, encode 1.7 and staging 1.0 (the code rows are in flight
-// meanwhile), scan 2.0, look-up 1.7, threshold test 2.3.  Staged in slot order (ids ranked through the bitmap, odd norms
-// first), so that position decides ties, list to staging took 8.1 and the encode another 2.1; the scan now pays 0.2 for
-// noting ties and the look-up 0.6 for settling them.  Launch 21 -> 18, chunk of three calls 293 -> 285.
+// meanwhile), scan 2.0, look-up 1.7, threshold test 2.3.  With 64 tokens, staged in slot order, so that position decides ties,
+// list to staging took 8.1 and the encode another 2.1; in list order the scan pays 0.2 for noting ties and the look-up 0.6 for
+// settling them.  Launch 21 -> 18, chunk of three calls 293 -> 285.
 // The scan was bound by the matrix units (two products per score) and the LDS (a group's codes and penalties, 5 KB, read
 // for 32 tokens): one product, and 64 or 128 tokens per read; 256 tokens x 3600 candidates 18 -> 9 us, launch at
 // 40 heads x 3600 tokens 113 -> 92.
