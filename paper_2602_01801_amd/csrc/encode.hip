@@ -11,12 +11,12 @@
 namespace fastar {
 
 constexpr int CLEAR_RUN = 4096;   // slots per workgroup that clears group records
-template <bool BF16, int D, int R>
+template <bool BF16, int D, int R, bool CLEAR>
 __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x, int64_t n_vec,
                                                      const int8_t *__restrict__ Rm, float qscale, int shift,
                                                      int8_t *__restrict__ code, unsigned long long *zero_fill,
                                                      int64_t zero_n, unsigned enc_blocks, ClearRecords clear) {
-    if (blockIdx.x >= enc_blocks) {   // uniform: the records of a run of slots
+    if (CLEAR && blockIdx.x >= enc_blocks) {   // uniform: the records of a run of slots
         const int per_head = (clear.C + CLEAR_RUN - 1) / CLEAR_RUN, at = (int)(blockIdx.x - enc_blocks);
         const int h = at / per_head, j0 = (at - h * per_head) * CLEAR_RUN;
         const int j1 = min(j0 + CLEAR_RUN, min(clear.len[h], clear.C));
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void encode_kernel(const void *__restrict__ x,
     const int lane = lane_id();
     const int col = lane & 15, g = lane >> 4;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t gthreads = (int64_t)enc_blocks * blockDim.x;
+    const int64_t gthreads = (int64_t)(CLEAR ? enc_blocks : gridDim.x) * blockDim.x;
     // optional: clear a 64-bit array for a later kernel of the same call
     for (int64_t i = gtid; i < zero_n; i += gthreads) zero_fill[i] = 0ull;
 
@@ -62,9 +62,14 @@ static void launch_encode(const void *x, int64_t n_vec, const fastar_codec *code
     int64_t blocks = (groups + 3) / 4;
     if (blocks > 4096) blocks = 4096;
     if (blocks < 1) blocks = 1;
-    const int64_t clearing = clear.win ? (int64_t)clear.H * ((clear.C + CLEAR_RUN - 1) / CLEAR_RUN) : 0;
-    hipLaunchKernelGGL((encode_kernel<BF16, D, R>), dim3((unsigned)(blocks + clearing)), dim3(256), 0, s, x, n_vec, codec->R,
-                       codec->qscale, codec->shift, code, zero_fill, zero_n, (unsigned)blocks, clear);
+    if (clear.win) {
+        const int64_t clearing = (int64_t)clear.H * ((clear.C + CLEAR_RUN - 1) / CLEAR_RUN);
+        hipLaunchKernelGGL((encode_kernel<BF16, D, R, true>), dim3((unsigned)(blocks + clearing)), dim3(256), 0, s, x, n_vec,
+                           codec->R, codec->qscale, codec->shift, code, zero_fill, zero_n, (unsigned)blocks, clear);
+    } else {
+        hipLaunchKernelGGL((encode_kernel<BF16, D, R, false>), dim3((unsigned)blocks), dim3(256), 0, s, x, n_vec, codec->R,
+                           codec->qscale, codec->shift, code, zero_fill, zero_n, (unsigned)blocks, clear);
+    }
 }
 
 // Internal launcher shared with tempcache_compress: encodes and optionally zero-fills an array.
