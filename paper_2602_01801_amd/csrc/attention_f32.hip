@@ -4,21 +4,28 @@
 // v_mfma_f32_16x16x4_f32 multiplies and adds in fp32 like a chain of fma, at twice the rate of the vector ALU, and needs
 // no operand broadcast: a wavefront owns 16 queries and walks tiles of 32 listed keys, with both contractions transposed
 // so that everything that belongs to a query stays in its lane (lane l: query l % 16):
-//     S^T = K Q^T    A = K rows straight from global memory (lane l: key l % 16, coordinates 16 c + 4 (l / 16) .. + 3),
+//     S^T = K Q^T    A = K rows by way of LDS (lane l: key l % 16, coordinates 16 c + 4 (l / 16) .. + 3),
 //                    B = Q in registers; accumulator register v of lane l is key 4 (l / 16) + v
 //     O^T = V^T P^T  B = the S^T registers as they are (k slot l / 16 of step v is key 4 (l / 16) + v),
-//                    A = V rows straight from global memory: which output column a row of A stands for is free, so block db
-//                    of D / 16 takes columns (D / 16) (l % 16) + db and a lane's elements of one V row are consecutive
-// No tile is shared inside a workgroup, so there is no LDS staging and no barrier in the loop; K of the next tile is in
-// flight under the second product and V under the first.
+//                    A = V rows straight from global memory: which output column a row of A stands for is free, so block
+//                    4 g + e of D / 16 takes columns 64 g + 4 (l % 16) + e: 16 lanes read 256 consecutive bytes of a row
+// No tile is shared inside a workgroup, so there is no barrier in the loop: a wavefront's tile of K goes from global memory
+// straight into its own piece of LDS, under the second product of the tile before; V is in flight under the first.
 //
-// What bounds it: a wavefront's chain of tiles (128 matrix instructions of 32 cycles per 32 keys at d = 128) while the launch
-// leaves compute units empty, the K and V rows every group fetches through L2 (8 flop per byte) where it fills the chip.
-// Hence 16 queries per wavefront, not 32, and KS = 4 wavefronts of a workgroup per query group: they take every fourth
-// tile and combine their partial sums through LDS.  Measured, d = 128, 15 key blocks of 64 per query block, us with 8 / 4 /
-// 2 / 1 wavefronts per group: 196 groups 35 / 32 / 52 / 97, 512 groups 72 / 64 / 59 / 104, 1076 groups 161 / 132 / 149 / 196,
-// 3516 groups (77 TFLOP/s) 455 / 357 / 359 / 385; one query per thread on the vector ALU took 1700 for the 196 groups.
+// Why K goes by way of LDS: operand A wants neighbouring lanes on different rows, and a load whose neighbouring lanes lie on
+// different 64-byte pieces takes one piece at a time: 16 rows x 64 bytes per instruction bring 38 bytes per ns and compute
+// unit wherever the data comes from, 1 KB in two rows or 256 bytes in four rows 125 to 135 from L2 (probe of such loads).  With K
+// read that way every size ran at 9 TB/s through the first level.
+// What bounds it now: where the chip is full, the matrix instructions: with the loads, the LDS reads, the softmax and the look-ups
+// taken out they alone take 0.87 of the launch (2.2 us per tile of 128 instructions and SIMD: real data lowers their
+// rate, and no vector instruction runs beside an fp32 one, probe); one wavefront per SIMD (196 groups) adds the latency of a
+// tile's chain.  Measured, d = 128, 64-row blocks, before -> now in us: 196 groups x 15 blocks 34.5 -> 27.7, 256 x 63 115 -> 91,
+// 1248 x 59 534 -> 423, 3680 x 13 336 -> 274 (88 TFLOP/s; the instructions alone reach 155 on data that does not change);
+// d = 64: 156 groups x 47 blocks 55.7 -> 38, 1024 x 32 120 -> 105.  Tried: scores of the next tile under the softmax (no gain:
+// nothing overlaps), loads spread among the products (no gain), tiles of 16 keys with three wavefronts per SIMD (no gain).
 #include "common.hpp"
+
+#include <type_traits>
 
 namespace fastar {
 
@@ -31,25 +38,35 @@ constexpr float LN2 = 0.6931471805599453f;
 __device__ __forceinline__ f32x4 mfma_f32_16x16x4(float a, float b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
+// Maximum over the four lanes of a query (lane % 16).
+__device__ __forceinline__ float max_of_quarters(float v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 
 // What masked positions (padding, rows past len, the end of the list) fetch: a row of the cache that nothing selects need not
-// be finite, and inf + -inf or 0 * inf would reach the output.  Offsets instead of row numbers in the table, so that the
-// choice costs nothing per load: 33 us at 196 groups x 15 key blocks against 32 with masked positions on row 0 (a branch that
-// clears their operands instead: 35).
-__device__ float zero_row[128];
+// be finite, and inf + -inf or 0 * inf would reach the output.
+__device__ __attribute__((aligned(16))) float zero_row[128];
 
-constexpr int KS = 4;     // wavefronts of a workgroup: they share one query group and split its tiles
-
-template <int D>
+// KS: wavefronts of a workgroup; they share one query group and split its tiles.
+// UNI: key blocks of 32 or 64 rows, so that a tile lies in one of them.
+template <int D, int KS, bool UNI>
 __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
     const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, const int32_t *__restrict__ cnt,
     const int32_t *__restrict__ len, const int32_t *__restrict__ sel, const int32_t *__restrict__ nsel, int n_q, int C,
     int BQ, int BK, int n_sel, int n_qb, int groups_per_block, int n_groups, float scale_log2, float *__restrict__ O,
     float *__restrict__ lse) {
     constexpr int CH = D / 16;   // 16-coordinate chunks of a row, and V columns per lane
-    __shared__ __attribute__((aligned(16))) long long tvrows[KS][TKF];
+    constexpr int RP = D / 4;    // 16-byte pieces of a row
+    constexpr int RI = 64 / RP;  // rows one direct load brings: 64 lanes of 16 bytes
+    constexpr int PS = 65;       // pitch of a register's 64 lanes among the partial sums (banks)
+    __shared__ __attribute__((aligned(16))) long long trows[KS][TKF];
     __shared__ __attribute__((aligned(16))) float tbiases[KS][TKF];
-    __shared__ float po[KS][4 * CH][64];       // partial O^T, as it sits in the registers
+    // the wavefronts' K tiles; after the loop the partial O^T, as it sits in the registers
+    __shared__ __attribute__((aligned(1024))) float ktiles[KS][TKF * D];   // rows at multiples of their size: see kaddr
+    static_assert(TKF * D >= 4 * CH * PS, "the partial sums fit");
     __shared__ float pm[KS][QW], pl[KS][QW];   // reference maxima and row sums
     const int tid = threadIdx.x, lane = tid & 63;
     const int ks = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -81,146 +98,246 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
             o[c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
     }
-    float m_run = -INFINITY, l_run = 0.0f;   // of this lane's query; l_run over this lane's keys only
+    float m_run = -INFINITY, m_safe = 0.0f, l_run = 0.0f;   // of this lane's query; l_run over this lane's keys only
 
-    // this wavefront's row table: V row and bias of the 32 positions of a tile (rows as byte offsets from the head's own)
-    long long *tvrow = tvrows[ks];
-    float *tbias = tbiases[ks];
-    struct Position {
-        long long k, v;
-        float bias;
+    // Row table of this wavefront's tile (byte offsets from the head's own K or V) for tiles with masked positions or of
+    // small key blocks, and the bias of its 32 positions.
+    long long *trow = trows[ks];
+    float *tbias = tbiases[ks], *ktile = ktiles[ks];
+    const long long zk = (const char *)zero_row - (const char *)Kh, zv = (const char *)zero_row - (const char *)Vh;
+    // What is known of a tile: its list entry (of position lane % 32; UNI: of the whole tile), asked for a step before it is
+    // resolved; `row`, the position's slot (-1: masked), `whole`: UNI and no position masked, `first`: UNI, its first slot;
+    // the position's multiplicity, asked for a step before it is used.
+    const int eshift = UNI ? __builtin_ctz(BK / TKF) : 0;
+    const int pl32 = lane & (TKF - 1);
+    auto entry = [&](int t) {
+        if (UNI) return sel_row[min(t >> eshift, n_listed - 1)];
+        return sel_row[min((t * TKF + pl32) / BK, n_listed - 1)];
     };
-    const Position masked = {(const char *)zero_row - (const char *)Kh, (const char *)zero_row - (const char *)Vh, -INFINITY};
-    auto lookup = [&](int t) {   // position lane % 32 of tile t
-        Position pos = masked;
-        const int p = t * TKF + (lane & 31);
-        if (p < n_pos) {
-            const int e = p / BK;
-            const int kb = sel_row[e];
-            const int k = kb * BK + (p - e * BK);
-            if (kb >= 0 && k < L) {
-                pos.k = pos.v = (long long)k * (D * 4);
-                pos.bias = cnt_h ? log2f((float)cnt_h[k]) : 0.0f;
+    struct Tile {
+        int first, row;
+        bool whole;
+    };
+    auto resolve = [&](int t, int kb) {
+        Tile x;
+        if (UNI) {
+            x.first = kb * BK + (t & ((1 << eshift) - 1)) * TKF;
+            const int live = kb < 0 ? 0 : L - x.first;
+            x.whole = live >= TKF;
+            x.row = pl32 < live ? x.first + pl32 : -1;
+        } else {
+            const int p = t * TKF + pl32;
+            const int k = kb * BK + p % BK;
+            x.first = 0;
+            x.whole = false;
+            x.row = p < n_pos && kb >= 0 && k < L ? k : -1;
+        }
+        return x;
+    };
+    // branch-free, so that waiting for it does not drain the loads behind it
+    const int32_t *np = cnt_h ? cnt_h : len;
+    const unsigned nmask = cnt_h ? 0x7FFFFFFFu : 0u;
+    auto multiplicity = [&](const Tile &x) { return np[(unsigned)max(x.row, 0) & nmask]; };
+    const int lrow = lane / RP, lpiece = lane % RP;
+    unsigned koff[16 / RI];   // this lane's piece of its row in the first 16 rows' loads
+#pragma unroll
+    for (int i = 0; i < 16 / RI; ++i) koff[i] = (unsigned)(lrow * (D * 4) + 16 * (lpiece ^ (i * RI + lrow)));
+    // K of a tile straight into LDS, rows [from, to) of it; piece c of row w lies at piece c ^ (w & 15) of it
+    auto load_k = [&](const Tile &x, int from, int to) {
+        if (UNI && x.whole) {
+            const char *base = (const char *)(Kh + (size_t)x.first * D);
+#pragma unroll
+            for (int i = from / RI; i < to / RI; ++i)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(base + i * RI * D * 4 + koff[i % (16 / RI)]),
+                    (__attribute__((address_space(3))) void *)(ktile + i * RI * D), 16, 0, 0);
+        } else {
+            if (from == 0 && lane < TKF) trow[lane] = x.row >= 0 ? (long long)x.row * (D * 4) : zk;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int i = from / RI; i < to / RI; ++i) {
+                const int w = i * RI + lrow;
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)((const char *)Kh + trow[w] + 16 * (lpiece ^ (w & 15))),
+                    (__attribute__((address_space(3))) void *)(ktile + i * RI * D), 16, 0, 0);
             }
         }
-        return pos;
     };
-    f32x4 kf[2][CH];
-    auto load_k = [&](long long krow) {   // the key of this lane's row of either half tile: lanes 0..31 hold positions 0..31
+    // V row of this lane's key 16 hh + 4 quarter + v, i = 4 hh + v
+    float vf[2][4][CH];
+    auto load_v = [&](auto whole, const Tile &x, int i) {
+        const char *vp;
+        if constexpr (decltype(whole)::value) {
+            vp = (const char *)(Vh + (size_t)x.first * D) + (unsigned)(quarter * (16 * D) + 16 * qc + ((i >> 2) * 16 + (i & 3)) * (D * 4));
+        } else {
+            vp = (const char *)(Vh + 4 * qc) + trow[(i >> 2) * 16 + 4 * quarter + (i & 3)];
+        }
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const float *kp = (const float *)((const char *)(Kh + 4 * quarter) + __shfl(krow, 16 * hh + qc, WAVE));
+        for (int c = 0; c < CH; c += 4) {
+            const f32x4 w = *(const f32x4 *)(vp + 64 * c);
 #pragma unroll
-            for (int c = 0; c < CH; ++c) kf[hh][c] = *(const f32x4 *)(kp + 16 * c);
+            for (int e = 0; e < 4; ++e) vf[i >> 2][i & 3][c + e] = w[e];
         }
     };
-    Position next = masked;
-    if (ks < nt) {
-        next = lookup(ks);
-        load_k(next.k);
-    }
-    for (int t = ks; t < nt; t += KS) {
-        if (lane < TKF) {
-            tvrow[lane] = next.v;
-            tbias[lane] = next.bias;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        // V rows of this lane's keys 16 hh + 4 quarter + v
-        float vf[2][4][CH];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float *vp = (const float *)((const char *)(Vh + CH * qc) + tvrow[16 * hh + 4 * quarter + v]);
-#pragma unroll
-                for (int c = 0; c < CH; c += 4) {
-                    const f32x4 w = *(const f32x4 *)(vp + c);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) vf[hh][v][c + e] = w[e];
-                }
-            }
-        }
-        if (t + KS < nt) next = lookup(t + KS);
-        f32x4 s[2];
+    // LDS address of piece `quarter` of this lane's key of the first half tile; chunk c is 64 c bytes on, by exclusive or
+    const unsigned kaddr = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float *)ktile + (unsigned)(qc * (D * 4) + 16 * (quarter ^ qc));
+    auto read_k = [&](int c, f32x4 (&f)[2]) {
+        const unsigned at = kaddr ^ (unsigned)(64 * c);
+        asm volatile("ds_read_b128 %0, %1" : "=v"(f[0]) : "v"(at));
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f[1]) : "v"(at), "n"(16 * D * 4));
+    };
+    auto wait_k = [&](f32x4 (&f)[2], int behind) {   // at most `behind` LDS reads of read_k later than f's
+        if (behind == 2) asm volatile("s_waitcnt lgkmcnt(4)" : "+v"(f[0]), "+v"(f[1]));
+        else if (behind == 1) asm volatile("s_waitcnt lgkmcnt(2)" : "+v"(f[0]), "+v"(f[1]));
+        else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0]), "+v"(f[1]));
+    };
+    // S^T of the tile in LDS
+    auto scores = [&](f32x4 (&s)[2]) {
+        f32x4 kf[4][2];   // operands are asked for two chunks ahead
+        read_k(0, kf[0]);
+        read_k(1, kf[1]);
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) s[hh] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c) {
+            if (c + 2 < CH) read_k(c + 2, kf[(c + 2) & 3]);
+            wait_k(kf[c & 3], c + 2 < CH ? 2 : c + 1 < CH ? 1 : 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int hh = 0; hh < 2; ++hh) s[hh] = mfma_f32_16x16x4(kf[hh][c][e], q[c][e], s[hh]);
-        if (t + KS < nt) load_k(next.k);
-        float mx = -INFINITY;
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const f32x4 bv = *(const f32x4 *)(tbias + 16 * hh + 4 * quarter);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                s[hh][v] = fmaf(s[hh][v], scale_log2, bv[v]);
-                mx = fmaxf(mx, s[hh][v]);
-            }
+                for (int hh = 0; hh < 2; ++hh) s[hh] = mfma_f32_16x16x4(kf[c & 3][hh][e], q[c][e], s[hh]);
         }
-        mx = fmaxf(mx, shfl_xor(mx, 16));
-        mx = fmaxf(mx, shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx);
-        const float m_safe = m_new == -INFINITY ? 0.0f : m_new;   // every key so far masked
-        const float alpha = exp2f(m_run - m_safe);
-        m_run = m_new;
-        l_run *= alpha;
+    };
+    auto store_bias = [&](const Tile &x, int n) {
+        const float bias = x.row < 0 ? -INFINITY : cnt_h ? log2f((float)n) : 0.0f;
+        if (lane < TKF) tbias[lane] = bias;
+    };
+
+    Tile cur = {0, -1, false};
+    int n_cur = 1, kb_next = -1;
+    if (ks < nt) {
+        cur = resolve(ks, entry(ks));
+        n_cur = multiplicity(cur);
+        kb_next = entry(ks + KS);
+        load_k(cur, 0, TKF);
+    }
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+    for (int c = 0; c < CH; ++c) asm volatile("" : "+v"(q[c]));   // waited for here, not in the loop
+    asm volatile("" : "+v"(n_cur));
+    if (!UNI) asm volatile("" : "+v"(kb_next));
+    auto step = [&](auto whole, int t) {
+        store_bias(cur, n_cur);
+        if constexpr (!decltype(whole)::value) {
+            if (lane < TKF) trow[lane] = cur.row >= 0 ? (long long)cur.row * (D * 4) : zv;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        const Tile next = resolve(t + KS, kb_next);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // K of the tile has landed
+        int n_next = multiplicity(next);
+        kb_next = entry(t + 2 * KS);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                s[hh][v] = exp2f(s[hh][v] - m_safe);
-                l_run += s[hh][v];
-            }
+        for (int i = 0; i < 8; ++i) load_v(whole, cur, i);
+        f32x4 s[2];
+        scores(s);
+        f32x4 bv[2];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) o[c] *= alpha;
+        for (int hh = 0; hh < 2; ++hh) bv[hh] = *(const f32x4 *)(tbias + 16 * hh + 4 * quarter);
+        // V is waited for before the next K is asked for: the compiler's wait would be for both
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
 #pragma unroll
+                for (int c = 0; c < CH; ++c) asm volatile("" : "+v"(vf[hh][v][c]));
+        asm volatile("" : "+v"(n_next)::"memory");
+        if (!UNI) asm volatile("" : "+v"(kb_next));
+        if (t + KS < nt) load_k(next, 0, TKF);   // the tile in LDS has been read: wait_k saw its last operand
+        float mx = -INFINITY;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s[hh][v] = fmaf(s[hh][v], scale_log2, bv[hh][v]);
+                mx = fmaxf(mx, s[hh][v]);
+            }
+        mx = max_of_quarters(mx);
+        if (__any(mx > m_run)) {   // (uniform) a new maximum: what is summed up so far moves to it
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // m_new is finite where it is new
+            const float al = m_new == -INFINITY ? 1.0f : alpha;
+            m_run = m_new;
+            m_safe = m_new == -INFINITY ? 0.0f : m_new;                  // every key so far masked
+            l_run *= al;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) o[c] *= al;
+        }
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s[hh][v] = __builtin_amdgcn_exp2f(s[hh][v] - m_safe);
+                l_run += s[hh][v];
+            }
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+#pragma unroll
                 for (int c = 0; c < CH; ++c) o[c] = mfma_f32_16x16x4(vf[hh][v][c], s[hh][v], o[c]);
+            }
+        cur = next;
+        n_cur = n_next;
+    };
+    for (int t = ks; t < nt;) {   // loops of their own, so that the sums stay in place
+        if constexpr (UNI)
+            for (; t < nt && cur.whole; t += KS) step(std::true_type{}, t);
+        for (; t < nt && !(UNI && cur.whole); t += KS) step(std::false_type{}, t);
     }
     float l_tot = l_run + shfl_xor(l_run, 16);
     l_tot += shfl_xor(l_tot, 32);
 
-    // The partial sums meet in LDS; each wavefront finishes its share of the columns.  o[c][v]: column
-    // CH * (4 quarter + v) + c of query qc.
+    // The partial sums meet in LDS and leave it in rows.  o[c][v]: column 64 (c / 4) + 4 (4 quarter + v) + c % 4 of query qc.
+    float *po = ktile;   // every wavefront is done with its own tiles
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int c = 0; c < CH; ++c) po[ks][v * CH + c][lane] = o[c][v];
+        for (int c = 0; c < CH; ++c) po[(v * CH + c) * PS + lane] = o[c][v];
     if (quarter == 0) {
         pm[ks][qc] = m_run;
         pl[ks][qc] = l_tot;
     }
     __syncthreads();
-    float m_all = -INFINITY;
+    static_assert(QW * RP % (KS * 64) == 0, "whole rounds");
 #pragma unroll
-    for (int k = 0; k < KS; ++k) m_all = fmaxf(m_all, pm[k][qc]);
-    float wgt[KS], l_all = 0.0f;
+    for (int i = 0; i < QW * RP / (KS * 64); ++i) {
+        const int row = (i * KS * 64 + tid) / RP, piece = tid % RP;   // 4 columns of one query
+        float m_all = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-        wgt[k] = m_all == -INFINITY ? 0.0f : exp2f(pm[k][qc] - m_all);
-        l_all += wgt[k] * pl[k][qc];
-    }
-    if (qc >= nq_here) return;
-    const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
-    float *orow = O + ((size_t)h * n_q + q0 + qc) * D + CH * (4 * quarter + ks);   // register v = ks is this wavefront's share
+        for (int k = 0; k < KS; ++k) m_all = fmaxf(m_all, pm[k][row]);
+        float wgt[KS], l_all = 0.0f;
 #pragma unroll
-    for (int c = 0; c < CH; c += 4) {
+        for (int k = 0; k < KS; ++k) {
+            wgt[k] = m_all == -INFINITY ? 0.0f : exp2f(pm[k][row] - m_all);
+            l_all += wgt[k] * pl[k][row];
+        }
+        const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
+        const float *pr = &ktiles[0][0] + ((piece & 3) * CH + 4 * (piece >> 4)) * PS + row + 16 * ((piece >> 2) & 3);
         f32x4 r = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int k = 0; k < KS; ++k) r[e] += wgt[k] * po[k][ks * CH + c + e][lane];
-        *(f32x4 *)(orow + c) = r * inv;
+            for (int k = 0; k < KS; ++k) r[e] += wgt[k] * pr[k * (TKF * D) + e * PS];
+        if (row < nq_here) {
+            *(f32x4 *)(O + ((size_t)h * n_q + q0 + row) * D + 4 * piece) = r * inv;
+            if (lse && piece == 0) lse[(size_t)h * n_q + q0 + row] = l_all > 0.0f ? (m_all + log2f(l_all)) * LN2 : -INFINITY;
+        }
     }
-    if (lse && quarter == 0 && ks == 0)
-        lse[(size_t)h * n_q + q0 + qc] = l_all > 0.0f ? (m_all + log2f(l_all)) * LN2 : -INFINITY;
+}
+
+template <int D>
+static auto kernel_of(int ks, bool uni) {
+    return ks == 2 ? (uni ? attn_f32_kernel<D, 2, true> : attn_f32_kernel<D, 2, false>)
+                   : (uni ? attn_f32_kernel<D, 4, true> : attn_f32_kernel<D, 4, false>);
 }
 
 }  // namespace f32a
@@ -232,8 +349,14 @@ int launch_attn_f32(const void *Q, int n_q, const void *K, const void *V, const 
     const int n_qb = (n_q + BQ - 1) / BQ, gpb = (BQ + QW - 1) / QW;
     const long long n_groups = (long long)H * n_qb * gpb;
     if (n_groups >= (1ll << 30)) return FASTAR_ERR_UNSUPPORTED;
+    const bool uni = BK == 32 || BK == 64;
+    const long long n_tiles = ((long long)n_sel * BK + TKF - 1) / TKF;
+    // Two wavefronts per group where four would have a tile or none each: up to two tiles always (us with two / four wavefronts:
+    // 224 groups 7.3 / 7.6, 1152 groups 18.5 / 25.3, 3680 groups 41 / 62), up to four where the chip is full (1152 groups
+    // 26.3 / 27.2; 32 groups of 8 tiles of 64 coordinates 8.7 / 6.3).
+    const int ks = n_tiles <= 2 || (n_tiles <= 4 && n_groups >= 1024) ? 2 : 4;
     const dim3 grid((unsigned)((n_groups + 7) / 8 * 8));
-    hipLaunchKernelGGL(d == 128 ? attn_f32_kernel<128> : attn_f32_kernel<64>, grid, dim3(KS * 64), 0, s, (const float *)Q,
+    hipLaunchKernelGGL((d == 128 ? kernel_of<128>(ks, uni) : kernel_of<64>(ks, uni)), grid, dim3(ks * 64), 0, s, (const float *)Q,
                        (const float *)K, (const float *)V, cnt, len, sel, nsel, n_q, C, BQ, BK, n_sel, n_qb, gpb, (int)n_groups,
                        scale_log2, (float *)O, lse);
     if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;

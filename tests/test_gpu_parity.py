@@ -551,6 +551,30 @@ def test_attention_skips_negative_and_dead_entries_inside_a_list():
     check_attention(Q, K, V, cnt, length, sel, nsel, BQ, BK, d ** -0.5, "bf16")
 
 
+@pytest.mark.parametrize("d,n_q,BQ,BK,n_sel", [
+    (128, 300, 128, 64, 1), (64, 2100, 128, 64, 2), (128, 2100, 128, 32, 4),      # two wavefronts per group of queries
+    (128, 300, 128, 64, 2), (64, 300, 64, 64, 3), (128, 100, 128, 32, 5), (128, 300, 100, 64, 30),   # four
+    (128, 300, 128, 16, 5), (64, 300, 128, 48, 23), (128, 70, 64, 1, 31), (64, 70, 64, 1, 65)])      # positions row by row
+def test_fp32_attention_over_whole_and_masked_tiles_in_any_order(d, n_q, BQ, BK, n_sel):
+    # Tiles of 32 keys that lie wholly in a live block and tiles with masked positions take different loads and may follow
+    # one another in any order: lists with padding, dead blocks and the block that len cuts at any place, repeats among them.
+    rng = np.random.default_rng(1000 * d + 10 * BK + n_sel)
+    H, n_kb = 4, 40
+    C = n_kb * BK + BK // 3
+    n_qb = -(-n_q // BQ)
+    Q, K, V = (rng.standard_normal((H, n, d)).astype(np.float32) for n in (n_q, C, C))
+    K *= np.linspace(0.2, 3.0, C, dtype=np.float32)[None, :, None]          # maxima that move along a list
+    cnt = rng.integers(1, 5, size=(H, C)).astype(np.int32)
+    lens = np.array([C, C - BK - BK // 2, 20 * BK + 1, 0], np.int32)
+    sel = rng.integers(0, n_kb + 1, size=(H, n_qb, n_sel)).astype(np.int32)
+    sel[:, ::2] = np.sort(sel[:, ::2], axis=-1)
+    sel[rng.random(sel.shape) < 0.1] = -1
+    nsel = rng.integers(0, n_sel + 1, size=(H, n_qb)).astype(np.int32)
+    nsel[:, 0] = n_sel
+    check_attention(Q, K, V, cnt, lens, sel, nsel, BQ, BK, d ** -0.5, "fp32")
+    check_attention(Q, K, V, None, lens, sel, nsel, BQ, BK, d ** -0.5, "fp32")
+
+
 @pytest.mark.parametrize("d,BQ,BK,n_kb,n_sel", [
     (128, 128, 1, 900, 48),      # single keys, the list ends inside a step of 32
     (64, 128, 1, 300, 45),
