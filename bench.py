@@ -463,6 +463,9 @@ def attn_kernel_name(n_items, H, C, n_tiles, ws, fp8=False, d=128):
                    (per_xcd > 64 and 5 <= tail <= 24 and n_tiles >= 150)):
             return "attn_fp8_d128_sk_kernel + attn_combine_kernel"
         return "attn_fp8_d128_parts_kernel + attn_combine_parts_kernel, or attn_fp8_d128_kernel" if ws and n_items <= 256 else "attn_fp8_d128_kernel"
+    if n_items <= 128 and n_tiles >= 2:   # groups of 32 queries whose wavefronts share the tiles
+        if n_tiles <= 8 or 12 <= n_items and n_tiles <= (20 if n_items > 64 else 24):
+            return "attn_bf16_waves_kernel<128, %d, true>" % (8 if n_items <= 64 and n_tiles >= 24 else 4)
     pp = "attn_bf16_d128_pp_kernel<4, true, %s, " % ("true" if H * C * d * 2 * 2 <= (256 << 20) else "false")
     if n_items <= 256 and n_tiles > 5:   # one block per workgroup, split over its two groups
         return pp + "true>" + (" (+ attn_combine_parts_kernel where that pays)" if ws and n_items <= 128 and n_tiles > 8 else "")

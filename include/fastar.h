@@ -367,8 +367,9 @@ int sparse_attn_fwd(const void *Q, int n_q, const void *K, const void *V, const 
  *     workgroups: whole rounds of query blocks are taken by one workgroup each, and the blocks left over are cut into
  *     equal shares of their tiles for all resident workgroups;
  *   - at most 128 pairs with more than 8 tiles of 64 listed keys each (n_sel * BK > 512): a block's tiles are cut into
- *     runs, a workgroup each, where that is expected to be faster than one workgroup per block.
- * Which launches these are follows from H, n_q, n_sel and BK alone (attn_split_full_per and attn_parts in common.hpp).
+ *     runs, a workgroup each, where that is expected to be faster than keeping a block in one launch.
+ * Which launches these are follows from H, n_q, n_sel and BK alone (attn_split_full_per and attn_parts in common.hpp,
+ * waves_per_group in attention.hip).
  * Every other call runs exactly as sparse_attn_fwd and leaves `ws` untouched.  Calls that may be in flight at the same
  * time (two streams, two threads) need a workspace each; one is enough for calls that follow one another on a stream.
  *   ws / ws_bytes  fastar_workspace_bytes(FASTAR_OP_ATTN, ...) bytes, 256-byte aligned; contents need not be kept

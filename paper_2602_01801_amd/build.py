@@ -9,8 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfastar.so")
 SOURCES = ["api.hip", "encode.hip", "select.hip", "tempcache.hip", "attention.hip", "attention_d128.hip",
-           "attention_d128_pp.hip", "attention_fp8.hip", "attention_f32.hip", "buckets.hip"]
-ASM_CHECKED = ["attention_d128.hip", "attention_d128_pp.hip", "attention_f32.hip"]  # kernels that read LDS through inline assembly
+           "attention_d128_pp.hip", "attention_waves.hip", "attention_fp8.hip", "attention_f32.hip", "buckets.hip"]
+ASM_CHECKED = ["attention_d128.hip", "attention_d128_pp.hip", "attention_waves.hip", "attention_f32.hip"]  # kernels that read LDS through inline assembly
 # Integer matrix-core results that feed plain ALU epilogues (arg-max, top-k scores): keep them in ordinary vector
 # registers, not accumulation registers that every ALU instruction would first have to copy from.
 PER_SOURCE_FLAGS = {src: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for src in ("tempcache.hip", "select.hip", "encode.hip", "buckets.hip")}

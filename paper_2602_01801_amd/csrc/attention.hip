@@ -11,12 +11,7 @@
 // Softmax runs in fp32 in the log2 domain with a running maximum; masked keys (padding of the list,
 // slots beyond len) get a -inf bias and zeroed K/V rows.
 //
-// Few query blocks (S > 1): the workgroup has S groups of wavefronts, group i takes every S-th tile from i on in tile space
-// of its own, and group 0 adds the others' sums up at the end.  A tile costs a chain of row table, gather, staging and
-// products (about 2 us for a lone workgroup), which otherwise follow one another: 39 blocks of
-// 64 queries x 11 tiles 21.5 -> 13.5 us with four groups.
-//
-// fp32: attention_f32.hip.
+// Few query blocks: attention_waves.hip; fp32: attention_f32.hip.
 #include "common.hpp"
 
 namespace fastar {
@@ -30,27 +25,6 @@ struct __attribute__((aligned(16))) TileMeta {
     float bias[TK];  // log2(cnt) of that row, -inf when masked
 };
 
-// Fill the row table of tile `t` (p = the thread's index in its group; threads 0..63).
-__device__ __forceinline__ void fill_meta(TileMeta &m, int t, const int32_t *__restrict__ sel_row, int n_listed,
-                                          int bk_shift, int L, const int32_t *__restrict__ cnt_h, int p) {
-    if (p < TK) {
-        const int listpos = t * TK + p;
-        const int entry = listpos >> bk_shift;
-        int key = -1;
-        if (entry < n_listed) {
-            const int kb = sel_row[entry];
-            if (kb >= 0) {
-                key = (kb << bk_shift) + (listpos & ((1 << bk_shift) - 1));
-                if (key >= L) key = -1;
-            }
-        }
-        float bias = -INFINITY;
-        if (key >= 0) bias = cnt_h ? __log2f((float)cnt_h[key]) : 0.0f;
-        m.idx[p] = key;
-        m.bias[p] = bias;
-    }
-}
-
 template <int D, int NW>
 struct AttnCfg {
     static constexpr int NT = NW * 64;
@@ -63,25 +37,21 @@ struct AttnCfg {
     static constexpr int K_BYTES = TK * KSTR * 2;
     static constexpr int V_BYTES = D * VSTR * 2;
     static constexpr int O_BYTES = NW * 32 * KSTR * 2;         // epilogue staging, reuses the tile space
-    static constexpr int PART_BYTES = (D / 2 + 2) * 64 * 4;    // a wavefront's accumulators, maxima and row sums
     static constexpr int TILE_BYTES = (K_BYTES + V_BYTES) > O_BYTES ? (K_BYTES + V_BYTES) : O_BYTES;
 };
 
-template <int D, int NW, int S>
-__global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
     const unsigned short *__restrict__ Q, const unsigned short *__restrict__ K, const unsigned short *__restrict__ V,
     const int32_t *__restrict__ cnt, const int32_t *__restrict__ len, const int32_t *__restrict__ sel,
     const int32_t *__restrict__ nsel, int n_q, int C, int bk_shift, int n_sel, int n_qb, int H, float scale_log2,
     unsigned short *__restrict__ O, float *__restrict__ lse) {
     typedef AttnCfg<D, NW> Cfg;
     constexpr int NT = Cfg::NT, KSTR = Cfg::KSTR, VSTR = Cfg::VSTR, CPR = Cfg::CPR;
-    static_assert((S - 1) * NW * Cfg::PART_BYTES <= S * Cfg::TILE_BYTES, "the groups' sums reuse the tile space");
-    __shared__ __attribute__((aligned(16))) unsigned char tile_mem[S * Cfg::TILE_BYTES];
-    __shared__ TileMeta meta_all[S][3];
-    const int grp = S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);   // wave-uniform
-    TileMeta *meta = meta_all[grp];
-    unsigned short *Ks = (unsigned short *)(tile_mem + grp * Cfg::TILE_BYTES);
-    unsigned short *Vt = (unsigned short *)(tile_mem + grp * Cfg::TILE_BYTES + Cfg::K_BYTES);
+    __shared__ __attribute__((aligned(16))) unsigned char tile_mem[Cfg::TILE_BYTES];
+    __shared__ TileMeta meta[3];
+    unsigned short *Ks = (unsigned short *)tile_mem;
+    unsigned short *Vt = (unsigned short *)(tile_mem + Cfg::K_BYTES);
 
     // workgroup -> (head, query block).  Workgroups are dealt round-robin to the 8 XCDs; give each
     // XCD a contiguous range of (head, block) pairs so that the K/V of a head stay in one L2.
@@ -95,7 +65,7 @@ __global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
         h = item / n_qb;
         b = item % n_qb;
     }
-    const int tid = threadIdx.x - grp * NT, lane = tid & 63, wave = tid >> 6;   // of the group
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, g = lane >> 5;
     const int L = min(len[h], C);
     const int n_listed = min(nsel[(size_t)h * n_qb + b], n_sel);
@@ -104,7 +74,6 @@ __global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
     const unsigned short *Kh = K + (size_t)h * C * D;
     const unsigned short *Vh = V + (size_t)h * C * D;
     const int nt = ((n_listed << bk_shift) + TK - 1) / TK;
-    const int steps = (nt + S - 1) / S;   // the same for every group: a tile past the list is all masked rows
 
     // Q fragments of this wavefront's 32 queries (B operand: column = query, k-slots = 8 coordinates)
     const int q_idx = b * (NW * 32) + wave * 32 + col;
@@ -170,20 +139,55 @@ __global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
         }
     };
 
-    auto fill = [&](int t) { fill_meta(meta[t % 3], t * S + grp, sel_row, n_listed, bk_shift, L, cnt_h, tid); };
-    if (steps > 0) {
-        fill(0);
-        if (steps > 1) fill(1);
+    // The row table of a tile is filled by the first wavefront, a lane per position, in three stages (list entry, multiplicity,
+    // table), of which a step does one for each of three tiles: nothing is waited for in the step that asks for it, nor behind
+    // that step's tile loads.  1160 blocks of 128 queries x 90 tiles 430 -> 394 us, 512 x 64 131 -> 122.
+    const bool filler = __builtin_amdgcn_readfirstlane(wave) == 0;
+    auto entry = [&](int t) { return sel_row[max(min((t * TK + lane) >> bk_shift, n_listed - 1), 0)]; };
+    auto resolve = [&](int t, int kb) {   // the position's row, -1: masked
+        const int listpos = t * TK + lane;
+        const int key = (kb << bk_shift) + (listpos & ((1 << bk_shift) - 1));
+        return (listpos >> bk_shift) < n_listed && kb >= 0 && key < L ? key : -1;
+    };
+    auto multiplicity = [&](int key) { return cnt_h ? cnt_h[max(key, 0)] : 1; };
+    auto fill = [&](int t, int key, int n) {
+        meta[t % 3].idx[lane] = key;
+        meta[t % 3].bias[lane] = key < 0 ? -INFINITY : cnt_h ? __log2f((float)n) : 0.0f;
+    };
+    int key2 = -1, n2 = 1, kb3 = -1;
+    if (nt > 0) {
+        if (filler) {
+            const int kb0 = entry(0);
+            int kb1 = -1, kb2 = -1, key1 = -1, n1 = 1;
+            if (nt > 1) {   // uniform; a single tile's chain is all there is to such a launch
+                kb1 = entry(1);
+                kb2 = entry(2);
+                kb3 = entry(3);
+            }
+            const int key0 = resolve(0, kb0), n0 = multiplicity(key0);
+            if (nt > 1) {
+                key1 = resolve(1, kb1);
+                key2 = resolve(2, kb2);
+                n1 = multiplicity(key1);
+                n2 = multiplicity(key2);
+            }
+            fill(0, key0, n0);
+            if (nt > 1) fill(1, key1, n1);
+        }
         __syncthreads();
         issue_loads(meta[0]);
     }
-    for (int t = 0; t < steps; ++t) {
+    for (int t = 0; t < nt; ++t) {
         __syncthreads();  // tile t-1 fully consumed; row table of tile t+1 visible
         store_tiles();
         __syncthreads();
-        if (t + 1 < steps) issue_loads(meta[(t + 1) % 3]);
-        if (t + 2 < steps) fill(t + 2);
-        if (S > 1 && t * S + grp >= nt) break;   // uniform for the wavefront; only in the last step, no barrier is left in the loop
+        if (filler && t + 2 < nt) {
+            fill(t + 2, key2, n2);
+            key2 = resolve(t + 3, kb3);
+            n2 = multiplicity(key2);
+            kb3 = entry(t + 4);
+        }
+        if (t + 1 < nt) issue_loads(meta[(t + 1) % 3]);
         const TileMeta &mt = meta[t % 3];
 
         // S^T = K Q^T : two blocks of 32 keys x 32 queries
@@ -232,7 +236,7 @@ __global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) o_acc[db][v] *= alpha;
 
-        // O^T += V^T P^T : four steps of 16 keys
+        // O^T += V^T P^T : four nt of 16 keys
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -255,32 +259,6 @@ __global__ __launch_bounds__(S * NW * 64, 2) void attn_bf16_kernel(
     }
 
     __syncthreads();
-    if constexpr (S > 1) {
-        // the other groups' accumulators, maxima and sums, lane by lane
-        if (grp > 0) {
-            float *part = (float *)(tile_mem + ((grp - 1) * NW + wave) * Cfg::PART_BYTES) + lane;
-#pragma unroll
-            for (int i = 0; i < D / 2; ++i) part[i * 64] = o_acc[i / 16][i % 16];
-            part[(D / 2) * 64] = m_run;
-            part[(D / 2 + 1) * 64] = l_run;
-        }
-        __syncthreads();
-        if (grp == 0) {
-#pragma unroll
-            for (int o = 1; o < S; ++o) {
-                const float *part = (const float *)(tile_mem + ((o - 1) * NW + wave) * Cfg::PART_BYTES) + lane;
-                const float m_o = part[(D / 2) * 64];
-                const float m_new = fmaxf(m_run, m_o), m_safe = m_new == -INFINITY ? 0.0f : m_new;
-                const float a0 = __builtin_amdgcn_exp2f(m_run - m_safe), a1 = __builtin_amdgcn_exp2f(m_o - m_safe);
-#pragma unroll
-                for (int i = 0; i < D / 2; ++i) o_acc[i / 16][i % 16] = fmaf(o_acc[i / 16][i % 16], a0, part[i * 64] * a1);
-                l_run = fmaf(l_run, a0, part[(D / 2 + 1) * 64] * a1);
-                m_run = m_new;
-            }
-        }
-        __syncthreads();
-        if (grp > 0) return;   // whole wavefronts; the last barrier orders a wavefront's own rows only
-    }
     // epilogue: normalise, transpose through LDS (each wavefront its own rows), store rows coalesced
     const float l_tot = l_run + shfl_xor(l_run, 32);
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
@@ -321,6 +299,10 @@ int launch_attn_bf16_d128_pp(const void *Q, int n_q, const void *K, const void *
                              const int32_t *len, int H, int C, const int32_t *sel, const int32_t *nsel, int bk_shift,
                              int n_sel, float scale_log2, void *O, float *lse, int n_parts, void *ws, hipStream_t s);
 
+int launch_attn_bf16_waves(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len, int H, int C,
+                           int d, const int32_t *sel, const int32_t *nsel, int BQ, int bk_shift, int n_sel, float scale_log2, int S,
+                           void *O, float *lse, hipStream_t s);
+
 size_t attn_sk_ws_bytes();
 int launch_attn_bf16_d128_sk(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt, const int32_t *len,
                              int H, int C, const int32_t *sel, const int32_t *nsel, int bk_shift, int n_sel,
@@ -329,6 +311,39 @@ int launch_attn_bf16_d128_sk(const void *Q, int n_q, const void *K, const void *
 }  // namespace fastar
 
 using namespace fastar;
+
+// Whether a launch of n_items query blocks takes the kernel whose wavefronts share a group of 32 queries, and then their number
+// per group (0: the other kernels).  us of the other kernels / of this one with 2 / 4 / 8 wavefronts, by groups x tiles of 32 keys:
+//   d = 64     256 x 16 13.2 / 10.1 / 7.8 / 7.9, x 32 21.2 / 16.6 / 11.2 / 10.3, x 128 68 / 52 / 30 / 24; 512 x 32 21.7 / 20.2 / 14.7 /
+//              15.3, x 128 68 / 63 / 40 / 39; 800 x 16 14.3 / 13.6 / 14.3 / 18.3, x 128 69 / 67 / 64 / 66; 1280 x 8 12.9 / 11.2 / 13.6 / 18.3,
+//              x 128 121 / 89 / 85 / 86; 2048 x 32 35.9 / 37.7 / 39.9 / 47.1 (with blocks of 64 queries 44 / 38 / 40)
+//   d = 128    64 x 16 14.1 / 12.3 / 8.9 / 10.1, x 48 17.7 / 28 / 17.5 / 17.3, x 64 19.4 / 36 / 21.6 / 20.5; 256 x 32 22 / 21 / 14.6 / 15.2,
+//              x 48 23.1 / 29 / 18.7 / 18.8; 512 x 32 23 / 27 / 21.8 / 27.3, x 64 33.8 / 48 / 35.7 / 41.4; 640 x 16 17 / 18.7 / 20.4 / 28.6
+//              (d = 128 with a workspace, that is with several workgroups per query block where that pays: x 24 with 40 groups 12.0,
+//              and 10.7 here)
+// A call without a workspace takes this kernel also where one with a workspace leaves fragments; where that one leaves none,
+// the two are the same.
+static int waves_per_group(int d, int BQ, int BK, int n_items, int n_sel, bool ws) {
+    const long long groups = (long long)n_items * (BQ / 32), tiles = ((long long)n_sel * BK + 31) / 32;
+    if (d == 64) {
+        if (groups > (BQ == 64 ? 4096 : 1280) || (groups > 640 && tiles <= 4)) return 0;
+        if (tiles <= 2) return 2;
+        if (groups > 512) return tiles >= 64 ? 4 : 2;
+        return tiles >= (groups <= 256 ? 24 : 64) ? 8 : 4;
+    }
+    if (BK != 64 || tiles < 4) return 0;   // rows by way of a table, and single tiles: no gain
+    if (BQ == 64) {
+        if (groups > 1024) return 0;
+        return groups > 512 ? 2 : groups <= 256 && tiles >= 48 ? 8 : 4;
+    }
+    if (groups > 512) return 0;
+    const int most = n_items > 64 ? 40 : 48;
+    if (tiles > 16 && (n_items < 12 || tiles > most)) {
+        const bool fragments = attn_parts(n_items, (int)((tiles + 1) / 2), 2, 1.65f, 0.0f) > 1;
+        if (fragments ? ws : tiles > most) return 0;
+    }
+    return groups <= 256 && tiles >= 48 ? 8 : 4;
+}
 
 static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt,
                             const int32_t *len, int H, int C, int d, int dtype, const int32_t *sel,
@@ -374,8 +389,8 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
         int bk_shift = 0;
         while ((1 << bk_shift) < BK) ++bk_shift;
         const dim3 grid((unsigned)(((n_qb * H + 7) / 8) * 8));
-#define FASTAR_ATTN(DD, NW, S)                                                                                     \
-    hipLaunchKernelGGL((attn_bf16_kernel<DD, NW, S>), grid, dim3(S * NW * 64), 0, s, (const unsigned short *)Q,          \
+#define FASTAR_ATTN(DD, NW)                                                                                        \
+    hipLaunchKernelGGL((attn_bf16_kernel<DD, NW>), grid, dim3(NW * 64), 0, s, (const unsigned short *)Q,                 \
                        (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, nsel, n_q, C, bk_shift, \
                        n_sel, n_qb, H, scale_log2, (unsigned short *)O, lse)
         // Two query blocks per workgroup in anti-phase (matrix | vector) on each SIMD; one workgroup fills a CU, so the
@@ -392,6 +407,8 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
         if (ws && d == 128 && BQ == 128 && full_per > 0)
             return launch_attn_bf16_d128_sk(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, ws,
                                             full_per, s);
+        if (const int S = waves_per_group(d, BQ, BK, n_items, n_sel, ws != nullptr))
+            return launch_attn_bf16_waves(Q, n_q, K, V, cnt, len, H, C, d, sel, nsel, BQ, bk_shift, n_sel, scale_log2, S, O, lse, s);
         // At most one query block per compute unit: both groups of the two-block kernel on one block (156 blocks of 48 tiles
         // 85 -> 51 us, one-block workgroups take 67), with a workspace several workgroups per block where that pays
         // (8 blocks of 96 tiles 161 -> 21 us).  Very short lists stay with the one-block kernel (3 tiles: 8.5 us against 9.5,
@@ -406,16 +423,8 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
                                             nullptr, s);
         if (d == 128)  // tuned path: direct-to-LDS tiles, LDS transpose loads
             return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
-        // d = 64.  At most one query block per compute unit: its tiles over several groups of wavefronts (256 blocks of 64
-        // queries x 11 tiles 22.1 -> 14.7 us, 40 tiles 70 -> 36; of 128 queries 21.9 -> 18.6 and 66 -> 49; lists of 2 tiles
-        // the same).  With 480 blocks it is already slower (2 tiles 9.7 -> 13.9, 11 tiles of 128 queries 28 -> 34).
-        if (n_items <= 256 && n_tiles > 2) {
-            if (BQ == 128) FASTAR_ATTN(64, 4, 2);
-            else FASTAR_ATTN(64, 2, 4);
-        } else {
-            if (BQ == 128) FASTAR_ATTN(64, 4, 1);
-            else FASTAR_ATTN(64, 2, 1);
-        }
+        if (BQ == 128) FASTAR_ATTN(64, 4);
+        else FASTAR_ATTN(64, 2);
 #undef FASTAR_ATTN
     } else {
         if (BQ > 128 || BK > 64) return FASTAR_ERR_UNSUPPORTED;

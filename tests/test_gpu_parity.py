@@ -1883,6 +1883,50 @@ def test_attention_of_64_wide_heads_split_over_groups_of_wavefronts(H, n_q, C, n
     assert np.array_equal(fin, np.isfinite(lse)) and np.abs(lse[fin] - lse_r[fin]).max() <= 2e-2
 
 
+@pytest.mark.parametrize("d,H,n_q,BQ,BK,n_sel", [
+    (64, 1, 70, 64, 64, 1), (64, 3, 300, 128, 1, 33), (64, 2, 200, 64, 32, 2), (64, 5, 4000, 128, 64, 2),      # 2 wavefronts per group
+    (64, 2, 333, 128, 64, 2), (64, 2, 333, 64, 16, 9), (64, 4, 2048, 128, 64, 12), (64, 5, 2560, 128, 64, 32),   # 4
+    (64, 1, 97, 128, 64, 12), (64, 3, 1000, 64, 64, 13), (64, 1, 260, 128, 2, 384),                      # 8
+    (64, 5, 4096, 128, 64, 3), (64, 41, 128, 64, 64, 2), (64, 65, 4000, 64, 64, 3),                      # the first that another kernel takes
+    (128, 1, 129, 128, 64, 2), (128, 3, 500, 128, 64, 8), (128, 16, 1024, 128, 64, 20), (128, 16, 1000, 64, 64, 7),
+    (128, 1, 200, 128, 64, 30), (128, 2, 333, 64, 64, 24), (128, 12, 2600, 64, 64, 9),
+    (128, 1, 200, 128, 64, 1), (128, 2, 200, 128, 32, 20), (128, 43, 384, 128, 64, 8)])
+def test_attention_whose_wavefronts_share_a_group_of_queries(d, H, n_q, BQ, BK, n_sel):
+    # every form of the kernel and both sides of the rule that chooses it; tiles of 32 keys that lie wholly in a live block and
+    # tiles with masked positions in any order (padding, dead blocks, the block that len cuts, repeats), rows that nothing
+    # selects not finite, groups of fewer than 32 queries, wavefronts without a tile
+    rng = np.random.default_rng(1000 * d + 10 * BK + n_sel + H)
+    g = torch.Generator(device="cuda").manual_seed(n_sel + H)
+    n_kb = max(6, n_sel // 2)
+    C = n_kb * BK + BK // 3
+    n_qb = -(-n_q // BQ)
+    Q, K, V = (torch.randn(H, n, d, device="cuda", generator=g).bfloat16() for n in (n_q, C, C))
+    K *= torch.linspace(0.2, 3.0, C, device="cuda")[None, :, None].bfloat16()         # maxima that move along a list
+    cnt = torch.randint(1, 6, (H, C), device="cuda", generator=g, dtype=torch.int32)
+    lens = np.resize(np.array([C, C - BK - BK // 2, (n_kb // 2) * BK + 1, 0], np.int32), H)
+    sel = rng.integers(0, n_kb + 1, size=(H, n_qb, n_sel)).astype(np.int32)
+    sel[:, ::2] = np.sort(sel[:, ::2], axis=-1)
+    sel[rng.random(sel.shape) < 0.1] = -1
+    nsel = rng.integers(0, n_sel + 1, size=(H, n_qb)).astype(np.int32)
+    nsel[:, 0] = n_sel
+    lens[0] = C
+    if H > 3:
+        nsel[3, 0] = n_sel                                                     # a head without live slots
+    for h in range(H):
+        K[h, lens[h]:], V[h, lens[h]:] = float("nan"), float("inf")
+    if H * n_q > 20000:                                                        # the oracle takes a few of the heads
+        few = [0, 1, 2, 3]
+    else:
+        few = list(range(H))
+    for c in (cnt, None):
+        O, lse = (to_host(x) for x in fa.sparse_attn_fwd(Q, K, V, c, to_dev(lens), to_dev(sel), to_dev(nsel), BQ, BK, d ** -0.5))
+        O_r, lse_r = oracle.sparse_attn_fwd(*(to_host(x[few].contiguous()) for x in (Q, K, V)), None if c is None else to_host(c[few]),
+                                            lens[few], sel[few], nsel[few], BQ, BK, d ** -0.5)
+        assert np.abs(to_f32(O[few]).astype(np.float64) - O_r).max() <= ATOL["bf16"]
+        fin = np.isfinite(lse_r)
+        assert np.array_equal(fin, np.isfinite(lse[few])) and np.abs(lse[few][fin] - lse_r[fin]).max() <= 2e-2
+
+
 @pytest.mark.parametrize("H,n_q,C,n_sel,BK,fp8", [
     (1, 128, 64 * 12, 6, 64, False),        # the shortest list that is split over a workgroup's two groups
     (2, 129, 64 * 40, 13, 64, False),       # odd number of tiles, a block of one query
