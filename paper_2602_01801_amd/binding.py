@@ -7,6 +7,7 @@ if the library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 
@@ -146,8 +147,16 @@ def _check(rc: int, what: str):
         raise FastarError(f"{what}: {lib().fastar_strerror(rc).decode()} ({rc})")
 
 
+# The handle of the current device's current stream.  torch.cuda.current_stream() builds a Stream object for it (3.0 us a call,
+# as much as a launch; these two take 0.15); torch builds without them fall back to it.
+_device_now = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or _device_now is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device_now())
 
 
 def _ptr(t):
@@ -170,6 +179,7 @@ def _dev(t: torch.Tensor, dtype=None):
     return t
 
 
+@functools.lru_cache(maxsize=256)   # a function of its arguments alone: a look-up instead of a foreign call per checked workspace
 def workspace_bytes(op: int, H: int, n_q: int, n_k: int, r: int = 32, BQ: int = 128, BK: int = 64,
                     n_rep: int = 4) -> int:
     return int(lib().fastar_workspace_bytes(op, H, n_q, n_k, r, BQ, BK, n_rep))
@@ -219,7 +229,8 @@ class Cache:
     def struct(self) -> _CacheStruct:
         H, C, d, r = self.shape
         for t in (self.K, self.V, self.code, self.cnt, self.stamp, self.len):
-            _dev(t)
+            if not t.is_cuda or not t.is_contiguous():   # _dev, without six calls of it
+                _dev(t)
         return _CacheStruct(self.K.data_ptr(), self.V.data_ptr(), self.code.data_ptr(), self.cnt.data_ptr(),
                             self.stamp.data_ptr(), self.len.data_ptr(), H, C, d, r, _dtype_code(self.K))
 

@@ -25,6 +25,26 @@ def sync():
     torch.cuda.synchronize()
 
 
+def test_calls_go_to_the_current_stream():
+    from paper_2602_01801_amd import binding
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+    for s in side:
+        with torch.cuda.stream(s):
+            assert binding._stream() == s.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert binding._stream() == torch.cuda.default_stream().cuda_stream
+    x = torch.randn(3, 70, 64, device="cuda")
+    codec = fa.Codec((torch.randint(0, 2, (64, 32), device="cuda") * 2 - 1).to(torch.int8), 30.0, 4)
+    want = fa.encode(x, codec)
+    side[0].wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side[0]):
+        torch.cuda._sleep(2000000)
+        y = x * 1.0                               # on the side stream, behind the sleep: the call has to be there too
+        got = fa.encode(y, codec)
+    torch.cuda.current_stream().wait_stream(side[0])
+    assert torch.equal(got, want)
+
+
 def test_init_is_idempotent_and_optional():
     # the one-time kernel set-up may be called any number of times, before or after other entry points
     fa.init()
