@@ -210,16 +210,20 @@ __global__ __launch_bounds__(SCORE_THREADS) void bucket_score_kernel(const unsig
 }
 
 // ---- candidates, then the exact top-k -------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void bucket_topk_kernel(const int32_t *__restrict__ score, int n_kb_cap,
+// ALONE: rows of up to TOPK_WAVE_MAX entries, a wavefront each; otherwise four.
+template <bool ALONE>
+__global__ __launch_bounds__(ALONE ? 64 : 256) void bucket_topk_kernel(const int32_t *__restrict__ score, int n_kb_cap,
                                                           const int32_t *__restrict__ len, int C, int BK, int n_qb,
                                                           int n_sel, int n_sink, int n_local, int32_t *__restrict__ sel,
                                                           int32_t *__restrict__ nsel) {
-    extern __shared__ unsigned keys[];   // min(n_kb_cap, TOPK_LDS_CAP) words: staging of the row's keys
+    extern __shared__ unsigned keys[];   // four wavefronts: min(n_kb_cap, TOPK_LDS_CAP) words, staging of the row's keys
     const int b = blockIdx.x, h = blockIdx.y;
     const int n = min((min(len[h], C) + BK - 1) / BK, n_kb_cap);
     const int32_t *row = score + ((size_t)h * n_qb + b) * n_kb_cap;
-    __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
-    topk_row(row, n, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, keys, scratch, n_sink, n_local, 1);
+    int32_t *out = sel + ((size_t)h * n_qb + b) * n_sel, *n_out = nsel + (size_t)h * n_qb + b;
+    __shared__ __attribute__((aligned(16))) unsigned scratch[ALONE ? TOPK_WAVE_BINS : TOPK_SCRATCH];
+    if constexpr (ALONE) topk_row_wave<TOPK_WAVE_MAX>(row, n, n_sel, out, n_out, scratch, n_sink, n_local, 1);
+    else topk_row(row, n, n_sel, out, n_out, keys, scratch, n_sink, n_local, 1);
 }
 
 struct BucketWs {
@@ -300,7 +304,9 @@ extern "C" int ann_select_buckets(const int32_t *qbucket, int n_q, const int32_t
                        dim3((n_kb_cap + SCORE_THREADS - 1) / SCORE_THREADS, H, (n_qb + SCORE_QB - 1) / SCORE_QB),
                        dim3(SCORE_THREADS), (size_t)SCORE_QB * W * 4, s, qmask, kmask, W, n_qb, n_kb_cap, score);
     FASTAR_LAUNCH_CHECK();
-    hipLaunchKernelGGL(bucket_topk_kernel, dim3(n_qb, H), dim3(256), (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score,
+    const bool alone = n_kb_cap <= TOPK_WAVE_MAX;
+    auto kernel = alone ? bucket_topk_kernel<true> : bucket_topk_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(n_qb, H), dim3(alone ? 64 : 256), alone ? 0 : (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score,
                        n_kb_cap, len, C, BK, n_qb, n_sel, n_sink, n_local, sel, nsel);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;

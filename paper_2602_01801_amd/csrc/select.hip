@@ -603,22 +603,40 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
     }
 }
 
-// Row (h, b) of `score` holds n entries (n = ceil(len[h]/BK) when len is given, else n_fixed).
-__global__ __launch_bounds__(256) void topk_kernel(const int32_t *__restrict__ score, int row_stride,
+// Row (h, b) of `score` holds n entries (n = ceil(len[h]/BK) when len is given, else n_fixed).  ALONE: rows of up to
+// TOPK_WAVE_MAX entries, a wavefront each; otherwise four.
+template <bool ALONE>
+__global__ __launch_bounds__(ALONE ? 64 : 256) void topk_kernel(const int32_t *__restrict__ score, int row_stride,
                                                    const int32_t *__restrict__ len, int len_cap, int BK, int n_fixed,
                                                    int n_qb, int n_sel, int32_t *__restrict__ sel,
                                                    int32_t *__restrict__ nsel, int n_sink, int n_local, int cand_min) {
     // staging of the row's keys: min(row_stride, TOPK_LDS_CAP) words of dynamic LDS (a static array of the full size
     // would hold the kernel to four workgroups per compute unit whatever the row length)
     extern __shared__ unsigned keys[];
-    __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
     const int b = blockIdx.x, h = blockIdx.y;
     int n = n_fixed;
     if (len) n = (min(len[h], len_cap) + BK - 1) / BK;
     n = min(n, row_stride);
     const int32_t *row = score + ((size_t)h * n_qb + b) * row_stride;
-    topk_row(row, n, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, keys, scratch, n_sink,
-             n_local, cand_min);
+    int32_t *out = sel + ((size_t)h * n_qb + b) * n_sel, *n_out = nsel + (size_t)h * n_qb + b;
+    if constexpr (ALONE) {
+        __shared__ __attribute__((aligned(16))) unsigned hist[TOPK_WAVE_BINS];
+        topk_row_wave<TOPK_WAVE_MAX>(row, n, n_sel, out, n_out, hist, n_sink, n_local, cand_min);
+    } else {
+        __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
+        topk_row(row, n, n_sel, out, n_out, keys, scratch, n_sink, n_local, cand_min);
+    }
+}
+
+static void launch_topk(const int32_t *score, int n_kb_cap, const int32_t *len, int C, int BK, int n_qb, int H, int n_sel, int32_t *sel,
+                        int32_t *nsel, int n_sink, int n_local, int cand_min, hipStream_t s) {
+    const dim3 grid(n_qb, H);
+    if (n_kb_cap <= TOPK_WAVE_MAX)
+        hipLaunchKernelGGL(topk_kernel<true>, grid, dim3(64), 0, s, score, n_kb_cap, len, C, BK, 0, n_qb, n_sel, sel, nsel, n_sink,
+                           n_local, cand_min);
+    else
+        hipLaunchKernelGGL(topk_kernel<false>, grid, dim3(256), (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score, n_kb_cap, len, C,
+                           BK, 0, n_qb, n_sel, sel, nsel, n_sink, n_local, cand_min);
 }
 
 // ---- AnnSA selection in one launch, short caches -------------------------------------------------------
@@ -629,6 +647,8 @@ __global__ __launch_bounds__(256) void topk_kernel(const int32_t *__restrict__ s
 // What bounds it: a chain of latencies (keys and queries, summaries, a round of keys per 4096 of them, top-k) in place of
 // three launches; 4 heads x 780 queries x 4096 slots 9.9 -> 6.9 us, x 9360 10.2 -> 9.3.
 constexpr int SHORT_THREADS = 1024;
+constexpr int SHORT_BLOCKS = 512;   // key blocks: at least 32 slots each
+static_assert(SHORT_BLOCKS * 32 >= short_keys(32) && SHORT_BLOCKS * 32 >= short_keys(64), "one wavefront selects from the row");
 template <int R>
 __global__ __launch_bounds__(SHORT_THREADS) void select_short_kernel(
     const int8_t *__restrict__ qcode, int n_q, const int8_t *__restrict__ kcode, const int32_t *__restrict__ len, int C, int BQ,
@@ -640,7 +660,7 @@ __global__ __launch_bounds__(SHORT_THREADS) void select_short_kernel(
     int32_t *smax = (int32_t *)slds;                              // [n_kb_cap]
     unsigned *qrow = (unsigned *)(slds + ((size_t)n_kb_cap * 4 + 15) / 16 * 16);   // [BQ][R] bytes
     __shared__ __attribute__((aligned(16))) int8_t srep[8 * R];
-    __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
+    __shared__ __attribute__((aligned(16))) unsigned hist[TOPK_WAVE_BINS];
     const int b = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g2 = lane >> 5;
@@ -705,9 +725,9 @@ __global__ __launch_bounds__(SHORT_THREADS) void select_short_kernel(
         }
     }
     __syncthreads();
-    if (wave >= 4) return;   // the selection is four wavefronts' work; barriers count those that are left
-    topk_row(smax, n_kb, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, nullptr, scratch, n_sink,
-             n_local);
+    if (wave > 0) return;
+    topk_row_wave<SHORT_BLOCKS>(smax, n_kb, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, hist, n_sink,
+                                n_local);
 }
 
 // ---- selection on sign codes (LSH family) -------------------------------------------------------------
@@ -1087,8 +1107,7 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
     else FASTAR_SELF(64, 8);
 #undef FASTAR_SELF
     FASTAR_LAUNCH_CHECK();
-    hipLaunchKernelGGL(topk_kernel, dim3(n_qb, H), dim3(256), (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score, n_kb_cap,
-                       len, C, BK, 0, n_qb, n_sel, sel, nsel, n_sink, n_local, INT_MIN);
+    launch_topk(score, n_kb_cap, len, C, BK, n_qb, H, n_sel, sel, nsel, n_sink, n_local, INT_MIN, s);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }
@@ -1157,12 +1176,8 @@ extern "C" int ann_select_cross(const int8_t *qcode, int n_q, const int8_t *pcod
     if (ws_bytes < select_cross_ws_bytes(H, n_q, n_p, BQ)) return FASTAR_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const size_t lds = (size_t)n_p * sizeof(int32_t);
-    if (r == 32)
-        hipLaunchKernelGGL(score_cross_kernel<32>, dim3(n_qb, H), dim3(256), lds, s, qcode, pcode, n_q, n_p, BQ, n_qb,
-                           n_sel, sel, nsel);
-    else
-        hipLaunchKernelGGL(score_cross_kernel<64>, dim3(n_qb, H), dim3(256), lds, s, qcode, pcode, n_q, n_p, BQ, n_qb,
-                           n_sel, sel, nsel);
+    auto kernel = r == 32 ? score_cross_kernel<32> : score_cross_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3(n_qb, H), dim3(256), lds, s, qcode, pcode, n_q, n_p, BQ, n_qb, n_sel, sel, nsel);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }
@@ -1259,8 +1274,7 @@ static int select_lsh_impl(const uint32_t *qbits, int n_q, const uint32_t *kbits
     }
     FASTAR_LAUNCH_CHECK();
     // with tables only key blocks with a collision are candidates
-    hipLaunchKernelGGL(topk_kernel, dim3(n_qb, H), dim3(256), (size_t)std::min(n_kb_cap, TOPK_LDS_CAP) * 4, s, score, n_kb_cap,
-                       len, C, BK, 0, n_qb, n_sel, sel, nsel, n_sink, n_local, band ? 1 : INT_MIN);
+    launch_topk(score, n_kb_cap, len, C, BK, n_qb, H, n_sel, sel, nsel, n_sink, n_local, band ? 1 : INT_MIN, s);
     FASTAR_LAUNCH_CHECK();
     return FASTAR_OK;
 }

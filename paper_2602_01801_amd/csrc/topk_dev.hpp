@@ -3,24 +3,147 @@
 
 #include <limits.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace fastar {
 
 constexpr int TOPK_LDS_CAP = 8192; // row entries cached in LDS by the callers of topk_row
-constexpr int TOPK_KPT = 16;       // rows of up to 256 * TOPK_KPT entries are selected from registers
-
-constexpr int TOPK_DIGIT = 9;                        // bits per pass over the keys
+constexpr int TOPK_WAVE_MAX = 1024;   // entries of a row that one wavefront selects from, from registers
+constexpr int TOPK_REG_MAX = 4096;    // ... and that four select from
+constexpr int TOPK_QUARTER_SEL = 128; // at most so many of them: a quarter of the row per wavefront
+constexpr int TOPK_DIGIT = 9;         // otherwise: bits per pass over the keys
 constexpr int TOPK_BINS = 1 << TOPK_DIGIT;
-constexpr int TOPK_SCRATCH = 2 * TOPK_BINS + 20;     // two histograms, a few words per wavefront
+constexpr int TOPK_WAVE_BINS = 256;
+constexpr int TOPK_SCRATCH = 4 * (TOPK_WAVE_BINS + 2 * TOPK_QUARTER_SEL) + 4;   // words: a histogram and a list for each wavefront, the lists' lengths
 
-// Rows of up to 4096 entries.  Every thread holds a run of KPT consecutive entries in registers (key + 1, 0: no entry).
+// Exact top-k by ONE wavefront: entry 64 e + lane of the row in register e (key + 1, 0: no entry), so positions come out in order
+// and no barrier is needed.  One histogram of 256 bins over the row's own range leaves, as a rule, a handful of entries in the
+// threshold's bin; the bits below are tried one by one, with a comparison and a scalar bit count per register, until exactly k
+// entries lie above.  What bounds it is the issue of one wavefront (about seven cycles an instruction alone on its SIMD), where
+// four wavefronts (the form further down) are a chain of barriers: 16 of 64 entries 2.0 -> 1.1 us, 64 of 512 2.9 -> 1.5; top-k launch
+// for 444 rows of 585 7.2 -> 5.8.  All bits one by one, ten of them on the average: 64 of 512 2.3 us, of 1024 3.9 (now 2.2).
+template <int NR>
+__device__ __forceinline__ int topk_count(const unsigned (&my)[NR], unsigned limit) {   // entries >= limit > 0; uniform
+    int c = 0;
+#pragma unroll
+    for (int e = 0; e < NR; ++e) c += __popcll(__ballot(my[e] >= limit));
+    return c;
+}
+// Passes the k largest entries (0 < k <= number of entries; ties: the first ones) to out(position, entry, key + 1), entries
+// ascending.  `forced` of the entries rank above all others; lo, hi: range of those (where there are any).  hist:
+// TOPK_WAVE_BINS words of LDS, 16-byte aligned, this wavefront's own.
+template <int NR, typename Out>
+__device__ __forceinline__ void topk_wave(const unsigned (&my)[NR], int k, int forced, unsigned lo, unsigned hi, unsigned *hist,
+                                          Out &&out) {
+    const int lane = lane_id();
+    unsigned T = (1u << 22) + 1u, need = (unsigned)k;   // threshold key + 1, and how many of the entries equal to it are taken
+    if (forced < k) {      // uniform
+        ((u32x4 *)hist)[lane] = u32x4{0u, 0u, 0u, 0u};
+        const unsigned span = hi - lo, want = (unsigned)(k - forced);
+        int shift = span ? max(24 - __clz(span), 0) : 0;   // the bins are the eight leading bits of the span
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int e = 0; e < NR; ++e)
+            if (my[e] - lo <= span) atomicAdd(&hist[(my[e] - lo) >> shift], 1u);   // neither missing nor forced
+        __builtin_amdgcn_wave_barrier();
+        // lane l owns the bins 255 - 4 l .. 252 - 4 l: where does the running count from the top reach `want`?
+        const u32x4 c4 = ((const u32x4 *)hist)[63 - lane];
+        const unsigned sum = (c4[0] + c4[1]) + (c4[2] + c4[3]), incl = wave_incl_scan(sum);
+        unsigned before = incl - sum, bin = 0u, left = 0u, count = 0u;
+        const bool mine = before < want && want <= incl;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned c = c4[3 - q];
+            const bool here = (before < want) & (want <= before + c);
+            bin = here ? (unsigned)(255 - 4 * lane - q) : bin;
+            left = here ? want - before : left;
+            count = here ? c : count;
+            before += c;
+        }
+        const int src = __ffsll((unsigned long long)__ballot(mine)) - 1;   // exactly one lane
+        bin = (unsigned)__builtin_amdgcn_readlane((int)bin, src);
+        left = (unsigned)__builtin_amdgcn_readlane((int)left, src);
+        count = (unsigned)__builtin_amdgcn_readlane((int)count, src);
+        T = lo + (bin << shift);
+        int above = k - (int)left;          // entries above what T may still become
+        bool whole = left == count;
+        for (unsigned step = (1u << shift) >> 1; step != 0u && !whole; step >>= 1) {   // uniform
+            const int c = topk_count(my, T + step);
+            if (c >= k) T += step;
+            else above = c;
+            whole = c == k;
+        }
+        need = (unsigned)(k - above);
+        if (whole) {   // everything from T on
+            T -= 1u;
+            need = 0u;
+        }
+    }
+    unsigned at = 0u, eq = 0u;   // entries taken, entries equal to T, of the registers before (uniform)
+    auto rank = [&](unsigned long long m, unsigned base) {   // of this lane among those of m, from base on
+        return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, base));
+    };
+    if (need == 0u) {   // uniform
+#pragma unroll
+        for (int e = 0; e < NR; ++e) {
+            const unsigned long long m = __ballot(my[e] > T);
+            if (my[e] > T) out((int)rank(m, at), 64 * e + lane, my[e]);
+            at += (unsigned)__popcll(m);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < NR; ++e) {
+            const bool is_eq = my[e] == T;   // T > 0
+            const unsigned long long m_eq = __ballot(is_eq);
+            const bool take = (my[e] > T) | (is_eq & (rank(m_eq, eq) < need));   // without branches
+            const unsigned long long m = __ballot(take);
+            if (take) out((int)rank(m, at), 64 * e + lane, my[e]);
+            at += (unsigned)__popcll(m);
+            eq += (unsigned)__popcll(m_eq);
+        }
+    }
+}
+// Selects from row[0 .. n), n <= 64 NR, of keys key_of(entry, score), and returns how many it passed to out(position, entry,
+// key + 1): at most n_sel, and no more than there are candidates.
+template <int NR, typename KeyOf, typename Out>
+__device__ __forceinline__ int topk_wave_of(const int32_t *row, int n, int n_sel, int forced, unsigned cand_key, KeyOf &&key_of,
+                                            unsigned *hist, Out &&out) {
+    if (n <= 0) return 0;   // uniform
+    const int lane = lane_id();
+    unsigned my[NR];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) my[e] = (unsigned)row[min(64 * e + lane, n - 1)];
+    __builtin_amdgcn_sched_barrier(0);   // all in flight at once (not each where its key turns out to be needed)
+#pragma unroll
+    for (int e = 0; e < NR; ++e) asm volatile("" : "+v"(my[e]));
+    unsigned hi = 0u, nlo = 0u;   // largest, and complement of the smallest, of the entries that are not forced (the last one counts again)
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+        const int t = min(64 * e + lane, n - 1);
+        my[e] = key_of(t, (int32_t)my[e]) + 1u;
+        const bool in = forced == 0 || my[e] != (1u << 22) + 1u;
+        hi = max(hi, in ? my[e] : 0u);
+        nlo = max(nlo, in ? ~my[e] : 0u);
+        my[e] = 64 * e + lane < n ? my[e] : 0u;
+    }
+    hi = (unsigned)__builtin_amdgcn_readlane((int)wave_max_last(hi), 63);
+    nlo = (unsigned)__builtin_amdgcn_readlane((int)wave_max_last(nlo), 63);
+    const int k = min(n_sel, cand_key == 0u ? n : topk_count(my, cand_key + 1u));
+    if (k > 0) topk_wave(my, k, forced, ~nlo, hi, hist, out);
+    return k;
+}
+
+// Rows of more than TOPK_WAVE_MAX and up to TOPK_REG_MAX entries from which more than TOPK_QUARTER_SEL are wanted, by four
+// wavefronts.  Every thread holds a run of KPT consecutive entries in registers (key + 1, 0: no entry).
 // What bounds it is the chain of barriers, and of same-address additions where the keys' leading bits are alike.  So the
 // row's range comes first (one barrier), the digits are those of its span, every wavefront reads the threshold digit off the
 // histogram itself (one barrier per pass), and once the threshold's bin holds at most 64 entries, as a rule after the
-// first pass, every wavefront ranks those (one barrier); one more for the positions.   Selection of 64 out of 512 / 2048 scores 4.9 / 9.5 -> 3.0 / 5.9 us (before: three fixed
-// digits with three barriers each and a compaction with three per 256 entries; 23 rounds of counting, a barrier each).
-// Digits of ten bits: no faster, and their 16 bins per lane cost registers.
+// first pass, every wavefront ranks those (one barrier); one more for the positions.  Selection of 64 out of 2048 scores
+// 9.5 -> 5.9 us (before: three fixed digits with three barriers each and a compaction with three per 256 entries).  Digits of ten
+// bits: no faster, and their 16 bins per lane cost registers.  One wavefront on 64 registers of keys instead: select of 400 out of
+// 4000 prompt tokens for 12 x 37 query blocks 22.8 -> 26.8 us, of 360 out of 3600 key blocks for 40 x 29 24.4 -> 22.7.
 template <int KPT, typename KeyOf>
 __device__ __forceinline__ void topk_from_registers(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
                                                     int32_t *__restrict__ nsel_out, unsigned *keys, int forced,
@@ -206,6 +329,34 @@ __device__ __forceinline__ int count_candidates(const int32_t *row, int n, int n
     return cand_w[0] + cand_w[1] + cand_w[2] + cand_w[3];
 }
 
+// Scores are sums of at most 64 products of 8-bit codes (or counts of equal hash bits): |score| < 2^21, and anything below
+// (the INT_MIN of a block without a live key) is clamped there, so an order-preserving key has 22 bits.
+__device__ __forceinline__ unsigned topk_key(int32_t sc) { return (unsigned)(max(sc, -(1 << 21)) + (1 << 21)); }
+
+// topk_row (below) of a row of up to MAX_N entries, by one wavefront.
+template <int MAX_N>
+__device__ __forceinline__ void topk_row_wave(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
+                                              int32_t *__restrict__ nsel_out, unsigned *hist, int n_sink = 0, int n_local = 0,
+                                              int cand_min = INT_MIN) {
+    const int first = min(n, max(n_sink, 0)), forced = first + min(max(n_local, 0), n - first);
+    const unsigned cand_key = cand_min > INT_MIN ? topk_key(cand_min) : 0u;
+    const auto key_of = [&](int t, int32_t sc) -> unsigned {
+        return (t < n_sink || t >= n - n_local) ? (1u << 22) : topk_key(sc);
+    };
+    const auto put = [&](int pos, int t, unsigned) { out[pos] = t; };
+    int k = 0;
+    const auto select = [&](auto nr) {   // uniform
+        constexpr int NR = decltype(nr)::value;
+        if constexpr (64 * NR <= MAX_N) k = topk_wave_of<NR>(row, n, n_sel, forced, cand_key, key_of, hist, put);
+    };
+    if (n <= 256) select(std::integral_constant<int, 4>{});
+    else if (n <= 512) select(std::integral_constant<int, 8>{});
+    else if (n <= 768) select(std::integral_constant<int, 12>{});
+    else select(std::integral_constant<int, 16>{});
+    if (lane_id() == 0) *nsel_out = k;
+    for (int t = k + lane_id(); t < n_sel; t += 64) out[t] = -1;
+}
+
 // ---- exact top-k per row ----------------------------------------------------------------------------
 // A row of n scores (row may point to global memory or to LDS).  The k = min(n_sel, n) largest are selected
 // (ties: lowest index) and their indices written ascending to out[0..k), the rest of out[0..n_sel) padded with
@@ -219,20 +370,67 @@ __device__ __forceinline__ int count_candidates(const int32_t *row, int n, int n
 __device__ __forceinline__ void topk_row(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
                                          int32_t *__restrict__ nsel_out, unsigned *keys, unsigned *scratch, int n_sink = 0,
                                          int n_local = 0, int cand_min = INT_MIN) {
-    // Scores are sums of at most 64 products of 8-bit codes (or counts of equal hash bits): |score| < 2^21, and
-    // anything below (the INT_MIN of a block without a live key) is clamped there, so an order-preserving key has
-    // 22 bits: three passes over 8-bit digits (the first has 6 significant bits) select exactly.
-    auto to_key0 = [](int32_t sc) -> unsigned { return (unsigned)(max(sc, -(1 << 21)) + (1 << 21)); };
+    // Keys have 22 bits: three passes over 8-bit digits (the first has 6 significant bits) select exactly.
     // key of entry t with score sc: real scores stay below 2^22, forced entries sit exactly there
     auto key_of = [&](int t, int32_t sc) -> unsigned {
-        return (t < n_sink || t >= n - n_local) ? (1u << 22) : to_key0(sc);
+        return (t < n_sink || t >= n - n_local) ? (1u << 22) : topk_key(sc);
     };
-    if (n <= TOPK_KPT * 256) {
+    if (n <= TOPK_WAVE_MAX) {   // uniform; the other wavefronts are done
+        if (threadIdx.x < 64) topk_row_wave<TOPK_WAVE_MAX>(row, n, n_sel, out, nsel_out, scratch, n_sink, n_local, cand_min);
+        return;
+    }
+    if (n <= TOPK_REG_MAX) {
         // Forced entries rank ahead of all others: the k - forced largest of the others are to be found.
         const int first = min(n, max(n_sink, 0)), forced = first + min(max(n_local, 0), n - first);
-        const unsigned cand_key = cand_min > INT_MIN ? to_key0(cand_min) : 0u;   // candidates: key + 1 > cand_key
-        if (n <= 4 * 256) topk_from_registers<5>(row, n, n_sel, out, nsel_out, keys, forced, cand_key, key_of, scratch);
-        else topk_from_registers<TOPK_KPT>(row, n, n_sel, out, nsel_out, keys, forced, cand_key, key_of, scratch);
+        const unsigned cand_key = cand_min > INT_MIN ? topk_key(cand_min) : 0u;   // candidates: key + 1 > cand_key
+        const int lane = lane_id(), wave = threadIdx.x >> 6;
+        if (n_sel > TOPK_QUARTER_SEL) {   // uniform
+            topk_from_registers<TOPK_REG_MAX / 256>(row, n, n_sel, out, nsel_out, keys, forced, cand_key, key_of, scratch);
+            return;
+        }
+        // every wavefront selects from its quarter, then one of them from the four lists; a wavefront's own words: histogram,
+        // keys and positions of its list
+        constexpr int OWN = TOPK_WAVE_BINS + 2 * TOPK_QUARTER_SEL, KEYS = TOPK_WAVE_BINS, POS = KEYS + TOPK_QUARTER_SEL;
+        static_assert(4 * OWN + 4 <= TOPK_SCRATCH, "the lists fit");
+        unsigned *own = scratch + wave * OWN, *lcnt = scratch + 4 * OWN;
+        const int per = (((n + 3) >> 2) + 63) & ~63, t0 = wave * per, m = min(max(n - t0, 0), per);
+        const int forced_here = max(min(first, t0 + m) - t0, 0) + max(t0 + m - max(n - (forced - first), t0), 0);
+        const auto key_here = [&](int t, int32_t sc) { return key_of(t0 + t, sc); };
+        const auto put = [&](int pos, int t, unsigned key) {
+            own[KEYS + pos] = key;
+            own[POS + pos] = (unsigned)(t0 + t);
+        };
+        const int c = per <= 512   ? topk_wave_of<8>(row + t0, m, n_sel, forced_here, cand_key, key_here, own, put)
+                      : per <= 768 ? topk_wave_of<12>(row + t0, m, n_sel, forced_here, cand_key, key_here, own, put)
+                                   : topk_wave_of<16>(row + t0, m, n_sel, forced_here, cand_key, key_here, own, put);
+        if (lane == 0) lcnt[wave] = (unsigned)c;
+        __syncthreads();
+        if (wave > 0) return;
+        const int n_list[4] = {(int)lcnt[0], (int)lcnt[1], (int)lcnt[2], (int)lcnt[3]};
+        const int k = min(n_sel, n_list[0] + n_list[1] + n_list[2] + n_list[3]);
+        const auto merge = [&](auto per_list) {   // registers per list
+            constexpr int PL = decltype(per_list)::value;
+            unsigned my[4 * PL], hi = 0u, nlo = 0u;
+#pragma unroll
+            for (int e = 0; e < 4 * PL; ++e) {
+                const int pos = 64 * (e % PL) + lane;
+                my[e] = scratch[(e / PL) * OWN + KEYS + pos];
+                my[e] = pos < n_list[e / PL] ? my[e] : 0u;
+                const bool in = my[e] != 0u && my[e] != (1u << 22) + 1u;
+                hi = max(hi, in ? my[e] : 0u);
+                nlo = max(nlo, in ? ~my[e] : 0u);
+            }
+            hi = (unsigned)__builtin_amdgcn_readlane((int)wave_max_last(hi), 63);
+            nlo = (unsigned)__builtin_amdgcn_readlane((int)wave_max_last(nlo), 63);
+            if (k > 0)
+                topk_wave(my, k, forced, ~nlo, hi, own, [&](int pos, int t, unsigned) {
+                    out[pos] = (int32_t)scratch[(t / (64 * PL)) * OWN + POS + t % (64 * PL)];
+                });
+        };
+        if (n_sel <= 64) merge(std::integral_constant<int, 1>{});
+        else merge(std::integral_constant<int, 2>{});
+        if (threadIdx.x == 0) *nsel_out = k;
+        for (int t = k + lane; t < n_sel; t += 64) out[t] = -1;
         return;
     }
     const int tid = threadIdx.x;

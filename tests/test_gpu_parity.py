@@ -183,6 +183,49 @@ def test_topk_of_rows_of_every_form_and_distribution(n, scores):
                 assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel), (n_sel, forced)
 
 
+# rows selected from by one wavefront (up to 1024 entries), by four with a quarter each (up to 4096, at most 128 wanted: lists of 64
+# or 128), and by four together; quarters whose last one is short, forced entries in the first and last of them
+@pytest.mark.parametrize("n", [1, 63, 64, 513, 768, 1024, 1025, 1281, 2049, 3073, 4096])
+@pytest.mark.parametrize("scores", ["spread", "two_values"])
+def test_topk_of_short_selections_from_rows_of_every_form(n, scores):
+    rng = np.random.default_rng(n)
+    r, BQ = 32, 64
+    kc = rand_codes(rng, -90, 90, 2, n, r)
+    if scores == "two_values":
+        kc = kc[:, rng.integers(0, min(2, n), size=n)]
+    qc = rand_codes(rng, -90, 90, 2, 100, r)
+    length = np.array([32 * n - 3, max(1, 32 * n - 70)], np.int32)
+    keys = np.ascontiguousarray(np.repeat(kc, 32, axis=1))
+    dq, dk, dp, dlen = to_dev(qc), to_dev(keys), to_dev(kc), to_dev(length)
+    for n_sel in (1, 63, 64, 65, 128, 129):
+        ref_sel, ref_nsel = oracle.ann_select_cross(qc, kc, BQ, n_sel)
+        sel, nsel = fa.ann_select_cross(dq, dp, BQ, n_sel)
+        assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel), n_sel
+        for forced in {(0, 0), (n_sel // 2, n_sel // 3), (0, n_sel), (n_sel, 0)}:
+            ref_sel, ref_nsel = oracle.ann_select_self(qc, keys, length, BQ, 2, 32, n_sel, *forced)
+            sel, nsel = fa.ann_select_self(dq, dk, dlen, BQ, 2, 32, n_sel, n_sink=forced[0], n_local=forced[1])
+            assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel), (n_sel, forced)
+
+
+@pytest.mark.parametrize("n_kb", [40, 700, 1500, 4000])
+@pytest.mark.parametrize("few", [True, False])     # fewer key blocks with a collision than are wanted, and more
+def test_topk_counts_candidates_in_rows_of_every_form(n_kb, few):
+    rng = np.random.default_rng(n_kb)
+    n_sel, BQ, BK, n_bits = 100, 64, 32, 64
+    q = rng.integers(0, 2 ** 32, size=(1, 130, n_bits // 32), dtype=np.uint32)
+    k = rng.integers(0, 2 ** 32, size=(1, n_kb * BK, n_bits // 32), dtype=np.uint32)
+    if few:
+        q[:] = 0            # all of the query's bands are zero; 30 key blocks have such a band
+        k |= 0x88888888     # none of the keys' 4-bit bands is
+        k[0, rng.choice(n_kb, 30, replace=False) * BK + 5] = 0
+    length = np.array([n_kb * BK - 9], np.int32)
+    band = 4 if few else 8
+    ref_sel, ref_nsel = oracle.ann_select_lsh_buckets(q, k, length, band, 0, BQ, 2, BK, n_sel, 1, 2)
+    sel, nsel = fa.ann_select_lsh_buckets(to_dev(q.view(np.int32)), to_dev(k.view(np.int32)), to_dev(length), band, 0, BQ, 2, BK, n_sel,
+                                          n_sink=1, n_local=2)
+    assert np.array_equal(to_host(nsel), ref_nsel) and np.array_equal(to_host(sel), ref_sel)
+
+
 @pytest.mark.parametrize("H,n_q,n_p,r,BQ,n_sel,span", [
     (2, 256, 64, 32, 128, 16, 60), (2, 4680, 512, 32, 128, 64, 50), (1, 300, 2048, 32, 128, 64, 4),
     (2, 100, 97, 64, 64, 10, 30), (1, 50, 20, 32, 128, 64, 30),
