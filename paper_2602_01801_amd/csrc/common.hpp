@@ -13,6 +13,8 @@
 namespace fastar {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) int i32x2;
@@ -55,6 +57,17 @@ __device__ __forceinline__ unsigned f32_to_bf16_bits(float f) {
 }
 __device__ __forceinline__ unsigned pack_bf16x2(float lo, float hi) {
     return f32_to_bf16_bits(lo) | (f32_to_bf16_bits(hi) << 16);
+}
+
+// The same by the conversion instruction: one for the pair.
+__device__ __forceinline__ unsigned cvt_bf16x2(float lo, float hi) {
+    const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(unsigned, v);
+}
+// Transposing LDS read: in each group of 16 lanes, lane 4q + m receives element m of the 8-byte pieces that the lanes q,
+// q + 4, q + 8 and q + 12 address.
+__device__ __forceinline__ bf16x4 ds_read_tr16(const void *p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((__attribute__((address_space(3))) bf16x4 *)p);
 }
 
 // ---- quantiser of the ANN code ----------------------------------------------------------------------

@@ -396,9 +396,10 @@ __global__ __launch_bounds__(256, 3) void score_self_stream_kernel(const int8_t 
 // and its maximum over four products stays in registers, without atomics.  (Every wavefront a quarter of the queries
 // against all tokens, maxima met in LDS: 5.4 us for 128 queries x 512 tokens, 13.6 x 2048; now 3.9 and 8.0.  The next codes
 // in flight as well: no faster.)
-template <int R>
+// in_flight() is called once, behind the first loads: what it asks for does not hold the scores up (loads come back in order).
+template <int R, typename F>
 __device__ __forceinline__ void score_cross_block(const int8_t *__restrict__ qc, const int8_t *__restrict__ pc, int n_q,
-                                                  int n_p, int BQ, int b, int32_t *smax) {
+                                                  int n_p, int BQ, int b, int32_t *smax, F &&in_flight) {
     constexpr int KS = R / 32;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, g2 = lane >> 5;
@@ -413,33 +414,48 @@ __device__ __forceinline__ void score_cross_block(const int8_t *__restrict__ qc,
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) afrag[u][ks] = *(const i32x4 *)(qc + (size_t)qrow * R + ks * 32 + 16 * g2);
         }
-        constexpr int PB = 4;   // groups of tokens whose codes are loaded together
-        for (int t0 = wave; t0 < n_groups; t0 += 4 * PB) {
-            i32x4 bfrag[PB][KS];
+        constexpr int PB = 4;   // groups of tokens in flight: the codes of a group four further on replace those just used
+        i32x4 bfrag[PB][KS];
+        auto load = [&](int u, int group) {
+            const int prow = min(group * 32 + col, n_p - 1);
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int prow = min((t0 + 4 * u) * 32 + col, n_p - 1);
+            for (int ks = 0; ks < KS; ++ks) bfrag[u][ks] = *(const i32x4 *)(pc + (size_t)prow * R + ks * 32 + 16 * g2);
+        };
+        auto score = [&](int u, int group) {
+            const int p = group * 32 + col;
+            int m = INT_MIN;
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) bfrag[u][ks] = *(const i32x4 *)(pc + (size_t)prow * R + ks * 32 + 16 * g2);
+            for (int qg = 0; qg < 4; ++qg) {
+                if (qg >= n_qg) break;   // uniform
+                i32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(afrag[qg][ks], bfrag[u][ks], acc);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) m = max(m, acc[v]);
             }
+            const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)m, (unsigned)m, false, false);
+            m = max((int)halves[0], (int)halves[1]);
+            if (g2 == 0 && p < n_p) smax[p] = q0 == b * BQ ? m : max(smax[p], m);   // the same lane every time
+        };
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int p = (t0 + 4 * u) * 32 + col;
-                if (t0 + 4 * u >= n_groups) break;   // uniform
-                int m = INT_MIN;
+        for (int u = 0; u < PB; ++u) load(u, wave + 4 * u);
+        if (q0 == b * BQ) {
+            __builtin_amdgcn_sched_barrier(0);
+            in_flight();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int t0 = wave;
+        for (; t0 + 4 * PB < n_groups; t0 += 4 * PB) {
 #pragma unroll
-                for (int qg = 0; qg < 4; ++qg) {
-                    if (qg >= n_qg) break;   // uniform
-                    i32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(afrag[qg][ks], bfrag[u][ks], acc);
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) m = max(m, acc[v]);
-                }
-                const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)m, (unsigned)m, false, false);
-                m = max((int)halves[0], (int)halves[1]);
-                if (g2 == 0 && p < n_p) smax[p] = q0 == b * BQ ? m : max(smax[p], m);   // the same lane every time
+            for (int u = 0; u < PB; ++u) {   // whole groups of four: t0 + 4 u + 4 < n_groups
+                score(u, t0 + 4 * u);
+                load(u, t0 + 4 * (PB + u));
             }
+        }
+#pragma unroll
+        for (int u = 0; u < PB; ++u) {
+            if (t0 + 4 * u >= n_groups) break;   // uniform
+            score(u, t0 + 4 * u);
         }
     }
     __syncthreads();
@@ -452,7 +468,7 @@ __global__ __launch_bounds__(256) void score_cross_kernel(const int8_t *__restri
     extern __shared__ int32_t smax[];  // [n_p]
     __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
     const int b = blockIdx.x, h = blockIdx.y;
-    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, BQ, b, smax);
+    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, BQ, b, smax, [] {});
     // the workgroup owns the whole row: select from LDS right away
     topk_row(smax, n_p, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, nullptr, scratch);
 }
@@ -466,11 +482,9 @@ __global__ __launch_bounds__(256) void score_cross_kernel(const int8_t *__restri
 namespace fused {
 constexpr int D = 128, TK = 64;
 constexpr int KROW = D * 2 + 16;          // bytes per staged K row (padded: 16 consecutive rows hit 16 different bank groups)
-constexpr int VROW = TK * 2 + 16;         // bytes per staged V^T row
-constexpr int OROW = D * 2 + 16;          // bytes per staged output row
-constexpr int TILE_BYTES = TK * KROW + D * VROW;   // 17408 + 18432; the output staging (128 rows x OROW) reuses it
+constexpr int VROW = D * 2 + 64;          // bytes per staged V row (the four rows of a transposing read lie in different quarters of the banks)
+constexpr int TILE_BYTES = TK * KROW + TK * VROW;
 static_assert(TOPK_SCRATCH * 4 <= TILE_BYTES, "the selection's scratch does, too");
-static_assert(128 * OROW <= TILE_BYTES, "output staging fits the tile region");
 __host__ __device__ inline size_t lds_bytes(int n_p) { return ((size_t)n_p * 4 + 15) / 16 * 16 + TK * 4 + 16 + TILE_BYTES; }
 }  // namespace fused
 
@@ -491,21 +505,20 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
     const int b = blockIdx.x, h = blockIdx.y;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int col = lane & 31, g = lane >> 5;
-    // this lane's query row as the second operand of K Q^T: in flight during the selection
+    // this lane's query row as the second operand of K Q^T: in flight during the scoring and the selection
     const int q_idx = b * 128 + wave * 32 + col;
     bf16x8 qf[D / 16];
-    {
+    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, 128, b, smax, [&] {
         const unsigned short *qrow = Q + ((size_t)h * n_q + min(q_idx, n_q - 1)) * D;
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) qf[s] = *(const bf16x8 *)(qrow + 16 * s + 8 * g);
-    }
-    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, 128, b, smax);
+    });
     topk_row(smax, n_p, n_sel, lsel, lcnt, nullptr, (unsigned *)ktile);   // the tile's memory is free until the gather
     __syncthreads();
     const int k = lcnt[0];
     if (tid < n_sel) sel[((size_t)h * n_qb + b) * n_sel + tid] = lsel[tid];
     if (tid == 0) nsel[(size_t)h * n_qb + b] = k;
-    // gather: K rows as they are, V rows transposed; slot p of the tile holds token lsel[p] (p >= k: token 0, masked below)
+    // gather: slot p of the tiles holds the rows of token lsel[p] (p >= k: token 0, masked below)
     const unsigned short *Kh = Kp + (size_t)h * n_p * D, *Vh = Vp + (size_t)h * n_p * D;
     {
         u32x4 kv[4], vv[4];
@@ -520,14 +533,7 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
         for (int e = 0; e < 4; ++e) {
             const int idx = e * 256 + tid, p = idx >> 4, c = idx & 15;
             *(u32x4 *)(ktile + p * KROW + c * 16) = kv[e];
-            // position of token slot p inside its 16: accumulator order (half g' = (o % 8) / 4 first, then o / 8, then o % 4)
-            const int o = p & 15;
-            const int pos = (p & ~15) + 8 * ((o & 7) >> 2) + 4 * (o >> 3) + (o & 3);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                *(unsigned short *)(vtile + (8 * c + 2 * w) * VROW + pos * 2) = (unsigned short)(vv[e][w] & 0xFFFFu);
-                *(unsigned short *)(vtile + (8 * c + 2 * w + 1) * VROW + pos * 2) = (unsigned short)(vv[e][w] >> 16);
-            }
+            *(u32x4 *)(vtile + p * VROW + c * 16) = vv[e];
         }
     }
     __syncthreads();
@@ -579,27 +585,39 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
-                const bf16x8 a = *(const bf16x8 *)(vtile + (32 * db + col) * VROW + (32 * kb + 16 * st + 8 * g) * 2);
+                // tokens in the order the score accumulators hold them: 4 g .. + 3 and 8 + 4 g .. + 3 of the 16; lane i of 16
+                // gets coordinate i of the four rows that the lanes 4 j + q address
+                const unsigned char *vp = vtile + (32 * kb + 16 * st + 4 * g + ((lane & 15) >> 2)) * VROW +
+                                          (32 * db + (lane & 16) + 4 * (lane & 3)) * 2;
+                const bf16x4 lo = ds_read_tr16(vp), hi = ds_read_tr16(vp + 8 * VROW);
+                const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
                 o_acc[db] = mfma_bf16_32x32x16(a, pf[kb][st], o_acc[db]);
             }
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-    __syncthreads();   // the tiles are dead: their LDS takes the output rows
-    unsigned char *orow = ktile + (size_t)(wave * 32 + col) * OROW;
+    // A lane holds four of every eight coordinates of its query; the halves of the wavefront trade theirs, so that a lane has
+    // eight neighbours for one store.  (By way of LDS, for whole rows: 1.5 us, with the rounding in software.)
+    if (q_idx < n_q) {
+        unsigned short *orow = O + ((size_t)h * n_q + q_idx) * D + 8 * g;
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+        for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            u32x2 w;
-            w[0] = pack_bf16x2(o_acc[db][4 * q4] * inv, o_acc[db][4 * q4 + 1] * inv);
-            w[1] = pack_bf16x2(o_acc[db][4 * q4 + 2] * inv, o_acc[db][4 * q4 + 3] * inv);
-            *(u32x2 *)(orow + (32 * db + 8 * q4 + 4 * g) * 2) = w;
-        }
-    __syncthreads();
-    for (int idx = tid; idx < 128 * 16; idx += 256) {
-        const int r = idx >> 4, c = idx & 15;
-        const int qi = b * 128 + r;
-        if (qi < n_q) *(u32x4 *)(O + ((size_t)h * n_q + qi) * D + 8 * c) = *(const u32x4 *)(ktile + (size_t)r * OROW + c * 16);
+            for (int a = 0; a < 2; ++a) {
+                unsigned x[2], y[2];
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    x[w] = cvt_bf16x2(o_acc[db][8 * a + 2 * w] * inv, o_acc[db][8 * a + 2 * w + 1] * inv);
+                    y[w] = cvt_bf16x2(o_acc[db][8 * a + 4 + 2 * w] * inv, o_acc[db][8 * a + 4 + 2 * w + 1] * inv);
+                }
+                u32x4 o;
+#pragma unroll
+                for (int w = 0; w < 2; ++w) {
+                    const auto t = __builtin_amdgcn_permlane32_swap(x[w], y[w], false, false);
+                    o[w] = t[0];
+                    o[2 + w] = t[1];
+                }
+                *(u32x4 *)(orow + 32 * db + 16 * a) = o;
+            }
     }
 }
 
