@@ -110,6 +110,13 @@ __device__ __forceinline__ unsigned wave_incl_scan(unsigned v) {
     v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast 31: the upper half adds the lower
     return v;
 }
+// The word of lane ^ 1, lane ^ 2 (STEP 0, 1) or of the mirror lane of the other four of eight (STEP 2): three steps combine eight
+// neighbouring lanes on the vector ALU.
+template <int STEP>
+__device__ __forceinline__ unsigned lane_of_eight(unsigned v) {
+    constexpr int CTRL = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : 0x141;   // quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
 // Maximum over a wavefront's lanes, in its last lane.
 __device__ __forceinline__ unsigned wave_max_last(unsigned v) {
     v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));

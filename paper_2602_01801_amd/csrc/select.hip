@@ -663,7 +663,8 @@ static void launch_topk(const int32_t *score, int n_kb_cap, const int32_t *len, 
 // and the keys the columns, so a lane keeps four of its sixteen results.  Nothing is masked: a run without queries is
 // replaced by the block's first one, and keys beyond the live ones by the last of them, which lies in the same key block.
 // What bounds it: a chain of latencies (keys and queries, summaries, a round of keys per 4096 of them, top-k) in place of
-// three launches; 4 heads x 780 queries x 4096 slots 9.9 -> 6.9 us, x 9360 10.2 -> 9.3.
+// three launches; 4 heads x 780 queries x 4096 slots 9.9 -> 6.9 us, x 9360 10.2 -> 9.3; 5.2 and 8.3 since the sums of the summaries
+// are split over lanes and one wavefront selects.
 constexpr int SHORT_THREADS = 1024;
 constexpr int SHORT_BLOCKS = 512;   // key blocks: at least 32 slots each
 static_assert(SHORT_BLOCKS * 32 >= short_keys(32) && SHORT_BLOCKS * 32 >= short_keys(64), "one wavefront selects from the row");
@@ -703,14 +704,30 @@ __global__ __launch_bounds__(SHORT_THREADS) void select_short_kernel(
     };
     if (wave < n_kb) load(wave, 0);
     __syncthreads();
-    for (int t = tid; t < n_rep * R; t += SHORT_THREADS) {   // as rep_kernel
+    // As rep_kernel, eight neighbouring lanes a sum (32 reads one after the other took 1.0 to 1.7 us).
+    const bool pow2 = (g & (g - 1)) == 0;   // uniform
+    const int g_shift = 31 - __clz(g);
+    for (int t0 = 0; t0 < n_rep * R * 8; t0 += SHORT_THREADS) {   // n_rep * R * 8 is a multiple of 256: whole wavefronts
+        const int t = (t0 + tid) >> 3, part = tid & 7;
+        if (t >= n_rep * R) break;
         const int u = t / R, j = t % R;
         const int q0 = u * g, q1 = min(q0 + g, n_here);
-        int s = g / 2;
-        for (int q = q0; q < q1; ++q) s += ((const int8_t *)qrow)[q * R + j];
-        int m = s / g;
-        if (s % g != 0 && s < 0) m -= 1;
-        srep[t] = (int8_t)m;
+        const int8_t *qb = (const int8_t *)qrow + j;
+        int s = 0, q = q0 + part;
+        for (; q + 24 < q1; q += 32) s += (qb[q * R] + qb[(q + 8) * R]) + (qb[(q + 16) * R] + qb[(q + 24) * R]);
+        for (; q < q1; q += 8) s += qb[q * R];
+        s += (int)lane_of_eight<0>((unsigned)s);
+        s += (int)lane_of_eight<1>((unsigned)s);
+        s += (int)lane_of_eight<2>((unsigned)s);
+        s += g / 2;
+        int m;   // floor(s / g)
+        if (pow2) {
+            m = s >> g_shift;
+        } else {
+            m = s / g;
+            if (s % g != 0 && s < 0) m -= 1;
+        }
+        if (part == 0) srep[t] = (int8_t)m;
     }
     __syncthreads();
     int u = col & (n_rep - 1);

@@ -153,6 +153,20 @@ def test_ann_select_self_at_the_edges_of_the_one_launch_form(H, n_q, C, r, BQ, n
     assert np.array_equal(to_host(sel), ref_sel)
 
 
+# runs of queries of any length: odd ones, shorter than the eight lanes that add one up, cut by the end of the queries
+@pytest.mark.parametrize("n_q,BQ,n_rep,r", [(150, 72, 4, 32), (100, 12, 4, 64), (211, 200, 8, 32), (77, 35, 1, 32), (33, 8, 8, 32), (130, 100, 2, 64)])
+def test_ann_select_self_in_one_launch_with_runs_of_any_length(n_q, BQ, n_rep, r):
+    rng = np.random.default_rng(n_q + BQ)
+    qc, kc = rand_codes(rng, -127, 127, 2, n_q, r), rand_codes(rng, -127, 127, 2, 1000, r)
+    qc[1] = -np.abs(qc[1])      # negative sums: rounded down
+    length = np.array([1000, 333], np.int32)
+    ref_sel, ref_nsel = oracle.ann_select_self(qc, kc, length, BQ, n_rep, 64, 3)
+    sel, nsel = fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), BQ, n_rep, 64, 3)
+    assert np.array_equal(to_host(nsel), ref_nsel)
+    assert np.array_equal(to_host(sel), ref_sel)
+
+
+
 # rows at the edges of the top-k's register forms (256 entries per round, 1024, 4096), selections from one entry to all
 @pytest.mark.parametrize("n", [2, 33, 256, 257, 769, 1024, 1025, 3840, 3841, 4096, 4097])
 @pytest.mark.parametrize("scores", ["spread", "narrow", "equal", "two_values", "outlier"])
