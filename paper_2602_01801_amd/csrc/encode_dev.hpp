@@ -80,12 +80,19 @@ struct CodeMatrix {
                     for (int cb = 0; cb < CB; ++cb) w[e] |= (unsigned)(uint8_t)p[cb] << (8 * cb);
                 }
             }
+            // byte cb of four words into one: pairs of words side by side first, two byte selections per word of the operand
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    a[ks][cb][m] = (int)pack_i8x4((int)(w[4 * m] >> (8 * cb)), (int)(w[4 * m + 1] >> (8 * cb)),
-                                                  (int)(w[4 * m + 2] >> (8 * cb)), (int)(w[4 * m + 3] >> (8 * cb)));
+            for (int m = 0; m < 4; ++m) {
+                const unsigned w0 = w[4 * m], w1 = w[4 * m + 1], w2 = w[4 * m + 2], w3 = w[4 * m + 3];
+                const unsigned l0 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), l1 = __builtin_amdgcn_perm(w3, w2, 0x05010400u);
+                a[ks][0][m] = (int)__builtin_amdgcn_perm(l1, l0, 0x05040100u);
+                a[ks][1][m] = (int)__builtin_amdgcn_perm(l1, l0, 0x07060302u);
+                if constexpr (CB == 4) {
+                    const unsigned h0 = __builtin_amdgcn_perm(w1, w0, 0x07030602u), h1 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
+                    a[ks][CB - 2][m] = (int)__builtin_amdgcn_perm(h1, h0, 0x05040100u);
+                    a[ks][CB - 1][m] = (int)__builtin_amdgcn_perm(h1, h0, 0x07060302u);
+                }
+            }
         }
     }
     // Entries 4 * CB * (lane / 16) .. of the code of the vector whose quantised coordinates are b (column lane % 16),
