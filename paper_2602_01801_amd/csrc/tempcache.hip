@@ -376,10 +376,14 @@ struct WindowScan {
                                                     const i32x4 (&pc)[NCH], bool ok, int t, int sub,
                                                     const u64 (*partbest)[TOKS], int &T, bool &tie) {
         static_assert(!ORDERED, "position order decides");
+        static_assert(TPT == 8 && SPLIT == 8, "a partial result per thread");
         constexpr int ROWS = 32 / TPT;
-        u64 best = partbest[0][t];
-#pragma unroll
-        for (int c = 1; c < SPLIT; ++c) best = better(best, partbest[c][t]);
+        // A tie may leave the threads with different groups; each sees the tie.
+        u64 best = partbest[sub][t];
+        const auto with = [&](unsigned lo, unsigned hi) { best = better(best, ((u64)hi << 32) | lo); };
+        with(lane_of_eight<0>((unsigned)best), lane_of_eight<0>((unsigned)(best >> 32)));
+        with(lane_of_eight<1>((unsigned)best), lane_of_eight<1>((unsigned)(best >> 32)));
+        with(lane_of_eight<2>((unsigned)best), lane_of_eight<2>((unsigned)(best >> 32)));
         T = (int)(unsigned)(best >> 32) - SCORE_BIAS;
         const bool seen = best != 0 && ok;
         tie = seen && ((unsigned)best & 1u);
@@ -392,8 +396,9 @@ struct WindowScan {
                 if (score(ccode, cpen, n_pad, pc, rw) == T) winner = min(winner, (unsigned)cslot[rw]);
             }
         }
-#pragma unroll
-        for (int off = 1; off < TPT; off <<= 1) winner = min(winner, (unsigned)shfl_xor((int)winner, off));
+        winner = min(winner, lane_of_eight<0>(winner));
+        winner = min(winner, lane_of_eight<1>(winner));
+        winner = min(winner, lane_of_eight<2>(winner));
         return winner;
     }
     // A second scan for candidates in any order, of which the best score is known (best_of: (winner so far, score) per token):
@@ -655,7 +660,8 @@ struct VerifyArgs {   // the verify step's arguments, for the launch that runs i
 // (timestamps inside the kernel, us): list 3.5, repeats 0.7, encode 1.7 and staging 1.0 (the code rows are in flight
 // meanwhile), scan 2.0, look-up 1.7, threshold test 2.3.  With 64 tokens, staged in slot order, so that position decides ties,
 // list to staging took 8.1 and the encode another 2.1; in list order the scan pays 0.2 for noting ties and the look-up 0.6 for
-// settling them.  Launch 21 -> 18, chunk of three calls 293 -> 285.
+// settling them.  Launch 21 -> 18, chunk of three calls 293 -> 285.  The look-up is 1.4 since a token's threads read a partial result
+// each and meet by lane moves, and one barrier hands over the results and tells of ties (2 heads x 256 tokens: 1.6 -> 1.15).
 // The scan was bound by the matrix units (two products per score) and the LDS (a group's codes and penalties, 5 KB, read
 // for 32 tokens): one product, and 64 or 128 tokens per read; 256 tokens x 3600 candidates 18 -> 9 us, launch at
 // 40 heads x 3600 tokens 113 -> 92.
@@ -720,6 +726,8 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
     constexpr bool RM_LDS = ENC && (size_t)D * R <= sizeof(partbest) && D * R / 8 <= WIN_THREADS;
     const bool rm_lds = RM_LDS && ((uintptr_t)Rm & 7) == 0;   // uniform
     __shared__ int n_tied;
+    __shared__ unsigned char s_tied[TOKS < 256 ? TOKS : 1];
+    if (tid == 0) n_tied = 0;
     u64 rm_part = 0;
     if (rm_lds && tid < D * R / 8) rm_part = ((const u64 *)Rm)[tid];
     int ce[CPT];
@@ -921,39 +929,55 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
         const int8_t *prow = ENC ? pcode + t * R : cp + ((size_t)h * n_new + min(tok, n_new - 1)) * R;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) pc[c] = *(const i32x4 *)(prow + 16 * c);
-        int T, j, S;   // best score, slot (-1: none), score with the parity
+        int T;   // best score
+        // takes down slot j (-1: none) and score S (with the parity) of this thread's token
+        auto result = [&](int j, int S) {
+            if (sub != 0) return;
+            if (tok < lim) {
+                if (!VERIFY && j >= 0) {
+                    win[(size_t)h * C + j] = 0;
+                    grp[(size_t)h * C + j] = 0;
+                }
+                jstar[(size_t)h * n_new + tok] = j;
+                sbest[(size_t)h * n_new + tok] = S;
+            }
+            // for the threshold test below; only this token's own threads (of this wavefront) have read the word
+            if (VERIFY) partbest[0][t] = ((u64)(unsigned)S << 32) | (u64)(unsigned)j;
+        };
         if constexpr (ORDERED) {
             int at;
             const bool seen = WS::look_up(ccode, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, at);
-            j = seen ? cslot[at] : -1;
-            S = !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T;
+            result(seen ? cslot[at] : -1, !seen ? 0 : metric == 0 ? 2 * T + (at < n_odd ? 1 : 0) : T);
+            if (VERIFY) __syncthreads();
         } else {
             bool tie;
             unsigned winner = WS::find(ccode, cslot, cpen, n_pad, pc, tok < lim, t, sub, partbest, T, tie);
+            auto settled = [&]() {
+                const bool seen = winner != 0xFFFFFFFFu;
+                result(seen ? (int)(winner & ~SLOT_EVEN) : -1, !seen ? 0 : metric == 0 ? 2 * T + (winner & SLOT_EVEN ? 0 : 1) : T);
+            };
             // Ties between groups are settled by the workgroup: one token in a thousand has one on drawn data, most of them on a
             // picture with flat areas.  (winner so far, T) per token, and a list of the tied ones.  Up to MANY of them share
             // the wavefronts, which go through all candidates; more, and all go through the matrix products once more.  Launch at 12 heads x
             // 1560 tokens, share of tokens and candidates that take one of two values 0 / 2 / 10 / 50 / 100 %, us: 19 / 22 / 32 / 132 /
-            // 344 with the workgroup on one token after the other; now 18 / 21 / 24 / 24 / 23.
-            if (__syncthreads_or(tie)) {   // the scan's words are done with
-                static_assert(SPLIT >= 3, "three rows of words");
-                constexpr int MANY = WIN_THREADS / 64;
-                unsigned *best_of = (unsigned *)partbest[1], *tied = (unsigned *)partbest[2];
-                if (tid == 0) n_tied = 0;
-                __syncthreads();
-                if (sub == 0) {
-                    best_of[2 * t] = winner;
-                    best_of[2 * t + 1] = (unsigned)(tie ? T : INT_MAX);   // INT_MAX: no candidate scores that
-                    if (tie) tied[atomicAdd(&n_tied, 1)] = (unsigned)t;
-                }
-                __syncthreads();
-                const int n = n_tied;
-                if (n > MANY) {   // uniform
+            // 344 with the workgroup on one token after the other; 18 / 21 / 24 / 24 / 23 this way.
+            constexpr int MANY = WIN_THREADS / 64;
+            unsigned *best_of = (unsigned *)partbest[1];   // the words of this token's own threads
+            if (sub == 0) {
+                best_of[2 * t] = winner;
+                best_of[2 * t + 1] = (unsigned)(tie ? T : INT_MAX);   // INT_MAX: no candidate scores that
+                if (tie) s_tied[atomicAdd(&n_tied, 1)] = (unsigned char)t;
+            }
+            if (!tie) settled();
+            __syncthreads();
+            const int n = n_tied;
+            if (n > 0) {   // uniform
+                if (n > MANY) {
                     WS::settle(ccode, cslot, cpen, n_pad, n_pad / 32, tq, ch, bfrag, best_of);
                 } else {
                     const int share = n > 4 ? 1 : n > 2 ? 2 : n > 1 ? 4 : 8;   // wavefronts per token
                     const int q = min(swave / share, n - 1);                    // the last token's repeat their work
-                    const int tt = (int)tied[q], best = (int)best_of[2 * tt + 1];
+                    const int tt = (int)s_tied[q], best = (int)best_of[2 * tt + 1];
                     const int8_t *trow = ENC ? pcode + tt * R : cp + ((size_t)h * n_new + min(base + tt, n_new - 1)) * R;
                     i32x4 tc[NCH];
 #pragma unroll
@@ -966,28 +990,15 @@ __global__ __launch_bounds__(WIN_THREADS, TOKS == 64 && R == 32 ? 4 : 2) void tc
                     if (lane == 63) atomicMin(&best_of[2 * tt], w);
                 }
                 __syncthreads();
-                if (tie) winner = best_of[2 * t];
-                __syncthreads();   // the words are handed on below
-            }
-            const bool seen = winner != 0xFFFFFFFFu;
-            j = seen ? (int)(winner & ~SLOT_EVEN) : -1;
-            S = !seen ? 0 : metric == 0 ? 2 * T + (winner & SLOT_EVEN ? 0 : 1) : T;
-        }
-        if (sub == 0) {
-            if (tok < lim) {
-                if (!VERIFY && j >= 0) {
-                    win[(size_t)h * C + j] = 0;
-                    grp[(size_t)h * C + j] = 0;
+                if (tie) {
+                    winner = best_of[2 * t];
+                    settled();
                 }
-                jstar[(size_t)h * n_new + tok] = j;
-                sbest[(size_t)h * n_new + tok] = S;
+                __syncthreads();
             }
-            // for the threshold test below; only this token's own threads (of this wavefront) have read the word
-            if (VERIFY) partbest[0][t] = ((u64)(unsigned)S << 32) | (u64)(unsigned)j;
         }
     }
     if constexpr (VERIFY) {
-        __syncthreads();
         constexpr int NPASS = TOKS * 16 / WIN_THREADS;   // tokens per 16-lane group
         constexpr int PB = TOKS >= 256 ? (BF16 ? 8 : 4) : 2;   // passes whose rows are loaded together (registers)
 #pragma unroll
@@ -2324,9 +2335,9 @@ constexpr int SETTLE_WAVES = SETTLE_THREADS / 64;
 constexpr int SETTLE_GROUPS = SETTLE_THREADS / 16;             // 16-lane groups: rows a workgroup moves at a time
 constexpr int SETTLE_SPT = SETTLE_SLICE / SETTLE_THREADS;      // slots per thread of a slice
 static_assert(SETTLE_SPT == 16 && AGE_BINS == 2 * SETTLE_THREADS, "a thread's slots are half a bitmap word, its bins two");
-// dynamic LDS: bitmap of the touched slots, unmerged tokens by rank, victims of the slice
+// dynamic LDS: bitmap of the touched slots, unmerged tokens by rank, victims of the slice (and a word for what is none)
 static size_t settle_lds_bytes(int C, int n_new) {
-    return (size_t)((C + 63) / 64) * 8 + (size_t)((n_new + 7) & ~7) * 2 + SETTLE_SLICE * 2;
+    return (size_t)((C + 63) / 64) * 8 + (size_t)((n_new + 7) & ~7) * 2 + SETTLE_SLICE * 2 + 16;
 }
 
 // Workgroups of tc_settle_kernel, per head, and whether it is the better way.  Shares of a slice's victims: as many as would have
@@ -2719,15 +2730,22 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
     const Pair ex = settle_scan({(unsigned)__popc(older), (unsigned)__popc(ties)}, wtot, turn, tot);
     const int take_ties = min(max(need - low_ties, 0), (int)tot.b);
     const int n_here = (int)tot.a + take_ties, rank0 = low_older + min(need, low_ties);
-    int ties_left = take_ties - (int)ex.b, idx = (int)ex.a + min((int)ex.b, take_ties);
-    for (unsigned todo = older | (ties_left > 0 ? ties : 0u); todo; todo &= todo - 1u) {
-        const int q = __ffs(todo) - 1;
-        if ((ties >> q) & 1u) {
-            if (ties_left <= 0) continue;
-            ties_left -= 1;
+    unsigned take = older;
+    {
+        int ties_left = take_ties - (int)ex.b;
+        unsigned first = ties_left > 0 ? ties : 0u;
+        for (; __popc(first) > ties_left && first; ) first &= ~(0x80000000u >> __clz(first));   // one thread of the slice
+        take |= first;
+    }
+    // all slots of the run, without branches: the others' go to a word of no meaning (victims are mostly whole runs; the set bits one
+    // after the other took 1.6 us longer)
+    if (__ballot(take != 0u)) {   // uniform
+        const int idx = (int)ex.a + min((int)ex.b, take_ties);
+#pragma unroll
+        for (int q = 0; q < SETTLE_SPT; ++q) {
+            const int at = (take >> q) & 1u ? idx + __popc(take & ((1u << q) - 1u)) : SETTLE_SLICE;
+            vict[at] = (unsigned short)(SETTLE_SPT * tid + q);
         }
-        vict[idx] = (unsigned short)(SETTLE_SPT * tid + q);
-        idx += 1;
     }
     __syncthreads();
     const int n_rows = n_here > share ? (n_here - share + n_reps - 1) / n_reps : 0;
