@@ -394,71 +394,80 @@ __global__ __launch_bounds__(256, 3) void score_self_stream_kernel(const int8_t 
 // smax[p] = max over the queries of block b of qcode[q] . pcode[p], for all n_p prompt tokens; whole workgroup.
 // A wavefront takes every fourth group of 32 prompt tokens against all queries, 128 at a time: a token's codes are read once
 // and its maximum over four products stays in registers, without atomics.  (Every wavefront a quarter of the queries
-// against all tokens, maxima met in LDS: 5.4 us for 128 queries x 512 tokens, 13.6 x 2048; now 3.9 and 8.0.  The next codes
-// in flight as well: no faster.)
+// against all tokens, maxima met in LDS: 5.4 us for 128 queries x 512 tokens, 13.6 x 2048; 3.9 and 8.0 this way.)
+// What bounds it is the issue of the wavefront: a product's result is there 64 cycles after it was asked for, so the next product
+// is under way while the maxima of one are taken, without branches between them (one after the other, each waited for: launch
+// for 2 x 256 queries x 2048 tokens 8.5 us, now 7.4; 1 x 128 x 12000 68.7, 60.7).
 // in_flight() is called once, behind the first loads: what it asks for does not hold the scores up (loads come back in order).
-template <int R, typename F>
-__device__ __forceinline__ void score_cross_block(const int8_t *__restrict__ qc, const int8_t *__restrict__ pc, int n_q,
-                                                  int n_p, int BQ, int b, int32_t *smax, F &&in_flight) {
+// maximum of m and the 16 results, three levels deep
+__device__ __forceinline__ int max_of_16(int m, const i32x16 &a) {
+    const int t0 = max(max(a[0], a[1]), a[2]), t1 = max(max(a[3], a[4]), a[5]), t2 = max(max(a[6], a[7]), a[8]);
+    const int t3 = max(max(a[9], a[10]), a[11]), t4 = max(max(a[12], a[13]), a[14]);
+    return max(max(m, max(max(t0, t1), a[15])), max(max(t2, t3), t4));
+}
+// Queries q0 .. q_end (at most 32 QG; rows beyond repeat the last one, which changes no maximum) against all tokens.
+template <int R, int QG, typename F>
+__device__ __forceinline__ void score_cross_queries(const int8_t *__restrict__ qc, const int8_t *__restrict__ pc, int n_p, int q0,
+                                                    int q_end, bool first, int32_t *smax, F &&in_flight) {
     constexpr int KS = R / 32;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 31, g2 = lane >> 5;
-    const int q_end = min((b + 1) * BQ, n_q), n_groups = (n_p + 31) / 32;
-    for (int q0 = b * BQ; q0 < q_end; q0 += 128) {
-        // rows beyond the block repeat its last query, which changes no maximum
-        const int n_qg = min((q_end - q0 + 31) / 32, 4);
-        i32x4 afrag[4][KS];
+    const int n_groups = (n_p + 31) / 32;
+    constexpr int PB = 4;   // groups of tokens in flight: the codes of a group four further on replace those just used
+    i32x4 afrag[QG][KS], bfrag[PB][KS];
+    auto load = [&](int u, int group) {
+        const int prow = min(group * 32 + col, n_p - 1);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int qrow = min(q0 + 32 * u + col, q_end - 1);
+        for (int ks = 0; ks < KS; ++ks) bfrag[u][ks] = *(const i32x4 *)(pc + (size_t)prow * R + ks * 32 + 16 * g2);
+    };
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) afrag[u][ks] = *(const i32x4 *)(qc + (size_t)qrow * R + ks * 32 + 16 * g2);
-        }
-        constexpr int PB = 4;   // groups of tokens in flight: the codes of a group four further on replace those just used
-        i32x4 bfrag[PB][KS];
-        auto load = [&](int u, int group) {
-            const int prow = min(group * 32 + col, n_p - 1);
+    for (int u = 0; u < QG; ++u) {
+        const int qrow = min(q0 + 32 * u + col, q_end - 1);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) bfrag[u][ks] = *(const i32x4 *)(pc + (size_t)prow * R + ks * 32 + 16 * g2);
-        };
-        auto score = [&](int u, int group) {
-            const int p = group * 32 + col;
-            int m = INT_MIN;
+        for (int ks = 0; ks < KS; ++ks) afrag[u][ks] = *(const i32x4 *)(qc + (size_t)qrow * R + ks * 32 + 16 * g2);
+    }
 #pragma unroll
-            for (int qg = 0; qg < 4; ++qg) {
-                if (qg >= n_qg) break;   // uniform
-                i32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int u = 0; u < PB; ++u) load(u, wave + 4 * u);
+    __builtin_amdgcn_sched_barrier(0);
+    in_flight();
+    __builtin_amdgcn_sched_barrier(0);
+    auto product = [&](int qg, int u) {
+        i32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(afrag[qg][ks], bfrag[u][ks], acc);
+        for (int ks = 0; ks < KS; ++ks) acc = mfma_i8_32x32x32(afrag[qg][ks], bfrag[u][ks], acc);
+        return acc;
+    };
+    i32x16 acc[2];
+    // the tokens of slot u; leaves the first product of slot `next` under way
+    auto score = [&](int u, int next, int group) {
+        static_assert(QG % 2 == 0, "two sets of results in turn");
+        const int p = group * 32 + col;
+        int m = INT_MIN;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) m = max(m, acc[v]);
-            }
-            const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)m, (unsigned)m, false, false);
-            m = max((int)halves[0], (int)halves[1]);
-            if (g2 == 0 && p < n_p) smax[p] = q0 == b * BQ ? m : max(smax[p], m);   // the same lane every time
-        };
-#pragma unroll
-        for (int u = 0; u < PB; ++u) load(u, wave + 4 * u);
-        if (q0 == b * BQ) {
+        for (int qg = 0; qg < QG; ++qg) {
+            acc[(qg + 1) & 1] = qg + 1 < QG ? product(qg + 1, u) : product(0, next);
             __builtin_amdgcn_sched_barrier(0);
-            in_flight();
+            m = max_of_16(m, acc[qg & 1]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        int t0 = wave;
-        for (; t0 + 4 * PB < n_groups; t0 += 4 * PB) {
+        const auto halves = __builtin_amdgcn_permlane32_swap((unsigned)m, (unsigned)m, false, false);
+        m = max((int)halves[0], (int)halves[1]);
+        if (g2 == 0 && p < n_p) smax[p] = first ? m : max(smax[p], m);   // the same lane every time
+    };
+    acc[0] = product(0, 0);
+    int t0 = wave;
+    for (; t0 + 4 * PB < n_groups; t0 += 4 * PB) {
 #pragma unroll
-            for (int u = 0; u < PB; ++u) {   // whole groups of four: t0 + 4 u + 4 < n_groups
-                score(u, t0 + 4 * u);
-                load(u, t0 + 4 * (PB + u));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            if (t0 + 4 * u >= n_groups) break;   // uniform
-            score(u, t0 + 4 * u);
+        for (int u = 0; u < PB; ++u) {   // whole groups of four: t0 + 4 u + 4 < n_groups
+            score(u, (u + 1) % PB, t0 + 4 * u);
+            load(u, t0 + 4 * (PB + u));
         }
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PB; ++u) {
+        if (t0 + 4 * u >= n_groups) break;   // uniform
+        score(u, (u + 1) % PB, t0 + 4 * u);
+    }
 }
 
 template <int R>
@@ -468,7 +477,13 @@ __global__ __launch_bounds__(256) void score_cross_kernel(const int8_t *__restri
     extern __shared__ int32_t smax[];  // [n_p]
     __shared__ __attribute__((aligned(16))) unsigned scratch[TOPK_SCRATCH];
     const int b = blockIdx.x, h = blockIdx.y;
-    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, BQ, b, smax, [] {});
+    const int8_t *qc = qcode + (size_t)h * n_q * R, *pc = pcode + (size_t)h * n_p * R;
+    const int q_end = min((b + 1) * BQ, n_q);
+    for (int q0 = b * BQ; q0 < q_end; q0 += 128) {   // uniform
+        if (q_end - q0 > 64) score_cross_queries<R, 4>(qc, pc, n_p, q0, q_end, q0 == b * BQ, smax, [] {});
+        else score_cross_queries<R, 2>(qc, pc, n_p, q0, q_end, q0 == b * BQ, smax, [] {});
+    }
+    __syncthreads();
     // the workgroup owns the whole row: select from LDS right away
     topk_row(smax, n_p, n_sel, sel + ((size_t)h * n_qb + b) * n_sel, nsel + (size_t)h * n_qb + b, nullptr, scratch);
 }
@@ -508,11 +523,12 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
     // this lane's query row as the second operand of K Q^T: in flight during the scoring and the selection
     const int q_idx = b * 128 + wave * 32 + col;
     bf16x8 qf[D / 16];
-    score_cross_block<R>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_q, n_p, 128, b, smax, [&] {
+    score_cross_queries<R, 4>(qcode + (size_t)h * n_q * R, pcode + (size_t)h * n_p * R, n_p, b * 128, min((b + 1) * 128, n_q), true, smax, [&] {
         const unsigned short *qrow = Q + ((size_t)h * n_q + min(q_idx, n_q - 1)) * D;
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) qf[s] = *(const bf16x8 *)(qrow + 16 * s + 8 * g);
     });
+    __syncthreads();
     topk_row(smax, n_p, n_sel, lsel, lcnt, nullptr, (unsigned *)ktile);   // the tile's memory is free until the gather
     __syncthreads();
     const int k = lcnt[0];
