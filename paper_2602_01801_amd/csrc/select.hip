@@ -531,15 +531,17 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
     __syncthreads();
     topk_row(smax, n_p, n_sel, lsel, lcnt, nullptr, (unsigned *)ktile);   // the tile's memory is free until the gather
     __syncthreads();
-    const int k = lcnt[0];
+    const int k = __builtin_amdgcn_readfirstlane(lcnt[0]);
     if (tid < n_sel) sel[((size_t)h * n_qb + b) * n_sel + tid] = lsel[tid];
     if (tid == 0) nsel[(size_t)h * n_qb + b] = k;
-    // gather: slot p of the tiles holds the rows of token lsel[p] (p >= k: token 0, masked below)
+    // gather: slot p of the tiles holds the rows of token lsel[p], zeros from k to the end of the last block of 32 in use
     const unsigned short *Kh = Kp + (size_t)h * n_p * D, *Vh = Vp + (size_t)h * n_p * D;
+    const bool two = k > 32;   // uniform
     {
         u32x4 kv[4], vv[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+            if (16 * e >= k) break;   // uniform
             const int idx = e * 256 + tid, p = idx >> 4, c = idx & 15;
             const int tok = p < k ? lsel[p] : 0;
             kv[e] = *(const u32x4 *)(Kh + (size_t)tok * D + 8 * c);
@@ -547,16 +549,22 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
+            if (e >= 2 && !two) break;   // uniform
             const int idx = e * 256 + tid, p = idx >> 4, c = idx & 15;
+            if (16 * e + 16 > k) {   // uniform
+                const u32x4 none = {0u, 0u, 0u, 0u};
+                kv[e] = p < k ? kv[e] : none;
+                vv[e] = p < k ? vv[e] : none;
+            }
             *(u32x4 *)(ktile + p * KROW + c * 16) = kv[e];
             *(u32x4 *)(vtile + p * VROW + c * 16) = vv[e];
         }
     }
     __syncthreads();
-    // S^T = K Q^T: rows = token slots (two blocks of 32), columns = this wavefront's 32 queries
+    // S^T = K Q^T: rows = token slots (two blocks of 32, the second where there are so many), columns = this wavefront's 32 queries.
+    // Softmax over the k live slots in one piece: register v of block kb is slot 32 kb + 8 (v / 4) + 4 g + v % 4.
     f32x16 s_acc[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    auto scores = [&](int kb) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) s_acc[kb][v] = 0.0f;
 #pragma unroll
@@ -564,51 +572,62 @@ __global__ __launch_bounds__(256) void cross_fused_kernel(const unsigned short *
             const bf16x8 a = *(const bf16x8 *)(ktile + (32 * kb + col) * KROW + (16 * s + 8 * g) * 2);
             s_acc[kb] = mfma_bf16_32x32x16(a, qf[s], s_acc[kb]);
         }
+    };
+    auto mask = [&](int kb) {
+        if (k >= 32 * kb + 32) return;   // uniform
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (32 * kb + 8 * (v >> 2) + 4 * g + (v & 3) >= k) s_acc[kb][v] = -INFINITY;
+    };
+    scores(0);
+    if (two) scores(1);
+    mask(0);
+    float mx = s_acc[0][0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s_acc[0][v]);
+    if (two) {
+        mask(1);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s_acc[1][v]);
     }
-    // softmax over the k live slots (register v of block kb is slot 32 kb + 8 (v / 4) + 4 g + v % 4)
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int slot = 32 * kb + 8 * (v >> 2) + 4 * g + (v & 3);
-            if (slot >= k) s_acc[kb][v] = -INFINITY;
-            mx = fmaxf(mx, s_acc[kb][v]);
-        }
-    mx = fmaxf(mx, shfl_xor(mx, 32));
+    {
+        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+    }
     const float neg_ms = mx == -INFINITY ? 0.0f : -mx * scale_log2;
     float l = 0.0f;
-    bf16x8 pf[2][2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int st = 0; st < 2; ++st)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float pv = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][8 * st + j], scale_log2, neg_ms));
-                const __bf16 pb = (__bf16)pv;
-                pf[kb][st][j] = pb;
-                l += (float)pb;   // the sum takes the rounded P, the values the second product sees
-            }
-    l += shfl_xor(l, 32);
-    // O^T = V^T P^T: rows = 32 of the d coordinates per block, columns = queries
     f32x16 o_acc[D / 32];
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db) {
+    for (int db = 0; db < D / 32; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o_acc[db][v] = 0.0f;
+    // O^T += V^T P^T of one block: rows = 32 of the d coordinates per block, columns = queries
+    auto weigh = [&](int kb) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int st = 0; st < 2; ++st) {
+            bf16x8 pf;
 #pragma unroll
-            for (int st = 0; st < 2; ++st) {
+            for (int j = 0; j < 8; ++j) {
+                pf[j] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s_acc[kb][8 * st + j], scale_log2, neg_ms));
+                l += (float)pf[j];   // the sum takes the rounded P, the values the second product sees
+            }
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db) {
                 // tokens in the order the score accumulators hold them: 4 g .. + 3 and 8 + 4 g .. + 3 of the 16; lane i of 16
                 // gets coordinate i of the four rows that the lanes 4 j + q address
                 const unsigned char *vp = vtile + (32 * kb + 16 * st + 4 * g + ((lane & 15) >> 2)) * VROW +
                                           (32 * db + (lane & 16) + 4 * (lane & 3)) * 2;
                 const bf16x4 lo = ds_read_tr16(vp), hi = ds_read_tr16(vp + 8 * VROW);
                 const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                o_acc[db] = mfma_bf16_32x32x16(a, pf[kb][st], o_acc[db]);
+                o_acc[db] = mfma_bf16_32x32x16(a, pf, o_acc[db]);
             }
+        }
+    };
+    weigh(0);
+    if (two) weigh(1);
+    {
+        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        l = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
     }
     const float inv = l > 0.0f ? 1.0f / l : 0.0f;
     // A lane holds four of every eight coordinates of its query; the halves of the wavefront trade theirs, so that a lane has

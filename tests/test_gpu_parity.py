@@ -521,6 +521,30 @@ def test_fused_prompt_selection_and_attention_matches_the_two_calls(H, n_q, n_p,
     assert np.abs(Of - storage_to_f64(to_host(O2))).max() <= ATOL["bf16"]
 
 
+# budgets at the edges of the rows that are gathered together (16) and multiplied together (32), prompts shorter than the budget
+@pytest.mark.parametrize("n_p,n_sel", [(100, 1), (100, 15), (100, 16), (100, 17), (100, 31), (100, 32), (100, 33), (100, 48), (100, 49),
+                                       (100, 63), (100, 64), (33, 64), (5, 20)])
+def test_fused_prompt_attention_at_every_edge_of_its_tiles_reads_nothing_of_other_tokens(n_p, n_sel):
+    rng = np.random.default_rng(n_p + n_sel)
+    H, n_q, d, r = 2, 200, 128, 32
+    codec = make_codec(0, 4, d, r)
+    Q, Kp, Vp = (to_storage(rng.standard_normal((H, n, d)).astype(np.float32), "bf16") for n in (n_q, n_p, n_p))
+    qc = oracle.encode(Q, codec.R, codec.qscale, codec.shift)
+    pc = oracle.encode(Kp, codec.R, codec.qscale, codec.shift)
+    sel_r, nsel_r = oracle.ann_select_cross(qc, pc, 128, n_sel)
+    O_r, _ = oracle.sparse_attn_fwd(Q, Kp, Vp, None, np.full((H,), n_p, np.int32), sel_r, nsel_r, 128, 1, d ** -0.5)
+    dQ, dK, dV, dqc, dpc = (to_dev(x) for x in (Q, Kp, Vp, qc, pc))
+    sel, nsel, O = fa.ann_cross_attn_fwd(dQ, dqc, dK, dV, dpc, 128, n_sel, d ** -0.5)
+    assert np.array_equal(to_host(sel), sel_r) and np.array_equal(to_host(nsel), nsel_r)
+    assert np.abs(storage_to_f64(to_host(O)) - O_r).max() <= ATOL["bf16"]
+    for h in range(H):      # rows that no block selects need not be finite
+        others = np.setdiff1d(np.arange(n_p), sel_r[h])
+        dK[h, torch.from_numpy(others).cuda()] = float("nan")
+        dV[h, torch.from_numpy(others).cuda()] = float("inf")
+    O2 = fa.ann_cross_attn_fwd(dQ, dqc, dK, dV, dpc, 128, n_sel, d ** -0.5)[2]
+    assert torch.equal(O.view(torch.int16), O2.view(torch.int16))
+
+
 def test_fused_prompt_attention_rejects_what_it_is_not_built_for():
     Q = torch.zeros((1, 128, 64), dtype=torch.bfloat16, device="cuda")
     code = torch.zeros((1, 128, 32), dtype=torch.int8, device="cuda")
