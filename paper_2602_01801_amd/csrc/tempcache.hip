@@ -2572,7 +2572,7 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
     kbase = kincl - kbase;   // unmerged tokens before the first count of this lane
     const int n_unm = __builtin_amdgcn_readlane(kincl, 63), e = L + n_unm - C;
     if (e <= 0) return;   // uniform over the head
-    unsigned distinct = 0, fmask = 0;
+    unsigned fmask = 0;
 #pragma unroll
     for (int k = 0; k < TPT; ++k)   // each touched slot counts once
         if ((tmask >> k) & 1u) fmask |= (((atomicOr(&touched[tj[k] >> 5], 1u << (tj[k] & 31)) >> (tj[k] & 31)) & 1u) ^ 1u) << k;
@@ -2590,7 +2590,6 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
             const int lead = __ffsll((unsigned long long)fm) - 1;
             const bool same = bin == (unsigned)__builtin_amdgcn_readlane((int)bin, lead), low = tj[k] < s0;
             const u64 sm = __ballot(first && same), lm = __ballot(first && same && low);
-            distinct += first ? 1u : 0u;
             if (lane == lead) {
                 atomicSub(&h_all[bin], (unsigned)__popcll(sm));
                 if (lm) atomicSub(&h_low[bin], (unsigned)__popcll(lm));
@@ -2601,28 +2600,26 @@ __global__ __launch_bounds__(SETTLE_THREADS, TPT == 4 && BF16 ? 8 : 4) void tc_s
             }
         }
     }
-    Pair tot;
-    settle_scan({distinct, 0u}, wtot, turn, tot);   // its barrier also publishes the lists, the bitmap and the histograms
-    const int n_el = L - (int)tot.a;
-    const bool take_all = n_el <= e;
+    __syncthreads();   // the lists, the bitmap and the histograms
     // Threshold: the bin, from the oldest on, in which the e-th slot lies; `need` of it are taken.  Victims: the slots of older
     // bins, and of this one those with the smallest stamps, ties in slot order.  low_*: how many of them lie below this slice.
     int bin = 0, need = 0, low_older = 0, low_ties = 0;
     bool exact = true;          // one stamp per bin
     unsigned tkey = 0u;         // otherwise the threshold among the bin's stamps
+    Pair tot;                   // of the eligible slots, and of those below this slice
+    const int b1 = AGE_BINS - 1 - 2 * tid, b0 = b1 - 1;   // this thread's bins, the older one first
+    const unsigned a1 = h_all[b1], a0 = h_all[b0], l1 = h_low[b1], l0 = h_low[b0];
+    const Pair older_of = settle_scan({a0 + a1, l0 + l1}, wtot, turn, tot);
+    const bool take_all = (int)tot.a <= e;
     if (take_all) {
-        settle_scan({h_low[2 * tid] + h_low[2 * tid + 1], 0u}, wtot, turn, tot);
-        low_older = (int)tot.a;
+        low_older = (int)tot.b;
     } else {
-        const int b1 = AGE_BINS - 1 - 2 * tid, b0 = b1 - 1;   // this thread's bins, the older one first
-        const unsigned a1 = h_all[b1], a0 = h_all[b0], l1 = h_low[b1], l0 = h_low[b0];
-        const Pair ex = settle_scan({a0 + a1, l0 + l1}, wtot, turn, tot);
-        const unsigned before = ex.a, want = (unsigned)e;
+        const unsigned before = older_of.a, want = (unsigned)e;
         if (before < want && want <= before + a0 + a1) {
             const bool in1 = want <= before + a1;
             sh[0] = in1 ? b1 : b0;
             sh[1] = (int)(want - before - (in1 ? 0u : a1));
-            sh[2] = (int)(ex.b + (in1 ? 0u : l1));
+            sh[2] = (int)(older_of.b + (in1 ? 0u : l1));
             sh[3] = (int)(in1 ? l1 : l0);
         }
         __syncthreads();
