@@ -19,7 +19,18 @@
 namespace fastar {
 
 constexpr int KB_PER_WG = 4;      // key blocks scored by one workgroup of score_self_kernel
-constexpr size_t LONG_CACHE_BLOCKS = 16 * 4096;   // key blocks over all heads from which the streaming kernel pays
+// Key blocks over all heads from which the streaming kernel pays, by the summaries' column blocks of 32 (it holds four): never for
+// one or two and for 64-entry codes, where the short kernel keeps more wavefronts in flight.  Call, streaming / short kernel, us:
+// 4: 10 heads x 64000 slots (10000) 17.3 / 17.5, 13 x 103000 (20930) 25.6 / 26.6, 20 x 150000 (46880) 44 / 49, 40 x 230400 113 / 128;
+// 3: 20 x 150000 41.7 / 41.6, 40 x 110000 (68760) 50.0 / 50.9, 40 x 230400 99 / 108; 2: 40 x 230400 88 / 82, 24 x 200000 49.6 / 45.6,
+// 40 x 115200 45 / 41; 64 entries: 4: 10 x 64000 33 / 22, 40 x 110000 95 / 93, 3: 20 x 230400 95 / 84, 2: 40 x 115200 86 / 61.
+// Codes of 2 and 4 bits keep one line.
+constexpr size_t LONG_CACHE_BLOCKS = 16 * 4096, LONG_CACHE_BLOCKS_4 = 20000;
+static bool streams(int r, int bits, int n_cb, size_t blocks) {
+    if (n_cb > 4 || r != 32) return false;
+    if (bits != 8) return blocks >= LONG_CACHE_BLOCKS;
+    return n_cb >= 3 && blocks >= (n_cb == 4 ? LONG_CACHE_BLOCKS_4 : LONG_CACHE_BLOCKS);
+}
 // Slots per head up to which one workgroup per query block scores them all (select_short_kernel); three launches against
 // one, us: r = 32, 2 x 2 query blocks, 4096 slots 9.3 -> 6.6, 9360 9.3 -> 8.9, 12288 9.6 -> 9.3; 12 x 21, 4096 11.1 -> 7.4,
 // 9360 11.7 -> 10.2, 12288 11.7 -> 12.2; r = 64, 6 x 21, 1024 11.7 -> 7.0, 4096 11.7 -> 9.3, 8192 11.8 -> 13.1.
@@ -29,7 +40,6 @@ constexpr int short_keys(int r) { return r == 32 ? 10240 : 4096; }
 // (32 MB) 10.9 -> 9.5, x 10240 (40 MB) 11.2 -> 12.7, 24 x 8 x 8192 (48 MB) 10.8 -> 12.6, 32 x 8 x 10240 (80 MB) 11.5 -> 16.7.
 constexpr int64_t SHORT_BYTES = 38 << 20;
 constexpr int SHORT_WGS = 256;     // its workgroups: no more than compute units (a second round: 11 us like the launches it replaces)
-constexpr int COL_CHUNK = 8;       // summary column blocks (of 32) kept in registers at a time
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -132,7 +142,11 @@ __device__ __forceinline__ int max_over_reps_i32(int x, int n_rep) {
 // ---- AnnSA scoring -----------------------------------------------------------------------------------
 // out[h][b][kb] = max over the summaries u of block b (whose run holds a query) and the live keys k of
 // key block kb of rep[b,u] . kcode[k].   D = A x B with A rows = 32 keys, B columns = 32 summaries.
-template <int R, int BITS>
+// COL_CHUNK: summary column blocks (of 32) per pass; their operands are registers, so it is no more than the call needs: what
+// bounds the launch is the codes' latency, and it wants wavefronts in flight (eight at every size held it to 94 registers and 1280
+// workgroups: call for 20 heads x 2000 queries x 100000 slots 28.8 us, with two 23.9; 12 x 1560 x 32760 12.6 -> 11.4; five for
+// 12 x 4680 x 37440 16.8 -> 16.1).
+template <int R, int BITS, int COL_CHUNK>
 __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restrict__ kcode, const int32_t *__restrict__ len,
                                                          const int8_t *__restrict__ rep, int C, int n_q, int BQ,
                                                          int n_rep, int BK, int n_qb, int n_kb_cap,
@@ -1132,10 +1146,11 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
     if (bits != 8 && !((bits == 4 || bits == 2) && r == 32)) return FASTAR_ERR_UNSUPPORTED;
     const int n_qb = (n_q + BQ - 1) / BQ;
     const int n_kb_cap = (C + BK - 1) / BK;
-    // long caches whose summaries fit four column blocks take the streaming kernel: about 2048 workgroups that
-    // sweep each head's key blocks together
-    const bool few_cols = (n_qb * n_rep + 31) / 32 <= 4;
-    const bool stream_kernel = few_cols && (size_t)n_kb_cap * H >= LONG_CACHE_BLOCKS;
+    // long caches whose summaries fit four column blocks take the streaming kernel: 768 workgroups that sweep each head's key
+    // blocks together
+    const int n_cb = (n_qb * n_rep + 31) / 32;
+    const bool stream_kernel = streams(r, bits, n_cb, (size_t)n_kb_cap * H);
+    const int per_pass = (n_cb + (n_cb + 7) / 8 - 1) / ((n_cb + 7) / 8);   // column blocks per pass, equal ones
     const size_t tile_bytes = (size_t)n_qb * KB_PER_WG * sizeof(int32_t);
     if (!stream_kernel && tile_bytes > 64 * 1024) return FASTAR_ERR_UNSUPPORTED;
     const SelfWs w = self_ws(H, n_q, C, r, BQ, BK, n_rep);
@@ -1160,16 +1175,26 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
     const dim3 grid((n_kb_cap + KB_PER_WG - 1) / KB_PER_WG, H);
     constexpr int stream_wgs = 768;   // three resident workgroups per CU (the kernel is built for 168 registers)
     const dim3 grid_stream((unsigned)std::max(1, std::min(std::max(1, stream_wgs / H), (n_kb_cap + 3) / 4)), H);
+    auto score_launch = [&](auto r_c, auto bits_c) {
+        constexpr int RR = decltype(r_c)::value, BB = decltype(bits_c)::value;
+        if constexpr (RR == 32) {
+            if (stream_kernel) {
+                hipLaunchKernelGGL((score_self_stream_kernel<RR, 4, BB>), grid_stream, dim3(256), 0, s, kcode, len, rep, C, n_q, BQ,
+                                   n_rep, BK, n_qb, n_kb_cap, score);
+                return;
+            }
+        }
+        auto kernel = per_pass <= 2   ? score_self_kernel<RR, BB, 2>
+                      : per_pass <= 4 ? score_self_kernel<RR, BB, 4>
+                      : per_pass == 5 ? score_self_kernel<RR, BB, 5>
+                                      : score_self_kernel<RR, BB, 8>;
+        hipLaunchKernelGGL(kernel, grid, dim3(256), tile_bytes, s, kcode, len, rep, C, n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score);
+    };
 #define FASTAR_SELF(RR, BB)                                                                                            \
     do {                                                                                                               \
         hipLaunchKernelGGL(rep_kernel<BB>, dim3(n_qb, H), dim3(128), 0, s, qcode, n_q, r, BQ, n_rep, n_qb, rep);       \
         FASTAR_LAUNCH_CHECK();                                                                                         \
-        if (!stream_kernel)                                                                                            \
-            hipLaunchKernelGGL((score_self_kernel<RR, BB>), grid, dim3(256), tile_bytes, s, kcode, len, rep, C, n_q, BQ, \
-                               n_rep, BK, n_qb, n_kb_cap, score);                                                      \
-        else                                                                                                           \
-            hipLaunchKernelGGL((score_self_stream_kernel<RR, 4, BB>), grid_stream, dim3(256), 0, s, kcode, len, rep, C, \
-                               n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score);                                             \
+        score_launch(std::integral_constant<int, RR>{}, std::integral_constant<int, BB>{});                            \
     } while (0)
     if (bits == 4) FASTAR_SELF(32, 4);
     else if (bits == 2) FASTAR_SELF(32, 2);

@@ -291,6 +291,22 @@ def test_selection_on_seeded_random_shapes(seed):
         assert np.array_equal(to_host(sel), ref_sel), what
 
 
+# summaries in one to nine column blocks of 32 (passes of 2, 4, 5 and 8, the last one short), and both sides of the streaming
+# kernel's line for three and four of them (20000 and 65536 key blocks over the heads)
+@pytest.mark.parametrize("H,n_q,C,r,BK", [
+    (2, 400, 12000, 32, 64), (2, 1100, 12000, 32, 64), (2, 2100, 12000, 64, 64), (2, 4200, 12000, 32, 64), (2, 5000, 11000, 64, 64),
+    (2, 9100, 11000, 32, 96), (1, 3500, 639968, 32, 32), (1, 3500, 640001, 32, 32), (1, 2500, 2097120, 32, 32), (1, 2500, 2097121, 32, 32),
+    (1, 2000, 2097152, 32, 32), (1, 3500, 640001, 64, 32)])
+def test_ann_select_self_with_summaries_of_every_number_of_columns(H, n_q, C, r, BK):
+    rng = np.random.default_rng(n_q + C)
+    qc, kc = rand_codes(rng, -60, 60, H, n_q, r), rand_codes(rng, -60, 60, H, C, r)
+    length = np.array([C, C - 777][:H], np.int32)
+    ref_sel, ref_nsel = oracle.ann_select_self(qc, kc, length, 128, 4, BK, 20)
+    sel, nsel = fa.ann_select_self(to_dev(qc), to_dev(kc), to_dev(length), 128, 4, BK, 20)
+    assert np.array_equal(to_host(nsel), ref_nsel)
+    assert np.array_equal(to_host(sel), ref_sel)
+
+
 def test_selection_is_deterministic_across_repeats():
     rng = np.random.default_rng(11)
     qc, kc = rand_codes(rng, -2, 2, 4, 1000, 32), rand_codes(rng, -2, 2, 4, 64 * 300, 32)
