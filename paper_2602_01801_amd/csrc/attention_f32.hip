@@ -252,18 +252,19 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
         asm volatile("" : "+v"(n_next)::"memory");
         if (!UNI) asm volatile("" : "+v"(kb_next));
         if (t + KS < nt) load_k(next, 0, TKF);   // the tile in LDS has been read: wait_k saw its last operand
-        float mx = -INFINITY;
+        float mx = -INFINITY, mn = INFINITY;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 s[hh][v] = fmaf(s[hh][v], scale_log2, bv[hh][v]);
                 mx = fmaxf(mx, s[hh][v]);
+                mn = fminf(mn, s[hh][v]);
             }
         mx = max_of_quarters(mx);
         if (__any(mx > m_run)) {   // (uniform) a new maximum: what is summed up so far moves to it
             const float m_new = fmaxf(m_run, mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // m_new is finite where it is new
+            const float alpha = exp2f(m_run - m_new);                    // m_new is finite where it is new
             const float al = m_new == -INFINITY ? 1.0f : alpha;
             m_run = m_new;
             m_safe = m_new == -INFINITY ? 0.0f : m_new;                  // every key so far masked
@@ -271,13 +272,18 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
 #pragma unroll
             for (int c = 0; c < CH; ++c) o[c] *= al;
         }
+        // The bare instruction makes weights below 2^-126 zero, exp2f does not, at five instructions each; the same elsewhere.
+        auto weights = [&](auto exponential) {
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+            for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                s[hh][v] = __builtin_amdgcn_exp2f(s[hh][v] - m_safe);
-                l_run += s[hh][v];
-            }
+                for (int v = 0; v < 4; ++v) {
+                    s[hh][v] = exponential(s[hh][v] - m_safe);
+                    l_run += s[hh][v];
+                }
+        };
+        if (__any(mn - m_safe < -126.0f)) weights([](float x) { return exp2f(x); });   // uniform
+        else weights([](float x) { return __builtin_amdgcn_exp2f(x); });
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
 #pragma unroll

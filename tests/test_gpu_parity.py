@@ -692,6 +692,25 @@ def test_fp32_attention_over_whole_and_masked_tiles_in_any_order(d, n_q, BQ, BK,
     check_attention(Q, K, V, None, lens, sel, nsel, BQ, BK, d ** -0.5, "fp32")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("at", [1, 40, 130])       # the light key: in the heavy one's tile, in another wavefront's, in a later tile of its own
+@pytest.mark.parametrize("heavy_first", [True, False])
+def test_fp32_attention_keeps_weights_below_the_normal_range(d, at, heavy_first):
+    # a weight of 2^-b on a value of 2^127: fp32 holds it down to b = 149, and so does the output.  Bound: b / log2(e) goes through
+    # two roundings before the exponential (b ln(2) 2^-23), a weight below 2^-126 is a whole multiple of 2^-149.
+    first, second = (0, at) if heavy_first else (at, 0)
+    for bits in (100, 126, 127, 130, 140):
+        Q, K, V = (torch.zeros(1, n, d, device="cuda") for n in (16, 256, 256))
+        Q[..., 0] = 1.0
+        K[0, :, 0] = -1e30                          # weight zero
+        K[0, first, 0], K[0, second, 0] = 0.0, -bits * np.log(2.0)
+        V[0, first, 0], V[0, second, 1] = 1.0, 2.0 ** 127
+        sel = torch.arange(4, dtype=torch.int32, device="cuda").view(1, 1, 4)
+        O, _ = fa.sparse_attn_fwd(Q, K, V, None, to_dev(np.array([256], np.int32)), sel, to_dev(np.array([[4]], np.int32)), 16, 64, 1.0)
+        got, want = to_host(O)[0, :, :2], np.array([1.0, 2.0 ** (127 - bits)])
+        assert (np.abs(got / want - 1.0) <= bits * 2.0 ** -23 + 2.0 ** (bits - 149)).all(), (bits, got[0])
+
+
 @pytest.mark.parametrize("d,BQ,BK,n_kb,n_sel", [
     (128, 128, 1, 900, 48),      # single keys, the list ends inside a step of 32
     (64, 128, 1, 300, 45),
