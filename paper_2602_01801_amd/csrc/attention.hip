@@ -393,6 +393,16 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
     hipLaunchKernelGGL((attn_bf16_kernel<DD, NW>), grid, dim3(NW * 64), 0, s, (const unsigned short *)Q,                 \
                        (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, nsel, n_q, C, bk_shift, \
                        n_sel, n_qb, H, scale_log2, (unsigned short *)O, lse)
+        // The kernels below start a tile's sums from log2(cnt) / scale, and let a reference maximum lag by octaves / scale; this
+        // one adds the bias behind the scaling, so that no scale is too small for it.
+        if (scale_log2 < ATTN_LEAST_SCALE_LOG2) {
+            if (d == 128 && BQ == 128) FASTAR_ATTN(128, 4);
+            else if (d == 128) FASTAR_ATTN(128, 2);
+            else if (BQ == 128) FASTAR_ATTN(64, 4);
+            else FASTAR_ATTN(64, 2);
+            FASTAR_LAUNCH_CHECK();
+            return FASTAR_OK;
+        }
         // Two query blocks per workgroup in anti-phase (matrix | vector) on each SIMD; one workgroup fills a CU, so the
         // work comes in rounds of 512 query blocks: when the last round would be less than half full, the kernel with
         // one block per workgroup (two workgroups per CU, started as slots free up) finishes earlier.

@@ -19,6 +19,8 @@
 // (the factor 2^6 cancels in O / l and is taken out of lse).
 #include <type_traits>
 
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace fastar {
@@ -638,7 +640,8 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
     if (const int rc = attn_fp8_setup(); rc != FASTAR_OK) return rc;
     const int n_qb = (n_q + 127) / 128;
     const int n_blk = (C + f8::TK - 1) / f8::TK;
-    const float scale_log2 = scale * 1.4426950408889634f;
+    // |q.k| <= 128 * 448^2 < 2^25: below that least scale a score counts for nothing beside the bias either way
+    const float scale_log2 = std::max(scale * 1.4426950408889634f, ATTN_LEAST_SCALE_LOG2);
     // with a workspace, a launch that would end in a short last round of workgroups is split (one entry = one tile)
     const int full_per = ws ? f8::split_full_per(n_qb * H, n_sel) : 0;
     if (full_per > 0) {

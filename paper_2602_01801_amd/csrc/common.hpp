@@ -168,6 +168,9 @@ struct TailMap {
     // position in the left-over sequence -> (head, block) pair; pairs >= total do not exist (the last range may be short)
     __host__ __device__ __forceinline__ int item(int vi) const { return (vi / tail_per()) * per + full_per + vi % tail_per(); }
 };
+// Least scale * log2(e) of the kernels that divide by it: 31 / scale (the largest multiplicity's bias) plus a score stays
+// far from the largest float.  Subnormal scales gave 0 * infinity.
+constexpr float ATTN_LEAST_SCALE_LOG2 = 0x1p-100f;
 constexpr int ATTN_SHARE_WORKGROUPS = 512;                      // resident workgroups that take the shares: two per CU
 constexpr int ATTN_PART_O_FLOATS = (128 / 32) * 16 * 64;        // O^T accumulators of one wavefront (d = 128)
 constexpr int ATTN_PART_FLOATS = 4 * (ATTN_PART_O_FLOATS + 2 * 64);   // one fragment of a query block: four wavefronts' accumulators, reference maxima, row sums

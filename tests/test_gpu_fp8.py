@@ -288,6 +288,17 @@ def test_fp8_attention_with_a_workspace_splits_the_launch_and_matches_the_plain_
         assert np.array_equal(ok, np.isfinite(lw[h, q0:q1])) and np.abs(lw[h, q0:q1][ok] - lse_r[0][ok]).max(initial=0.0) <= 0.05
 
 
+@pytest.mark.parametrize("scale", [1e-45, 1e-39, 1e-38, 5.4e-31, 5.6e-31])
+def test_fp8_attention_with_scales_down_to_the_smallest(scale):
+    rng = np.random.default_rng(21)
+    c = rand_cache(rng, 2, 64 * 20 + 9, 128, [64 * 20 + 9, 700], "bf16")
+    Q = to_storage(rng.standard_normal((2, 200, 128)).astype(np.float32), "bf16")
+    sel = np.tile(np.arange(0, 20, 2, dtype=np.int32), (2, 2, 1))
+    nsel = np.full((2, 2), 10, np.int32)
+    for use_cnt in (True, False):
+        check_fp8_attention(Q, c, sel, nsel, scale, use_cnt)
+
+
 def test_fp8_attention_with_steadily_climbing_logits_and_a_dominant_key():
     # the reference maximum is updated lazily: scores that climb along the key list, and one key that dominates a row
     rng = np.random.default_rng(9)

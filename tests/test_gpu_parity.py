@@ -692,6 +692,20 @@ def test_fp32_attention_over_whole_and_masked_tiles_in_any_order(d, n_q, BQ, BK,
     check_attention(Q, K, V, None, lens, sel, nsel, BQ, BK, d ** -0.5, "fp32")
 
 
+@pytest.mark.parametrize("d,BQ,BK,n_q", [(64, 64, 64, 100), (64, 128, 16, 200), (128, 64, 64, 100), (128, 128, 64, 200), (128, 128, 1, 200)])
+@pytest.mark.parametrize("scale", [1e-45, 1e-39, 1e-38, 5.4e-31, 5.6e-31])   # subnormal, and both sides of the least scale that is divided by
+def test_attention_with_scales_down_to_the_smallest(d, BQ, BK, n_q, scale):
+    rng = np.random.default_rng(d + BQ + BK)
+    C, n_sel = 40 * BK + 5, 12
+    n_qb = -(-n_q // BQ)
+    Q, K, V = (to_storage(rng.standard_normal((2, n, d)).astype(np.float32), "bf16") for n in (n_q, C, C))
+    cnt = rng.integers(1, 6, size=(2, C)).astype(np.int32)
+    sel = np.sort(rng.permuted(np.tile(np.arange(41, dtype=np.int32), (2, n_qb, 1)), axis=-1)[..., :n_sel], axis=-1)
+    nsel = np.full((2, n_qb), n_sel, np.int32)
+    for c in (cnt, None):
+        check_attention(Q, K, V, c, np.array([C, C - BK], np.int32), sel, nsel, BQ, BK, scale, "bf16")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("at", [1, 40, 130])       # the light key: in the heavy one's tile, in another wavefront's, in a later tile of its own
 @pytest.mark.parametrize("heavy_first", [True, False])
