@@ -450,30 +450,23 @@ def cpu_baseline(cfg, pipe, oracle_cache, oracle_prev, oracle_fid, host_chunks, 
 
 
 def attn_kernel_name(n_items, H, C, n_tiles, ws, fp8=False, d=128):
-    """Which kernel the self-attention call launches (bf16 or the 8-bit copy, d = 128, BQ = 128, BK = 64) for this many
-    (head, query block) pairs, cache capacity (bf16: K and V of all heads within 256 MB: bias rows written in the matrix
-    phase) and 64-key tiles per query block; ws: the call carries a workspace."""
-    per_xcd = (n_items + 7) // 8
-    tail = per_xcd % 64
-    if ws and not fp8 and per_xcd > 64 and 0 < tail <= 24 and n_tiles * (1.2 - 0.0375 * tail) > 30.0:   # a short last round is shared out
-        return "attn_bf16_d128_sk_kernel + attn_combine_kernel"
+    """Which kernel the self-attention call launches (bf16 or the 8-bit copy, BQ = 128, BK = 64) for this many (head, query
+    block) pairs, cache capacity (bf16: K and V of all heads within 256 MB: bias rows written in the matrix phase) and
+    64-key tiles per query block; ws: the call carries a workspace."""
     if fp8:
-        tail96 = per_xcd % 96
+        per_xcd = (n_items + 7) // 8
+        tail, tail96 = per_xcd % 64, per_xcd % 96
         if ws and ((per_xcd > 96 and tail96 > 0 and (tail96 <= 24 and n_tiles >= 120 or tail96 <= 40 and n_tiles >= 150)) or
                    (per_xcd > 64 and 5 <= tail <= 24 and n_tiles >= 150)):
             return "attn_fp8_d128_sk_kernel + attn_combine_kernel"
         return "attn_fp8_d128_parts_kernel + attn_combine_parts_kernel, or attn_fp8_d128_kernel" if ws and n_items <= 256 else "attn_fp8_d128_kernel"
-    if n_items <= 128 and n_tiles >= 2:   # groups of 32 queries whose wavefronts share the tiles
-        if n_tiles <= 8 or 12 <= n_items and n_tiles <= (20 if n_items > 64 else 24):
-            return "attn_bf16_waves_kernel<128, %d, true>" % (8 if n_items <= 64 and n_tiles >= 24 else 4)
+    import paper_2602_01801_amd as fa
+    kernel, n = fa.attn_route(n_items, d, 128, 64, n_tiles, ws)
     pp = "attn_bf16_d128_pp_kernel<4, true, %s, " % ("true" if H * C * d * 2 * 2 <= (256 << 20) else "false")
-    if n_items <= 256 and n_tiles > 5:   # one block per workgroup, split over its two groups
-        return pp + "true>" + (" (+ attn_combine_parts_kernel where that pays)" if ws and n_items <= 128 and n_tiles > 8 else "")
-    if n_items <= 512 and n_tiles <= 5 and (n_items <= 256 or n_tiles <= 2):
-        return "attn_bf16_d128_kernel<4>"
-    if n_items <= 512 or n_items % 512 == 0 or n_items % 512 >= 256:
-        return pp + "false>"
-    return "attn_bf16_d128_kernel<4>"
+    return {"plain": "attn_bf16_kernel<%d, 4>" % d, "waves": "attn_bf16_waves_kernel<%d, %d, true>" % (d, n),
+            "one": "attn_bf16_d128_kernel<4>", "one_shared": "attn_bf16_d128_sk_kernel + attn_combine_kernel",
+            "pair": pp + "false>",
+            "pair_split": pp + "true>" + (" (+ attn_combine_parts_kernel, %d workgroups per block)" % n if n > 1 else "")}[kernel]
 
 
 TRAFFIC_FILES = {"cfg2": "cfg2_chunk_step_hbm_traffic.txt", "cfg5full": "cfg5full_chunk_step_hbm_traffic.txt",

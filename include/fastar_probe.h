@@ -1,5 +1,5 @@
 /*
- * Measurement probes and one test hook of libfastar: NOT part of the method and not needed by any caller of fastar.h.
+ * Measurement probes and test hooks of libfastar: NOT part of the method and not needed by any caller of fastar.h.
  * The benchmark uses them to report what this chip reaches on the two rooflines the kernels are priced
  * against, measured in the same process as the kernels.
  */
@@ -25,6 +25,19 @@ extern "C" {
  */
 int fastar_probe_mfma_bf16(int iters, int random_operands, float *sink, double *flops_out, void *stream);
 int fastar_probe_copy(const void *src, void *dst, size_t bytes, void *stream);
+
+/*
+ * Which kernel a bf16 call of sparse_attn_fwd (with_workspace: sparse_attn_fwd_ws) takes for n_items (head, query block)
+ * pairs, from the rule that the call itself follows; for benchmarks and tests that name a kernel.  Launches nothing and
+ * needs no GPU.  Returns, or a negative error code:
+ *   0  one query block per workgroup, 64-wide heads (and scales below 2^-100 of either width)
+ *   1  groups of 32 queries, *n wavefronts each
+ *   2  one query block per workgroup, 128-wide heads
+ *   3  the same, blocks of a short last round cut into shares; *n blocks of every XCD are not
+ *   4  two query blocks per workgroup
+ *   5  one query block for a whole workgroup of that kernel, or for *n workgroups and a second launch (*n > 1)
+ */
+int fastar_probe_attn_route(int n_items, int d, int BQ, int BK, int n_sel, int with_workspace, int *n);
 
 /*
  * Test hook for the one place where workgroups of a launch wait for each other: the eviction plan of

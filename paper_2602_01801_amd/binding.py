@@ -124,6 +124,8 @@ def lib() -> ctypes.CDLL:
         L.fastar_probe_mfma_bf16.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.POINTER(ctypes.c_double), ctypes.c_void_p]
         L.fastar_probe_copy.restype = ctypes.c_int
         L.fastar_probe_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
+        L.fastar_probe_attn_route.restype = ctypes.c_int
+        L.fastar_probe_attn_route.argtypes = [ctypes.c_int] * 6 + [ctypes.POINTER(ctypes.c_int)]
         L.fastar_debug_plan_wait.restype = ctypes.c_int
         L.fastar_debug_plan_wait.argtypes = [ctypes.c_int, ctypes.c_int]
         _lib = L
@@ -134,7 +136,7 @@ EXPORTS = ("fastar_init", "fastar_version", "fastar_strerror", "fastar_workspace
            "ann_cross_attn_fwd",
            "ann_select_self", "ann_select_self_forced", "ann_select_self_static", "ann_prompt_buckets", "ann_select_buckets", "fastar_encode_packed", "ann_select_self_packed", "ann_select_cross", "sparse_attn_fwd", "sparse_attn_fwd_ws", "fastar_kv_to_fp8",
            "sparse_attn_fwd_fp8", "sparse_attn_fwd_fp8_ws", "fastar_encode_sign", "ann_select_lsh", "ann_select_lsh_buckets",
-           "fastar_probe_mfma_bf16", "fastar_probe_copy", "fastar_debug_plan_wait")
+           "fastar_probe_mfma_bf16", "fastar_probe_copy", "fastar_probe_attn_route", "fastar_debug_plan_wait")
 
 
 def init() -> None:
@@ -596,6 +598,19 @@ def probe_mfma_bf16(iters: int = 20000, random_operands: bool = False) -> float:
 def debug_plan_wait(spin_limit: int = -1, extra_arrivals: int = 0) -> None:
     """Test hook (fastar_debug_plan_wait): bound the eviction plan's waits and add arrivals that never come."""
     _check(lib().fastar_debug_plan_wait(spin_limit, extra_arrivals), "fastar_debug_plan_wait")
+
+
+ATTN_KERNELS = ("plain", "waves", "one", "one_shared", "pair", "pair_split")   # as fastar_probe_attn_route numbers them
+
+
+def attn_route(n_items: int, d: int, BQ: int, BK: int, n_sel: int, ws: bool) -> tuple[str, int]:
+    """Which kernel a bf16 sparse_attn_fwd call takes for n_items (head, query block) pairs, and its number of wavefronts per
+    group, whole blocks per XCD or workgroups per block (fastar_probe.h).  Needs no GPU."""
+    n = ctypes.c_int()
+    rc = lib().fastar_probe_attn_route(n_items, d, BQ, BK, n_sel, int(ws), ctypes.byref(n))
+    if rc < 0:
+        _check(rc, "fastar_probe_attn_route")
+    return ATTN_KERNELS[rc], n.value
 
 
 def probe_copy(mib: int = 1024, reps: int = 5) -> float:

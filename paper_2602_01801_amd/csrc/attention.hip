@@ -345,6 +345,46 @@ static int waves_per_group(int d, int BQ, int BK, int n_items, int n_sel, bool w
     return groups <= 256 && tiles >= 48 ? 8 : 4;
 }
 
+// Which kernel a bf16 call of n_items (head, query block) pairs takes.  `n`: wavefronts per group of queries (ATTN_WAVES), pairs
+// per XCD that are taken whole (ATTN_ONE_SHARED), runs of tiles per query block (ATTN_PAIR_SPLIT).
+struct AttnRoute {
+    int kernel, n;
+};
+static AttnRoute attn_route(int d, int BQ, int BK, int n_items, int n_sel, float scale_log2, bool ws) {
+    // The other kernels start a tile's sums from log2(cnt) / scale, and let a reference maximum lag by octaves / scale; this
+    // one adds the bias behind the scaling, so that no scale is too small for it.
+    if (scale_log2 < ATTN_LEAST_SCALE_LOG2) return {ATTN_PLAIN, 0};
+    // With a workspace, and more query blocks than the chip holds at once in a number that leaves a short last
+    // round (an XCD holds 64 workgroups of the one-block kernel; a round that only a few of them take part in lasts
+    // half as long as a full one, with most of the chip idle): the one-block kernel on whole rounds, then the query
+    // blocks left over cut into equal shares of their tiles for all resident workgroups (long enough shares to pay for
+    // the fragments and their combination).
+    const int n_tiles = (int)(((long long)n_sel * BK + 63) / 64);
+    const int full_per = attn_split_full_per(n_items, n_tiles);
+    if (ws && d == 128 && BQ == 128 && full_per > 0) return {ATTN_ONE_SHARED, full_per};
+    if (const int S = waves_per_group(d, BQ, BK, n_items, n_sel, ws)) return {ATTN_WAVES, S};
+    // At most one query block per compute unit: both groups of the two-block kernel on one block (156 blocks of 48 tiles
+    // 85 -> 51 us, one-block workgroups take 67), with a workspace several workgroups per block where that pays
+    // (8 blocks of 96 tiles 161 -> 21 us).  Very short lists stay with the one-block kernel (3 tiles: 8.5 us against 9.5,
+    // 6 tiles 12.2 against 12.1), also beyond 256 blocks (444 blocks of 64 single keys 9.9 us against 11.2).
+    if (d == 128 && BQ == 128 && n_items <= 256 && n_tiles > 5)
+        return {ATTN_PAIR_SPLIT, ws ? attn_parts(n_items, n_tiles, 2, 1.65f, 0.0f) : 1};
+    if (d == 128 && BQ == 128 && n_items <= 512 && n_tiles <= 5 && (n_items <= 256 || n_tiles <= 2)) return {ATTN_ONE, 0};
+    // Two query blocks per workgroup in anti-phase (matrix | vector) on each SIMD; one workgroup fills a CU, so the
+    // work comes in rounds of 512 query blocks: when the last round would be less than half full, the kernel with
+    // one block per workgroup (two workgroups per CU, started as slots free up) finishes earlier.
+    if (d == 128 && BQ == 128 && (n_items <= 512 || n_items % 512 == 0 || n_items % 512 >= 256)) return {ATTN_PAIR, 0};
+    return {d == 128 ? ATTN_ONE : ATTN_PLAIN, 0};
+}
+
+extern "C" int fastar_probe_attn_route(int n_items, int d, int BQ, int BK, int n_sel, int with_workspace, int *n) {
+    if (n_items <= 0 || n_sel <= 0 || !n) return FASTAR_ERR_INVALID_ARG;
+    if ((d != 64 && d != 128) || (BQ != 64 && BQ != 128) || BK <= 0 || BK > 64 || (BK & (BK - 1))) return FASTAR_ERR_UNSUPPORTED;
+    const AttnRoute r = attn_route(d, BQ, BK, n_items, n_sel, 1.0f, with_workspace != 0);
+    *n = r.n;
+    return r.kernel;
+}
+
 static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V, const int32_t *cnt,
                             const int32_t *len, int H, int C, int d, int dtype, const int32_t *sel,
                             const int32_t *nsel, int BQ, int BK, int n_sel, float scale, void *O, float *lse,
@@ -393,47 +433,26 @@ static int sparse_attn_impl(const void *Q, int n_q, const void *K, const void *V
     hipLaunchKernelGGL((attn_bf16_kernel<DD, NW>), grid, dim3(NW * 64), 0, s, (const unsigned short *)Q,                 \
                        (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, nsel, n_q, C, bk_shift, \
                        n_sel, n_qb, H, scale_log2, (unsigned short *)O, lse)
-        // The kernels below start a tile's sums from log2(cnt) / scale, and let a reference maximum lag by octaves / scale; this
-        // one adds the bias behind the scaling, so that no scale is too small for it.
-        if (scale_log2 < ATTN_LEAST_SCALE_LOG2) {
-            if (d == 128 && BQ == 128) FASTAR_ATTN(128, 4);
-            else if (d == 128) FASTAR_ATTN(128, 2);
-            else if (BQ == 128) FASTAR_ATTN(64, 4);
-            else FASTAR_ATTN(64, 2);
-            FASTAR_LAUNCH_CHECK();
-            return FASTAR_OK;
+        const AttnRoute route = attn_route(d, BQ, BK, n_qb * H, n_sel, scale_log2, ws != nullptr);
+        switch (route.kernel) {
+            case ATTN_ONE_SHARED:
+                return launch_attn_bf16_d128_sk(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, ws,
+                                                route.n, s);
+            case ATTN_WAVES:
+                return launch_attn_bf16_waves(Q, n_q, K, V, cnt, len, H, C, d, sel, nsel, BQ, bk_shift, n_sel, scale_log2, route.n,
+                                              O, lse, s);
+            case ATTN_PAIR_SPLIT:
+                return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse,
+                                                route.n, ws, s);
+            case ATTN_PAIR:
+                return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, 0,
+                                                nullptr, s);
+            case ATTN_ONE:   // direct-to-LDS tiles, LDS transpose loads
+                return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
         }
-        // Two query blocks per workgroup in anti-phase (matrix | vector) on each SIMD; one workgroup fills a CU, so the
-        // work comes in rounds of 512 query blocks: when the last round would be less than half full, the kernel with
-        // one block per workgroup (two workgroups per CU, started as slots free up) finishes earlier.
-        const int n_items = n_qb * H;
-        // With a workspace, and more query blocks than the chip holds at once in a number that leaves a short last
-        // round (an XCD holds 64 workgroups of the one-block kernel; a round that only a few of them take part in lasts
-        // half as long as a full one, with most of the chip idle): the one-block kernel on whole rounds, then the query
-        // blocks left over cut into equal shares of their tiles for all resident workgroups (long enough shares to pay for
-        // the fragments and their combination).
-        const int n_tiles = (int)(((long long)n_sel * BK + 63) / 64);
-        const int full_per = attn_split_full_per(n_items, n_tiles);
-        if (ws && d == 128 && BQ == 128 && full_per > 0)
-            return launch_attn_bf16_d128_sk(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, ws,
-                                            full_per, s);
-        if (const int S = waves_per_group(d, BQ, BK, n_items, n_sel, ws != nullptr))
-            return launch_attn_bf16_waves(Q, n_q, K, V, cnt, len, H, C, d, sel, nsel, BQ, bk_shift, n_sel, scale_log2, S, O, lse, s);
-        // At most one query block per compute unit: both groups of the two-block kernel on one block (156 blocks of 48 tiles
-        // 85 -> 51 us, one-block workgroups take 67), with a workspace several workgroups per block where that pays
-        // (8 blocks of 96 tiles 161 -> 21 us).  Very short lists stay with the one-block kernel (3 tiles: 8.5 us against 9.5,
-        // 6 tiles 12.2 against 12.1), also beyond 256 blocks (444 blocks of 64 single keys 9.9 us against 11.2).
-        if (d == 128 && BQ == 128 && n_items <= 256 && n_tiles > 5)
-            return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse,
-                                            ws ? attn_parts(n_items, n_tiles, 2, 1.65f, 0.0f) : 1, ws, s);
-        if (d == 128 && BQ == 128 && n_items <= 512 && n_tiles <= 5 && (n_items <= 256 || n_tiles <= 2))
-            return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
-        if (d == 128 && BQ == 128 && (n_items <= 512 || n_items % 512 == 0 || n_items % 512 >= 256))
-            return launch_attn_bf16_d128_pp(Q, n_q, K, V, cnt, len, H, C, sel, nsel, bk_shift, n_sel, scale_log2, O, lse, 0,
-                                            nullptr, s);
-        if (d == 128)  // tuned path: direct-to-LDS tiles, LDS transpose loads
-            return launch_attn_bf16_d128(Q, n_q, K, V, cnt, len, H, C, sel, nsel, BQ, bk_shift, n_sel, scale_log2, O, lse, s);
-        if (BQ == 128) FASTAR_ATTN(64, 4);
+        if (d == 128 && BQ == 128) FASTAR_ATTN(128, 4);
+        else if (d == 128) FASTAR_ATTN(128, 2);
+        else if (BQ == 128) FASTAR_ATTN(64, 4);
         else FASTAR_ATTN(64, 2);
 #undef FASTAR_ATTN
     } else {

@@ -203,6 +203,15 @@ inline int attn_parts(int n_items, int n_tiles, int tiles_per_step, float one_us
     }
     return best;
 }
+// Kernels of bf16 attention (fastar_probe_attn_route returns these numbers).
+enum AttnKernel {
+    ATTN_PLAIN,        // attention.hip: a block per workgroup, tiles staged by way of registers
+    ATTN_WAVES,        // attention_waves.hip: groups of 32 queries whose wavefronts share the tiles
+    ATTN_ONE,          // attention_d128.hip: a block per workgroup
+    ATTN_ONE_SHARED,   // ... the last round's blocks cut into equal shares
+    ATTN_PAIR,         // attention_d128_pp.hip: two blocks per workgroup
+    ATTN_PAIR_SPLIT,   // ... one block for both halves of a workgroup, or for several workgroups
+};
 int launch_attn_combine_parts(const void *ws, int n_parts, int n_q, int n_qb, int H, float scale_log2, float lse_offset, void *O,
                               float *lse, hipStream_t s);
 int launch_attn_combine(const void *ws, int n_q, int n_qb, TailMap tm, int NT, float scale_log2, float lse_offset, void *O,
