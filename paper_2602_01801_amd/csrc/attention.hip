@@ -12,6 +12,8 @@
 // slots beyond len) get a -inf bias and zeroed K/V rows.
 //
 // Few query blocks: attention_waves.hip; fp32: attention_f32.hip.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace fastar {
@@ -313,35 +315,47 @@ int launch_attn_bf16_d128_sk(const void *Q, int n_q, const void *K, const void *
 using namespace fastar;
 
 // Whether a launch of n_items query blocks takes the kernel whose wavefronts share a group of 32 queries, and then their number
-// per group (0: the other kernels).  us of the other kernels / of this one with 2 / 4 / 8 wavefronts, by groups x tiles of 32 keys:
-//   d = 64     256 x 16 13.2 / 10.1 / 7.8 / 7.9, x 32 21.2 / 16.6 / 11.2 / 10.3, x 128 68 / 52 / 30 / 24; 512 x 32 21.7 / 20.2 / 14.7 /
-//              15.3, x 128 68 / 63 / 40 / 39; 800 x 16 14.3 / 13.6 / 14.3 / 18.3, x 128 69 / 67 / 64 / 66; 1280 x 8 12.9 / 11.2 / 13.6 / 18.3,
-//              x 128 121 / 89 / 85 / 86; 2048 x 32 35.9 / 37.7 / 39.9 / 47.1 (with blocks of 64 queries 44 / 38 / 40)
-//   d = 128    64 x 16 14.1 / 12.3 / 8.9 / 10.1, x 48 17.7 / 28 / 17.5 / 17.3, x 64 19.4 / 36 / 21.6 / 20.5; 256 x 32 22 / 21 / 14.6 / 15.2,
-//              x 48 23.1 / 29 / 18.7 / 18.8; 512 x 32 23 / 27 / 21.8 / 27.3, x 64 33.8 / 48 / 35.7 / 41.4; 640 x 16 17 / 18.7 / 20.4 / 28.6
-//              (d = 128 with a workspace, that is with several workgroups per query block where that pays: x 24 with 40 groups 12.0,
-//              and 10.7 here)
-// A call without a workspace takes this kernel also where one with a workspace leaves fragments; where that one leaves none,
-// the two are the same.
+// per group (0: the other kernels).  Time of this kernel over that of the others by query blocks and list entries of 64 keys, the
+// two in turn, lists a tenth of the cache (differences of 0.02 are noise); us where they say more.
+//   d = 64, BQ = 64     4 to 256 blocks 0.95 (1 entry) to 0.2 (128); 700 x 2 1.02, x 3 0.97, x 16 0.73; 1024 x 3 1.01, x 64 0.77; 1100 x 3 1.03,
+//                       x 5 0.97; 1300 x 4 1.03, x 5 1.00, x 8 0.95; 1500 x 6 1.02, x 8 1.00, x 16 0.97 (the others' one round is full);
+//                       1540 to 2040 x 3 0.89 to 0.93, x 64 0.67 to 0.75; 2060 to 4000 x 3 0.95 to 0.99, x 4 0.93 to 0.98, x 64 0.78 to 0.92,
+//                       x 128 0.88 to 1.02; 6000 x 4 0.99, x 64 0.98, x 128 1.09
+//   d = 64, BQ = 128    4 to 128 blocks 0.98 (1) to 0.2; 160 x 1 1.07, x 2 0.99; 240 x 2 1.05, x 3 1.00, x 64 0.67; 320 x 3 0.95; 328 to 448 x 8
+//                       0.97 to 1.01, x 16 0.86 to 0.97, x 128 0.75 to 0.87; 512 x 16 1.00, x 32 0.96; 640 to 760 x 16 1.02 to 1.16
+//   d = 128, BQ = 64    4 to 128 blocks 0.89 (2) to 0.4; 160 to 256 x 2 1.16, x 4 1.06, x 6 0.98 to 1.01, x 8 0.90 to 0.94, x 128 0.74; 288 to 384
+//                       x 2 1.00, x 3 0.97, x 32 0.81, x 128 0.84 to 0.89, x 300 1.00; 448 x 2 1.12, x 8 1.01, x 32 0.97, x 200 1.18
+//   d = 128, BQ = 128   2 to 64 blocks 0.82 (2) to 0.5 (1000); 68 to 128 x 2 1.09, x 4 1.00 to 1.03, x 6 0.95, x 20 0.97 to 0.99, x 32 0.99 to
+//                       1.00; 96 x 400 358 -> 384 us, 128 x 1000 868 -> 1005 (every group fetches its rows for itself, here from HBM)
+//     with a workspace, where the others leave fragments, the last entry count that is no slower: 12 blocks 22, 16 24, 20 28, 28 32,
+//     40 32, 48 36, 64 40; 72 x 20 25.1 against 26.5 us, x 24 28.7 against 24.8.  Below 12 blocks the change comes between 16 and 20
+//     (4 x 16 12.8 against 13.6, x 20 14.9 against 14.4); their lists of 9 entries and more keep the fragments they had.
+// Where a call with a workspace leaves no fragments, one without takes the same kernel.
 static int waves_per_group(int d, int BQ, int BK, int n_items, int n_sel, bool ws) {
     const long long groups = (long long)n_items * (BQ / 32), tiles = ((long long)n_sel * BK + 31) / 32;
     if (d == 64) {
-        if (groups > (BQ == 64 ? 4096 : 1280) || (groups > 640 && tiles <= 4)) return 0;
+        if (BQ == 64) {
+            const int least = groups <= 640 ? 1 : groups <= 2048 ? 5 : groups <= 2600 ? 10 : groups <= 3072 ? 16 : groups <= 4096 ? 5 : 8;
+            if (groups > 8192 || tiles < least || (groups > 4096 && tiles > 128)) return 0;
+        } else {
+            const int least = groups <= 512 ? 1 : groups <= 640 ? 3 : groups <= 1280 ? 5 : 32;
+            if (groups > 1792 || tiles < least) return 0;
+            if (groups > 1280) return 4;
+        }
         if (tiles <= 2) return 2;
         if (groups > 512) return tiles >= 64 ? 4 : 2;
         return tiles >= (groups <= 256 ? 24 : 64) ? 8 : 4;
     }
     if (BK != 64 || tiles < 4) return 0;   // rows by way of a table, and single tiles: no gain
     if (BQ == 64) {
-        if (groups > 1024) return 0;
-        return groups > 512 ? 2 : groups <= 256 && tiles >= 48 ? 8 : 4;
+        if (groups > 512) return groups <= 768 && tiles >= 6 ? 2 : 0;
+        if (groups > 256) return tiles >= 16 ? 4 : 0;
+        return tiles >= 48 ? 8 : 4;
     }
     if (groups > 512) return 0;
-    const int most = n_items > 64 ? 40 : 48;
-    if (tiles > 16 && (n_items < 12 || tiles > most)) {
-        const bool fragments = attn_parts(n_items, (int)((tiles + 1) / 2), 2, 1.65f, 0.0f) > 1;
-        if (fragments ? ws : tiles > most) return 0;
-    }
+    const bool many = n_items > 64, fragments = ws && attn_parts(n_items, (int)((tiles + 1) / 2), 2, 1.65f, 0.0f) > 1;
+    if (many && (tiles < 12 || tiles > (fragments ? 40 : 64))) return 0;
+    if (!many && fragments && tiles > (n_items < 12 ? 16 : std::min(64, 28 + n_items))) return 0;
     return groups <= 256 && tiles >= 48 ? 8 : 4;
 }
 
