@@ -142,10 +142,11 @@ __device__ __forceinline__ int max_over_reps_i32(int x, int n_rep) {
 // ---- AnnSA scoring -----------------------------------------------------------------------------------
 // out[h][b][kb] = max over the summaries u of block b (whose run holds a query) and the live keys k of
 // key block kb of rep[b,u] . kcode[k].   D = A x B with A rows = 32 keys, B columns = 32 summaries.
-// COL_CHUNK: summary column blocks (of 32) per pass; their operands are registers, so it is no more than the call needs: what
-// bounds the launch is the codes' latency, and it wants wavefronts in flight (eight at every size held it to 94 registers and 1280
-// workgroups: call for 20 heads x 2000 queries x 100000 slots 28.8 us, with two 23.9; 12 x 1560 x 32760 12.6 -> 11.4; five for
-// 12 x 4680 x 37440 16.8 -> 16.1).
+// COL_CHUNK: summary column blocks (of 32) per pass; their operands are registers, so it is what the call's equal passes need,
+// from two to eight: what bounds the launch is the codes' latency, and it wants wavefronts in flight.  Calls in us, eight at every
+// size / as many as the call has: one block of columns, 12 heads x 37440 slots 12.7 / 11.6; three 14.3 / 13.1, 20 x 100000 34.3 / 30.3,
+// 64-entry codes 47.8 / 38.8; five 16.6 / 16.0; six 17.7 / 17.5, 40 x 57600 with 64-entry codes 70.3 / 59.3; seven 18.8 / 18.6, 40 x 115200
+// with 64-entry codes 158 / 141; twice seven, 12 x 60000 with 64-entry codes 52.3 / 45.9.
 template <int R, int BITS, int COL_CHUNK>
 __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restrict__ kcode, const int32_t *__restrict__ len,
                                                          const int8_t *__restrict__ rep, int C, int n_q, int BQ,
@@ -1185,8 +1186,11 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
             }
         }
         auto kernel = per_pass <= 2   ? score_self_kernel<RR, BB, 2>
-                      : per_pass <= 4 ? score_self_kernel<RR, BB, 4>
+                      : per_pass == 3 ? score_self_kernel<RR, BB, 3>
+                      : per_pass == 4 ? score_self_kernel<RR, BB, 4>
                       : per_pass == 5 ? score_self_kernel<RR, BB, 5>
+                      : per_pass == 6 ? score_self_kernel<RR, BB, 6>
+                      : per_pass == 7 ? score_self_kernel<RR, BB, 7>
                                       : score_self_kernel<RR, BB, 8>;
         hipLaunchKernelGGL(kernel, grid, dim3(256), tile_bytes, s, kcode, len, rep, C, n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score);
     };

@@ -291,10 +291,12 @@ def test_selection_on_seeded_random_shapes(seed):
         assert np.array_equal(to_host(sel), ref_sel), what
 
 
-# summaries in one to nine column blocks of 32 (passes of 2, 4, 5 and 8, the last one short), and both sides of the streaming
+# summaries in one to fourteen column blocks of 32 (passes of two to eight, the last one short), and both sides of the streaming
 # kernel's line for three and four of them (20000 and 65536 key blocks over the heads)
 @pytest.mark.parametrize("H,n_q,C,r,BK", [
     (2, 400, 12000, 32, 64), (2, 1100, 12000, 32, 64), (2, 2100, 12000, 64, 64), (2, 4200, 12000, 32, 64), (2, 5000, 11000, 64, 64),
+    (2, 2100, 12000, 32, 64), (2, 3400, 12000, 32, 64), (2, 6100, 12000, 32, 64), (2, 7100, 11000, 64, 64), (1, 8100, 11000, 32, 64),
+    (1, 11200, 11000, 64, 64), (1, 13400, 11000, 32, 64),
     (2, 9100, 11000, 32, 96), (1, 3500, 639968, 32, 32), (1, 3500, 640001, 32, 32), (1, 2500, 2097120, 32, 32), (1, 2500, 2097121, 32, 32),
     (1, 2000, 2097152, 32, 32), (1, 3500, 640001, 64, 32)])
 def test_ann_select_self_with_summaries_of_every_number_of_columns(H, n_q, C, r, BK):
