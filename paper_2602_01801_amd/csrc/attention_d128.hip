@@ -628,8 +628,9 @@ __global__ __launch_bounds__(256) void attn_combine_parts_kernel(const float *__
 int launch_attn_combine(const void *ws, int n_q, int n_qb, TailMap tm, int NT, float scale_log2, float lse_offset, void *O,
                         float *lse, hipStream_t s) {
     using namespace d128;
-    hipLaunchKernelGGL(attn_combine_kernel, dim3(SK_WORKGROUPS, D / 32), dim3(256), 4 * 32 * (32 + 8) * 2, s, (const float *)ws,
-                       SK_WORKGROUPS, n_q, n_qb, tm, NT, scale_log2, lse_offset, (unsigned short *)O, lse);
+    const int P = tm.shares(NT);
+    hipLaunchKernelGGL(attn_combine_kernel, dim3(P, D / 32), dim3(256), 4 * 32 * (32 + 8) * 2, s, (const float *)ws,
+                       P, n_q, n_qb, tm, NT, scale_log2, lse_offset, (unsigned short *)O, lse);
     if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;
     return FASTAR_OK;
 }
@@ -695,7 +696,7 @@ int launch_attn_bf16_d128_sk(const void *Q, int n_q, const void *K, const void *
     const TailMap tm = {(n_qb * H + 7) / 8, full_per, n_qb * H};
     if (full_per < 0 || full_per >= tm.per) return FASTAR_ERR_INVALID_ARG;
     const int n_plain = 8 * full_per;
-    hipLaunchKernelGGL(attn_bf16_d128_sk_kernel, dim3(n_plain + SK_WORKGROUPS), dim3(256), LDS_BYTES, s, (const unsigned short *)Q,
+    hipLaunchKernelGGL(attn_bf16_d128_sk_kernel, dim3(n_plain + tm.shares(NT)), dim3(256), LDS_BYTES, s, (const unsigned short *)Q,
                        (const unsigned short *)K, (const unsigned short *)V, cnt, len, sel, nsel, n_q, C, bk_shift, n_sel,
                        n_qb, tm, n_plain, NT, scale_log2, 1.0f / scale_log2, (unsigned short *)O, lse, (float *)ws);
     if (hipGetLastError() != hipSuccess) return FASTAR_ERR_HIP;

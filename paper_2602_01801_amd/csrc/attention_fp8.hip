@@ -647,7 +647,7 @@ static int sparse_attn_fp8_impl(const void *Q, int n_q, const uint8_t *K8, const
     if (full_per > 0) {
         const TailMap tm = {(n_qb * H + 7) / 8, full_per, n_qb * H};
         const int n_plain = 8 * full_per;
-        hipLaunchKernelGGL(f8::attn_fp8_d128_sk_kernel, dim3(n_plain + ATTN_SHARE_WORKGROUPS), dim3(256), f8::LDS_BYTES,
+        hipLaunchKernelGGL(f8::attn_fp8_d128_sk_kernel, dim3(n_plain + tm.shares(n_sel)), dim3(256), f8::LDS_BYTES,
                            (hipStream_t)stream, (const unsigned short *)Q, K8, V8T, cnt, len, sel, nsel, n_q, C, n_blk,
                            n_sel, n_qb, tm, n_plain, n_sel, scale_log2, 1.0f / scale_log2, (unsigned short *)O, lse,
                            (float *)ws);

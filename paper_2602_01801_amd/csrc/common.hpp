@@ -161,17 +161,19 @@ struct DeviceOnce {
 // ---- split attention launches (sparse_attn_fwd_ws, sparse_attn_fwd_fp8_ws) ---------------------------------------
 // The (head, query block) pairs are dealt to the 8 XCDs in contiguous ranges of `per`; the first `full_per` pairs of every
 // range are taken by one workgroup each, the others are cut into equal shares of their tiles (attention_d128.hip).
+constexpr int ATTN_SHARE_WORKGROUPS = 512;   // the most workgroups that take the shares: as many as are resident, two per CU
 struct TailMap {
     int per, full_per, total;   // pairs per XCD range, of them taken whole, pairs in all
     __host__ __device__ __forceinline__ int tail_per() const { return per - full_per; }
     __host__ __device__ __forceinline__ long long tiles(int NT) const { return (long long)8 * tail_per() * NT; }
+    // workgroups that share them: a tile each at least, as a share without one leaves no fragment (a multiple of 8 either way)
+    int shares(int NT) const { return (int)(tiles(NT) < ATTN_SHARE_WORKGROUPS ? tiles(NT) : ATTN_SHARE_WORKGROUPS); }
     // position in the left-over sequence -> (head, block) pair; pairs >= total do not exist (the last range may be short)
     __host__ __device__ __forceinline__ int item(int vi) const { return (vi / tail_per()) * per + full_per + vi % tail_per(); }
 };
 // Least scale * log2(e) of the kernels that divide by it: 31 / scale (the largest multiplicity's bias) plus a score stays
 // far from the largest float.  Subnormal scales gave 0 * infinity.
 constexpr float ATTN_LEAST_SCALE_LOG2 = 0x1p-100f;
-constexpr int ATTN_SHARE_WORKGROUPS = 512;                      // resident workgroups that take the shares: two per CU
 constexpr int ATTN_PART_O_FLOATS = (128 / 32) * 16 * 64;        // O^T accumulators of one wavefront (d = 128)
 constexpr int ATTN_PART_FLOATS = 4 * (ATTN_PART_O_FLOATS + 2 * 64);   // one fragment of a query block: four wavefronts' accumulators, reference maxima, row sums
 // Whether a launch of n_items pairs with n_tiles 64-key tiles each is split, and how many pairs per range are taken

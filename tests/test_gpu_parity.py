@@ -1965,6 +1965,26 @@ def test_attention_with_a_workspace_runs_short_lists_as_without_and_rejects_a_sh
         fa.sparse_attn_fwd(Q, K, V, None, lens, sel, nsel, 128, 64, 0.1, ws=ws[:1024])
 
 
+@pytest.mark.parametrize("H,n_sel", [(513, 26), (516, 40), (520, 63), (520, 64), (528, 28), (1029, 50)])   # 64 tiles: as many as workgroups
+def test_attention_with_fewer_left_over_tiles_than_workgroups_that_share_them(H, n_sel):
+    # one or two query blocks per XCD are left over: not every one of 512 shares has a tile, and one without leaves no fragment,
+    # whatever the workspace held
+    assert fa.attn_route(H, 128, 128, 64, n_sel, True)[0] == "one_shared"
+    rng = np.random.default_rng(H + n_sel)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    n_q, C, few = 100, 64 * n_sel, 3
+    rep = lambda x: x.repeat(H // few + 1, *[1] * (x.dim() - 1))[:H].contiguous()  # noqa: E731
+    Q, K, V = (torch.randn(few, n, 128, device="cuda", generator=g).bfloat16() for n in (n_q, C, C))
+    lens = np.array([C, C - 100, C], np.int32)
+    sel = np.stack([rng.permutation(n_sel) for _ in range(few)])[:, None, :].astype(np.int32)
+    nsel = np.array([[n_sel], [n_sel], [n_sel // 2]], np.int32)
+    ws = torch.full((fa.workspace_bytes(fa.OP_ATTN, H, n_q, C),), 0xFF, dtype=torch.uint8, device="cuda")
+    O, lse = fa.sparse_attn_fwd(*(rep(x) for x in (Q, K, V)), None, *(rep(to_dev(x)) for x in (lens, sel, nsel)), 128, 64, 0.1, ws=ws)
+    O_r, lse_r = (rep(torch.from_numpy(x).cuda()) for x in oracle.sparse_attn_fwd(*(to_host(x) for x in (Q, K, V)), None, lens, sel, nsel, 128, 64, 0.1))
+    assert float((O - O_r).abs().max()) <= ATOL["bf16"]
+    assert float((lse - lse_r).abs().max()) <= 2e-2
+
+
 @pytest.mark.parametrize("kind,H,n_q,n_sel,BQ,BK,used", [
     ("bf16", 1, 512, 10, 128, 64, True),         # few query blocks, long lists: fragments
     ("bf16", 32, 512, 50, 128, 64, True),        # 128 pairs, the most that are cut
