@@ -2026,13 +2026,14 @@ def test_which_attention_launches_use_their_workspace(kind, H, n_q, n_sel, BQ, B
 
 
 @pytest.mark.parametrize("H,n_q,C,n_sel,BQ,BK", [
-    (1, 64, 64 * 12, 3, 64, 64),         # the shortest list that is split: one group of wavefronts without a tile
-    (3, 777, 64 * 20 - 9, 11, 64, 64),   # groups of unequal numbers of tiles, the last key block cut by len
-    (2, 300, 64 * 20, 13, 128, 64),      # two groups
+    (1, 64, 64 * 12, 3, 64, 64),         # four wavefronts per group of queries
+    (3, 777, 64 * 20 - 9, 11, 64, 64),   # wavefronts with unequal numbers of tiles, the last key block cut by len
+    (2, 300, 64 * 20, 13, 128, 64),      # eight
     (2, 260, 640, 300, 64, 1),           # single keys, the last tile not full
-    (1, 64 * 256, 640, 5, 64, 64), (1, 64 * 257, 640, 5, 64, 64),   # the last split launch and the first that is not
+    (1, 64 * 256, 640, 5, 64, 64), (1, 64 * 257, 640, 5, 64, 64),   # 512 groups, four wavefronts; 514, two
 ])
-def test_attention_of_64_wide_heads_split_over_groups_of_wavefronts(H, n_q, C, n_sel, BQ, BK):
+def test_attention_of_64_wide_heads_over_few_query_blocks(H, n_q, C, n_sel, BQ, BK):
+    assert fa.attn_route(H * -(-n_q // BQ), 64, BQ, BK, n_sel, False)[0] == "waves"
     rng = np.random.default_rng(H * 31 + n_sel)
     g = torch.Generator(device="cuda").manual_seed(n_sel)
     Q, K, V = (torch.randn(H, n, 64, device="cuda", generator=g).bfloat16() for n in (n_q, C, C))
@@ -2043,7 +2044,7 @@ def test_attention_of_64_wide_heads_split_over_groups_of_wavefronts(H, n_q, C, n
     sel = np.stack([np.stack([np.sort(rng.choice(n_kb, n_sel, replace=False)) for _ in range(n_qb)]) for _ in range(H)]).astype(np.int32)
     nsel = np.full((H, n_qb), n_sel, np.int32)
     if n_qb > 3:
-        nsel[-1, 1:4] = 1, 0, 2                # lists shorter than the number of groups
+        nsel[-1, 1:4] = 1, 0, 2                # lists shorter than the number of wavefronts
         for b, n in ((1, 1), (2, 0), (3, 2)):
             sel[-1, b, n:] = -1
     if H > 2:
@@ -2055,18 +2056,24 @@ def test_attention_of_64_wide_heads_split_over_groups_of_wavefronts(H, n_q, C, n
     assert np.array_equal(fin, np.isfinite(lse)) and np.abs(lse[fin] - lse_r[fin]).max() <= 2e-2
 
 
-@pytest.mark.parametrize("d,H,n_q,BQ,BK,n_sel", [
-    (64, 1, 70, 64, 64, 1), (64, 3, 300, 128, 1, 33), (64, 2, 200, 64, 32, 2), (64, 5, 4000, 128, 64, 2),      # 2 wavefronts per group
-    (64, 2, 333, 128, 64, 2), (64, 2, 333, 64, 16, 9), (64, 4, 2048, 128, 64, 12), (64, 5, 2560, 128, 64, 32),   # 4
-    (64, 1, 97, 128, 64, 12), (64, 3, 1000, 64, 64, 13), (64, 1, 260, 128, 2, 384),                      # 8
-    (64, 5, 4096, 128, 64, 3), (64, 41, 128, 64, 64, 2), (64, 65, 4000, 64, 64, 3),                      # the first that another kernel takes
-    (128, 1, 129, 128, 64, 2), (128, 3, 500, 128, 64, 8), (128, 16, 1024, 128, 64, 20), (128, 16, 1000, 64, 64, 7),
-    (128, 1, 200, 128, 64, 30), (128, 2, 333, 64, 64, 24), (128, 12, 2600, 64, 64, 9),
-    (128, 1, 200, 128, 64, 1), (128, 2, 200, 128, 32, 20), (128, 43, 384, 128, 64, 8)])
-def test_attention_whose_wavefronts_share_a_group_of_queries(d, H, n_q, BQ, BK, n_sel):
-    # every form of the kernel and both sides of the rule that chooses it; tiles of 32 keys that lie wholly in a live block and
+@pytest.mark.parametrize("S,d,H,n_q,BQ,BK,n_sel", [
+    (2, 64, 1, 70, 64, 64, 1), (2, 64, 3, 300, 128, 1, 33), (2, 64, 2, 200, 64, 32, 2), (2, 64, 5, 4096, 128, 64, 3),
+    (2, 64, 5, 4000, 128, 64, 2), (2, 64, 64, 1024, 64, 64, 3), (2, 64, 64, 2048, 64, 64, 3), (2, 64, 64, 1300, 64, 16, 40),
+    (4, 64, 2, 333, 128, 64, 2), (4, 64, 2, 333, 64, 16, 9), (4, 64, 41, 128, 64, 64, 2), (4, 64, 56, 1024, 128, 64, 16), (4, 64, 5, 2560, 64, 1, 2000),
+    (8, 64, 4, 2048, 128, 64, 12), (8, 64, 5, 2560, 128, 32, 64), (8, 64, 1, 97, 128, 64, 12), (8, 64, 3, 1000, 64, 64, 13), (8, 64, 1, 260, 128, 2, 384),
+    # the first on the other side of a line
+    (0, 64, 23, 897, 128, 64, 2), (0, 64, 161, 128, 128, 64, 2), (0, 64, 321, 128, 128, 64, 15), (0, 64, 449, 128, 128, 64, 20), (0, 64, 321, 64, 64, 64, 2),
+    (0, 64, 65, 1010, 64, 64, 4), (0, 64, 65, 1300, 64, 64, 7), (0, 64, 65, 4000, 64, 64, 3),
+    (2, 128, 9, 2048, 64, 64, 3), (4, 128, 1, 129, 128, 64, 2), (4, 128, 3, 500, 128, 64, 8), (4, 128, 16, 1000, 64, 64, 8), (4, 128, 16, 1024, 128, 64, 32),
+    (8, 128, 1, 200, 128, 64, 30), (8, 128, 2, 333, 64, 64, 24),
+    (0, 128, 1, 200, 128, 64, 1), (0, 128, 2, 200, 128, 32, 20), (0, 128, 43, 384, 128, 64, 8), (0, 128, 16, 1024, 128, 64, 33), (0, 128, 13, 640, 128, 64, 5),
+    (0, 128, 16, 1000, 64, 64, 7), (0, 128, 8, 3072, 64, 64, 2), (0, 128, 5, 4928, 64, 64, 9)])
+def test_attention_whose_wavefronts_share_a_group_of_queries(S, d, H, n_q, BQ, BK, n_sel):
+    # every form of the kernel (S wavefronts per group) and both sides of the rule that chooses it; tiles of 32 keys that lie wholly in a live block and
     # tiles with masked positions in any order (padding, dead blocks, the block that len cuts, repeats), rows that nothing
     # selects not finite, groups of fewer than 32 queries, wavefronts without a tile
+    kernel, n = fa.attn_route(H * -(-n_q // BQ), d, BQ, BK, n_sel, False)
+    assert (n if kernel == "waves" else 0) == S
     rng = np.random.default_rng(1000 * d + 10 * BK + n_sel + H)
     g = torch.Generator(device="cuda").manual_seed(n_sel + H)
     n_kb = max(6, n_sel // 2)
@@ -2097,6 +2104,82 @@ def test_attention_whose_wavefronts_share_a_group_of_queries(d, H, n_q, BQ, BK, 
         assert np.abs(to_f32(O[few]).astype(np.float64) - O_r).max() <= ATOL["bf16"]
         fin = np.isfinite(lse_r)
         assert np.array_equal(fin, np.isfinite(lse[few])) and np.abs(lse[few][fin] - lse_r[fin]).max() <= 2e-2
+
+
+# What each kernel of the large launches is given, and what proves that it is that one: (kernel, its number or None), heads repeated
+LARGE_LAUNCHES = [
+    (("pair_split", 1), 128, 128, 64, 11, 24, False), (("pair_split", 1), 128, 128, 32, 3, 41, False), (("pair_split", 1), 128, 128, 64, 18, 75, False),
+    (("pair_split", None), 128, 128, 64, 3, 50, True), (("pair_split", None), 128, 128, 64, 9, 75, True),
+    (("pair", 0), 128, 128, 64, 40, 24, False), (("pair", 0), 128, 128, 64, 40, 3, True), (("pair", 0), 128, 128, 8, 64, 60, False),
+    (("one", 0), 128, 128, 64, 25, 2, False), (("one", 0), 128, 128, 64, 11, 5, True), (("one", 0), 128, 128, 64, 43, 24, False),
+    (("one_shared", 64), 128, 128, 64, 43, 75, True), (("one_shared", 64), 128, 128, 16, 50, 200, True),
+    (("one", 0), 128, 64, 64, 33, 24, False), (("one", 0), 128, 64, 64, 20, 7, False), (("one", 0), 128, 64, 16, 3, 90, False),
+    (("plain", 0), 64, 128, 64, 38, 10, False), (("plain", 0), 64, 128, 16, 38, 45, False), (("plain", 0), 64, 128, 1, 38, 500, False),
+    (("plain", 0), 64, 64, 64, 117, 7, False), (("plain", 0), 64, 64, 8, 117, 55, False), (("plain", 0), 64, 64, 64, 342, 12, False),
+    (("plain", 0), 64, 64, 64, 171, 70, False)]
+
+
+def check_large_launch(want, Q, K, V, cnt, lens, sel, nsel, BQ, BK, scale, reps, use_ws):
+    """The layer's heads `reps` times over, so that the launch is as large as its kernel wants it; the oracle takes them once."""
+    H, n_q, d = Q.shape
+    kernel, n = fa.attn_route(reps * sel.shape[0] * sel.shape[1], d, BQ, BK, sel.shape[2], use_ws)
+    assert kernel == want[0] and (n == want[1] if want[1] is not None else n > 1), (kernel, n)
+    many = lambda x: None if x is None else to_dev(x).repeat(reps, *[1] * (x.ndim - 1))  # noqa: E731
+    ws = torch.full((fa.workspace_bytes(fa.OP_ATTN, reps * H, n_q, K.shape[1]),), 0xFF, dtype=torch.uint8, device="cuda") if use_ws else None
+    O, lse = fa.sparse_attn_fwd(*(many(x) for x in (Q, K, V, cnt, lens, sel, nsel)), BQ, BK, scale, ws=ws)
+    O_r, lse_r = (torch.from_numpy(x).cuda() for x in oracle.sparse_attn_fwd(Q, K, V, cnt, lens, sel, nsel, BQ, BK, scale))
+    assert float((O.view(reps, H, n_q, d) - O_r).abs().max()) <= ATOL["bf16"]
+    lse, fin = lse.view(reps, H, n_q).double(), torch.isfinite(lse_r)
+    assert bool((torch.isfinite(lse) == fin).all()) and float((lse - lse_r)[:, fin].abs().max()) <= 2e-2
+
+
+@pytest.mark.parametrize("seed", [1, 2])
+@pytest.mark.parametrize("want,d,BQ,BK,reps,n_sel,use_ws", LARGE_LAUNCHES)
+def test_attention_kernels_of_large_launches_on_random_lists(want, d, BQ, BK, reps, n_sel, use_ws, seed):
+    """Ragged queries and caches, lists of no entry to all with repeats, negative and dead ones, dead slots and the rows of no list not
+    finite, with and without multiplicities."""
+    rng = np.random.default_rng(1000 * seed + reps + n_sel)
+    H, n_q, n_kb = 4, 3 * BQ - int(rng.integers(1, BQ)), max(6, min(n_sel // 2, 40))
+    C = n_kb * BK + BK // 3
+    lens = np.array([C, C - BK - BK // 2, (n_kb // 2) * BK + 1, 0], np.int32)
+    Q, K, V = (rng.standard_normal((H, n, d)).astype(np.float32) for n in (n_q, C, C))
+    Q *= rng.choice([0.3, 1.0, 3.0], size=(H, n_q, 1)).astype(np.float32)
+    for h in range(H):
+        K[h, lens[h]:], V[h, lens[h]:] = np.nan, np.inf
+    Q, K, V = (to_storage(x, "bf16") for x in (Q, K, V))
+    cnt = rng.integers(1, 9, size=(H, C)).astype(np.int32)
+    sel = rng.integers(0, n_kb + 1, size=(H, 3, n_sel)).astype(np.int32)
+    sel[:, ::2] = np.sort(sel[:, ::2], axis=-1)
+    sel[rng.random(sel.shape) < 0.1] = -1
+    nsel = rng.integers(0, n_sel + 1, size=(H, 3)).astype(np.int32)
+    nsel[:, 0], nsel[1, 1], nsel[2, 1] = n_sel, 0, 1
+    for c in (cnt, None):
+        check_large_launch(want, Q, K, V, c, lens, sel, nsel, BQ, BK, d ** -0.5, reps, use_ws)
+
+
+@pytest.mark.parametrize("want,d,BQ,C,reps,use_ws", [
+    (("pair_split", 1), 128, 128, 64 * 24, 33, False), (("pair_split", None), 128, 128, 64 * 50, 9, True), (("pair", 0), 128, 128, 64 * 24, 100, False),
+    (("pair", 0), 128, 128, 64 * 40, 120, False), (("pair_split", 1), 128, 128, 64 * 96, 60, False),     # K and V beyond 256 MB
+    (("one", 0), 128, 128, 64 * 24, 129, False), (("one_shared", 64), 128, 128, 64 * 40, 129, True), (("one", 0), 128, 64, 64 * 24, 100, False),
+    (("plain", 0), 64, 128, 64 * 24, 120, False), (("plain", 0), 64, 64, 64 * 66, 513, False), (("waves", 8), 64, 64, 64 * 24, 1, False),
+    (("waves", 4), 128, 128, 64 * 24, 20, False)])
+def test_attention_kernels_of_large_launches_follow_logits_that_keep_growing(want, d, BQ, C, reps, use_ws):
+    """Scores that climb along a list, slowly and then fast, or fall: the kernels that move their reference maximum by a margin only
+    meet both sides of it in every tile."""
+    rng = np.random.default_rng(d + BQ + reps)
+    H, n_q, BK = 2, 2 * BQ, 64
+    base = rng.standard_normal((H, 1, d)).astype(np.float32)
+    Q = to_storage(base + 0.3 * rng.standard_normal((H, n_q, d)).astype(np.float32), "bf16")
+    ramp = np.linspace(0.0, 1.0, C, dtype=np.float32)[None, :, None]
+    ramp = np.where(np.arange(C)[None, :, None] < C // 2, 0.25 * ramp, ramp * ramp * 3.0)
+    K = to_storage(base * ramp + 0.3 * rng.standard_normal((H, C, d)).astype(np.float32), "bf16")
+    V = to_storage(rng.standard_normal((H, C, d)).astype(np.float32), "bf16")
+    cnt = rng.integers(1, 5, size=(H, C)).astype(np.int32)
+    sel = np.tile(np.arange(C // BK, dtype=np.int32), (H, n_q // BQ, 1))
+    sel[1] = sel[1, :, ::-1]
+    nsel = np.full((H, n_q // BQ), C // BK, np.int32)
+    for scale in (d ** -0.5, 4.0 * d ** -0.5):
+        check_large_launch(want, Q, K, V, cnt, np.full((H,), C, np.int32), sel, nsel, BQ, BK, scale, reps, use_ws)
 
 
 @pytest.mark.parametrize("H,n_q,C,n_sel,BK,fp8", [
