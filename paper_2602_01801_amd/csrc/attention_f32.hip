@@ -19,9 +19,10 @@
 // What bounds it now: where the chip is full, the matrix instructions: with the loads, the LDS reads, the softmax and the look-ups
 // taken out they alone take 0.87 of the launch (2.2 us per tile of 128 instructions and SIMD: real data lowers their
 // rate, and no vector instruction runs beside an fp32 one, probe); one wavefront per SIMD (196 groups) adds the latency of a
-// tile's chain.  Measured, d = 128, 64-row blocks, before -> now in us: 196 groups x 15 blocks 34.5 -> 27.7, 256 x 63 115 -> 91,
-// 1248 x 59 534 -> 423, 3680 x 13 336 -> 274 (88 TFLOP/s; the instructions alone reach 155 on data that does not change);
-// d = 64: 156 groups x 47 blocks 55.7 -> 38, 1024 x 32 120 -> 105.  Tried: scores of the next tile under the softmax (no gain:
+// tile's chain.  Measured, d = 128, 64-row blocks, K by rows -> by way of LDS, in us: 196 groups x 15 blocks 34.4 -> 26.4, 256 x 63 113 -> 89,
+// 1248 x 59 489 -> 402, 3680 x 13 330 -> 261 (92 TFLOP/s; the instructions alone reach 155 on data that does not change);
+// d = 64: 156 groups x 47 blocks 54.7 -> 37.4, 1024 x 32 116 -> 103.  Asking of every tile whether a weight lies below 2^-126 is 2 to 5 % of
+// that where the chip is full (389, 256, 98.5 without; in one branch with the maximum's: 403, 264, 107).  Tried: scores of the next tile under the softmax (no gain:
 // nothing overlaps), loads spread among the products (no gain), tiles of 16 keys with three wavefronts per SIMD (no gain).
 #include "common.hpp"
 
@@ -272,8 +273,7 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
 #pragma unroll
             for (int c = 0; c < CH; ++c) o[c] *= al;
         }
-        // The bare instruction makes weights below 2^-126 zero, exp2f does not, at five instructions each; the same elsewhere.
-        auto weights = [&](auto exponential) {
+        auto weigh = [&](auto exponential) {
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
@@ -281,16 +281,18 @@ __global__ __launch_bounds__(KS * 64, 2) void attn_f32_kernel(
                     s[hh][v] = exponential(s[hh][v] - m_safe);
                     l_run += s[hh][v];
                 }
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) o[c] = mfma_f32_16x16x4(vf[hh][v][c], s[hh][v], o[c]);
+                }
         };
-        if (__any(mn - m_safe < -126.0f)) weights([](float x) { return exp2f(x); });   // uniform
-        else weights([](float x) { return __builtin_amdgcn_exp2f(x); });
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-#pragma unroll
-                for (int c = 0; c < CH; ++c) o[c] = mfma_f32_16x16x4(vf[hh][v][c], s[hh][v], o[c]);
-            }
+        // The bare instruction makes weights below 2^-126 zero, exp2f does not, at five instructions each; elsewhere they are the
+        // same.  The products are in either branch so that the exponentials run between them.
+        if (__any(mn - m_safe < -126.0f)) weigh([](float x) { return exp2f(x); });   // uniform
+        else weigh([](float x) { return __builtin_amdgcn_exp2f(x); });
         cur = next;
         n_cur = n_next;
     };
