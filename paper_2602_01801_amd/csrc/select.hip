@@ -20,16 +20,17 @@ namespace fastar {
 
 constexpr int KB_PER_WG = 4;      // key blocks scored by one workgroup of score_self_kernel
 // Key blocks over all heads from which the streaming kernel pays, by the summaries' column blocks of 32 (it holds four): never for
-// one or two and for 64-entry codes, where the short kernel keeps more wavefronts in flight.  Call, streaming / short kernel, us:
-// 4: 10 heads x 64000 slots (10000) 17.3 / 17.5, 13 x 103000 (20930) 25.6 / 26.6, 20 x 150000 (46880) 44 / 49, 40 x 230400 113 / 128;
-// 3: 20 x 150000 41.7 / 41.6, 40 x 110000 (68760) 50.0 / 50.9, 40 x 230400 99 / 108; 2: 40 x 230400 88 / 82, 24 x 200000 49.6 / 45.6,
-// 40 x 115200 45 / 41; 64 entries: 4: 10 x 64000 33 / 22, 40 x 110000 95 / 93, 3: 20 x 230400 95 / 84, 2: 40 x 115200 86 / 61.
+// up to three and for 64-entry codes, where the other one keeps more wavefronts in flight.  Call, streaming / the other, us:
+// 4: 10 heads x 64000 slots (10000) 17.4 / 17.6, 13 x 103000 (20930) 27.9 / 28.6, 20 x 150000 41 / 46, 40 x 150000 62 / 73, 40 x 230400
+// 108 / 115; 3: 10 x 64000 18.3 / 16.6, 20 x 150000 41.1 / 39.6, 40 x 110000 (68760) 49.4 / 48.1, 40 x 230400 95.3 / 94.7, 64 x 230400 157 / 146;
+// 2: 40 x 230400 88 / 82, 24 x 200000 49.6 / 45.6, 40 x 115200 45 / 41; 64 entries: 4: 10 x 64000 33 / 22, 40 x 110000 95 / 93, 3: 20 x 230400
+// 95 / 84, 2: 40 x 115200 86 / 61.
 // Codes of 2 and 4 bits keep one line.
 constexpr size_t LONG_CACHE_BLOCKS = 16 * 4096, LONG_CACHE_BLOCKS_4 = 20000;
 static bool streams(int r, int bits, int n_cb, size_t blocks) {
     if (n_cb > 4 || r != 32) return false;
     if (bits != 8) return blocks >= LONG_CACHE_BLOCKS;
-    return n_cb >= 3 && blocks >= (n_cb == 4 ? LONG_CACHE_BLOCKS_4 : LONG_CACHE_BLOCKS);
+    return n_cb == 4 && blocks >= LONG_CACHE_BLOCKS_4;
 }
 // Slots per head up to which one workgroup per query block scores them all (select_short_kernel); three launches against
 // one, us: r = 32, 2 x 2 query blocks, 4096 slots 9.3 -> 6.6, 9360 9.3 -> 8.9, 12288 9.6 -> 9.3; 12 x 21, 4096 11.1 -> 7.4,
@@ -146,7 +147,8 @@ __device__ __forceinline__ int max_over_reps_i32(int x, int n_rep) {
 // from two to eight: what bounds the launch is the codes' latency, and it wants wavefronts in flight.  Calls in us, eight at every
 // size / as many as the call has: one block of columns, 12 heads x 37440 slots 12.7 / 11.6; three 14.3 / 13.1, 20 x 100000 34.3 / 30.3,
 // 64-entry codes 47.8 / 38.8; five 16.6 / 16.0; six 17.7 / 17.5, 40 x 57600 with 64-entry codes 70.3 / 59.3; seven 18.8 / 18.6, 40 x 115200
-// with 64-entry codes 158 / 141; twice seven, 12 x 60000 with 64-entry codes 52.3 / 45.9.
+// with 64-entry codes 158 / 141; twice seven, 12 x 60000 with 64-entry codes 52.3 / 45.9.  Codes of 2 and 4 bits have two, four, five and
+// eight: with the others as well, 60 KB more code, the launches of this file took 0.2 to 0.4 us longer (12 x 4680 x 37440).
 template <int R, int BITS, int COL_CHUNK>
 __global__ __launch_bounds__(256) void score_self_kernel(const int8_t *__restrict__ kcode, const int32_t *__restrict__ len,
                                                          const int8_t *__restrict__ rep, int C, int n_q, int BQ,
@@ -406,6 +408,14 @@ __global__ __launch_bounds__(256, 3) void score_self_stream_kernel(const int8_t 
 // ---- AnnCA scoring -----------------------------------------------------------------------------------
 // score[p] = max over the queries q of block b of qcode[q] . pcode[p], kept in LDS, then the top n_sel of the row.
 // D = A x B with A rows = 32 queries, B columns = 32 prompt tokens.
+
+// Maximum of m and the 16 results, three levels deep.
+__device__ __forceinline__ int max_of_16(int m, const i32x16 &a) {
+    const int t0 = max(max(a[0], a[1]), a[2]), t1 = max(max(a[3], a[4]), a[5]), t2 = max(max(a[6], a[7]), a[8]);
+    const int t3 = max(max(a[9], a[10]), a[11]), t4 = max(max(a[12], a[13]), a[14]);
+    return max(max(m, max(max(t0, t1), a[15])), max(max(t2, t3), t4));
+}
+
 // smax[p] = max over the queries of block b of qcode[q] . pcode[p], for all n_p prompt tokens; whole workgroup.
 // A wavefront takes every fourth group of 32 prompt tokens against all queries, 128 at a time: a token's codes are read once
 // and its maximum over four products stays in registers, without atomics.  (Every wavefront a quarter of the queries
@@ -414,12 +424,6 @@ __global__ __launch_bounds__(256, 3) void score_self_stream_kernel(const int8_t 
 // is under way while the maxima of one are taken, without branches between them (one after the other, each waited for: launch
 // for 2 x 256 queries x 2048 tokens 8.5 us, now 7.4; 1 x 128 x 12000 68.7, 60.7).
 // in_flight() is called once, behind the first loads: what it asks for does not hold the scores up (loads come back in order).
-// maximum of m and the 16 results, three levels deep
-__device__ __forceinline__ int max_of_16(int m, const i32x16 &a) {
-    const int t0 = max(max(a[0], a[1]), a[2]), t1 = max(max(a[3], a[4]), a[5]), t2 = max(max(a[6], a[7]), a[8]);
-    const int t3 = max(max(a[9], a[10]), a[11]), t4 = max(max(a[12], a[13]), a[14]);
-    return max(max(m, max(max(t0, t1), a[15])), max(max(t2, t3), t4));
-}
 // Queries q0 .. q_end (at most 32 QG; rows beyond repeat the last one, which changes no maximum) against all tokens.
 template <int R, int QG, typename F>
 __device__ __forceinline__ void score_cross_queries(const int8_t *__restrict__ qc, const int8_t *__restrict__ pc, int n_p, int q0,
@@ -507,8 +511,8 @@ __global__ __launch_bounds__(256) void score_cross_kernel(const int8_t *__restri
 // One workgroup = one query block: scores and exact top-n_sel as above (the list also goes to sel / nsel), then the
 // selected prompt rows are gathered into LDS once and the four wavefronts (32 queries each) attend to them:
 // S^T = K Q^T, softmax over the at most 64 tokens in one piece (no running maximum), O^T = V^T P^T.  V is stored
-// transposed ([d][token]) with the tokens of each 16 in the order the score accumulators hold them, so that the
-// accumulators, converted to bf16, are the second product's operand as they are.
+// in rows like K and transposed by the LDS reads, which take the tokens of each 16 in the order the score accumulators hold
+// them, so that the accumulators, converted to bf16, are the second product's operand as they are.
 namespace fused {
 constexpr int D = 128, TK = 64;
 constexpr int KROW = D * 2 + 16;          // bytes per staged K row (padded: 16 consecutive rows hit 16 different bank groups)
@@ -1186,12 +1190,14 @@ static int select_self_impl(const int8_t *qcode, int n_q, const int8_t *kcode, c
             }
         }
         auto kernel = per_pass <= 2   ? score_self_kernel<RR, BB, 2>
-                      : per_pass == 3 ? score_self_kernel<RR, BB, 3>
-                      : per_pass == 4 ? score_self_kernel<RR, BB, 4>
+                      : per_pass <= 4 ? score_self_kernel<RR, BB, 4>
                       : per_pass == 5 ? score_self_kernel<RR, BB, 5>
-                      : per_pass == 6 ? score_self_kernel<RR, BB, 6>
-                      : per_pass == 7 ? score_self_kernel<RR, BB, 7>
                                       : score_self_kernel<RR, BB, 8>;
+        if constexpr (BB == 8) {
+            if (per_pass == 3) kernel = score_self_kernel<RR, BB, 3>;
+            if (per_pass == 6) kernel = score_self_kernel<RR, BB, 6>;
+            if (per_pass == 7) kernel = score_self_kernel<RR, BB, 7>;
+        }
         hipLaunchKernelGGL(kernel, grid, dim3(256), tile_bytes, s, kcode, len, rep, C, n_q, BQ, n_rep, BK, n_qb, n_kb_cap, score);
     };
 #define FASTAR_SELF(RR, BB)                                                                                            \

@@ -292,7 +292,7 @@ def test_selection_on_seeded_random_shapes(seed):
 
 
 # summaries in one to fourteen column blocks of 32 (passes of two to eight, the last one short), and both sides of the streaming
-# kernel's line for three and four of them (20000 and 65536 key blocks over the heads)
+# kernel's line for four of them (20000 key blocks over the heads), long caches with fewer
 @pytest.mark.parametrize("H,n_q,C,r,BK", [
     (2, 400, 12000, 32, 64), (2, 1100, 12000, 32, 64), (2, 2100, 12000, 64, 64), (2, 4200, 12000, 32, 64), (2, 5000, 11000, 64, 64),
     (2, 2100, 12000, 32, 64), (2, 3400, 12000, 32, 64), (2, 6100, 12000, 32, 64), (2, 7100, 11000, 64, 64), (1, 8100, 11000, 32, 64),
