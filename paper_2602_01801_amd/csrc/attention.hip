@@ -11,7 +11,8 @@
 // Softmax runs in fp32 in the log2 domain with a running maximum; masked keys (padding of the list,
 // slots beyond len) get a -inf bias and zeroed K/V rows.
 //
-// Few query blocks: attention_waves.hip; fp32: attention_f32.hip.
+// This kernel serves 64-wide heads (and scales too small to divide by); few query blocks: attention_waves.hip, 128-wide heads:
+// attention_d128.hip and attention_d128_pp.hip, fp32: attention_f32.hip.  Which call takes which: attn_route below.
 #include <algorithm>
 
 #include "common.hpp"
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_bf16_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) o_acc[db][v] *= alpha;
 
-        // O^T += V^T P^T : four nt of 16 keys
+        // O^T += V^T P^T : four steps of 16 keys
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll

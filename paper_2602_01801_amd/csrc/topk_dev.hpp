@@ -370,7 +370,6 @@ __device__ __forceinline__ void topk_row_wave(const int32_t *row, int n, int n_s
 __device__ __forceinline__ void topk_row(const int32_t *row, int n, int n_sel, int32_t *__restrict__ out,
                                          int32_t *__restrict__ nsel_out, unsigned *keys, unsigned *scratch, int n_sink = 0,
                                          int n_local = 0, int cand_min = INT_MIN) {
-    // Keys have 22 bits: three passes over 8-bit digits (the first has 6 significant bits) select exactly.
     // key of entry t with score sc: real scores stay below 2^22, forced entries sit exactly there
     auto key_of = [&](int t, int32_t sc) -> unsigned {
         return (t < n_sink || t >= n - n_local) ? (1u << 22) : topk_key(sc);
