@@ -181,7 +181,8 @@ def _dev(t: torch.Tensor, dtype=None):
     return t
 
 
-@functools.lru_cache(maxsize=256)   # a function of its arguments alone: a look-up instead of a foreign call per checked workspace
+# a function of its arguments alone: a look-up instead of a foreign call per checked workspace; typed, so that 2.0 is not 2
+@functools.lru_cache(maxsize=256, typed=True)
 def workspace_bytes(op: int, H: int, n_q: int, n_k: int, r: int = 32, BQ: int = 128, BK: int = 64,
                     n_rep: int = 4) -> int:
     return int(lib().fastar_workspace_bytes(op, H, n_q, n_k, r, BQ, BK, n_rep))

@@ -52,6 +52,13 @@ def test_workspace_sizes(L):
     assert workspace_bytes(99, 1, 1, 1) == 0
 
 
+def test_workspace_sizes_refuse_what_is_no_integer_whatever_was_asked_before(L):
+    from paper_2602_01801_amd import OP_ATTN, workspace_bytes
+    assert workspace_bytes(OP_ATTN, 2, 128, 640) > 0
+    with pytest.raises(ctypes.ArgumentError):
+        workspace_bytes(OP_ATTN, 2.0, 128, 640)   # equals 2, and hashes like it
+
+
 def test_null_and_inconsistent_arguments_return_error_codes_without_a_gpu(L):
     null = ctypes.c_void_p(0)
     assert L.ann_select_self(null, 128, null, null, 1, 256, 32, 128, 4, 64, 2, null, null, null, 0, null) == -1
