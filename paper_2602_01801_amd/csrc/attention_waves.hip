@@ -9,10 +9,10 @@
 // L2, which is what bounds it as the blocks become many (at d = 128 18 TB/s), so the launcher keeps the other kernels there.
 // Both products are computed transposed, as in the other bf16 kernels: S^T = K Q^T from the keys' bias on, O^T = V^T P^T with
 // the S^T registers as the second operand.
-// Measured (us, before -> now): d = 64: 2 blocks of 128 queries x 60 entries 70 -> 19, 57 x 47 62 -> 19, 39 blocks of 64 x 11
-// 13.6 -> 8.2; d = 128: 64 x 7 14.9 -> 10.3 (the split two-block kernel), 27 x 18 18.9 -> 15.3 (its parts), 45 x 3 8.7 -> 7.1 (the
-// one-block kernel).  Tiles of 64 keys and half of the resident wavefronts at d = 64: the same within 5 %; 16 wavefronts per group:
-// slower at every size.
+// Measured (us, the kernel that took it before -> this one; launches back to back): d = 64: 2 blocks of 128 queries x 60 entries 66.7 ->
+// 19.7, 57 x 47 60.5 -> 19.8, 39 blocks of 64 x 11 13.4 -> 8.7; d = 128: 64 x 7 13.1 -> 9.2 (the split two-block kernel), 27 x 18 17.8 ->
+// 13.7 (its parts), 49 x 3 8.7 -> 7.1 (the one-block kernel).  Tiles of 64 keys and half of the resident wavefronts at d = 64: the same
+// within 5 %; 16 wavefronts per group: slower at every size.
 #include "common.hpp"
 
 #include <type_traits>
